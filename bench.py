@@ -219,7 +219,7 @@ def main() -> int:
                              workspace=workspace)
 
         # few long paths: the library's hint asks for the walk back to be cut into stretches, as the autograd op does
-        stretches = 1 if w.stream else sig.sig_backward_chunks_hint(w.B, w.L, w.d, w.N, w.basepoint)
+        stretches = 1 if w.stream else sig.sig_backward_chunks_fastest(w.B, w.L, w.d, w.N, w.basepoint)
         if stretches > 1:
             need = sig.sig_backward_chunked_workspace_bytes(w.B, w.L, w.d, w.N, w.basepoint, stretches)
             workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)

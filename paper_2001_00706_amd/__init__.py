@@ -28,6 +28,7 @@ from .binding import (  # noqa: F401
     sig_backward,
     sig_backward_chunked,
     sig_backward_chunked_workspace_bytes,
+    sig_backward_chunks_fastest,
     sig_backward_chunks_hint,
     sig_backward_workspace_bytes,
     sig_combine,

@@ -35,7 +35,7 @@ class _Signature(torch.autograd.Function):
         bp = basepoint_value.contiguous() if basepoint_value is not None else bool(basepoint)
         grad_bp = torch.empty_like(basepoint_value) if basepoint_value is not None else None
         B, L, _ = path.shape
-        chunks = 1 if stream else binding.sig_backward_chunks_hint(B, L, d, depth, bool(basepoint), binding._dtype_of(path))
+        chunks = 1 if stream else binding.sig_backward_chunks_fastest(B, L, d, depth, bool(basepoint), binding._dtype_of(path))
         if chunks > 1:   # few long paths: the walk back along the path cut into stretches
             grad_path = binding.sig_backward_chunked(path, grad_out, depth, chunks, basepoint=bp, grad_basepoint=grad_bp)
         else:

@@ -41,6 +41,7 @@ EXPORTED_SYMBOLS = (
     "sig_backward_chunked",
     "sig_backward_chunked_workspace_bytes",
     "sig_backward_chunks_hint",
+    "sig_backward_chunks_fastest",
     "sig_combine_strided",
     "sig_combine_backward",
     "sig_combine_backward_workspace_bytes",
@@ -160,6 +161,8 @@ def load_library() -> ctypes.CDLL:
         lib.sig_backward_chunked_workspace_bytes.argtypes = [i64, i64, i32, i32, i32, i32, i32]
         lib.sig_backward_chunks_hint.restype = i32
         lib.sig_backward_chunks_hint.argtypes = [i64, i64, i32, i32, i32, i32]
+        lib.sig_backward_chunks_fastest.restype = i32
+        lib.sig_backward_chunks_fastest.argtypes = [i64, i64, i32, i32, i32, i32]
         lib.sig_combine_backward.restype = i32
         lib.sig_combine_backward.argtypes = [vp, vp, vp, i64, i32, i32, i32, vp, vp, vp, i64, vp]
         lib.sig_combine_backward_workspace_bytes.restype = i64
@@ -403,8 +406,13 @@ def sig_backward_chunked_workspace_bytes(B: int, L: int, d: int, N: int, basepoi
 
 
 def sig_backward_chunks_hint(B: int, L: int, d: int, N: int, basepoint: bool = False, dtype: int = SIG_F32) -> int:
-    """The number of stretches `sig_backward_chunked` should be given for this shape; 1 where `sig_backward` is faster."""
+    """A number of stretches for `sig_backward_chunked` that keeps its workspace small; 1 for short or many paths."""
     return int(load_library().sig_backward_chunks_hint(B, L, d, N, int(bool(basepoint)), dtype))
+
+
+def sig_backward_chunks_fastest(B: int, L: int, d: int, N: int, basepoint: bool = False, dtype: int = SIG_F32) -> int:
+    """The number of stretches with which `sig_backward_chunked` is fastest; 1 where `sig_backward` is the better call."""
+    return int(load_library().sig_backward_chunks_fastest(B, L, d, N, int(bool(basepoint)), dtype))
 
 
 def sig_backward_chunked(path, grad_out, N: int, chunks: int, basepoint=False, grad_path=None, workspace=None,

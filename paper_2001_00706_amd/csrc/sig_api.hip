@@ -370,12 +370,13 @@ sig_status sig_backward(const void *path, const void *sig, const void *grad_out,
 }
 
 // Layout of a gradient computed stretch by stretch: K stretches of m increments per path, served as the B K short paths
-// of `rows`; the workspace holds, each 256-byte aligned, the stretches' points, their signatures, the running products,
-// the gradients with respect to those, the stretches' point gradients and the workspace of the gradient kernels.
+// of `rows`; the workspace holds, each 256-byte aligned, the stretches' points, their signatures (later the gradients),
+// the signatures up to the end of each and of what comes after it, the stretches' point gradients and the workspace of
+// the gradient kernels.
 struct StretchPlan {
     int64_t K, m;
     sig::Shape rows;
-    int64_t at_points, at_sigs, at_prefix, at_grads, at_point_grads, at_inner, inner_bytes, total;
+    int64_t at_points, at_sigs, at_prefix, at_suffix, at_point_grads, at_inner, inner_bytes, total;
 };
 
 static sig_status plan_backward_chunked(int64_t B, int64_t L, int d, int N, int basepoint, int chunks, sig_dtype dtype, sig::Shape &sh,
@@ -406,8 +407,8 @@ static sig_status plan_backward_chunked(int64_t B, int64_t L, int d, int N, int 
     pl.at_points = 0;
     pl.at_sigs = pl.at_points + points;
     pl.at_prefix = pl.at_sigs + sigs;
-    pl.at_grads = pl.at_prefix + sigs;
-    pl.at_point_grads = pl.at_grads + sigs;
+    pl.at_suffix = pl.at_prefix + sigs;
+    pl.at_point_grads = pl.at_suffix + sigs;
     pl.at_inner = pl.at_point_grads + points;
     pl.total = pl.at_inner + round_up(pl.inner_bytes);
     return SIG_OK;
@@ -436,47 +437,23 @@ sig_status sig_backward_chunked(const void *path, const void *grad_out, int64_t 
     if (workspace == nullptr || workspace_bytes < pl.total || reinterpret_cast<uintptr_t>(workspace) % 16 != 0) return SIG_ERR_INVALID_ARG;
     sh.basepoint_value = basepoint_value;
     char *ws = static_cast<char *>(workspace);
-    void *points = ws + pl.at_points, *sigs = ws + pl.at_sigs, *prefix = ws + pl.at_prefix, *grads = ws + pl.at_grads,
+    void *points = ws + pl.at_points, *sigs = ws + pl.at_sigs, *prefix = ws + pl.at_prefix, *suffix = ws + pl.at_suffix,
          *point_grads = ws + pl.at_point_grads, *inner = ws + pl.at_inner;
     const Family family = resolve(pl.rows, dtype, SIG_VARIANT_AUTO, points, sigs);
     if (family == Family::None) return SIG_ERR_UNSUPPORTED;
     // the stretches as paths of their own, and their signatures
     if (sig::launch_stretch_gather(sh, dtype, pl.K, pl.m, path, points, hip_stream) != hipSuccess) return SIG_ERR_HIP;
     if (launch_family(family, pl.rows, dtype, points, sigs, hip_stream) != hipSuccess) return SIG_ERR_HIP;
-    // the signature of the path up to the end of every stretch: a running product along each path's stretches, by one
-    // workgroup per path while a signature fits its LDS three times over, else a launch per product
-    const int64_t elem = dtype == SIG_F32 ? int64_t(sizeof(float)) : int64_t(sizeof(double));
-    if (3 * sh.S * elem <= 64 * 1024 || pl.K == 1) {
-        if (sig::launch_copy_rows(dtype, sigs, sh.S, prefix, sh.S, sh.S, pl.rows.B, hip_stream) != hipSuccess) return SIG_ERR_HIP;
-        if (pl.K > 1) {
-            const hipError_t err = dtype == SIG_F32
-                                       ? sig::launch_chunk_prefix_f32(pl.rows, B, pl.K, 1, static_cast<float *>(prefix), hip_stream)
-                                       : sig::launch_chunk_prefix_f64(pl.rows, B, pl.K, 1, static_cast<double *>(prefix), hip_stream);
-            if (err != hipSuccess) return SIG_ERR_HIP;
-        }
+    // the signature of the path up to the end of every stretch, that of what comes after it, and through the latter the
+    // gradient with respect to the former, which takes the place of the stretches' own signatures
+    void *grads = sigs;
+    if (pl.K > 1) {
+        if (sig::launch_product_scan(pl.rows, dtype, B, pl.K, sigs, prefix, suffix, hip_stream) != hipSuccess) return SIG_ERR_HIP;
     } else {
-        const int64_t per_path = pl.K * sh.S;
-        if (sig::launch_copy_rows(dtype, sigs, per_path, prefix, per_path, sh.S, B, hip_stream) != hipSuccess) return SIG_ERR_HIP;
-        sig::Shape paths = pl.rows;
-        paths.B = B;
-        const int64_t strides[7] = {per_path, per_path, per_path, 0, 0, 0, 0};
-        for (int64_t c = 1; c < pl.K; ++c) {
-            const char *left = static_cast<const char *>(prefix) + (c - 1) * sh.S * elem;
-            const char *right = static_cast<const char *>(sigs) + c * sh.S * elem;
-            char *product = static_cast<char *>(prefix) + c * sh.S * elem;
-            const hipError_t err =
-                dtype == SIG_F32 ? sig::launch_combine_f32(paths, reinterpret_cast<const float *>(left), reinterpret_cast<const float *>(right),
-                                                           reinterpret_cast<float *>(product), hip_stream, strides)
-                                 : sig::launch_combine_f64(paths, reinterpret_cast<const double *>(left), reinterpret_cast<const double *>(right),
-                                                           reinterpret_cast<double *>(product), hip_stream, strides);
-            if (err != hipSuccess) return SIG_ERR_HIP;
-        }
+        prefix = sigs;
+        grads = suffix;
     }
-    // the gradient with respect to each of them, from the last stretch back
-    if (sig::launch_copy_rows(dtype, grad_out, sh.S, static_cast<char *>(grads) + (pl.K - 1) * sh.S * elem, pl.K * sh.S, sh.S, B,
-                              hip_stream) != hipSuccess)
-        return SIG_ERR_HIP;
-    if (sig::launch_stretch_adjoint_chain(pl.rows, dtype, pl.K, sigs, grads, hip_stream) != hipSuccess) return SIG_ERR_HIP;
+    if (sig::launch_stretch_adjoint_all(pl.rows, dtype, pl.K, suffix, grad_out, grads, hip_stream) != hipSuccess) return SIG_ERR_HIP;
     // every stretch walked backwards on its own, then the point gradients added up
     const hipError_t err =
         dtype == SIG_F32
@@ -497,11 +474,9 @@ int sig_backward_chunks_hint(int64_t B, int64_t L, int d, int N, int basepoint, 
     if (dtype != SIG_F32 && dtype != SIG_F64) return 0;
     sig::Shape sh;
     if (make_shape(B, L, d, N, 0, basepoint, sh) != SIG_OK) return 0;
-    // Depth 2 has a closed form with no walk at all.  Otherwise the walk is one increment after the other, and cutting
-    // it pays once the stretches' walks are shorter by more than the two chains between them cost (the running
-    // products and the gradients with respect to them, a few microseconds per stretch each): measured from 512
-    // increments on, best near sqrt(n_inc) / 2 stretches for signatures up to 2048 scalars, fewer for larger ones
-    // (a quarter of sqrt(n_inc) once the chains take a launch per stretch).
+    // Depth 2 has a closed form with no walk at all.  Otherwise about sqrt(n_inc) / 2 stretches for signatures up to 2048
+    // scalars, fewer for larger ones: a workspace of a few dozen signatures per path.  (More stretches are faster yet:
+    // sig_backward_chunks_fastest.)
     if (N < 3 || B < 1 || B > 128 || sh.n_inc < 512) return 1;
     const int64_t elem = dtype == SIG_F32 ? int64_t(sizeof(float)) : int64_t(sizeof(double));
     const int64_t per_stretch = sh.S <= 2048 ? 4 : 3 * sh.S * elem <= 64 * 1024 ? 8 : 16;
@@ -512,6 +487,46 @@ int sig_backward_chunks_hint(int64_t B, int64_t L, int d, int N, int basepoint, 
         const int64_t bytes = sig_backward_chunked_workspace_bytes(B, L, d, N, basepoint, int(next), dtype);
         if (bytes < 0 || bytes > (int64_t(2) << 30)) break;
         chunks = int(next);
+    }
+    return chunks;
+}
+
+int sig_backward_chunks_fastest(int64_t B, int64_t L, int d, int N, int basepoint, sig_dtype dtype)
+{
+    if (dtype != SIG_F32 && dtype != SIG_F64) return 0;
+    sig::Shape sh;
+    if (make_shape(B, L, d, N, 0, basepoint, sh) != SIG_OK) return 0;
+    if (N < 3 || B < 1) return 1;   // depth 2 has a closed form with no walk at all
+    // What a call takes in microseconds, fitted to sweeps over 1 .. 128 paths of 100 .. 65 536 increments at eleven (d, N), in
+    // 1 to 1024 stretches (predicted / measured: 1 x 65 537 points, d = 4, N = 6 in 512: 208 / 236; 8 x 401, d = 7, N = 5 in
+    // 16: 145 / 139; 32 x 513, d = 4, N = 6 in 8: 100 / 106; 128 x 401, d = 16, N = 4 in one piece: 460 / 498).
+    //   * The walk: one increment takes 0.3 to 0.55 while a path's threads fill one wavefront (and at d = 4), 0.8 to 1.25 beyond,
+    //     up to about 160 000 threads at a time; more threads share the time out.
+    //   * The rounds of products double with every doubling of the stretches: 10 for two more launches, about 4.5 where
+    //     most rounds share one.
+    //   * Every stretch's signature is written and read some dozen times: 3.5 per 10^6 bytes where four words move as a
+    //     vector, else 5.
+    //   * The launches around these: 24.
+    const int64_t elem = dtype == SIG_F32 ? int64_t(sizeof(float)) : int64_t(sizeof(double));
+    double threads = double(sh.pw[d <= 8 ? (N > 2 ? N - 2 : 1) : N - 1]);
+    if (dtype == SIG_F32 && d == 16 && N == 4) threads = 512;
+    const double step = threads <= 64 || d == 4 ? 0.4 : 1.15, round = sh.S <= 512 ? 4.5 : 10.5;
+    const double per_row = (d % 4 == 0 ? 3.5e-6 : 5e-6) * double(sh.S * elem);
+    const auto walk = [&](int64_t K) {
+        const double load = double(B) * double(K) * threads / 160e3;
+        return double(sh.n_inc) / double(K) * step * (load > 1 ? load : 1);
+    };
+    // a call in stretches is a dozen launches and more instead of two: it has to gain that much on the host as well
+    double best = walk(1) - 40, joined = 24;
+    int chunks = 1;
+    for (int64_t K = 2; K <= 65536 && sh.n_inc / K >= 16; K *= 2) {
+        joined += round;
+        const double time = joined + walk(K) + per_row * double(B) * double(K);
+        if (time >= best) continue;
+        const int64_t bytes = sig_backward_chunked_workspace_bytes(B, L, d, N, basepoint, int(K), dtype);
+        if (bytes < 0 || bytes > (int64_t(2) << 30)) break;
+        best = time;
+        chunks = int(K);
     }
     return chunks;
 }
@@ -651,25 +666,7 @@ static sig_status forward_chunked(const void *path, int64_t B, int64_t L, int d,
     char *ws1 = ws0 + sh.B * sh.S * elem;
     if (launch_family(family, sh, dtype, path, ws0, hip_stream) != hipSuccess) return SIG_ERR_HIP;
     // ... then neighbours joined pairwise (Chen's identity), halving the count each round
-    sig::Shape rows = sh;
-    rows.chunks = 1;
-    const char *src = ws0;
-    char *spare = ws1;
-    for (int64_t count = sh.B / 2; count >= B; count /= 2) {
-        rows.B = count;
-        char *dst = count == B ? static_cast<char *>(out) : spare;
-        const int64_t strides[7] = {2 * sh.S, 2 * sh.S, sh.S, 0, 0, 0, 0};
-        const hipError_t err =
-            dtype == SIG_F32
-                ? sig::launch_combine_f32(rows, reinterpret_cast<const float *>(src), reinterpret_cast<const float *>(src) + sh.S,
-                                          reinterpret_cast<float *>(dst), hip_stream, strides)
-                : sig::launch_combine_f64(rows, reinterpret_cast<const double *>(src), reinterpret_cast<const double *>(src) + sh.S,
-                                          reinterpret_cast<double *>(dst), hip_stream, strides);
-        if (err != hipSuccess) return SIG_ERR_HIP;
-        spare = const_cast<char *>(src);
-        src = dst;
-    }
-    return SIG_OK;
+    return sig::launch_product_reduce(sh, dtype, B, chunks, ws0, ws1, out, hip_stream) == hipSuccess ? SIG_OK : SIG_ERR_HIP;
 }
 
 sig_status sig_forward_chunked(const void *path, int64_t B, int64_t L, int d, int N, int basepoint,

@@ -7,11 +7,16 @@
 // a running product.  The second follows from S_c = S_{c-1} [x] C_c, which is linear in S_{c-1}:
 //     g_{c-1}[u] = sum_v g_c[u v] C_c[v],      v over all words with |u v| <= N, the empty one (C[empty] = 1) included,
 // starting from g_{K-1} = the gradient with respect to the whole signature.  Given both, the stretches are independent
-// and the ordinary gradient kernels serve them as B K short paths.  This file holds the plumbing around them: copying
-// the stretches out as paths of their own (m + 1 points, the last point of a path repeated where the last stretch is
-// short: increments of zero change no signature), the chain of g_c, and adding the stretches' point gradients up (a
-// point shared by two stretches ends an increment of one and starts one of the other; the repeated last points sum to
-// the gradient of the increment that ends at the real one).
+// and the ordinary gradient kernels serve them as B K short paths.
+// One stretch after the other, both recurrences would be chains of K steps of a few microseconds each.  The product is
+// associative, so the S_c and the products T_c = C_{c+1} [x] .. [x] C_{K-1} of what comes after a stretch are formed along a
+// binary tree in 2 log2 K rounds (sig_product_tree.hip), and every g_c comes from the last one in one step,
+//     g_c[u] = sum_v g_{K-1}[u v] T_c[v].
+// One path of 65 537 points at d = 4, N = 6: 232 us in 512 stretches; with the chains 1377 us in 64, their best.
+// This file holds the plumbing around the gradient kernels: copying the stretches out as paths of their own (m + 1 points, the
+// last point of a path repeated where the last stretch is short: increments of zero change no signature), the step from
+// g_{K-1} to every g_c, and adding the stretches' point gradients up (a point shared by two stretches ends an increment of
+// one and starts one of the other; the repeated last points sum to the gradient of the increment that ends at the real one).
 #include "sig_internal.h"
 #include "sig_lane_ops.h"
 
@@ -41,31 +46,13 @@ sig_stretch_gather_kernel(Shape sh, int64_t K, int64_t m, const T *__restrict__ 
     }
 }
 
-// dst[r][0 .. len) = src[r][0 .. len) for `rows` rows that lie src_stride and dst_stride scalars apart
-template <typename T>
-__global__ void __launch_bounds__(256)
-sig_copy_rows_kernel(const T *__restrict__ src, int64_t src_stride, T *__restrict__ dst, int64_t dst_stride, int64_t len, int64_t rows)
-{
-    const int64_t total = rows * len;
-    for (int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x; e < total; e += int64_t(gridDim.x) * 256) {
-        const int64_t r = e / len, i = e - r * len;
-        dst[r * dst_stride + i] = src[r * src_stride + i];
-    }
-}
-
-// How the words of each level are spread over a wavefront's lanes in the chain of gradients: a word of level i sums
-// sum_{j = 1 .. N - i} d^j products, and teams of 2^team_log2[i] lanes (1, 4, 16 or 64) share a word's sums.
-struct ChainTeams {
+// How the words of each level are spread over a wavefront's lanes: a word of level i sums sum_{j = 1 .. N - i} d^j products,
+// and teams of 2^team_log2[i] lanes (1, 4, 16 or 64) share a word's sums.
+struct AdjointTeams {
     unsigned char team_log2[SIG_MAX_DEPTH + 1];
 };
 
-// gout = the gradient gin carried through the right multiplication by the signature cs.  For a word u of level i the
-// sum over the words v of level j is a dot product of d^j consecutive scalars of level i + j of gin with level j of cs.
-// An item is a wavefront's worth of teams of one level; the calling wavefront takes the items item0, item0 + step, .. of
-// every level (STEP > 0: step is that constant, and the levels' items are dealt out in turn so that no wavefront is
-// always first).  The order of the additions is fixed.  The result goes to gout and, if given, to gout2 as well.
-// `lv` is the level table in LDS (see below): d^j and the offsets of levels j and i + j are built up as j grows.
-struct ChainLevels {
+struct AdjointLevels {
     int words[SIG_MAX_DEPTH + 2];   // d^i
     int off[SIG_MAX_DEPTH + 2];     // offset of level i; off[N + 1] = S
     int team_log2[SIG_MAX_DEPTH + 2];
@@ -73,7 +60,7 @@ struct ChainLevels {
 
 // The level tables as 32-bit numbers in LDS (S < 2^31), written by one thread at positions known at compile time: the
 // shape sits in scalar registers, where a run-time index would move it to scratch memory.  Needs a barrier after it.
-__device__ __forceinline__ void chain_levels_fill(const Shape &sh, const ChainTeams &teams, ChainLevels *lv)
+__device__ __forceinline__ void adjoint_levels_fill(const Shape &sh, const AdjointTeams &teams, AdjointLevels *lv)
 {
     if (threadIdx.x == 0) {
 #pragma unroll
@@ -86,8 +73,13 @@ __device__ __forceinline__ void chain_levels_fill(const Shape &sh, const ChainTe
     }
 }
 
+// gout = the gradient gin carried through the right multiplication by the signature cs.  For a word u of level i the
+// sum over the words v of level j is a dot product of d^j consecutive scalars of level i + j of gin with level j of cs.
+// An item is a wavefront's worth of teams of one level; the calling wavefront takes the items item0, item0 + step, .. of
+// every level (STEP > 0: step is that constant, and the levels' items are dealt out in turn so that no wavefront is
+// always first).  The order of the additions is fixed.
 template <typename T, int STEP>
-__device__ __forceinline__ void stretch_adjoint_items(int N, int d, const ChainLevels *lv, const T *gin, const T *cs, T *gout, T *gout2,
+__device__ __forceinline__ void stretch_adjoint_items(int N, int d, const AdjointLevels *lv, const T *gin, const T *cs, T *gout,
                                                       int item0, int step_runtime)
 {
     const int lane = threadIdx.x & 63;
@@ -115,75 +107,57 @@ __device__ __forceinline__ void stretch_adjoint_items(int N, int d, const ChainL
                 }
             }
             for (int hop = team >> 1; hop >= 1; hop >>= 1) acc += __shfl_xor(acc, hop, 64);   // the same for every lane
-            if (on && member == 0) {
-                acc += gin[base + word];
-                gout[base + word] = acc;
-                if (gout2 != nullptr) gout2[base + word] = acc;
-            }
+            if (on && member == 0) gout[base + word] = acc + gin[base + word];
         }
         if (STEP > 0) dealt = (dealt + items) & (STEP - 1);
     }
 }
 
-// One step of the chain, g[b][c - 1] from g[b][c] and C[b][c], spread over the grid (rows of K signatures per path).
-template <typename T>
-__global__ void __launch_bounds__(256)
-sig_stretch_adjoint_kernel(Shape sh, ChainTeams teams, int64_t K, int64_t c, const T *__restrict__ C, T *g)
+// g[b][c] = the gradient g_last[b] carried through the right multiplication by F[b][c]; the last stretch has nothing
+// after it and takes g_last as it is.  A workgroup of WAVES wavefronts per stretch holds g_last and the levels of F that
+// take part (below N: `used` scalars) in LDS.
+template <typename T, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES)
+sig_stretch_adjoint_all_kernel(Shape sh, AdjointTeams teams, int64_t K, int used, const T *__restrict__ F, const T *__restrict__ g_last,
+                               T *__restrict__ g)
 {
-    __shared__ ChainLevels lv;
-    chain_levels_fill(sh, teams, &lv);
+    extern __shared__ __align__(16) unsigned char adjoint_smem[];
+    __shared__ AdjointLevels lv;
+    const int S = int(sh.S), tid = threadIdx.x;
+    const int64_t r = blockIdx.x, b = r / K;
+    T *gl = reinterpret_cast<T *>(adjoint_smem), *fl = gl + S;
+    const T *g_row = g_last + b * sh.S, *f_row = F + r * sh.S;
+    T *out = g + r * sh.S;
+    if (r - b * K == K - 1) {
+        for (int e = tid; e < S; e += 64 * WAVES) out[e] = g_row[e];
+        return;
+    }
+    adjoint_levels_fill(sh, teams, &lv);
+    for (int e = tid; e < S; e += 64 * WAVES) gl[e] = g_row[e];
+    for (int e = tid; e < used; e += 64 * WAVES) fl[e] = f_row[e];
     __syncthreads();
-    const int64_t b = blockIdx.y;
-    stretch_adjoint_items<T, 0>(sh.N, sh.d, &lv, g + (b * K + c) * sh.S, C + (b * K + c) * sh.S, g + (b * K + c - 1) * sh.S, nullptr,
-                                int(blockIdx.x) * 4 + (threadIdx.x >> 6), int(gridDim.x) * 4);
+    stretch_adjoint_items<T, WAVES>(sh.N, sh.d, &lv, gl, fl, out, tid >> 6, WAVES);
 }
 
-constexpr int kChainPerThread = 8;   // scalars of a stretch's signature a thread fetches ahead: `used` <= 8192
-
-// The whole chain of a path in one workgroup of 16 wavefronts, while two gradients and the `used` scalars of a signature
-// that take part (its levels below N) fit the LDS: the
-// gradient being carried stays in LDS (two buffers take turns as source and result), the next stretch's signature is
-// fetched into registers while the current step computes, and the barriers order LDS traffic only, so a step waits
-// for no memory access but its own signature's arrival.
+// The same straight from memory, for signatures that do not fit the LDS: the items of a stretch are spread over the grid.
 template <typename T>
-__global__ void __launch_bounds__(1024)
-sig_stretch_adjoint_chain_kernel(Shape sh, ChainTeams teams, int64_t K, int used, const T *__restrict__ C, T *__restrict__ g)
+__global__ void __launch_bounds__(256)
+sig_stretch_adjoint_each_kernel(Shape sh, AdjointTeams teams, int64_t rows, int64_t K, const T *__restrict__ F,
+                                const T *__restrict__ g_last, T *__restrict__ g)
 {
-    extern __shared__ __align__(16) unsigned char chain_smem[];
-    __shared__ ChainLevels lv;
-    chain_levels_fill(sh, teams, &lv);   // the barrier of the first step comes before its first use
-    const int S = int(sh.S), tid = threadIdx.x;
-    T *from = reinterpret_cast<T *>(chain_smem), *to = from + S, *cl = to + S;
-    const int64_t b = blockIdx.x;
-    // of a stretch's signature the levels below N are used: the words v of the sums have at most N - 1 letters
-    T creg[kChainPerThread];
-    const T *c_next = C + (b * K + K - 1) * sh.S, *g_last = g + (b * K + K - 1) * sh.S;
-#pragma unroll
-    for (int r = 0; r < kChainPerThread; ++r) {
-        const int e = tid + 1024 * r;
-        creg[r] = e < used ? c_next[e] : T(0);
-    }
-    for (int e = tid; e < S; e += 1024) from[e] = g_last[e];
-    for (int64_t c = K - 1; c >= 1; --c) {
-#pragma unroll
-        for (int r = 0; r < kChainPerThread; ++r) {
-            const int e = tid + 1024 * r;
-            if (e < used) cl[e] = creg[r];
+    __shared__ AdjointLevels lv;
+    adjoint_levels_fill(sh, teams, &lv);
+    __syncthreads();
+    for (int64_t r = blockIdx.y; r < rows; r += gridDim.y) {
+        const int64_t b = r / K;
+        const T *g_row = g_last + b * sh.S;
+        T *out = g + r * sh.S;
+        if (r - b * K == K - 1) {
+            for (int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x; e < sh.S; e += int64_t(gridDim.x) * 256) out[e] = g_row[e];
+            continue;
         }
-        lds_barrier();
-        if (c > 1) {
-            c_next = C + (b * K + c - 1) * sh.S;
-#pragma unroll
-            for (int r = 0; r < kChainPerThread; ++r) {
-                const int e = tid + 1024 * r;
-                creg[r] = e < used ? c_next[e] : T(0);
-            }
-        }
-        stretch_adjoint_items<T, 16>(sh.N, sh.d, &lv, from, cl, to, g + (b * K + c - 1) * sh.S, tid >> 6, 16);
-        lds_barrier();
-        T *spare = from;
-        from = to;
-        to = spare;
+        stretch_adjoint_items<T, 0>(sh.N, sh.d, &lv, g_row, F + r * sh.S, out, int(blockIdx.x) * 4 + (threadIdx.x >> 6),
+                                    int(gridDim.x) * 4);
     }
 }
 
@@ -235,19 +209,11 @@ hipError_t stretch_gather(const Shape &sh, int64_t K, int64_t m, const T *path, 
     return hipGetLastError();
 }
 
-template <typename T>
-hipError_t copy_rows(const T *src, int64_t src_stride, T *dst, int64_t dst_stride, int64_t len, int64_t rows, hipStream_t st)
+// The teams of every level, and how many items they make in all.
+AdjointTeams adjoint_teams(const Shape &sh, int64_t &items)
 {
-    hipLaunchKernelGGL((sig_copy_rows_kernel<T>), dim3(grid_for(rows * len)), dim3(256), 0, st, src, src_stride, dst, dst_stride, len, rows);
-    return hipGetLastError();
-}
-
-template <typename T>
-hipError_t stretch_adjoint_chain(const Shape &sh, int64_t K, const T *C, T *g, hipStream_t st)
-{
-    if (K < 2) return hipSuccess;
-    ChainTeams teams;
-    int64_t items = 0;
+    AdjointTeams teams;
+    items = 0;
     for (int i = 0; i <= SIG_MAX_DEPTH; ++i) teams.team_log2[i] = 0;
     for (int i = 1; i <= sh.N; ++i) {
         int64_t cost = 0;
@@ -256,22 +222,29 @@ hipError_t stretch_adjoint_chain(const Shape &sh, int64_t K, const T *C, T *g, h
         const int64_t per_item = 64 >> teams.team_log2[i];
         items += (sh.pw[i] + per_item - 1) / per_item;
     }
-    const int64_t paths = sh.B / K;   // sh.B counts stretches
-    const int64_t used = sh.off[sh.N];   // levels 1 .. N - 1 of a stretch's signature
-    const size_t lds = (2 * size_t(sh.S) + size_t(used)) * sizeof(T);
-    if (lds + sizeof(ChainLevels) <= 64 * 1024 && used <= 1024 * kChainPerThread) {
-        hipLaunchKernelGGL((sig_stretch_adjoint_chain_kernel<T>), dim3(unsigned(paths)), dim3(1024), lds, st, sh, teams, K, int(used), C,
-                           g);
+    return teams;
+}
+
+template <typename T>
+hipError_t stretch_adjoint_all(const Shape &sh, int64_t K, const T *F, const T *g_last, T *g, hipStream_t st)
+{
+    int64_t items = 0;
+    const AdjointTeams teams = adjoint_teams(sh, items);
+    const int64_t used = sh.off[sh.N];
+    const size_t lds = (size_t(sh.S) + size_t(used)) * sizeof(T);
+    if (lds + sizeof(AdjointLevels) <= 64 * 1024 && sh.B <= 0x7fffffff) {
+        if (sh.S >= 1024)
+            hipLaunchKernelGGL((sig_stretch_adjoint_all_kernel<T, 16>), dim3(unsigned(sh.B)), dim3(1024), lds, st, sh, teams, K, int(used),
+                               F, g_last, g);
+        else
+            hipLaunchKernelGGL((sig_stretch_adjoint_all_kernel<T, 4>), dim3(unsigned(sh.B)), dim3(256), lds, st, sh, teams, K, int(used), F,
+                               g_last, g);
         return hipGetLastError();
     }
     const int64_t groups = (items + 3) / 4;
-    const dim3 grid(unsigned(groups < 4096 ? groups : 4096), unsigned(paths));
-    for (int64_t c = K - 1; c >= 1; --c) {
-        hipLaunchKernelGGL((sig_stretch_adjoint_kernel<T>), grid, dim3(256), 0, st, sh, teams, K, c, C, g);
-        const hipError_t err = hipGetLastError();
-        if (err != hipSuccess) return err;
-    }
-    return hipSuccess;
+    const dim3 grid(unsigned(groups < 4096 ? groups : 4096), unsigned(sh.B < 65535 ? sh.B : 65535));
+    hipLaunchKernelGGL((sig_stretch_adjoint_each_kernel<T>), grid, dim3(256), 0, st, sh, teams, sh.B, K, F, g_last, g);
+    return hipGetLastError();
 }
 
 template <typename T>
@@ -290,18 +263,13 @@ hipError_t launch_stretch_gather(const Shape &sh, sig_dtype dtype, int64_t K, in
                             : stretch_gather(sh, K, m, static_cast<const double *>(path), static_cast<double *>(rows), st);
 }
 
-hipError_t launch_copy_rows(sig_dtype dtype, const void *src, int64_t src_stride, void *dst, int64_t dst_stride, int64_t len,
-                            int64_t rows, hipStream_t st)
+hipError_t launch_stretch_adjoint_all(const Shape &sh, sig_dtype dtype, int64_t K, const void *F, const void *g_last, void *g,
+                                      hipStream_t st)
 {
-    return dtype == SIG_F32
-               ? copy_rows(static_cast<const float *>(src), src_stride, static_cast<float *>(dst), dst_stride, len, rows, st)
-               : copy_rows(static_cast<const double *>(src), src_stride, static_cast<double *>(dst), dst_stride, len, rows, st);
-}
-
-hipError_t launch_stretch_adjoint_chain(const Shape &sh, sig_dtype dtype, int64_t K, const void *C, void *g, hipStream_t st)
-{
-    return dtype == SIG_F32 ? stretch_adjoint_chain(sh, K, static_cast<const float *>(C), static_cast<float *>(g), st)
-                            : stretch_adjoint_chain(sh, K, static_cast<const double *>(C), static_cast<double *>(g), st);
+    return dtype == SIG_F32 ? stretch_adjoint_all(sh, K, static_cast<const float *>(F), static_cast<const float *>(g_last),
+                                                  static_cast<float *>(g), st)
+                            : stretch_adjoint_all(sh, K, static_cast<const double *>(F), static_cast<const double *>(g_last),
+                                                  static_cast<double *>(g), st);
 }
 
 hipError_t launch_stretch_scatter(const Shape &sh, sig_dtype dtype, int64_t K, int64_t m, const void *grows, void *gpath, void *gbase,

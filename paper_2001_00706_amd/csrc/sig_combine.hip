@@ -7,6 +7,7 @@
 // Consecutive threads share the prefix (one broadcast read of a) and walk consecutive suffixes
 // (coalesced reads of b), so the kernel runs at memory speed: 3 S scalars per path.
 #include "sig_internal.h"
+#include "sig_product.h"
 
 namespace sig {
 namespace {
@@ -19,73 +20,26 @@ struct Strides {
     int64_t a_outer, b_outer, out_outer;  // outer strides
 };
 
-// D: the channel count when it is one of the common ones (division by a constant is a multiply
-// and a shift), 0 for any other d (division by the runtime value).
-template <typename T, int D>
+// D: the channel count when it is one of the common ones (division by a constant is a multiply and a shift), 0 for any
+// other d (division by the runtime value).
+// V = several consecutive words per thread that differ only in their last letter: each term is one broadcast scalar of `a`
+// times consecutive scalars of `b`, and the letters are worked out once for all of them.  Four words, moved as vectors, for
+// channel counts that are multiples of 4 (then every level size and offset is a multiple of 4 too), else all d words of a
+// prefix: 0.6 the time of a word per thread at d = 5 and 7 (tree of products, 128 paths).
+template <typename T, typename V, int D>
 __global__ void __launch_bounds__(256)
 sig_combine_kernel(Shape sh, Strides rs, const T *__restrict__ a, const T *__restrict__ b, T *__restrict__ out)
 {
-    const uint32_t S = uint32_t(sh.S);
-    const int N = sh.N;
-    const uint32_t d = D > 0 ? uint32_t(D) : uint32_t(sh.d);
+    constexpr uint32_t kWords = sizeof(V) / sizeof(T);
+    static_assert(kWords == 1 || D % kWords == 0, "the words of a thread share their prefix");
+    const uint32_t n = uint32_t(sh.S) / kWords;
     for (int64_t p = blockIdx.y; p < sh.B; p += gridDim.y) {
         const int64_t q = p / rs.n_inner, r = p - q * rs.n_inner;
         const T *ap = a + q * rs.a_outer + r * rs.a;
         const T *bp = b + q * rs.b_outer + r * rs.b;
         T *op = out + q * rs.out_outer + r * rs.out;
-        for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < S; i += gridDim.x * blockDim.x) {
-            int k = 1;
-            while (k < N && i >= uint32_t(sh.off[k + 1])) ++k;
-            const uint32_t idx = i - uint32_t(sh.off[k]);
-            T acc = ap[i] + bp[i];
-            // peel letters off the end of the word: prefix w_1..w_j and suffix w_{j+1}..w_k, j = k-1 .. 1
-            uint32_t prefix = idx, suffix = 0, scale = 1;
-            for (int j = k - 1; j >= 1; --j) {
-                const uint32_t letter = prefix % d;
-                prefix /= d;
-                suffix += letter * scale;
-                scale *= d;
-                acc += ap[uint32_t(sh.off[j]) + prefix] * bp[uint32_t(sh.off[k - j]) + suffix];
-            }
-            op[i] = acc;
-        }
-    }
-}
-
-// Four consecutive words per thread, for channel counts that are multiples of 4 (then every level
-// size and offset is a multiple of 4 too): the four words differ only in their last letter, so each
-// term is one broadcast scalar of `a` times four consecutive scalars of `b`, and all traffic moves
-// in 4-scalar vectors.
-template <typename T, int D>
-__global__ void __launch_bounds__(256)
-sig_combine_vec4_kernel(Shape sh, Strides rs, const T *__restrict__ a, const T *__restrict__ b, T *__restrict__ out)
-{
-    static_assert(D % 4 == 0, "vector path needs d to be a multiple of 4");
-    typedef T T4 __attribute__((ext_vector_type(4)));
-    const uint32_t S4 = uint32_t(sh.S) / 4;
-    const int N = sh.N;
-    for (int64_t p = blockIdx.y; p < sh.B; p += gridDim.y) {
-        const int64_t q = p / rs.n_inner, r = p - q * rs.n_inner;
-        const T *ap = a + q * rs.a_outer + r * rs.a;
-        const T *bp = b + q * rs.b_outer + r * rs.b;
-        T *op = out + q * rs.out_outer + r * rs.out;
-        for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < S4; v += gridDim.x * blockDim.x) {
-            const uint32_t i = 4 * v;
-            int k = 1;
-            while (k < N && i >= uint32_t(sh.off[k + 1])) ++k;
-            const uint32_t idx = i - uint32_t(sh.off[k]);
-            T4 acc = *reinterpret_cast<const T4 *>(ap + i) + *reinterpret_cast<const T4 *>(bp + i);
-            uint32_t prefix = idx, suffix = 0, scale = 1;
-            for (int j = k - 1; j >= 1; --j) {
-                const uint32_t letter = prefix % D;   // for j = k-1 this is the (4-aligned) last letter
-                prefix /= D;
-                suffix += letter * scale;
-                scale *= D;
-                acc += ap[uint32_t(sh.off[j]) + prefix] *
-                       *reinterpret_cast<const T4 *>(bp + uint32_t(sh.off[k - j]) + suffix);
-            }
-            *reinterpret_cast<T4 *>(op + i) = acc;
-        }
+        for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x)
+            *reinterpret_cast<V *>(op + kWords * v) = product_word<T, V, D>(ap, bp, kWords * v, uint32_t(sh.d));
     }
 }
 
@@ -113,23 +67,25 @@ hipError_t launch_combine(const Shape &sh, const T *a, const T *b, T *out, hipSt
     const bool aligned = (reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b) | reinterpret_cast<uintptr_t>(out)) %
                                  (4 * sizeof(T)) == 0 &&
                          (rs.a | rs.b | rs.out | rs.a_outer | rs.b_outer | rs.out_outer) % 4 == 0;
+    typedef typename Four<T>::type V4;
     if (aligned && (sh.d == 4 || sh.d == 8 || sh.d == 16)) {
         const dim3 grid4(unsigned((sh.S / 4 + 255) / 256 < 4096 ? (sh.S / 4 + 255) / 256 : 4096), by);
-        if (sh.d == 4) hipLaunchKernelGGL((sig_combine_vec4_kernel<T, 4>), grid4, block, 0, st, sh, rs, a, b, out);
-        if (sh.d == 8) hipLaunchKernelGGL((sig_combine_vec4_kernel<T, 8>), grid4, block, 0, st, sh, rs, a, b, out);
-        if (sh.d == 16) hipLaunchKernelGGL((sig_combine_vec4_kernel<T, 16>), grid4, block, 0, st, sh, rs, a, b, out);
+        if (sh.d == 4) hipLaunchKernelGGL((sig_combine_kernel<T, V4, 4>), grid4, block, 0, st, sh, rs, a, b, out);
+        if (sh.d == 8) hipLaunchKernelGGL((sig_combine_kernel<T, V4, 8>), grid4, block, 0, st, sh, rs, a, b, out);
+        if (sh.d == 16) hipLaunchKernelGGL((sig_combine_kernel<T, V4, 16>), grid4, block, 0, st, sh, rs, a, b, out);
         return hipGetLastError();
     }
+    const dim3 grid_d(unsigned((sh.S / sh.d + 255) / 256 < 4096 ? (sh.S / sh.d + 255) / 256 : 4096), by);
     switch (sh.d) {
-        case 2: hipLaunchKernelGGL((sig_combine_kernel<T, 2>), grid, block, 0, st, sh, rs, a, b, out); break;
-        case 3: hipLaunchKernelGGL((sig_combine_kernel<T, 3>), grid, block, 0, st, sh, rs, a, b, out); break;
-        case 4: hipLaunchKernelGGL((sig_combine_kernel<T, 4>), grid, block, 0, st, sh, rs, a, b, out); break;
-        case 5: hipLaunchKernelGGL((sig_combine_kernel<T, 5>), grid, block, 0, st, sh, rs, a, b, out); break;
-        case 6: hipLaunchKernelGGL((sig_combine_kernel<T, 6>), grid, block, 0, st, sh, rs, a, b, out); break;
-        case 7: hipLaunchKernelGGL((sig_combine_kernel<T, 7>), grid, block, 0, st, sh, rs, a, b, out); break;
-        case 8: hipLaunchKernelGGL((sig_combine_kernel<T, 8>), grid, block, 0, st, sh, rs, a, b, out); break;
-        case 16: hipLaunchKernelGGL((sig_combine_kernel<T, 16>), grid, block, 0, st, sh, rs, a, b, out); break;
-        default: hipLaunchKernelGGL((sig_combine_kernel<T, 0>), grid, block, 0, st, sh, rs, a, b, out); break;
+        case 2: hipLaunchKernelGGL((sig_combine_kernel<T, Siblings<T, 2>, 2>), grid_d, block, 0, st, sh, rs, a, b, out); break;
+        case 3: hipLaunchKernelGGL((sig_combine_kernel<T, Siblings<T, 3>, 3>), grid_d, block, 0, st, sh, rs, a, b, out); break;
+        case 4: hipLaunchKernelGGL((sig_combine_kernel<T, T, 4>), grid, block, 0, st, sh, rs, a, b, out); break;
+        case 5: hipLaunchKernelGGL((sig_combine_kernel<T, Siblings<T, 5>, 5>), grid_d, block, 0, st, sh, rs, a, b, out); break;
+        case 6: hipLaunchKernelGGL((sig_combine_kernel<T, Siblings<T, 6>, 6>), grid_d, block, 0, st, sh, rs, a, b, out); break;
+        case 7: hipLaunchKernelGGL((sig_combine_kernel<T, Siblings<T, 7>, 7>), grid_d, block, 0, st, sh, rs, a, b, out); break;
+        case 8: hipLaunchKernelGGL((sig_combine_kernel<T, T, 8>), grid, block, 0, st, sh, rs, a, b, out); break;
+        case 16: hipLaunchKernelGGL((sig_combine_kernel<T, T, 16>), grid, block, 0, st, sh, rs, a, b, out); break;
+        default: hipLaunchKernelGGL((sig_combine_kernel<T, T, 0>), grid, block, 0, st, sh, rs, a, b, out); break;
     }
     return hipGetLastError();
 }

@@ -96,12 +96,21 @@ hipError_t launch_gather_f32(const Shape &sh, const float *in, const int64_t *in
 hipError_t launch_gather_f64(const Shape &sh, const double *in, const int64_t *index, int64_t n, double *out, hipStream_t st);
 int64_t lyndon_indices_host(const Shape &sh, int64_t *indices, int64_t cap);
 
+// Products along a binary tree of the K >= 2 signatures C of each path, [paths][K][S] (sh: d, N, S; see
+// sig_product_tree.hip).  Scan: I = the products of every path's first 1, 2, .. K signatures, F = of those behind each of them
+// ([paths][K][S] both; what the last row of F holds afterwards is undefined).  Reduce: out [paths][S] = the product of
+// all K; C is overwritten, `spare` is scratch memory for (K + 1) / 2 rows per path.
+hipError_t launch_product_scan(const Shape &sh, sig_dtype dtype, int64_t paths, int64_t K, const void *C, void *I, void *F,
+                               hipStream_t st);
+hipError_t launch_product_reduce(const Shape &sh, sig_dtype dtype, int64_t paths, int64_t K, void *C, void *spare, void *out,
+                                 hipStream_t st);
+
 // Plumbing of the gradient computed stretch by stretch (sig_backward_chunked.hip); `sh` is the whole call's shape
-// except for the chain, which takes the shape of the B K stretches.  K stretches of m increments per path.
+// except for the adjoint, which takes the shape of the B K stretches.  K stretches of m increments per path.
 hipError_t launch_stretch_gather(const Shape &sh, sig_dtype dtype, int64_t K, int64_t m, const void *path, void *rows, hipStream_t st);
-hipError_t launch_copy_rows(sig_dtype dtype, const void *src, int64_t src_stride, void *dst, int64_t dst_stride, int64_t len,
-                            int64_t rows, hipStream_t st);
-hipError_t launch_stretch_adjoint_chain(const Shape &sh, sig_dtype dtype, int64_t K, const void *C, void *g, hipStream_t st);
+// The gradients with respect to every S_c from the one with respect to the last, g_last [B][S], through the T_c.
+hipError_t launch_stretch_adjoint_all(const Shape &sh, sig_dtype dtype, int64_t K, const void *F, const void *g_last, void *g,
+                                      hipStream_t st);
 hipError_t launch_stretch_scatter(const Shape &sh, sig_dtype dtype, int64_t K, int64_t m, const void *grows, void *gpath, void *gbase,
                                   hipStream_t st);
 

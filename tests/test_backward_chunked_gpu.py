@@ -54,6 +54,29 @@ def test_stretches_walked_back_side_by_side(B, L, d, N, chunks, dtype):
     check(brownian_paths(B, L, d, seed=L + d).astype(dtype), N, chunks)
 
 
+# the tree of products: counts next to powers of two (a last node without a neighbour on one or several levels), the first
+# counts whose rounds no longer fit the single launch at the top (68 | 69 signatures of 120 scalars, 24 | 25 of 340, 11 | 12 of
+# 1456 in rows of several paths), levels moved as vectors (d = 4, 12), as whole groups of siblings (d = 3, 7) and word by word (d = 13)
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("B,L,d,N,chunks", [
+    (2, 138, 3, 4, 137), (3, 70, 3, 4, 69), (2, 69, 3, 4, 68), (1, 35, 3, 4, 17), (1, 258, 2, 3, 257), (2, 66, 4, 4, 65),
+    (2, 26, 4, 4, 25), (1, 66, 13, 2, 33), (2, 24, 13, 3, 23), (1, 40, 12, 3, 13), (2, 35, 7, 3, 34), (1, 47, 7, 4, 23),
+])
+def test_tree_of_products(B, L, d, N, chunks, dtype):
+    check(brownian_paths(B, L, d, seed=L + d).astype(dtype), N, chunks)
+
+
+def test_fastest_count():
+    h = sig.sig_backward_chunks_fastest
+    for B, L, d, N in ((1, 65537, 4, 6), (2, 4000, 6, 3), (32, 801, 8, 4)):
+        chunks = h(B, L, d, N)
+        assert chunks >= 4 and chunks & (chunks - 1) == 0 and (L - 1) // chunks >= 16
+        assert sig.sig_backward_chunked_workspace_bytes(B, L, d, N, False, chunks) <= 2 << 30
+    assert h(1024, 128, 4, 6) == 1 and h(1, 100000, 4, 2) == 1 and h(1, 100, 4, 4) == 1   # many, depth 2, short
+    assert h(2, 1, 3, 4) == 0 and h(1, 100, 0, 4) == 0
+    check(brownian_paths(2, 1500, 3, seed=4), 4, h(2, 1500, 3, 4))
+
+
 @pytest.mark.parametrize("B,L,d,N,chunks", [(2, 64, 3, 4, 4), (1, 65, 4, 4, 8), (3, 30, 5, 3, 7), (2, 9, 2, 5, 9)])
 def test_with_the_origin_as_basepoint(B, L, d, N, chunks):
     check(brownian_paths(B, L, d, seed=3).astype(np.float64) + 0.3, N, chunks, basepoint=True)
