@@ -18,9 +18,10 @@
 // that prefix does), and of the cotangent of a prefix only the part that arrived through its own words; the map from
 // cotangents to the gradient is linear, so only the increments' gradients are ever summed.
 //
-// The per-increment gradients go to a workspace [B][n_inc][16]; the closing kernel of the prefix-tree family turns
+// The per-increment gradients go to a workspace [B][n_inc][16]; `launch_increment_sums` turns
 // them into point gradients (a point ends one increment and starts the next).
-#include "sig_tree_backward_impl.h"
+#include "sig_internal.h"
+#include "sig_lane_ops.h"
 
 namespace sig {
 namespace {
@@ -223,11 +224,7 @@ hipError_t launch_backward_d16_f32(const Shape &sh, const float *path, const flo
                        sh.n_inc, sh.basepoint, static_cast<const float *>(sh.basepoint_value));
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    const int64_t total = sh.B * (sh.n_inc + 1) * kD16;
-    const unsigned grid = unsigned((total + 255) / 256 < 65536 ? (total + 255) / 256 : 65536);
-    hipLaunchKernelGGL((sig_tree_backward_reduce_kernel<float, kD16>), dim3(grid), dim3(256), 0, st, sh, int64_t(1), gz, gpath,
-                       gbase);
-    return hipGetLastError();
+    return launch_increment_sums<float>(sh, 1, gz, gpath, gbase, st);
 }
 
 }  // namespace sig

@@ -14,7 +14,11 @@
 // word.  They meet as follows: a transposing butterfly over the lane quad leaves lane w_3 with the quad's sum of
 // channel w_3; its own w_3 term joins as it stands; the quad's sums of the w_2 and w_1 terms join in the lane whose
 // w_3 equals that letter; two row rotations sum the four quads of a row; rows and wavefronts meet in LDS once per tile.
-#include "sig_tree_backward_impl.h"
+//
+// Two paths share a workgroup, so that its four wavefronts go to the four SIMDs of a compute unit: with a workgroup per path
+// (two wavefronts) the SIMDs ended up with one to three each, depending on what ran before.
+#include "sig_internal.h"
+#include "sig_lane_ops.h"
 
 namespace sig {
 namespace {
@@ -22,7 +26,9 @@ namespace {
 constexpr int kOffD4[8] = {0, 0, 4, 20, 84, 340, 1364, 5460};   // offset of level k (1-based); [7] = S(4, 6)
 constexpr int kS46 = 5460;
 constexpr int kG4Tile = 32;      // increments per tile
-constexpr int kG4Threads = 128;
+constexpr int kG4PathThreads = 128;
+constexpr int kG4Paths = 2;      // paths per workgroup
+constexpr int kG4Threads = kG4Paths * kG4PathThreads;
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
@@ -34,15 +40,19 @@ __device__ __forceinline__ float dpp_move(float v)
 
 __global__ void __launch_bounds__(kG4Threads)
 sig_backward_d4_n6_kernel(const float *__restrict__ path, const float *__restrict__ sig, const float *__restrict__ gout,
-                          float *__restrict__ gz, int64_t L, int64_t n_inc, int basepoint, const float *__restrict__ bpv)
+                          float *__restrict__ gz, int64_t B, int64_t L, int64_t n_inc, int basepoint, const float *__restrict__ bpv)
 {
-    __shared__ __align__(16) float zt[kG4Tile * 4];                 // increments of the tile
-    __shared__ float part[kG4Tile * 2 * 4 * 4];                     // [increment][wavefront][row][channel]
+    __shared__ __align__(16) float zt_all[kG4Paths][kG4Tile * 4];   // increments of the tile
+    __shared__ float part_all[kG4Paths][kG4Tile * 2 * 4 * 4];       // [increment][wavefront][row][channel]
 
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int slot = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / kG4PathThreads);
+    const int tid = threadIdx.x % kG4PathThreads, lane = tid & 63;
+    float *zt = zt_all[slot], *part = part_all[slot];
     const int h = __builtin_amdgcn_readfirstlane(tid >> 6);         // wavefront: fourth letters 2h, 2h + 1
     const int w1 = lane >> 4, w2 = (lane >> 2) & 3, w3 = lane & 3;
-    const int64_t b = blockIdx.x;
+    const int64_t row = int64_t(blockIdx.x) * kG4Paths + slot;
+    const bool live = row < B;                                      // an odd path out: its neighbour repeats it, unwritten
+    const int64_t b = live ? row : B - 1;
     const f4 *x4 = reinterpret_cast<const f4 *>(path) + b * L;
     const float *sg = sig + b * kS46;
     const float *go = gout + b * kS46;
@@ -189,7 +199,7 @@ sig_backward_d4_n6_kernel(const float *__restrict__ path, const float *__restric
         __syncthreads();
         if (tid < kG4Tile * 4) {
             const int i = tid >> 2, c = tid & 3;
-            if (i < nt) {
+            if (i < nt && live) {
                 float total = 0.0f;
 #pragma unroll
                 for (int r = 0; r < 8; ++r) total += part[(i * 8 + r) * 4 + c];
@@ -214,15 +224,11 @@ hipError_t launch_backward_d4n6_f32(const Shape &sh, const float *path, const fl
     if (!backward_d4n6_supported(sh)) return hipErrorNotSupported;
     if (workspace == nullptr || workspace_bytes < backward_d4n6_workspace_bytes(sh)) return hipErrorInvalidValue;
     float *gz = static_cast<float *>(workspace);
-    hipLaunchKernelGGL(sig_backward_d4_n6_kernel, dim3(unsigned(sh.B)), dim3(kG4Threads), 0, st, path, sig, gout, gz, sh.L,
-                       sh.n_inc, sh.basepoint, static_cast<const float *>(sh.basepoint_value));
+    hipLaunchKernelGGL(sig_backward_d4_n6_kernel, dim3(unsigned((sh.B + kG4Paths - 1) / kG4Paths)), dim3(kG4Threads), 0, st, path, sig,
+                       gout, gz, sh.B, sh.L, sh.n_inc, sh.basepoint, static_cast<const float *>(sh.basepoint_value));
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    const int64_t total = sh.B * (sh.n_inc + 1) * 4;
-    const unsigned grid = unsigned((total + 255) / 256 < 65536 ? (total + 255) / 256 : 65536);
-    hipLaunchKernelGGL((sig_tree_backward_reduce_kernel<float, 4>), dim3(grid), dim3(256), 0, st, sh, int64_t(1), gz, gpath,
-                       gbase);
-    return hipGetLastError();
+    return launch_increment_sums<float>(sh, 1, gz, gpath, gbase, st);
 }
 
 }  // namespace sig

@@ -1,0 +1,117 @@
+// The last step of the gradient kernels that leave partial gradients per increment: their sums, and from the increments'
+// gradients those of the points (paper section 5.3: z_l = x_{l+1} - x_l, so a point receives the gradient of the increment it
+// ends minus that of the one it starts).
+//
+// partial: [row][n_partials][n_inc][d].  What bounds this is the trip to memory per partial, so eight of them are in flight
+// per thread, and with many partials a workgroup sums a run of a row's scalars once (every point needs two neighbouring
+// increments), SPLIT threads to a scalar: 128 paths of 128 points, d = 4, fp64, 64 partials: 8.6 us; a thread per scalar
+// that adds one term after the other, twice, took 28.  From 16 partials on; with fewer the barriers cost as much as they save.
+#include "sig_internal.h"
+
+namespace sig {
+namespace {
+
+constexpr int kInFlight = 8;
+constexpr int kRun = 128;
+constexpr int kSplit = 8;
+
+// p[0] + p[stride] + .. + p[(count - 1) stride], added in that order
+template <typename T>
+__device__ __forceinline__ T strided_sum(const T *p, int64_t stride, int64_t count)
+{
+    T sum = T(0);
+    for (int64_t g = 0; g < count; g += kInFlight) {
+        T v[kInFlight];
+#pragma unroll
+        for (int i = 0; i < kInFlight; ++i) v[i] = p[(g + i < count ? g + i : g) * stride];   // unconditional: all in flight together
+#pragma unroll
+        for (int i = 0; i < kInFlight; ++i) sum += g + i < count ? v[i] : T(0);
+    }
+    return sum;
+}
+
+// v = scalar f of a row's points, the basepoint among them where there is one
+template <typename T>
+__device__ __forceinline__ void put(const Shape &sh, int64_t row, int64_t f, T v, T *gpath, T *gbase)
+{
+    const int64_t d = sh.d;
+    if (!sh.basepoint)
+        gpath[row * sh.L * d + f] = v;
+    else if (f >= d)
+        gpath[row * sh.L * d + f - d] = v;
+    else if (gbase != nullptr)
+        gbase[row * d + f] = v;
+}
+
+// A thread per scalar of the points.
+template <typename T>
+__global__ void __launch_bounds__(256)
+sig_increment_sums_few_kernel(Shape sh, int64_t n_partials, const T *__restrict__ partial, T *__restrict__ gpath, T *__restrict__ gbase)
+{
+    const int64_t d = sh.d, n = sh.n_inc * d;   // scalars of a row's increments; the points have d more
+    const int64_t f = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (f >= n + d) return;
+    for (int64_t row = blockIdx.y; row < sh.B; row += gridDim.y) {
+        const T *p = partial + row * n_partials * n;
+        T ends, starts;   // of the increment that ends in the point and of the one that starts there
+        if (n_partials == 1) {
+            ends = f >= d ? p[f - d] : T(0);
+            starts = f < n ? p[f] : T(0);
+        } else {
+            ends = f >= d ? strided_sum(p + f - d, n, n_partials) : T(0);
+            starts = f < n ? strided_sum(p + f, n, n_partials) : T(0);
+        }
+        put(sh, row, f, ends - starts, gpath, gbase);
+    }
+}
+
+// kRun scalars of the increments per workgroup, of which kRun - d points' follow (d < kRun).
+template <typename T>
+__global__ void __launch_bounds__(kRun * kSplit)
+sig_increment_sums_kernel(Shape sh, int64_t n_partials, const T *__restrict__ partial, T *__restrict__ gpath, T *__restrict__ gbase)
+{
+    __shared__ T part[kSplit][kRun];
+    const int64_t d = sh.d, n = sh.n_inc * d;
+    const int t = threadIdx.x % kRun, share = threadIdx.x / kRun;
+    const int64_t f = int64_t(blockIdx.x) * (kRun - d) + t;   // scalar of the points
+    const int64_t e = f - d;                                  // the scalar of the increments this thread sums
+    const int64_t per = (n_partials + kSplit - 1) / kSplit, g0 = share * per, left = n_partials - g0;
+    for (int64_t row = blockIdx.y; row < sh.B; row += gridDim.y) {
+        T sum = T(0);
+        if (e >= 0 && e < n && left > 0) sum = strided_sum(partial + (row * n_partials + g0) * n + e, n, left < per ? left : per);
+        part[share][t] = sum;
+        __syncthreads();
+        if (share == 0 && t < kRun - d && f < n + d) {
+            T ends = part[0][t], starts = part[0][t + d];
+#pragma unroll
+            for (int s = 1; s < kSplit; ++s) {
+                ends += part[s][t];
+                starts += part[s][t + d];
+            }
+            put(sh, row, f, ends - starts, gpath, gbase);
+        }
+        __syncthreads();   // the next row's sums overwrite these
+    }
+}
+
+}  // namespace
+
+template <typename T>
+hipError_t launch_increment_sums(const Shape &sh, int64_t n_partials, const T *partial, T *gpath, T *gbase, hipStream_t st)
+{
+    const bool many = n_partials >= 16 && sh.d <= kRun / 2;
+    const int64_t points = (sh.n_inc + 1) * sh.d, per_group = many ? kRun - sh.d : 256;
+    const int64_t groups = (points + per_group - 1) / per_group;
+    if (groups > 0x7fffffff) return hipErrorNotSupported;
+    const dim3 grid(unsigned(groups), unsigned(sh.B < 65535 ? sh.B : 65535));
+    if (many)
+        hipLaunchKernelGGL((sig_increment_sums_kernel<T>), grid, dim3(kRun * kSplit), 0, st, sh, n_partials, partial, gpath, gbase);
+    else
+        hipLaunchKernelGGL((sig_increment_sums_few_kernel<T>), grid, dim3(256), 0, st, sh, n_partials, partial, gpath, gbase);
+    return hipGetLastError();
+}
+
+template hipError_t launch_increment_sums<float>(const Shape &, int64_t, const float *, float *, float *, hipStream_t);
+template hipError_t launch_increment_sums<double>(const Shape &, int64_t, const double *, double *, double *, hipStream_t);
+
+}  // namespace sig

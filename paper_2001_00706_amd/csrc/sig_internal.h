@@ -218,6 +218,11 @@ hipError_t launch_backward_n2_f32(const Shape &sh, const float *path, const floa
 hipError_t launch_backward_n2_f64(const Shape &sh, const double *path, const double *gout, double *gpath, double *gbase,
                                   hipStream_t st);
 
+// gpath (and gbase, may be null) from n_partials partial gradients per increment, partial [B][n_partials][n_inc][d]: their
+// sums, then for every point the sum of the increment it ends minus that of the one it starts.
+template <typename T>
+hipError_t launch_increment_sums(const Shape &sh, int64_t n_partials, const T *partial, T *gpath, T *gbase, hipStream_t st);
+
 // Prefix-tree gradient kernels (d = 2..8 at N = 2..9, d = 9..16 at N = 2..6, any alignment): no communication between threads; the
 // per-increment partial gradients go to a workspace of `tree_backward_workspace_bytes` and are summed by a second
 // kernel.

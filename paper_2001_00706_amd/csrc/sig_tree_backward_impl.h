@@ -329,39 +329,6 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
     }
 }
 
-// gpath[row][point] = (sum of the partial gradients of the increment the point ends) - (of the one it starts);
-// a basepoint only starts increment 0.
-template <typename T, int D>
-__global__ void __launch_bounds__(256)
-sig_tree_backward_reduce_kernel(Shape sh, int64_t n_partials, const T *__restrict__ partial, T *__restrict__ gpath,
-                                T *__restrict__ gbase)
-{
-    const int64_t per_row = (sh.n_inc + 1) * D;   // one extra "increment" -1 / n_inc at the ends
-    const int64_t total = sh.B * per_row;
-    for (int64_t e = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; e < total; e += int64_t(gridDim.x) * blockDim.x) {
-        const int64_t row = e / per_row, rem = e % per_row;
-        const int64_t j = rem / D;   // output slot j: ends increment j-1, starts increment j
-        const int c = int(rem % D);
-        const T *pr = partial + row * n_partials * sh.n_inc * D;
-        T ends = T(0), starts = T(0);
-        for (int64_t g = 0; g < n_partials; ++g) {
-            if (j >= 1) ends += pr[(g * sh.n_inc + (j - 1)) * D + c];
-            if (j < sh.n_inc) starts += pr[(g * sh.n_inc + j) * D + c];
-        }
-        const T v = ends - starts;
-        if (sh.basepoint) {
-            // slot 0 is the basepoint, slot j >= 1 the point j-1
-            if (j == 0) {
-                if (gbase != nullptr) gbase[row * D + c] = v;
-            } else {
-                gpath[(row * sh.L + (j - 1)) * D + c] = v;
-            }
-        } else {
-            gpath[(row * sh.L + j) * D + c] = v;
-        }
-    }
-}
-
 template <typename T, int D, int N>
 hipError_t launch_tb_dn(const Shape &sh, const T *path, const T *sig, const T *gout, T *gpath,
                         T *gbase, T *partial, hipStream_t st)
@@ -377,11 +344,7 @@ hipError_t launch_tb_dn(const Shape &sh, const T *path, const T *sig, const T *g
                            gout, partial);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    const int64_t total = sh.B * (sh.n_inc + 1) * D;
-    const unsigned grid = unsigned((total + 255) / 256 < 65536 ? (total + 255) / 256 : 65536);
-    hipLaunchKernelGGL((sig_tree_backward_reduce_kernel<T, D>), dim3(grid), dim3(256), 0, st, sh, TS::kPartials, partial, gpath,
-                       gbase);
-    return hipGetLastError();
+    return launch_increment_sums<T>(sh, TS::kPartials, partial, gpath, gbase, st);
 }
 
 template <int D, int N>

@@ -337,40 +337,6 @@ sig_wide_backward_kernel(Shape sh, WbPlan pl, const T *__restrict__ path, const 
     }
 }
 
-// gpath[row][point] = (sum of the partial gradients of the increment the point ends) - (of the one it starts);
-// a basepoint only starts increment 0.
-template <typename T>
-__global__ void __launch_bounds__(256)
-sig_wide_backward_reduce_kernel(Shape sh, int64_t n_partials, const T *__restrict__ partial, T *__restrict__ gpath,
-                                T *__restrict__ gbase)
-{
-    const int d = sh.d;
-    const int64_t per_row = (sh.n_inc + 1) * d;   // one extra "increment" -1 / n_inc at the ends
-    const int64_t total = sh.B * per_row;
-    for (int64_t e = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; e < total; e += int64_t(gridDim.x) * blockDim.x) {
-        const int64_t row = e / per_row, rem = e - row * per_row;
-        const int64_t j = rem / d;   // output slot j: ends increment j - 1, starts increment j
-        const int c = int(rem - j * d);
-        const T *pr = partial + row * n_partials * sh.n_inc * d;
-        T ends = T(0), starts = T(0);
-        for (int64_t g = 0; g < n_partials; ++g) {
-            if (j >= 1) ends += pr[(g * sh.n_inc + (j - 1)) * d + c];
-            if (j < sh.n_inc) starts += pr[(g * sh.n_inc + j) * d + c];
-        }
-        const T v = ends - starts;
-        if (sh.basepoint) {
-            // slot 0 is the basepoint, slot j >= 1 the point j - 1
-            if (j == 0) {
-                if (gbase != nullptr) gbase[row * d + c] = v;
-            } else {
-                gpath[(row * sh.L + (j - 1)) * d + c] = v;
-            }
-        } else {
-            gpath[(row * sh.L + j) * d + c] = v;
-        }
-    }
-}
-
 bool wb_plan(const Shape &sh, size_t elem, WbPlan &pl)
 {
     if (sh.N < 2 || sh.N > 9 || sh.d < 1 || sh.chunks > 1 || sh.S >= (int64_t(1) << 31) || sh.n_inc < 1) return false;
@@ -425,11 +391,7 @@ hipError_t launch_wb_t(const Shape &sh, const T *path, const T *sig, const T *go
 #undef SIG_WB_LAUNCH_B
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    const int64_t total = sh.B * (sh.n_inc + 1) * sh.d;
-    const unsigned rgrid = unsigned((total + 255) / 256 < 65536 ? (total + 255) / 256 : 65536);
-    hipLaunchKernelGGL((sig_wide_backward_reduce_kernel<T>), dim3(rgrid), dim3(256), 0, st, sh, pl.groups_per_path, partial, gpath,
-                       gbase);
-    return hipGetLastError();
+    return launch_increment_sums<T>(sh, pl.groups_per_path, partial, gpath, gbase, st);
 }
 
 }  // namespace
