@@ -13,13 +13,29 @@
 //     gradient of an increment is the sum of every thread's contribution.  (The cotangent a prefix has of
 //     its own in the output gradient is given to the first thread below it.)
 //   * That one sum, over all threads of a path and per increment, is finished by a second kernel: every
-//     workgroup (for paths of at most 64 words: every thread) writes its partial sums to a workspace
-//     [row][group][increment][d].
+//     workgroup (for paths of at most one wavefront: every word, or every word of P-1 letters) writes its partial
+//     sums to a workspace [row][group][increment][d].
+//
+// Horner terms and cotangents are carried with their factorials taken out, Hh^(k)_j = T^(k)_j / (k-j)! and
+// Dh^(k)_j = D^(k)_j (k-j)!: then Hh^(k)_j = Hh^(k)_{j-1} z + A_j / (k-j)!, Dh^(k)_{j-1} = Dh^(k)_j z, and a word's contribution to
+// its last letter is sum_k Hh^(k)_{j-1} Dh^(k)_j, with a constant factor left only in A_j / (k-j)! and in what a prefix
+// receives, sum_k Dh^(k)_j / (k-j)!.
+//
+// Up to 8 channels (short paths: where tb_packed_rows says) nothing is summed over lanes while an increment is worked on: a
+// lane leaves its d + P numbers (the subtree's share of every channel, the shares of the word's own letters) in LDS, and
+// after kBatch increments a lane per (increment, group) adds up the rows of a group, the d words that share their first
+// P-1 letters.  There the last letter is known from the row and the others are the group's, so they are sorted into
+// channels once per group and batch, not once per word and increment.  What bounds the kernel is the issue of vector
+// instructions: per wavefront and increment 430 of them at d = N = 7 with the sums formed by lane exchanges, 330 this way
+// (756 -> 545 us for 32 paths of 128 points; d = 5, N = 7: 157 -> 95; d = 6, N = 6: 163 -> 90; 128 paths of 64 points at
+// d = 7, N = 5: 92 -> 46).
 #ifndef SIG_TREE_BACKWARD_IMPL_H_
 #define SIG_TREE_BACKWARD_IMPL_H_
 
 #include "sig_internal.h"
 #include "sig_lane_ops.h"
+
+#include <type_traits>
 
 namespace sig {
 namespace {
@@ -38,50 +54,89 @@ __host__ __device__ constexpr int64_t tb_off(int d, int k)   // offset of level 
     return off;
 }
 
-template <int D, int N>
+// ROWS: the lanes' numbers go through LDS; otherwise sums by lane exchanges.
+template <typename T, int D, int N, bool ROWS>
 struct TbShape {
     // levels kept per thread below its word: two (d + d^2 scalars) up to 8 channels, one (d scalars) beyond
     static constexpr int U = N - 1 < (D <= 8 ? 2 : 1) ? N - 1 : (D <= 8 ? 2 : 1);
     static constexpr int P = N - U;
     static constexpr int64_t kWords = tb_off(D, P + 1) - tb_off(D, P);   // threads a path needs
     static constexpr bool kMulti = kWords >= 256;   // a path spans several workgroups
-    // From 65 words on, a path takes whole wavefronts (2..4, idle lanes at the end), each wavefront sums its lanes'
-    // parts of an increment's gradient and the sums meet in LDS once per tile: one partial sum per path and
-    // workgroup.  Shorter paths are packed thread after thread and every thread writes its own part (summing
-    // over a wavefront costs d x 7 instructions per increment, which a path of one wavefront does not win back).
+    // From 65 words on, a path takes whole wavefronts (2..4, idle lanes at the end), each of which sums up an increment's
+    // gradient, and the sums meet in LDS once per tile: one partial sum per path and workgroup.  Shorter paths are packed
+    // one after the other, and every group or thread writes its own part.
     static constexpr bool kWide = kWords > 64;
+    static constexpr bool kRows = ROWS;
+    // Lanes of a wavefront in use, and the groups of d words they hold.  Packed paths get whole groups; the wavefronts
+    // of a longer path take 64 words each, so that a group may be split between two (its sums are then formed in two parts).
+    static constexpr int kLanes = kRows && !kWide ? 64 / D * D : 64;
+    static constexpr bool kSplit = kRows && kWide && 64 % D != 0;
+    static constexpr int kGroups = !kRows ? 1 : kSplit ? (64 + D - 2) / D + 1 : 64 / D;
     static constexpr int kWavesPerPath = kMulti ? 4 : int((kWords + 63) / 64);
     static constexpr int kPathsPerGroup =
-        kWide ? (kMulti ? 1 : 4 / kWavesPerPath) : (256 / kWords < kTbMaxPaths ? int(256 / kWords) : kTbMaxPaths);
+        kWide ? (kMulti ? 1 : 4 / kWavesPerPath) : (4 * kLanes / kWords < kTbMaxPaths ? int(4 * kLanes / kWords) : kTbMaxPaths);
     static constexpr int64_t kGroupsPerPath = kMulti ? (kWords + 255) / 256 : 1;   // workgroups per path
-    static constexpr int64_t kPartials = kWide ? kGroupsPerPath : kWords;          // partial sums per path and increment
+    static constexpr int64_t kPartials = kWide ? kGroupsPerPath : kRows ? kWords / D : kWords;   // partial sums per path and increment
+    static constexpr int64_t kPartialsRoom = kWide ? kGroupsPerPath : kWords;                    // ... that the workspace has room for
     static constexpr int64_t kS = tb_off(D, N + 1);
+    // a lane's row: d channels, the last letter's share, those of the letters before it
+    static constexpr int kVec = 16 / int(sizeof(T));             // scalars of a 16-byte access
+    static constexpr int kRow = kRows ? (D + P + kVec - 1) / kVec * kVec : kVec;
+    static constexpr int kZRow = (D + kVec - 1) / kVec * kVec;   // scalars an increment takes in LDS
+    // Groups lie an odd number of 16-byte pieces apart, so that the lanes that read them side by side hit different banks
+    // (d = 4 in fp64, 128 paths of 128 points at N = 5: 77 us, without this 125).
+    static constexpr int kGroupPad = kRows && D * kRow / kVec % 2 == 0 ? kVec : 0;
+    static constexpr int kIncSize = kLanes * kRow + kGroups * kGroupPad;   // scalars an increment of the batch takes
+    // increments per batch: a lane per (increment, group), as many as leave room for three workgroups on a compute unit
+    static constexpr int kOther = int(sizeof(T)) * (kPathsPerGroup * kTbTile * kZRow + (kWide ? kTbTile * 4 * D : 1) + kRow);
+    static constexpr int kRoom = (53 * 1024 - kOther) / (4 * kIncSize * int(sizeof(T)));
+    static constexpr int kBatch = !kRows ? 1 : kRoom < 64 / kGroups ? (kRoom < 1 ? 1 : kRoom) : 64 / kGroups;
 };
+
+// Orders a wavefront's own LDS writes before its reads of what other lanes wrote (LDS serves a wavefront in order; this keeps
+// the compiler from moving accesses across).
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
+__host__ __device__ constexpr double inv_factorial(int n)
+{
+    double f = 1;
+    for (int i = 2; i <= n; ++i) f *= i;
+    return 1 / f;
+}
 
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-template <typename T, int D, int N, bool STREAM>
+template <typename T, int D, int N, bool STREAM, bool ROWS>
 __global__ void __launch_bounds__(256)
 sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restrict__ sig,
                          const T *__restrict__ gout, T *__restrict__ partial)
 {
-    using TS = TbShape<D, N>;
+    using TS = TbShape<T, D, N, ROWS>;
     constexpr int U = TS::U, P = TS::P, PPG = TS::kPathsPerGroup;
     constexpr int H1 = U >= 1 ? D : 1, H2 = U >= 2 ? D * D : 1;
+    constexpr int ZR = TS::kZRow, LANES = TS::kLanes, ROW = TS::kRow, BATCH = TS::kBatch, GROUPS = TS::kGroups, INC = TS::kIncSize;
     constexpr int64_t kS = TS::kS;
-    __shared__ T zt[PPG * kTbTile * D];
+    __shared__ __align__(16) T zt[PPG * kTbTile * ZR];
     __shared__ T part[TS::kWide ? kTbTile * 4 * D : 1];   // [increment of the tile][wavefront][channel]
+    // [wavefront][increment of the batch][lane][number], and a row of zeros
+    __shared__ __align__(16) T rows[TS::kRows ? 4 * BATCH * INC + ROW : 1];
 
     constexpr int WPP = TS::kWavesPerPath;
-    const int tid = threadIdx.x;
-    const int slot_raw = TS::kMulti ? 0 : TS::kWide ? (tid >> 6) / WPP : tid / int(TS::kWords);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int item = wave * LANES + lane;   // the thread's place among the lanes in use
+    const int slot_raw = TS::kMulti ? 0 : TS::kWide ? wave / WPP : item / int(TS::kWords);
     const int slot = slot_raw < PPG ? slot_raw : PPG - 1;
-    const int64_t u_raw = TS::kMulti  ? int64_t(blockIdx.x % TS::kGroupsPerPath) * 256 + tid
-                          : TS::kWide ? int64_t(tid - slot_raw * WPP * 64)
-                                      : int64_t(tid % int(TS::kWords));
+    const int64_t u_raw = TS::kMulti  ? int64_t(blockIdx.x % TS::kGroupsPerPath) * (4 * LANES) + item
+                          : TS::kWide ? int64_t(item - slot_raw * WPP * LANES)
+                                      : int64_t(item % int(TS::kWords));
     const int64_t row = TS::kMulti ? int64_t(blockIdx.x / TS::kGroupsPerPath) : int64_t(blockIdx.x) * PPG + slot;
-    const bool live = u_raw < TS::kWords && slot_raw < PPG && row < sh.B;
+    const bool live = lane < LANES && u_raw < TS::kWords && slot_raw < PPG && row < sh.B;
     const int64_t u = live ? u_raw : 0;   // idle threads shadow word 0 of a valid row and contribute nothing
     const int64_t my_row = live ? row : (row < sh.B ? row : 0);
 
@@ -99,9 +154,9 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
             width *= D;
         }
     }
-    T rk[N + 2];
+    T rf[N + 2];   // 1 / m!
 #pragma unroll
-    for (int m = 1; m <= N + 1; ++m) rk[m] = T(1) / T(m);
+    for (int m = 0; m <= N + 1; ++m) rf[m] = T(inv_factorial(m));
 
     const int64_t per_row = STREAM ? sh.n_inc * kS : kS;
     const T *sg = sig + my_row * per_row;
@@ -153,9 +208,28 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
     const int64_t row0 = TS::kMulti ? int64_t(blockIdx.x / TS::kGroupsPerPath) : int64_t(blockIdx.x) * PPG;
     const T *bpv = static_cast<const T *>(sh.basepoint_value);
     // where the partial sums go: [row][group][increment][D]; group = the workgroup's number inside its path (wavefront
-    // sums) or the thread's word (short paths)
+    // sums), the word's first P-1 letters or the whole word (short paths)
     const int64_t wg_group = TS::kMulti ? int64_t(blockIdx.x % TS::kGroupsPerPath) : 0;
-    T *pp = partial + (my_row * TS::kPartials + (TS::kWide ? wg_group : u)) * sh.n_inc * D;
+    // After a batch lane s of a wavefront adds up group g = s % GROUPS at increment s / GROUPS of the batch.  The rows of group g
+    // begin at lane g D - skip; its letters are those of any of its lanes, and so is the place its sums go to.
+    const int sum_group = lane % GROUPS, sum_inc = lane / GROUPS;
+    const int skip = TS::kSplit ? __builtin_amdgcn_readfirstlane(int((u_raw - lane) % D)) : 0;
+    const int first_lane = sum_group * D - skip;
+    const int some_lane = first_lane < 0 ? 0 : first_lane < LANES ? first_lane : LANES - 1;
+    int gl[P + 1];   // letters 1 .. P-1 of that group
+#pragma unroll
+    for (int j = 1; j < P; ++j) gl[j] = TS::kRows ? __shfl(cl[j], some_lane) : 0;
+    int64_t sum_at = 0;   // scalar offset of its partial sums, negative: none
+    if constexpr (!TS::kWide) {
+        const int64_t mine = live ? (my_row * TS::kPartials + (TS::kRows ? u / D : u)) * sh.n_inc * D : -1;
+        sum_at = TS::kRows ? __shfl(mine, some_lane) : mine;
+    }
+    T *my_rows = rows + wave * (BATCH * INC);
+    const int my_row_at = lane * ROW + (lane + skip) / D * TS::kGroupPad;
+    const T *zeros = rows + 4 * BATCH * INC;
+    if constexpr (TS::kRows) {
+        if (tid < ROW) rows[4 * BATCH * INC + tid] = T(0);   // the first tile's barriers come before its first use
+    }
 
     for (int64_t t0 = ((sh.n_inc - 1) / kTbTile) * kTbTile; t0 >= 0; t0 -= kTbTile) {
         const int nt = int(sh.n_inc - t0 < kTbTile ? sh.n_inc - t0 : kTbTile);
@@ -169,13 +243,13 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
                 const T lo = i_hi > 0 ? x[(i_hi - 1) * D + c] : bpv != nullptr ? bpv[(row0 + p) * D + c] : T(0);
                 z = x[i_hi * D + c] - lo;
             }
-            zt[e] = z;
+            zt[(p * kTbTile + i) * ZR + c] = z;
         }
         __syncthreads();
 
         for (int i = nt - 1; i >= 0; --i) {
             const int64_t s = t0 + i;
-            const T *zrow = zt + (slot * kTbTile + i) * D;
+            const T *zrow = zt + (slot * kTbTile + i) * ZR;
             T zc[P + 1];
 #pragma unroll
             for (int j = 1; j <= P; ++j) zc[j] = zrow[cl[j]];
@@ -193,18 +267,18 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
                 A = s > 0 ? load_share(sg + (s - 1) * kS, false, U >= 2, false) : Share{};
             }
 
-            // ---- up: Hn[j][k] = T^(k)_j at this thread's word; the signature before the increment
-            T Hn[P + 1][N + 2];
+            // ---- up: Hh[j][k] = T^(k)_j / (k-j)! at this thread's word; the signature before the increment
+            T Hh[P + 1][N + 2];
             T a_lo[P + 1];
             a_lo[1] = STREAM ? A.lo[1] : A.lo[1] - zc[1];
 #pragma unroll
-            for (int k = 2; k <= N; ++k) Hn[1][k] = fma_t(zc[1], rk[k], a_lo[1]);
+            for (int k = 2; k <= N; ++k) Hh[1][k] = fma_t(zc[1], rf[k], a_lo[1] * rf[k - 1]);
 #pragma unroll
             for (int j = 2; j <= P; ++j) {
                 if (j < N) {
-                    a_lo[j] = STREAM ? A.lo[j] : fma_t(-Hn[j - 1][j], zc[j], A.lo[j]);
+                    a_lo[j] = STREAM ? A.lo[j] : fma_t(-Hh[j - 1][j], zc[j], A.lo[j]);
 #pragma unroll
-                    for (int k = j + 1; k <= N; ++k) Hn[j][k] = fma_t(Hn[j - 1][k], zc[j] * rk[k - j + 1], a_lo[j]);
+                    for (int k = j + 1; k <= N; ++k) Hh[j][k] = fma_t(Hh[j - 1][k], zc[j], a_lo[j] * rf[k - j]);
                 } else {
                     a_lo[j] = T(0);
                 }
@@ -213,8 +287,8 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
             if constexpr (U >= 2) {
 #pragma unroll
                 for (int c = 0; c < D; ++c) {
-                    a_h1[c] = STREAM ? A.h1[c] : fma_t(-Hn[P][P + 1], zu[c], A.h1[c]);
-                    Th1[c] = fma_t(Hn[P][N], zu[c] * rk[2], a_h1[c]);
+                    a_h1[c] = STREAM ? A.h1[c] : fma_t(-Hh[P][P + 1], zu[c], A.h1[c]);
+                    Th1[c] = fma_t(Hh[P][N], zu[c], a_h1[c]);
                 }
             }
             if constexpr (!STREAM) {
@@ -230,7 +304,7 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
             T dz[D];
 #pragma unroll
             for (int c = 0; c < D; ++c) dz[c] = T(0);
-            T Dc[N + 2];   // Dc[k] = this thread's part of D^(k)_j at its prefix of the level j being processed
+            T Dc[N + 2];   // Dc[k] = this thread's part of D^(k)_j (k-j)! at its prefix of the level j being processed
 #pragma unroll
             for (int k = 0; k <= N + 1; ++k) Dc[k] = T(0);
             T Dh[H1];
@@ -250,50 +324,114 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
                 T acc1 = T(0), acc2 = T(0);
 #pragma unroll
                 for (int c = 0; c < D; ++c) {
-                    dz[c] = fma_t(Hn[P][P + 1], G.h1[c], dz[c]);
+                    dz[c] = fma_t(Hh[P][P + 1], G.h1[c], dz[c]);
                     acc1 = fma_t(G.h1[c], zu[c], acc1);
                     if constexpr (U >= 2) {
-                        dz[c] = fma_t(Hn[P][P + 2] * rk[2], Dh[c], dz[c]);
+                        dz[c] = fma_t(Hh[P][P + 2], Dh[c], dz[c]);
                         acc2 = fma_t(Dh[c], zu[c], acc2);
                         G.h1[c] += Dh[c];
                     }
                 }
                 Dc[P + 1] = acc1;
-                if constexpr (U >= 2) Dc[P + 2] = acc2 * rk[2];
+                if constexpr (U >= 2) Dc[P + 2] = acc2;
             }
             // levels P .. 1 along the word: one scalar per chain, this thread's part only
+            T contrib[P + 1];   // to the channels of the word's letters
 #pragma unroll
             for (int j = P; j >= 1; --j) {
-                T contrib = j >= 2 ? Hn[j >= 2 ? j - 1 : 1][j] * G.lo[j] : G.lo[j];   // T^(k)_0 = 1
+                contrib[j] = j >= 2 ? Hh[j >= 2 ? j - 1 : 1][j] * G.lo[j] : G.lo[j];   // T^(k)_0 = 1
                 T g_add = T(0);
 #pragma unroll
                 for (int k = j + 1; k <= N; ++k) {
-                    const T tp = j >= 2 ? Hn[j >= 2 ? j - 1 : 1][k] * rk[k - j + 1] : rk[k - j + 1];
-                    contrib = fma_t(tp, Dc[k], contrib);
-                    g_add += Dc[k];
+                    contrib[j] = fma_t(j >= 2 ? Hh[j >= 2 ? j - 1 : 1][k] : rf[k], Dc[k], contrib[j]);
+                    g_add = k == j + 1 ? Dc[k] : fma_t(Dc[k], rf[k - j], g_add);
                 }
                 if (j >= 2) {
 #pragma unroll
-                    for (int k = N; k >= j + 1; --k) Dc[k] = Dc[k] * (zc[j] * rk[k - j + 1]);
+                    for (int k = N; k >= j + 1; --k) Dc[k] *= zc[j];
                     Dc[j] = G.lo[j] * zc[j];
                 }
                 G.lo[j] += g_add;
-#pragma unroll
-                for (int c = 0; c < D; ++c) dz[c] += cl[j] == c ? contrib : T(0);
             }
 
             // ---- this thread's (wavefront's) part of the increment's gradient
-            if constexpr (TS::kWide) {
-                // the wavefronts do not wait for one another inside a tile: their sums meet in LDS at its end
+            if constexpr (TS::kRows) {
+                const int ib = (nt - 1 - i) % BATCH;
+                if (lane < LANES) {
+                    T *r = my_rows + ib * INC + my_row_at;
 #pragma unroll
-                for (int c = 0; c < D; ++c) {
-                    const T total = group_sum<0, 6, T>(live ? dz[c] : T(0));
-                    if ((tid & 63) == c) part[(i * 4 + (tid >> 6)) * D + c] = total;
+                    for (int c = 0; c < D; ++c) r[c] = dz[c];
+                    r[D] = contrib[P];
+#pragma unroll
+                    for (int j = 1; j < P; ++j) r[D + j] = contrib[j];
+                }
+                if (ib == BATCH - 1 || i == 0) {   // increment i + ib - k of the tile lies in place k of the batch
+                    wave_lds_order();
+                    T sum[D];
+#pragma unroll
+                    for (int c = 0; c < D; ++c) sum[c] = T(0);
+                    if (sum_inc <= ib) {
+                        T own[P + 1];
+#pragma unroll
+                        for (int j = 1; j < P; ++j) own[j] = T(0);
+#pragma unroll
+                        for (int w = 0; w < D; ++w) {   // the group's words by their last letter
+                            const T *r = my_rows + sum_inc * INC + (first_lane + w) * ROW + sum_group * TS::kGroupPad;
+                            if constexpr (TS::kSplit) r = unsigned(first_lane + w) < unsigned(LANES) ? r : zeros;
+#pragma unroll
+                            for (int c = 0; c < D; ++c) sum[c] += r[c];
+                            sum[w] += r[D];
+#pragma unroll
+                            for (int j = 1; j < P; ++j) own[j] += r[D + j];
+                        }
+#pragma unroll
+                        for (int j = 1; j < P; ++j)
+#pragma unroll
+                            for (int c = 0; c < D; ++c) sum[c] += gl[j] == c ? own[j] : T(0);
+                    }
+                    if constexpr (TS::kWide) {
+                        // the wavefront's groups: a lane per increment and channel (the rows have been read)
+                        wave_lds_order();
+                        if (sum_inc <= ib) {
+#pragma unroll
+                            for (int c = 0; c < D; ++c) my_rows[(sum_inc * GROUPS + sum_group) * ZR + c] = sum[c];
+                        }
+                        wave_lds_order();
+                        const int k = lane / D, c = lane - k * D;
+                        if (k <= ib) {
+                            T total = T(0);
+#pragma unroll
+                            for (int g = 0; g < GROUPS; ++g) total += my_rows[(k * GROUPS + g) * ZR + c];
+                            part[((i + ib - k) * 4 + wave) * D + c] = total;
+                        }
+                        wave_lds_order();   // the next batch's rows overwrite these
+                    } else {
+                        if (sum_inc <= ib && sum_at >= 0) {
+                            T *pp = partial + sum_at + (t0 + i + ib - sum_inc) * D;
+#pragma unroll
+                            for (int c = 0; c < D; ++c) pp[c] = sum[c];
+                        }
+                        wave_lds_order();
+                    }
                 }
             } else {
-                if (live) {
 #pragma unroll
-                    for (int c = 0; c < D; ++c) pp[s * D + c] = dz[c];
+                for (int j = P; j >= 1; --j)
+#pragma unroll
+                    for (int c = 0; c < D; ++c) dz[c] += cl[j] == c ? contrib[j] : T(0);
+                if constexpr (TS::kWide) {
+                    // the wavefronts do not wait for one another inside a tile: their sums meet in LDS at its end
+#pragma unroll
+                    for (int c = 0; c < D; ++c) {
+                        const T total = group_sum<0, 6, T>(live ? dz[c] : T(0));
+                        if (lane == c) part[(i * 4 + wave) * D + c] = total;
+                    }
+                } else {
+                    if (live) {
+                        T *pp = partial + sum_at + s * D;
+#pragma unroll
+                        for (int c = 0; c < D; ++c) pp[c] = dz[c];
+                    }
                 }
             }
 
@@ -329,26 +467,48 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
     }
 }
 
-template <typename T, int D, int N>
-hipError_t launch_tb_dn(const Shape &sh, const T *path, const T *sig, const T *gout, T *gpath,
-                        T *gbase, T *partial, hipStream_t st)
+// Whether paths packed into a wavefront add up their numbers through LDS (one partial sum per group of d words) or write one
+// per thread.  In final mode few threads wait for the batches' trips through LDS, many for the partial sums in memory (100
+// points, us, through LDS | per thread: fp32 d = 7, N = 4, 256 paths 66 | 70, 32 paths 63 | 56, 2048 paths 94 | 213; d = 3, N = 5:
+// 48 | 42 and 64 | 72 at 256 and 2048; fp64 d = 4, N = 5: 66 | 55 and 141 | 258).  In stream mode the stores also stand between
+// the loads of one increment and the next (fp32 d = 5, N = 4, 64 paths: 82 | 139; d = 6, N = 4: 96 | 157), all the more the more
+// words there are; up to eight words and few paths the batches cost more (d = 7, N = 3, 8 paths: 96 | 89; fp64 d = 6, N = 3: 124 | 101).
+inline bool tb_packed_rows(int64_t words, int64_t rows, size_t elem, bool stream)
 {
-    using TS = TbShape<D, N>;
+    if (stream) return words >= 9 || (elem == 4 && rows * words >= 300);
+    return rows * words >= (elem == 4 ? 8000 : 18000);
+}
+
+template <typename T, int D, int N, bool STREAM, bool ROWS>
+hipError_t launch_tb_mode(const Shape &sh, const T *path, const T *sig, const T *gout, T *gpath, T *gbase, T *partial, hipStream_t st)
+{
+    using TS = TbShape<T, D, N, ROWS>;
     const int64_t groups = TS::kMulti ? sh.B * TS::kGroupsPerPath : (sh.B + TS::kPathsPerGroup - 1) / TS::kPathsPerGroup;
     if (groups > 0x7fffffff) return hipErrorNotSupported;
-    if (sh.stream)
-        hipLaunchKernelGGL((sig_tree_backward_kernel<T, D, N, true>), dim3(unsigned(groups)), dim3(256), 0, st, sh, path, sig,
-                           gout, partial);
-    else
-        hipLaunchKernelGGL((sig_tree_backward_kernel<T, D, N, false>), dim3(unsigned(groups)), dim3(256), 0, st, sh, path, sig,
-                           gout, partial);
-    hipError_t err = hipGetLastError();
+    hipLaunchKernelGGL((sig_tree_backward_kernel<T, D, N, STREAM, ROWS>), dim3(unsigned(groups)), dim3(256), 0, st, sh, path, sig, gout, partial);
+    const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     return launch_increment_sums<T>(sh, TS::kPartials, partial, gpath, gbase, st);
 }
 
+template <typename T, int D, int N>
+hipError_t launch_tb_dn(const Shape &sh, const T *path, const T *sig, const T *gout, T *gpath,
+                        T *gbase, T *partial, hipStream_t st)
+{
+    const auto launch = [&](auto rows) {
+        constexpr bool R = decltype(rows)::value;
+        return sh.stream ? launch_tb_mode<T, D, N, true, R>(sh, path, sig, gout, gpath, gbase, partial, st)
+                         : launch_tb_mode<T, D, N, false, R>(sh, path, sig, gout, gpath, gbase, partial, st);
+    };
+    if constexpr (D > 8) return launch(std::false_type{});
+    if constexpr (!TbShape<T, D, N, false>::kWide) {
+        if (!tb_packed_rows(TbShape<T, D, N, false>::kWords, sh.B, sizeof(T), sh.stream != 0)) return launch(std::false_type{});
+    }
+    if constexpr (D <= 8) return launch(std::true_type{});
+}
+
 template <int D, int N>
-int64_t tb_partials() { return TbShape<D, N>::kPartials; }
+int64_t tb_partials() { return TbShape<float, D, N, false>::kPartialsRoom; }   // the same for both types and modes
 
 constexpr int kTbMaxDepth = 9;       // d = 2..8
 constexpr int kTbWideMaxDepth = 6;   // d = 9..16

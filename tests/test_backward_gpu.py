@@ -421,3 +421,23 @@ def test_a_training_step_can_be_captured_in_a_graph_and_replayed():
         torch.cuda.synchronize()
         for a, b in zip(got, (s, lg, gp, prod, g_log, g_sig, g_a, g_b)):
             assert torch.equal(a, b), rep
+
+
+# Many short paths: the prefix-tree kernels add up the numbers of a group of words through LDS, a batch of increments at a
+# time, and every path's groups write one partial sum each; one path more or less than the rule's line takes the other
+# route.  Lengths that end inside a tile of 32 increments and inside a batch; every path against the oracle.
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("d,N,L", [(2, 5, 36), (3, 3, 5), (3, 5, 34), (4, 4, 38), (5, 3, 7), (5, 4, 35), (6, 4, 34), (7, 3, 40),
+                                   (7, 4, 4), (8, 3, 35), (8, 4, 3)])
+def test_tree_gradient_many_short_paths(d, N, L, dtype):
+    words = d ** (N - 2)
+    line = -(-(8000 if dtype == np.float32 else 18000) // words)
+    for B in (line, line - 1):
+        check(brownian_paths(B, L, d, seed=d + N).astype(dtype), N, False)
+
+
+# Paths of 65 words and more: a wavefront's 64 words cut groups in two (d = 3, 5, 6, 7)
+@pytest.mark.parametrize("d,N", [(3, 6), (3, 8), (5, 5), (5, 6), (6, 5), (7, 5), (2, 9), (4, 6)])
+def test_tree_gradient_split_groups(d, N):
+    for dtype, L in ((np.float32, 36), (np.float64, 6)):
+        check(brownian_paths(3, L, d, seed=d + N).astype(dtype), N, False)
