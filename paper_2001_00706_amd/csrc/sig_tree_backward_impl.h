@@ -231,21 +231,36 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
         if (tid < ROW) rows[4 * BATCH * INC + tid] = T(0);   // the first tile's barriers come before its first use
     }
 
-    for (int64_t t0 = ((sh.n_inc - 1) / kTbTile) * kTbTile; t0 >= 0; t0 -= kTbTile) {
+    // This thread's scalars of the tile at t0, the end and the start of an increment, fetched while the tile after it is worked
+    // on (tiles are taken from the last to the first)
+    constexpr int kStaged = PPG * kTbTile * D, kPerThread = (kStaged + 255) / 256;
+    T hi[kPerThread], lo[kPerThread];
+    auto fetch = [&](int64_t t0) {
+#pragma unroll
+        for (int q = 0; q < kPerThread; ++q) {
+            const int e = tid + 256 * q < kStaged ? tid + 256 * q : kStaged - 1;
+            const int p = e / (kTbTile * D), i = (e / D) % kTbTile, c = e % D;
+            const bool on = row0 + p < sh.B && t0 + i < sh.n_inc;
+            const int64_t r = on ? row0 + p : row0;
+            const T *x = path + r * sh.L * D;
+            const int64_t i_hi = on ? t0 + i + (sh.basepoint ? 0 : 1) : (sh.basepoint ? 0 : 1);
+            hi[q] = x[i_hi * D + c];
+            lo[q] = i_hi > 0 ? x[(i_hi - 1) * D + c] : bpv != nullptr ? bpv[r * D + c] : T(0);
+            if (!on) lo[q] = hi[q];
+        }
+    };
+    const int64_t last_tile = ((sh.n_inc - 1) / kTbTile) * kTbTile;
+    fetch(last_tile);
+    for (int64_t t0 = last_tile; t0 >= 0; t0 -= kTbTile) {
         const int nt = int(sh.n_inc - t0 < kTbTile ? sh.n_inc - t0 : kTbTile);
         __syncthreads();
-        for (int e = tid; e < PPG * kTbTile * D; e += 256) {
-            const int p = e / (kTbTile * D), i = (e / D) % kTbTile, c = e % D;
-            T z = T(0);
-            if (row0 + p < sh.B && i < nt) {
-                const T *x = path + (row0 + p) * sh.L * D;
-                const int64_t i_hi = t0 + i + (sh.basepoint ? 0 : 1);
-                const T lo = i_hi > 0 ? x[(i_hi - 1) * D + c] : bpv != nullptr ? bpv[(row0 + p) * D + c] : T(0);
-                z = x[i_hi * D + c] - lo;
-            }
-            zt[(p * kTbTile + i) * ZR + c] = z;
+#pragma unroll
+        for (int q = 0; q < kPerThread; ++q) {
+            const int e = tid + 256 * q;
+            if (e < kStaged) zt[e / D * ZR + e % D] = hi[q] - lo[q];
         }
         __syncthreads();
+        if (t0 > 0) fetch(t0 - kTbTile);
 
         for (int i = nt - 1; i >= 0; --i) {
             const int64_t s = t0 + i;
@@ -256,6 +271,7 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
             T zu[D];
 #pragma unroll
             for (int c = 0; c < D; ++c) zu[c] = zrow[c];
+            __builtin_amdgcn_sched_barrier(0);   // every read is issued before the first is used
 
             Share G_ahead = {};
             if constexpr (kAhead) {

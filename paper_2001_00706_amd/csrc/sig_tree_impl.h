@@ -33,6 +33,10 @@ __host__ __device__ constexpr int64_t tree_off(int d, int k)   // offset of leve
     return off;
 }
 
+struct TreeRow {   // a row (a path or a chunk of one): its path, the number of its first increment, how many it has
+    int64_t path, inc0, n;
+};
+
 template <int D, int N>
 struct TreeShape {
     // levels kept per thread below its word: two (d + d^2 scalars) up to 8 channels, one (d scalars) beyond
@@ -48,14 +52,18 @@ struct TreeShape {
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
+// (fp64 at seven channels, long paths of words: three wavefronts per SIMD, where the compiler would take registers for two:
+// 512 paths of 100 points, N = 6 571 -> 525 us)
 template <typename T, int D, int N>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, sizeof(T) == 8 && D == 7 && N >= 5 ? 3 : 1)
 sig_tree_kernel(Shape sh, const T *__restrict__ path, T *__restrict__ out)
 {
     using TS = TreeShape<D, N>;
     constexpr int U = TS::U, P = TS::P, PPG = TS::kPathsPerGroup;
     constexpr int H1 = U >= 1 ? D : 1, H2 = U >= 2 ? D * D : 1;
-    __shared__ T zt[PPG * kTreeTile * D];
+    constexpr int kStaged = PPG * kTreeTile * D, kPerThread = (kStaged + 255) / 256;   // increments' scalars of a tile
+    __shared__ T zt[kStaged];
+    __shared__ TreeRow served[PPG];   // the rows this workgroup serves, for the staging of their increments
 
     const int tid = threadIdx.x;
     // which path of the workgroup, which word of the path
@@ -88,15 +96,40 @@ sig_tree_kernel(Shape sh, const T *__restrict__ path, T *__restrict__ out)
 #pragma unroll
     for (int c = 0; c < H2; ++c) B2[c] = T(0);
 
-    // the rows (paths or chunks of paths) this workgroup serves, for the staging of their increments
+    // the rows (paths or chunks of paths) this workgroup serves; rows past the end of the batch have no increments
     const int64_t row0 = TS::kWords >= 256 ? int64_t(blockIdx.x / TS::kGroupsPerPath) : int64_t(blockIdx.x) * PPG;
+    if (tid < PPG) {
+        const bool there = row0 + tid < sh.B;
+        const ChunkView cv = chunk_view(there ? row0 + tid : 0, sh.chunks, sh.chunk_len, sh.n_inc);
+        served[tid] = {cv.path, cv.inc0, there ? cv.n : 0};
+    }
+    __syncthreads();
     int64_t n_max = 0;   // most increments among them
-    for (int p = 0; p < PPG; ++p)
-        if (row0 + p < sh.B) {
-            const ChunkView cv = chunk_view(row0 + p, sh.chunks, sh.chunk_len, sh.n_inc);
-            n_max = cv.n > n_max ? cv.n : n_max;
-        }
+    for (int p = 0; p < PPG; ++p) n_max = served[p].n > n_max ? served[p].n : n_max;
     const T *bpv = static_cast<const T *>(sh.basepoint_value);
+    // This thread's scalars of the tile at t0: the end and the start of an increment.  Increments past the end of a row add
+    // nothing; the loads are unconditional, on indices clamped into a path, so that they are in flight together, and
+    // they are issued before the tile ahead of them is worked on, so that the trip to memory per tile is not waited for (with
+    // the reads below issued together: 512 paths of 100 points at d = 5, N = 5 28.2 -> 25.8 us, 32 of 128 at d = 12, N = 4
+    // 24.7 -> 21.1, in fp64 128 of 128 at d = 4, N = 5 29.5 -> 24).
+    T hi[kPerThread], lo[kPerThread];
+    auto fetch = [&](int64_t t0) {
+#pragma unroll
+        for (int q = 0; q < kPerThread; ++q) {
+            const int e = tid + 256 * q < kStaged ? tid + 256 * q : kStaged - 1;
+            const int p = e / (kTreeTile * D), i = (e / D) % kTreeTile, c = e % D;
+            const TreeRow r = served[p];
+            const bool on = t0 + i < r.n;
+            const T *x = path + r.path * sh.L * D;
+            const int64_t i_hi = on ? r.inc0 + t0 + i + (sh.basepoint ? 0 : 1) : (sh.basepoint ? 0 : 1);
+            const bool first = i_hi == 0;   // the increment from the basepoint
+            hi[q] = x[i_hi * D + c];
+            lo[q] = bpv != nullptr && first ? bpv[r.path * D + c] : x[(first ? 0 : i_hi - 1) * D + c];
+            if (first && bpv == nullptr) lo[q] = T(0);
+            if (!on) lo[q] = hi[q];
+        }
+    };
+    fetch(0);
     // chunks laid out in a stream-mode output: this thread's chunk, and the rows it reads and writes
     const ChunkView mine = chunk_view(live ? row : 0, sh.chunks, sh.chunk_len, sh.n_inc);
     const int64_t first_row = mine.path * sh.n_inc + mine.inc0;   // the row of the chunk's first increment
@@ -139,43 +172,41 @@ sig_tree_kernel(Shape sh, const T *__restrict__ path, T *__restrict__ out)
 
     for (int64_t t0 = 0; t0 < n_max; t0 += kTreeTile) {
         __syncthreads();
-        for (int e = tid; e < PPG * kTreeTile * D; e += 256) {
-            const int p = e / (kTreeTile * D), i = (e / D) % kTreeTile, c = e % D;
-            // rows past the end of the batch and increments past the end of a row add nothing; both loads are
-            // unconditional, on indices clamped into a path, so that they are in flight together
-            const ChunkView cv = chunk_view(row0 + p < sh.B ? row0 + p : 0, sh.chunks, sh.chunk_len, sh.n_inc);
-            const bool on = row0 + p < sh.B && t0 + i < cv.n;
-            const T *x = path + cv.path * sh.L * D;
-            const int64_t i_hi = on ? cv.inc0 + t0 + i + (sh.basepoint ? 0 : 1) : (sh.basepoint ? 0 : 1);
-            const bool first = i_hi == 0;   // the increment from the basepoint
-            const T hi = x[i_hi * D + c];
-            const T lo = bpv != nullptr && first ? bpv[cv.path * D + c] : x[(first ? 0 : i_hi - 1) * D + c];
-            zt[e] = on ? hi - (first && bpv == nullptr ? T(0) : lo) : T(0);
-        }
+#pragma unroll
+        for (int q = 0; q < kPerThread; ++q)
+            if (tid + 256 * q < kStaged) zt[tid + 256 * q] = hi[q] - lo[q];
         __syncthreads();
+        if (t0 + kTreeTile < n_max) fetch(t0 + kTreeTile);
         const int nt = int(n_max - t0 < kTreeTile ? n_max - t0 : kTreeTile);
         const T *zrow = zt + slot * kTreeTile * D;
         for (int s = 0; s < nt; ++s, zrow += D) {
+            // the increment at the letters of the word and whole: every read is issued before the first is used (left to
+            // itself the compiler moves each next to its use where that saves registers, a wait per letter: 64 paths of 100
+            // points at d = 2, N = 8 37.8 -> 24 us, d = 3, N = 8 40 -> 26.5, d = 5, N = 6 36 -> 26).  With seven channels
+            // arithmetic may still move up between the reads (512 paths, N = 5: 72 us without that, 68 with).
+            T zl[P + 1], zu[D];
+#pragma unroll
+            for (int i = 1; i <= P; ++i) zl[i] = zrow[cl[i]];
+#pragma unroll
+            for (int c = 0; c < D; ++c) zu[c] = zrow[c];
+            __builtin_amdgcn_sched_barrier(D == 7 ? 1 : 0);
             // Horner terms along the word: Hn[k] = T^(k)_i for the level i just passed, k > i
             T Hn[N + 2];
             {
-                const T zc = zrow[cl[1]];
+                const T zc = zl[1];
 #pragma unroll
                 for (int k = 2; k <= N; ++k) Hn[k] = fma_t(zc, rk[k], A[1]);
                 A[1] += zc;
             }
 #pragma unroll
             for (int i = 2; i <= P; ++i) {
-                const T zc = zrow[cl[i]];
+                const T zc = zl[i];
                 const T a = A[i];
                 A[i] = fma_t(Hn[i], zc, a);
 #pragma unroll
                 for (int k = i + 1; k <= N; ++k) Hn[k] = fma_t(Hn[k], zc * rk[k - i + 1], a);
             }
             if constexpr (U >= 1) {
-                T zu[D];
-#pragma unroll
-                for (int c = 0; c < D; ++c) zu[c] = zrow[c];
                 if constexpr (U == 1) {
 #pragma unroll
                     for (int c = 0; c < D; ++c) B1[c] = fma_t(Hn[P + 1], zu[c], B1[c]);
