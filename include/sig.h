@@ -311,6 +311,13 @@ sig_status sig_lyndon_indices(int d, int N, int64_t *indices, int64_t capacity);
 sig_status sig_lyndon_gather(const void *log_sig, int64_t rows, int d, int N, const int64_t *indices, int64_t n,
                              sig_dtype dtype, void *out, hipStream_t hip_stream);
 
+/* sig_log and sig_lyndon_gather in one, without forming the coefficients that are not kept: out[r][i] =
+ * log(sig[r])[indices[i]].
+ *   sig        DEVICE pointer [rows][S];  indices  DEVICE pointer to n offsets in [0, S);  out  DEVICE pointer [rows][n].
+ * SIG_ERR_UNSUPPORTED beyond depth 9; other errors as for sig_lyndon_gather. */
+sig_status sig_log_words(const void *sig, int64_t rows, int d, int N, const int64_t *indices, int64_t n, sig_dtype dtype, void *out,
+                         hipStream_t hip_stream);
+
 /* Gradient through sig_log (section 5.3 treats every operation as a differentiable primitive; the paper's
  * benchmarks time the logsignature backwards as well): given grad_log = dLoss/d sig_log(sig), writes
  * grad_sig = dLoss/d sig.  Deterministic: partial sums are added in a fixed order, no atomics.

@@ -42,6 +42,7 @@ from .binding import (  # noqa: F401
     sig_invert,
     sig_log,
     sig_log_backward,
+    sig_log_words,
     sig_log_backward_workspace_bytes,
     sig_logsignature,
     sig_logsignature_channels,

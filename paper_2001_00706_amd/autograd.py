@@ -138,10 +138,9 @@ class _SignatureToLogsignature(torch.autograd.Function):
     @staticmethod
     def forward(ctx, sig, channels, depth, mode):
         sig = sig.contiguous()
-        full = binding.sig_log(sig, channels, depth)
         ctx.save_for_backward(sig)
         ctx.args = (channels, depth, mode)
-        return full if mode == "expand" else binding.sig_lyndon_gather(full, channels, depth)
+        return binding.sig_log(sig, channels, depth) if mode == "expand" else binding.sig_log_words(sig, channels, depth)
 
     @staticmethod
     def backward(ctx, grad_out):

@@ -52,6 +52,7 @@ EXPORTED_SYMBOLS = (
     "sig_combine_many_workspace_bytes",
     "sig_invert",
     "sig_log",
+    "sig_log_words",
     "sig_logsignature_channels",
     "sig_lyndon_indices",
     "sig_lyndon_gather",
@@ -181,6 +182,8 @@ def load_library() -> ctypes.CDLL:
         lib.sig_combine_strided.argtypes = [vp, i64, vp, i64, i64, i32, i32, i32, vp, i64, vp]
         lib.sig_log.restype = i32
         lib.sig_log.argtypes = [vp, i64, i32, i32, i32, vp, vp]
+        lib.sig_log_words.restype = i32
+        lib.sig_log_words.argtypes = [vp, i64, i32, i32, vp, i64, i32, vp, vp]
         lib.sig_logsignature_channels.restype = i64
         lib.sig_logsignature_channels.argtypes = [i32, i32]
         lib.sig_lyndon_indices.restype = i32
@@ -573,6 +576,7 @@ def sig_log(sig, d: int, N: int, out=None):
     return out
 
 
+_LOG_WORDS_MAX_DEPTH = 9   # of sig_log_words in the library
 _lyndon_tables = {}
 
 
@@ -609,6 +613,33 @@ def sig_lyndon_gather(log_sig, d: int, N: int, out=None):
     with _on_device(log_sig.device):
         status = int(load_library().sig_lyndon_gather(log_sig.data_ptr(), rows, d, N, table.data_ptr(), n, dtype,
                                                       out.data_ptr(), _current_stream()))
+    if status != SIG_OK:
+        raise SigError(status, sig_status_string(status))
+    return out
+
+
+def sig_log_words(sig, d: int, N: int, out=None):
+    """`sig_lyndon_gather(sig_log(sig, d, N), d, N)` without forming the coefficients that are not kept."""
+    import torch
+
+    _check_gpu("sig_log_words", sig)
+    dtype = _dtype_of(sig)
+    S = sig_signature_channels(d, N)
+    if S < 0 or sig.shape[-1] != S or not sig.is_contiguous():
+        raise ValueError(f"sig must be contiguous with {S} channels last")
+    if N > _LOG_WORDS_MAX_DEPTH:
+        return sig_lyndon_gather(sig_log(sig, d, N), d, N, out=out)
+    table = _lyndon_table(d, N, sig.device)
+    n = table.numel()
+    shape = (*sig.shape[:-1], n)
+    if out is None:
+        out = torch.empty(shape, dtype=sig.dtype, device=sig.device)
+    elif out.dtype != sig.dtype or out.device != sig.device or tuple(out.shape) != shape or not out.is_contiguous():
+        raise ValueError(f"out must be a contiguous tensor of shape {shape}")
+    rows = sig.numel() // S
+    with _on_device(sig.device):
+        status = int(load_library().sig_log_words(sig.data_ptr(), rows, d, N, table.data_ptr(), n, dtype, out.data_ptr(),
+                                                  _current_stream()))
     if status != SIG_OK:
         raise SigError(status, sig_status_string(status))
     return out
@@ -685,8 +716,8 @@ def sig_logsignature(path, N: int, stream: bool = False, basepoint=False, invers
     if mode not in ("words", "expand"):
         raise ValueError('mode must be "words" or "expand"')
     d = path.shape[2]
-    full = sig_log(sig_signature(path, N, stream=stream, basepoint=basepoint, inverse=inverse), d, N)
-    return full if mode == "expand" else sig_lyndon_gather(full, d, N)
+    sig = sig_signature(path, N, stream=stream, basepoint=basepoint, inverse=inverse)
+    return sig_log(sig, d, N) if mode == "expand" else sig_log_words(sig, d, N)
 
 
 def sig_forward_chunked_workspace_bytes(B: int, L: int, d: int, N: int, basepoint: bool, chunks: int,

@@ -800,6 +800,24 @@ sig_status sig_lyndon_gather(const void *log_sig, int64_t rows, int d, int N, co
     return err == hipSuccess ? SIG_OK : SIG_ERR_HIP;
 }
 
+sig_status sig_log_words(const void *sig, int64_t rows, int d, int N, const int64_t *indices, int64_t n, sig_dtype dtype, void *out,
+                         hipStream_t hip_stream)
+{
+    if (dtype != SIG_F32 && dtype != SIG_F64) return SIG_ERR_INVALID_ARG;
+    sig::Shape sh;
+    const sig_status st = make_rows_shape(rows, d, N, sh);
+    if (st != SIG_OK) return st;
+    if (n < 0 || n > sh.S) return SIG_ERR_INVALID_ARG;
+    if (rows == 0 || n == 0) return SIG_OK;
+    if (sig == nullptr || indices == nullptr || out == nullptr) return SIG_ERR_INVALID_ARG;
+    if (!sig::log_words_supported(sh)) return SIG_ERR_UNSUPPORTED;
+    const hipError_t err =
+        dtype == SIG_F32
+            ? sig::launch_log_words_f32(sh, static_cast<const float *>(sig), indices, n, static_cast<float *>(out), hip_stream)
+            : sig::launch_log_words_f64(sh, static_cast<const double *>(sig), indices, n, static_cast<double *>(out), hip_stream);
+    return err == hipSuccess ? SIG_OK : SIG_ERR_HIP;
+}
+
 int64_t sig_log_backward_workspace_bytes(int64_t rows, int d, int N, sig_dtype dtype)
 {
     if (dtype != SIG_F32 && dtype != SIG_F64) return -1;

@@ -94,6 +94,10 @@ hipError_t launch_log_f32(const Shape &sh, const float *in, float *out, hipStrea
 hipError_t launch_log_f64(const Shape &sh, const double *in, double *out, hipStream_t st);
 hipError_t launch_gather_f32(const Shape &sh, const float *in, const int64_t *index, int64_t n, float *out, hipStream_t st);
 hipError_t launch_gather_f64(const Shape &sh, const double *in, const int64_t *index, int64_t n, double *out, hipStream_t st);
+// Chosen coefficients of the logarithm without the others, out[r][i] = log(in[r])[index[i]] (N <= 9, S < 2^31).
+bool log_words_supported(const Shape &sh);
+hipError_t launch_log_words_f32(const Shape &sh, const float *in, const int64_t *index, int64_t n, float *out, hipStream_t st);
+hipError_t launch_log_words_f64(const Shape &sh, const double *in, const int64_t *index, int64_t n, double *out, hipStream_t st);
 int64_t lyndon_indices_host(const Shape &sh, int64_t *indices, int64_t cap);
 
 // Products along a binary tree of the K >= 2 signatures C of each path, [paths][K][S] (sh: d, N, S; see

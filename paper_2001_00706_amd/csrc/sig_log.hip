@@ -12,8 +12,8 @@
 // logsignature: psi(log(Sig)) is the vector of coefficients of the Lyndon words (appendix A.2.4): a gather
 // with an index table that `sig_lyndon_indices` computes on the host.
 #include "sig_internal.h"
+#include "sig_power_words.h"
 
-#include <type_traits>
 #include <vector>
 
 namespace sig {
@@ -83,13 +83,37 @@ __host__ __device__ constexpr uint32_t fixed_off(int d, int k)   // offset of le
     return off;
 }
 
+// One word of c x + x * R at level k: the same additions in the same order wherever it is formed.
+template <typename T, int D, int N>
+__device__ __forceinline__ T horner_word(const T *x, const T *R, T c, int k, uint32_t idx)
+{
+    T xv[N], rv[N];
+    uint32_t prefix = idx, suffix = 0, scale = 1;
+#pragma unroll
+    for (int j = k - 1; j >= 1; --j) {
+        const uint32_t letter = prefix % uint32_t(D);
+        prefix /= uint32_t(D);
+        suffix += letter * scale;
+        scale *= uint32_t(D);
+        xv[j] = x[fixed_off(D, j) + prefix];
+        rv[j] = R[fixed_off(D, k - j) + suffix];
+    }
+    T acc = c * x[fixed_off(D, k) + idx];
+#pragma unroll
+    for (int j = k - 1; j >= 1; --j) acc += xv[j] * rv[j];
+    return acc;
+}
+
 // The same computation for a channel count and depth known at compile time, signature and R in LDS: every loop
 // over passes, levels and splits is unrolled, so the offsets are constants, the letters come off with shifts or
 // multiplications, and the operands of all splits of a word are fetched before any of them is used (the generic
 // kernel above waits for two LDS round trips per split).
-template <typename T, int D, int N>
+// WORDS: out[r][i] = the coefficient at index[i], i < n, the same bits as without: the last round, three quarters and more of
+// the work, feeds no other, so only the chosen words of it are formed (1024 signatures of d = 4, N = 6, the 964 Lyndon words:
+// 18 us; all words and a gather took 26 + 7).
+template <typename T, int D, int N, bool WORDS>
 __global__ void __launch_bounds__(256)
-sig_log_fixed_kernel(int64_t rows, const T *__restrict__ in, T *__restrict__ out)
+sig_log_fixed_kernel(int64_t rows, const T *__restrict__ in, const int64_t *__restrict__ index, uint32_t n, T *__restrict__ out)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr uint32_t S = fixed_off(D, N + 1);
@@ -99,32 +123,27 @@ sig_log_fixed_kernel(int64_t rows, const T *__restrict__ in, T *__restrict__ out
         for (uint32_t i = threadIdx.x; i < S; i += 256) x[i] = in[r * S + i];
         __syncthreads();
 #pragma unroll
-        for (int m = N; m >= 1; --m) {
+        for (int m = N; m >= (WORDS ? 2 : 1); --m) {
             const T c = (m & 1 ? T(1) : T(-1)) / T(m);
 #pragma unroll
             for (int k = N - m + 1; k >= 1; --k) {
                 const uint32_t off_k = fixed_off(D, k), n_k = fixed_off(D, k + 1) - off_k;
-                for (uint32_t idx = threadIdx.x; idx < n_k; idx += 256) {
-                    T xv[N], rv[N];
-                    uint32_t prefix = idx, suffix = 0, scale = 1;
-#pragma unroll
-                    for (int j = k - 1; j >= 1; --j) {
-                        const uint32_t letter = prefix % uint32_t(D);
-                        prefix /= uint32_t(D);
-                        suffix += letter * scale;
-                        scale *= uint32_t(D);
-                        xv[j] = x[fixed_off(D, j) + prefix];
-                        rv[j] = R[fixed_off(D, k - j) + suffix];
-                    }
-                    T acc = c * x[off_k + idx];
-#pragma unroll
-                    for (int j = k - 1; j >= 1; --j) acc += xv[j] * rv[j];
-                    R[off_k + idx] = acc;
-                }
+                for (uint32_t idx = threadIdx.x; idx < n_k; idx += 256) R[off_k + idx] = horner_word<T, D, N>(x, R, c, k, idx);
                 __syncthreads();
             }
         }
-        for (uint32_t i = threadIdx.x; i < S; i += 256) out[r * S + i] = R[i];
+        if constexpr (WORDS) {
+            for (uint32_t i = threadIdx.x; i < n; i += 256) {
+                const uint32_t w = uint32_t(index[i]);
+                T v = x[w];
+#pragma unroll
+                for (int k = 2; k <= N; ++k)
+                    if (w >= fixed_off(D, k) && w < fixed_off(D, k + 1)) v = horner_word<T, D, N>(x, R, T(1), k, w - fixed_off(D, k));
+                out[r * n + i] = v;
+            }
+        } else {
+            for (uint32_t i = threadIdx.x; i < S; i += 256) out[r * S + i] = R[i];
+        }
         __syncthreads();
     }
 }
@@ -137,64 +156,6 @@ sig_log_fixed_kernel(int64_t rows, const T *__restrict__ in, T *__restrict__ out
 // reads the k(k+1)/2 coefficients of its sub-words (neighbouring threads share all but k of them) and spends
 // about k^3/6 multiply-adds.  Nothing is written but the result, so signatures of any size spread over the
 // whole chip without synchronisation.
-constexpr int kDirectMaxDepth = 9;
-
-template <int I, int End, typename F>
-__device__ __forceinline__ void static_for(F &&f)   // f(integral_constant<int, I>), ..., f(integral_constant<int, End - 1>)
-{
-    if constexpr (I < End) {
-        f(std::integral_constant<int, I>{});
-        static_for<I + 1, End>(f);
-    }
-}
-
-template <typename T, int D, int K>
-__device__ __forceinline__ T log_of_word(const T *__restrict__ x, uint32_t idx, uint32_t d, const uint32_t (&off)[kDirectMaxDepth + 2])
-{
-    uint32_t w[K];   // letters, first to last
-    {
-        uint32_t rest = idx;
-#pragma unroll
-        for (int t = K - 1; t >= 0; --t) {
-            w[t] = D > 0 ? rest % uint32_t(D) : rest % d;
-            rest = D > 0 ? rest / uint32_t(D) : rest / d;
-        }
-    }
-    // xs[at(i, j)] = x[w_{i+1}..w_j], 0 <= i < j <= K, packed.  Every index below is a compile-time constant
-    // (static_for, not a loop the compiler may or may not unroll: at K = 9 it left some of them rolled, which put
-    // this array in scratch memory and made the kernel 6 times slower), so the arrays live in registers.
-    constexpr auto at = [](int i, int j) { return i * K - i * (i - 1) / 2 + (j - i - 1); };
-    T xs[K * (K + 1) / 2];
-    static_for<0, K>([&](auto ic) {
-        constexpr int i = decltype(ic)::value;
-        uint32_t val = 0;
-        static_for<i + 1, K + 1>([&](auto jc) {
-            constexpr int j = decltype(jc)::value;
-            val = val * (D > 0 ? uint32_t(D) : d) + w[j - 1];
-            xs[at(i, j)] = x[off[j - i] + val];
-        });
-    });
-    // P_1[j] = x[w_1..w_j]; P_m[j] = sum_{m-1 <= i < j} P_{m-1}[i] x[w_{i+1}..w_j]
-    T prev[K + 1], cur[K + 1];
-    static_for<1, K + 1>([&](auto jc) { prev[decltype(jc)::value] = xs[at(0, decltype(jc)::value)]; });
-    T result = prev[K];
-    static_for<2, K + 1>([&](auto mc) {
-        constexpr int m = decltype(mc)::value;
-        static_for<m, K + 1>([&](auto jc) {
-            constexpr int j = decltype(jc)::value;
-            T acc = T(0);
-            static_for<m - 1, j>([&](auto ic) {
-                constexpr int i = decltype(ic)::value;
-                acc += prev[i] * xs[at(i, j)];
-            });
-            cur[j] = acc;
-        });
-        result += ((m & 1) ? T(1) : T(-1)) / T(m) * cur[K];
-        static_for<m, K + 1>([&](auto jc) { prev[decltype(jc)::value] = cur[decltype(jc)::value]; });
-    });
-    return result;
-}
-
 template <typename T, int D>
 __global__ void __launch_bounds__(256)
 sig_log_direct_kernel(Shape sh, const T *__restrict__ in, T *__restrict__ out)
@@ -234,6 +195,64 @@ sig_log_direct_kernel(Shape sh, const T *__restrict__ in, T *__restrict__ out)
     }
 }
 
+// The same for chosen words only, out[r][i] = log(1 + x[r])[index[i]]: with the Lyndon words, about one word in k of those of
+// k letters, most of the work above is not done at all and nothing is written that a gather would have to pick from
+// (32 signatures of d = 5, N = 7: 6.8 us, where all words and the gather take 23 + 4; of d = N = 7: 36 against 204 + 12).
+// What bounds it is the reads of the sub-words; consecutive words of the index share most of them.
+template <typename T, int D>
+__global__ void __launch_bounds__(256)
+sig_log_words_kernel(Shape sh, const T *__restrict__ in, const int64_t *__restrict__ index, uint32_t n, T *__restrict__ out)
+{
+    const uint32_t d = D > 0 ? uint32_t(D) : uint32_t(sh.d);
+    uint32_t off[kDirectMaxDepth + 2];   // level offsets, by the channel count alone: the deepest ones may wrap, no word lies there
+    off[1] = 0;
+    {
+        uint32_t size = d;
+#pragma unroll
+        for (int k = 2; k <= kDirectMaxDepth + 1; ++k) {
+            off[k] = off[k - 1] + size;
+            size *= d;
+        }
+    }
+    const int N = sh.N;
+    const int64_t total = sh.B * int64_t(n);
+    for (int64_t e = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; e < total; e += int64_t(gridDim.x) * blockDim.x) {
+        const int64_t r = e / n;
+        const uint32_t i = uint32_t(index[e - r * n]);
+        const T *x = in + r * sh.S;
+        int k = 1;
+        uint32_t base = 0;
+#pragma unroll
+        for (int j = 2; j <= kDirectMaxDepth; ++j)
+            if (j <= N && i >= off[j]) {
+                k = j;
+                base = off[j];
+            }
+        const uint32_t idx = i - base;
+        T v;
+        switch (k) {
+            case 1: v = x[i]; break;
+            case 2: v = log_of_word<T, D, 2>(x, idx, d, off); break;
+            case 3: v = log_of_word<T, D, 3>(x, idx, d, off); break;
+            case 4: v = log_of_word<T, D, 4>(x, idx, d, off); break;
+            case 5: v = log_of_word<T, D, 5>(x, idx, d, off); break;
+            case 6: v = log_of_word<T, D, 6>(x, idx, d, off); break;
+            case 7: v = log_of_word<T, D, 7>(x, idx, d, off); break;
+            case 8: v = log_of_word<T, D, 8>(x, idx, d, off); break;
+            default: v = log_of_word<T, D, 9>(x, idx, d, off); break;
+        }
+        out[e] = v;
+    }
+}
+
+template <typename T, int D>
+void launch_words(const Shape &sh, const T *in, const int64_t *index, int64_t n, T *out, hipStream_t st)
+{
+    const int64_t total = sh.B * n;
+    const unsigned grid = unsigned((total + 255) / 256 < (1 << 20) ? (total + 255) / 256 : (1 << 20));
+    hipLaunchKernelGGL((sig_log_words_kernel<T, D>), dim3(grid), dim3(256), 0, st, sh, in, index, uint32_t(n), out);
+}
+
 template <typename T, int D>
 void launch_direct(const Shape &sh, const T *in, T *out, hipStream_t st)
 {
@@ -242,13 +261,17 @@ void launch_direct(const Shape &sh, const T *in, T *out, hipStream_t st)
     hipLaunchKernelGGL((sig_log_direct_kernel<T, D>), dim3(grid), dim3(256), 0, st, sh, in, out);
 }
 
+// index null: every word
 template <typename T, int D, int N>
-bool try_fixed(const Shape &sh, const T *in, T *out, unsigned grid, hipStream_t st)
+bool try_fixed(const Shape &sh, const T *in, const int64_t *index, int64_t n, T *out, unsigned grid, hipStream_t st)
 {
     constexpr size_t lds = 2 * size_t(fixed_off(D, N + 1)) * sizeof(T);
     if constexpr (lds <= 64 * 1024) {
         if (sh.d == D && sh.N == N) {
-            hipLaunchKernelGGL((sig_log_fixed_kernel<T, D, N>), dim3(grid), dim3(256), lds, st, sh.B, in, out);
+            if (index != nullptr)
+                hipLaunchKernelGGL((sig_log_fixed_kernel<T, D, N, true>), dim3(grid), dim3(256), lds, st, sh.B, in, index, uint32_t(n), out);
+            else
+                hipLaunchKernelGGL((sig_log_fixed_kernel<T, D, N, false>), dim3(grid), dim3(256), lds, st, sh.B, in, index, uint32_t(n), out);
             return true;
         }
     }
@@ -265,21 +288,29 @@ sig_gather_kernel(const T *__restrict__ in, int64_t in_stride, const int64_t *__
             out[r * n + i] = in[r * in_stride + index[i]];
 }
 
+unsigned row_grid(const Shape &sh) { return unsigned(sh.B < (int64_t(1) << 20) ? sh.B : (int64_t(1) << 20)); }
+
+template <typename T>
+bool try_any_fixed(const Shape &sh, const T *in, const int64_t *index, int64_t n, T *out, hipStream_t st)
+{
+    const unsigned grid = row_grid(sh);
+    return try_fixed<T, 2, 2>(sh, in, index, n, out, grid, st) || try_fixed<T, 2, 3>(sh, in, index, n, out, grid, st) ||
+           try_fixed<T, 2, 4>(sh, in, index, n, out, grid, st) || try_fixed<T, 2, 5>(sh, in, index, n, out, grid, st) ||
+           try_fixed<T, 2, 6>(sh, in, index, n, out, grid, st) || try_fixed<T, 2, 7>(sh, in, index, n, out, grid, st) ||
+           try_fixed<T, 3, 2>(sh, in, index, n, out, grid, st) || try_fixed<T, 3, 3>(sh, in, index, n, out, grid, st) ||
+           try_fixed<T, 3, 4>(sh, in, index, n, out, grid, st) || try_fixed<T, 3, 5>(sh, in, index, n, out, grid, st) ||
+           try_fixed<T, 3, 6>(sh, in, index, n, out, grid, st) || try_fixed<T, 4, 2>(sh, in, index, n, out, grid, st) ||
+           try_fixed<T, 4, 3>(sh, in, index, n, out, grid, st) || try_fixed<T, 4, 4>(sh, in, index, n, out, grid, st) ||
+           try_fixed<T, 4, 5>(sh, in, index, n, out, grid, st) || try_fixed<T, 4, 6>(sh, in, index, n, out, grid, st) ||
+           try_fixed<T, 8, 2>(sh, in, index, n, out, grid, st) || try_fixed<T, 8, 3>(sh, in, index, n, out, grid, st) ||
+           try_fixed<T, 8, 4>(sh, in, index, n, out, grid, st);
+}
+
 template <typename T>
 hipError_t launch_log(const Shape &sh, const T *in, T *out, hipStream_t st)
 {
-    const unsigned grid = unsigned(sh.B < (int64_t(1) << 20) ? sh.B : (int64_t(1) << 20));
-    if (try_fixed<T, 2, 2>(sh, in, out, grid, st) || try_fixed<T, 2, 3>(sh, in, out, grid, st) ||
-        try_fixed<T, 2, 4>(sh, in, out, grid, st) || try_fixed<T, 2, 5>(sh, in, out, grid, st) ||
-        try_fixed<T, 2, 6>(sh, in, out, grid, st) || try_fixed<T, 2, 7>(sh, in, out, grid, st) ||
-        try_fixed<T, 3, 2>(sh, in, out, grid, st) || try_fixed<T, 3, 3>(sh, in, out, grid, st) ||
-        try_fixed<T, 3, 4>(sh, in, out, grid, st) || try_fixed<T, 3, 5>(sh, in, out, grid, st) ||
-        try_fixed<T, 3, 6>(sh, in, out, grid, st) || try_fixed<T, 4, 2>(sh, in, out, grid, st) ||
-        try_fixed<T, 4, 3>(sh, in, out, grid, st) || try_fixed<T, 4, 4>(sh, in, out, grid, st) ||
-        try_fixed<T, 4, 5>(sh, in, out, grid, st) || try_fixed<T, 4, 6>(sh, in, out, grid, st) ||
-        try_fixed<T, 8, 2>(sh, in, out, grid, st) || try_fixed<T, 8, 3>(sh, in, out, grid, st) ||
-        try_fixed<T, 8, 4>(sh, in, out, grid, st))
-        return hipGetLastError();
+    const unsigned grid = row_grid(sh);
+    if (try_any_fixed<T>(sh, in, nullptr, 0, out, st)) return hipGetLastError();
     if (sh.N <= kDirectMaxDepth) {
         switch (sh.d) {
             case 2: launch_direct<T, 2>(sh, in, out, st); break;
@@ -308,6 +339,23 @@ hipError_t launch_log(const Shape &sh, const T *in, T *out, hipStream_t st)
 }
 
 template <typename T>
+hipError_t launch_log_words(const Shape &sh, const T *in, const int64_t *index, int64_t n, T *out, hipStream_t st)
+{
+    if (try_any_fixed<T>(sh, in, index, n, out, st)) return hipGetLastError();
+    switch (sh.d) {
+        case 2: launch_words<T, 2>(sh, in, index, n, out, st); break;
+        case 3: launch_words<T, 3>(sh, in, index, n, out, st); break;
+        case 4: launch_words<T, 4>(sh, in, index, n, out, st); break;
+        case 5: launch_words<T, 5>(sh, in, index, n, out, st); break;
+        case 6: launch_words<T, 6>(sh, in, index, n, out, st); break;
+        case 7: launch_words<T, 7>(sh, in, index, n, out, st); break;
+        case 8: launch_words<T, 8>(sh, in, index, n, out, st); break;
+        default: launch_words<T, 0>(sh, in, index, n, out, st); break;
+    }
+    return hipGetLastError();
+}
+
+template <typename T>
 hipError_t launch_gather(const Shape &sh, const T *in, const int64_t *index, int64_t n, T *out, hipStream_t st)
 {
     const unsigned bx = unsigned((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
@@ -327,6 +375,17 @@ hipError_t launch_gather_f32(const Shape &sh, const float *in, const int64_t *in
 hipError_t launch_gather_f64(const Shape &sh, const double *in, const int64_t *index, int64_t n, double *out, hipStream_t st)
 {
     return launch_gather(sh, in, index, n, out, st);
+}
+
+bool log_words_supported(const Shape &sh) { return sh.N <= kDirectMaxDepth && sh.S < (int64_t(1) << 31); }
+
+hipError_t launch_log_words_f32(const Shape &sh, const float *in, const int64_t *index, int64_t n, float *out, hipStream_t st)
+{
+    return launch_log_words(sh, in, index, n, out, st);
+}
+hipError_t launch_log_words_f64(const Shape &sh, const double *in, const int64_t *index, int64_t n, double *out, hipStream_t st)
+{
+    return launch_log_words(sh, in, index, n, out, st);
 }
 
 // Offsets of the coefficients of all Lyndon words of length 1..N inside a flat element: by length, and

@@ -16,9 +16,10 @@
 // One launch per step walks every M_l once, in contiguous pieces: column sums stay in the lanes, row dots are
 // reduced inside a wavefront.  Pieces of one matrix go to different workgroups, which write partial sums; a
 // second launch adds them up in a fixed order (no atomics: the result does not depend on scheduling).
-// The R_m are recomputed first, one launch per m, into the workspace.
+// The R_m are recomputed first, into the workspace.
 #include "sig_internal.h"
 #include "sig_lane_ops.h"
+#include "sig_power_words.h"
 
 namespace sig {
 namespace {
@@ -43,13 +44,25 @@ struct LbLevel {               // the matrix M_l of one step
     int64_t apart_off, bpart_off;   // where its partial sums start inside a batch row's share of the buffers
 };
 
-struct LbStep {
+// LEVELS: room for as many matrices (a launch copies its arguments: two kilobytes for all depths, half of one up to depth 9)
+template <int LEVELS>
+struct LbStepOf {
     int count;                 // matrices: l = 1..count, G has count + 1 levels
     uint32_t wgs;              // workgroups per batch row
     uint32_t S_next, S_cur;    // S(n - 1), S(n)
     int64_t apart_stride, bpart_stride;   // per batch row
-    LbLevel lv[SIG_MAX_DEPTH];
+    LbLevel lv[LEVELS];
 };
+typedef LbStepOf<SIG_MAX_DEPTH> LbStep;
+constexpr int kLbFewLevels = 8;
+typedef LbStepOf<kLbFewLevels> LbFewStep;
+
+LbFewStep few_levels(const LbStep &stp)
+{
+    LbFewStep f{stp.count, stp.wgs, stp.S_next, stp.S_cur, stp.apart_stride, stp.bpart_stride, {}};
+    for (int i = 0; i < kLbFewLevels; ++i) f.lv[i] = stp.lv[i];
+    return f;
+}
 
 template <typename T>
 __device__ __forceinline__ T lanes_sum(T s, uint32_t lg)   // sum over aligned groups of 2^lg lanes (lg <= 6)
@@ -65,13 +78,13 @@ __device__ __forceinline__ T lanes_sum(T s, uint32_t lg)   // sum over aligned g
     return s;
 }
 
-// R_m = c_m x + x * R_{m+1} at levels 1..n (n = N - m + 1); R_{m+1} null for m = N.  One thread per scalar.
-template <typename T, int D>
+// R_m = c_m x + x * R_{m+1} at levels 1..n (n = N - m + 1); R_{m+1} null for m = N.  One thread per scalar.  (Beyond depth 9.)
+template <typename T>
 __global__ void __launch_bounds__(kLbThreads)
 log_bwd_horner_kernel(Shape sh, int n, T c_m, const T *__restrict__ x, const T *__restrict__ r_next, T *__restrict__ r_out,
                       int64_t r_stride)
 {
-    const uint32_t d = D > 0 ? uint32_t(D) : uint32_t(sh.d);
+    const uint32_t d = uint32_t(sh.d);
     const int64_t S_n = sh.off[n + 1];
     const int64_t gid = int64_t(blockIdx.x) * kLbThreads + threadIdx.x;
     if (gid >= sh.B * S_n) return;
@@ -95,10 +108,77 @@ log_bwd_horner_kernel(Shape sh, int n, T c_m, const T *__restrict__ x, const T *
     r_out[row * r_stride + q] = acc;
 }
 
-// One step: partial column sums (x^T M_l) and row dots (M_l R_l) of every matrix of the step.
-template <typename T>
+// All R_m, m = 2 .. N, at once (N <= 9): R_m = sum_{q >= 1} c_{m+q-1} x^{[x] q} at levels 1 .. N-m+1, a thread per word of up to N-1
+// letters, which forms the powers of x at its word once.  One launch instead of N - 1 that wait for one another.
+template <typename T, int D, int K>
+__device__ __forceinline__ void r_of_word(const T *__restrict__ x, uint32_t idx, uint32_t d, const uint32_t (&off)[kDirectMaxDepth + 2], int N,
+                                          uint32_t at, T *__restrict__ r)
+{
+    T power[K + 1];
+    powers_of_word<T, D, K>(x, idx, d, off, power);
+    for (int m = N; m >= 2; --m) {   // R_N first
+        const int n = N - m + 1;
+        if (K <= n) {
+            T v = T(0);
+#pragma unroll
+            for (int q = 1; q <= K; ++q) v += ((m + q) & 1 ? T(-1) : T(1)) / T(m + q - 1) * power[q];
+            r[at] = v;
+        }
+        uint32_t size = d, total = 0;   // S(n)
+        for (int k = 1; k <= n; ++k) {
+            total += size;
+            size *= d;
+        }
+        r += total;
+    }
+}
+
+template <typename T, int D>
 __global__ void __launch_bounds__(kLbThreads)
-log_bwd_main_kernel(LbStep stp, const T *__restrict__ x, int64_t x_stride, int64_t x_group, const T *__restrict__ G,
+log_bwd_r_kernel(Shape sh, const T *__restrict__ x, T *__restrict__ r_out, int64_t r_stride)
+{
+    const uint32_t d = D > 0 ? uint32_t(D) : uint32_t(sh.d);
+    const int N = sh.N;
+    uint32_t off[kDirectMaxDepth + 2];
+    off[1] = 0;
+    {
+        uint32_t size = d;   // the deepest offsets may wrap; no word lies there
+#pragma unroll
+        for (int k = 2; k <= kDirectMaxDepth + 1; ++k) {
+            off[k] = off[k - 1] + size;
+            size *= d;
+        }
+    }
+    const int64_t S_low = sh.off[N], gid = int64_t(blockIdx.x) * kLbThreads + threadIdx.x;
+    if (gid >= sh.B * S_low) return;
+    const int64_t row = gid / S_low;
+    const uint32_t q = uint32_t(gid - row * S_low);
+    const T *xr = x + row * sh.S;
+    T *r = r_out + row * r_stride;
+    int k = 1;
+    uint32_t base = 0;
+#pragma unroll
+    for (int j = 2; j < kDirectMaxDepth; ++j)
+        if (j < N && q >= off[j]) {
+            k = j;
+            base = off[j];
+        }
+    switch (k) {
+        case 1: r_of_word<T, D, 1>(xr, q - base, d, off, N, q, r); break;
+        case 2: r_of_word<T, D, 2>(xr, q - base, d, off, N, q, r); break;
+        case 3: r_of_word<T, D, 3>(xr, q - base, d, off, N, q, r); break;
+        case 4: r_of_word<T, D, 4>(xr, q - base, d, off, N, q, r); break;
+        case 5: r_of_word<T, D, 5>(xr, q - base, d, off, N, q, r); break;
+        case 6: r_of_word<T, D, 6>(xr, q - base, d, off, N, q, r); break;
+        case 7: r_of_word<T, D, 7>(xr, q - base, d, off, N, q, r); break;
+        default: r_of_word<T, D, 8>(xr, q - base, d, off, N, q, r); break;
+    }
+}
+
+// One step: partial column sums (x^T M_l) and row dots (M_l R_l) of every matrix of the step.
+template <typename T, typename Step>
+__global__ void __launch_bounds__(kLbThreads)
+log_bwd_main_kernel(Step stp, const T *__restrict__ x, int64_t x_stride, int64_t x_group, const T *__restrict__ G,
                     int64_t g_stride, const T *__restrict__ R, int64_t r_stride, T *__restrict__ apart, T *__restrict__ bpart)
 {
     __shared__ T prod[2][kLbThreads];
@@ -202,9 +282,9 @@ log_bwd_main_kernel(LbStep stp, const T *__restrict__ x, int64_t x_stride, int64
 //   first: gx is written, not added to.   last: G_{m+1} = G_N has one level and goes straight into gx with c_N.
 //   plus_g: the column sums are the gradient of the right factor of a group product, whose unit term adds G
 //           itself at every level (G_next then has as many levels as G).
-template <typename T>
+template <typename T, typename Step>
 __global__ void __launch_bounds__(kLbThreads)
-log_bwd_finish_kernel(LbStep stp, int64_t rows, T c_m, T c_last, int first, int last, int plus_g, const T *__restrict__ G,
+log_bwd_finish_kernel(Step stp, int64_t rows, T c_m, T c_last, int first, int last, int plus_g, const T *__restrict__ G,
                       int64_t g_stride, const T *__restrict__ apart, const T *__restrict__ bpart, T *__restrict__ G_next,
                       int64_t gn_stride, T *__restrict__ gx, int64_t gx_stride)
 {
@@ -724,6 +804,22 @@ scatter_kernel(const T *__restrict__ in, const int64_t *__restrict__ index, int6
             out[r * out_stride + index[i]] = in[r * n + i];
 }
 
+// Zeros and scatter in one launch, a workgroup per row, while a row is short (up to 8192 scalars: 256 rows of 1554, 2.8 us
+// against 2.3 + 2.4 for the two kernels above; beyond, they spread a row over more workgroups).
+constexpr int64_t kScatterRow = 8192;
+
+template <typename T>
+__global__ void __launch_bounds__(kLbThreads)
+scatter_row_kernel(const T *__restrict__ in, const int64_t *__restrict__ index, int64_t n, int64_t rows, int64_t S, T *out)
+{
+    for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
+        T *o = out + r * S;
+        for (int64_t i = threadIdx.x; i < S; i += kLbThreads) o[i] = T(0);
+        __syncthreads();
+        for (int64_t i = threadIdx.x; i < n; i += kLbThreads) o[index[i]] = in[r * n + i];
+    }
+}
+
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
 // The work of the step whose cotangent G has n levels (n >= 2).
@@ -851,11 +947,35 @@ int64_t r_offset(const Shape &sh, int m)
 }
 
 template <typename T, int D>
-void launch_horner(const Shape &sh, int n, T c_m, const T *x, const T *r_next, T *r_out, int64_t r_stride, hipStream_t st)
+void launch_r(const Shape &sh, const T *x, T *r_out, int64_t r_stride, hipStream_t st)
 {
-    const int64_t threads = sh.B * sh.off[n + 1];
-    hipLaunchKernelGGL((log_bwd_horner_kernel<T, D>), dim3(unsigned((threads + kLbThreads - 1) / kLbThreads)), dim3(kLbThreads),
-                       0, st, sh, n, c_m, x, r_next, r_out, r_stride);
+    const int64_t threads = sh.B * sh.off[sh.N];
+    hipLaunchKernelGGL((log_bwd_r_kernel<T, D>), dim3(unsigned((threads + kLbThreads - 1) / kLbThreads)), dim3(kLbThreads), 0, st, sh, x,
+                       r_out, r_stride);
+}
+
+// One step of the chain of launches; see the two kernels.
+template <typename T, typename Step>
+hipError_t launch_step(const Step &stp, int64_t rows, const T *x, int64_t x_stride, int64_t x_group, const T *G, int64_t g_stride, const T *R,
+                       int64_t r_stride, T *apart, T *bpart, T c_m, T c_last, int first, int last, int plus_g, T *G_next, int64_t gn_stride,
+                       T *gx, int64_t gx_stride, hipStream_t st)
+{
+    const int64_t wgs = rows * int64_t(stp.wgs);
+    if (wgs > 0x7fffffff) return hipErrorNotSupported;
+    hipLaunchKernelGGL((log_bwd_main_kernel<T, Step>), dim3(unsigned(wgs)), dim3(kLbThreads), 0, st, stp, x, x_stride, x_group, G, g_stride,
+                       R, r_stride, apart, bpart);
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+    const int64_t threads = rows * (int64_t(stp.S_next) + stp.S_cur + (plus_g ? stp.S_cur - stp.S_next : 0));
+    hipLaunchKernelGGL((log_bwd_finish_kernel<T, Step>), dim3(unsigned((threads + kLbThreads - 1) / kLbThreads)), dim3(kLbThreads), 0, st,
+                       stp, rows, c_m, c_last, first, last, plus_g, G, g_stride, apart, bpart, G_next, gn_stride, gx, gx_stride);
+    return hipGetLastError();
+}
+
+template <typename T, typename... Args>
+hipError_t launch_step_any(const LbStep &stp, Args... args)
+{
+    return stp.count <= kLbFewLevels ? launch_step<T>(few_levels(stp), args...) : launch_step<T>(stp, args...);
 }
 
 template <typename T, int LOGD, int NT, int N>
@@ -925,40 +1045,36 @@ hipError_t launch_log_backward(const Shape &sh, const T *x, const T *g, T *gx, v
     T *bpart = reinterpret_cast<T *>(base + ws.b_off);
     auto coef = [](int m) { return (m & 1 ? T(1) : T(-1)) / T(m); };
 
-    for (int m = N; m >= 2; --m) {
-        const int n = N - m + 1;
-        const T *r_next = m == N ? nullptr : Rs + r_offset(sh, m + 1);
-        T *r_out = Rs + r_offset(sh, m);
+    if (N <= kDirectMaxDepth) {
         switch (sh.d) {
-            case 2: launch_horner<T, 2>(sh, n, coef(m), x, r_next, r_out, ws.r_stride, st); break;
-            case 3: launch_horner<T, 3>(sh, n, coef(m), x, r_next, r_out, ws.r_stride, st); break;
-            case 4: launch_horner<T, 4>(sh, n, coef(m), x, r_next, r_out, ws.r_stride, st); break;
-            case 5: launch_horner<T, 5>(sh, n, coef(m), x, r_next, r_out, ws.r_stride, st); break;
-            case 6: launch_horner<T, 6>(sh, n, coef(m), x, r_next, r_out, ws.r_stride, st); break;
-            case 7: launch_horner<T, 7>(sh, n, coef(m), x, r_next, r_out, ws.r_stride, st); break;
-            case 8: launch_horner<T, 8>(sh, n, coef(m), x, r_next, r_out, ws.r_stride, st); break;
-            default: launch_horner<T, 0>(sh, n, coef(m), x, r_next, r_out, ws.r_stride, st); break;
+            case 2: launch_r<T, 2>(sh, x, Rs, ws.r_stride, st); break;
+            case 3: launch_r<T, 3>(sh, x, Rs, ws.r_stride, st); break;
+            case 4: launch_r<T, 4>(sh, x, Rs, ws.r_stride, st); break;
+            case 5: launch_r<T, 5>(sh, x, Rs, ws.r_stride, st); break;
+            case 6: launch_r<T, 6>(sh, x, Rs, ws.r_stride, st); break;
+            case 7: launch_r<T, 7>(sh, x, Rs, ws.r_stride, st); break;
+            case 8: launch_r<T, 8>(sh, x, Rs, ws.r_stride, st); break;
+            default: launch_r<T, 0>(sh, x, Rs, ws.r_stride, st); break;
         }
         const hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
+    } else {
+        for (int m = N; m >= 2; --m) {
+            const int n = N - m + 1;
+            const int64_t threads = sh.B * sh.off[n + 1];
+            hipLaunchKernelGGL((log_bwd_horner_kernel<T>), dim3(unsigned((threads + kLbThreads - 1) / kLbThreads)), dim3(kLbThreads), 0, st, sh,
+                               n, coef(m), x, m == N ? nullptr : Rs + r_offset(sh, m + 1), Rs + r_offset(sh, m), ws.r_stride);
+            const hipError_t err = hipGetLastError();
+            if (err != hipSuccess) return err;
+        }
     }
     for (int m = 1; m <= N - 1; ++m) {
-        const int n = N - m + 1;
-        const LbStep stp = plan_step(sh, n);
+        const LbStep stp = plan_step(sh, N - m + 1);
         const T *G = m == 1 ? g : Gb[m & 1];
-        const int64_t g_stride = m == 1 ? sh.S : ws.g_stride;
-        T *G_next = Gb[(m + 1) & 1];
-        const int64_t wgs = sh.B * int64_t(stp.wgs);
-        if (wgs > 0x7fffffff) return hipErrorNotSupported;
-        hipLaunchKernelGGL((log_bwd_main_kernel<T>), dim3(unsigned(wgs)), dim3(kLbThreads), 0, st, stp, x, sh.S, int64_t(1), G, g_stride,
-                           Rs + r_offset(sh, m + 1), ws.r_stride, apart, bpart);
-        hipError_t err = hipGetLastError();
-        if (err != hipSuccess) return err;
-        const int64_t threads = sh.B * (int64_t(stp.S_next) + stp.S_cur);
-        hipLaunchKernelGGL((log_bwd_finish_kernel<T>), dim3(unsigned((threads + kLbThreads - 1) / kLbThreads)), dim3(kLbThreads),
-                           0, st, stp, sh.B, coef(m), coef(N), int(m == 1), int(m == N - 1), 0, G, g_stride, apart, bpart, G_next,
-                           ws.g_stride, gx, sh.S);
-        err = hipGetLastError();
+        const hipError_t err =
+            launch_step_any<T>(stp, sh.B, x, int64_t(sh.S), int64_t(1), G, int64_t(m == 1 ? sh.S : ws.g_stride),
+                               static_cast<const T *>(Rs + r_offset(sh, m + 1)), int64_t(ws.r_stride), apart, bpart, T(coef(m)), T(coef(N)),
+                               int(m == 1), int(m == N - 1), 0, Gb[(m + 1) & 1], int64_t(ws.g_stride), gx, int64_t(sh.S), st);
         if (err != hipSuccess) return err;
     }
     return hipSuccess;
@@ -1002,17 +1118,9 @@ hipError_t launch_combine_backward(const Shape &sh, const T *a, const T *b, cons
     }
     T *apart = reinterpret_cast<T *>(base + ws.a_off);
     T *bpart = reinterpret_cast<T *>(base + ws.b_off);
-    const LbStep stp = plan_step(sh, sh.N);
-    const int64_t wgs = sh.B * int64_t(stp.wgs);
-    if (wgs > 0x7fffffff) return hipErrorNotSupported;
-    hipLaunchKernelGGL((log_bwd_main_kernel<T>), dim3(unsigned(wgs)), dim3(kLbThreads), 0, st, stp, a, sh.S, a_group, g, sh.S, b,
-                       sh.S, apart, bpart);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
-    const int64_t threads = sh.B * 2 * int64_t(stp.S_cur);
-    hipLaunchKernelGGL((log_bwd_finish_kernel<T>), dim3(unsigned((threads + kLbThreads - 1) / kLbThreads)), dim3(kLbThreads), 0,
-                       st, stp, sh.B, T(1), T(0), 1, 0, 1, g, sh.S, apart, bpart, gb, sh.S, ga_rows, sh.S);
-    err = hipGetLastError();
+    const hipError_t err =
+        launch_step_any<T>(plan_step(sh, sh.N), sh.B, a, int64_t(sh.S), a_group, g, int64_t(sh.S), b, int64_t(sh.S), apart, bpart, T(1), T(0), 1, 0,
+                           1, gb, int64_t(sh.S), ga_rows, int64_t(sh.S), st);
     if (err != hipSuccess || a_group == 1) return err;
     hipLaunchKernelGGL((group_sum_kernel<T>), dim3(sum_grid), dim3(kLbThreads), 0, st, ga_rows, groups, a_group, int64_t(sh.S), ga);
     return hipGetLastError();
@@ -1021,6 +1129,11 @@ hipError_t launch_combine_backward(const Shape &sh, const T *a, const T *b, cons
 template <typename T>
 hipError_t launch_scatter(const Shape &sh, const T *in, const int64_t *index, int64_t n, T *out, hipStream_t st)
 {
+    if (sh.S <= kScatterRow) {
+        const unsigned grid = unsigned(sh.B < 65536 ? sh.B : 65536);
+        hipLaunchKernelGGL((scatter_row_kernel<T>), dim3(grid), dim3(kLbThreads), 0, st, in, index, n, sh.B, sh.S, out);
+        return hipGetLastError();
+    }
     const int64_t total = sh.B * sh.S;
     const int64_t fill_groups = (total + kLbThreads - 1) / kLbThreads;
     hipLaunchKernelGGL((fill_zero_kernel<T>), dim3(unsigned(fill_groups < 65536 ? fill_groups : 65536)), dim3(kLbThreads), 0, st,

@@ -1,0 +1,88 @@
+// Powers of an element of the truncated tensor algebra word by word, for the kernels of the logarithm and of its gradient.
+#ifndef SIG_POWER_WORDS_H_
+#define SIG_POWER_WORDS_H_
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <type_traits>
+
+namespace sig {
+
+constexpr int kDirectMaxDepth = 9;
+
+template <int I, int End, typename F>
+__device__ __forceinline__ void static_for(F &&f)   // f(integral_constant<int, I>), ..., f(integral_constant<int, End - 1>)
+{
+    if constexpr (I < End) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, End>(f);
+    }
+}
+
+// power[m] = x^{[x] m} at the word of K letters number idx of its level, m = 1 .. K: P_m[j], the sum over the cuts of the first j
+// letters into m pieces of the product of their coefficients, by dynamic programming over the cuts.
+template <typename T, int D, int K>
+__device__ __forceinline__ void powers_of_word(const T *__restrict__ x, uint32_t idx, uint32_t d, const uint32_t (&off)[kDirectMaxDepth + 2],
+                                               T (&power)[K + 1])
+{
+    uint32_t w[K];   // letters, first to last
+    {
+        uint32_t rest = idx;
+#pragma unroll
+        for (int t = K - 1; t >= 0; --t) {
+            w[t] = D > 0 ? rest % uint32_t(D) : rest % d;
+            rest = D > 0 ? rest / uint32_t(D) : rest / d;
+        }
+    }
+    // xs[at(i, j)] = x[w_{i+1}..w_j], 0 <= i < j <= K, packed.  Every index below is a compile-time constant
+    // (static_for, not a loop the compiler may or may not unroll: at K = 9 it left some of them rolled, which put
+    // this array in scratch memory and made the kernel 6 times slower), so the arrays live in registers.
+    constexpr auto at = [](int i, int j) { return i * K - i * (i - 1) / 2 + (j - i - 1); };
+    T xs[K * (K + 1) / 2];
+    static_for<0, K>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        uint32_t val = 0;
+        static_for<i + 1, K + 1>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            val = val * (D > 0 ? uint32_t(D) : d) + w[j - 1];
+            xs[at(i, j)] = x[off[j - i] + val];
+        });
+    });
+    // P_1[j] = x[w_1..w_j]; P_m[j] = sum_{m-1 <= i < j} P_{m-1}[i] x[w_{i+1}..w_j]
+    T prev[K + 1], cur[K + 1];
+    static_for<1, K + 1>([&](auto jc) { prev[decltype(jc)::value] = xs[at(0, decltype(jc)::value)]; });
+    power[1] = prev[K];
+    static_for<2, K + 1>([&](auto mc) {
+        constexpr int m = decltype(mc)::value;
+        static_for<m, K + 1>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            T acc = T(0);
+            static_for<m - 1, j>([&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                acc += prev[i] * xs[at(i, j)];
+            });
+            cur[j] = acc;
+        });
+        power[m] = cur[K];
+        static_for<m, K + 1>([&](auto jc) { prev[decltype(jc)::value] = cur[decltype(jc)::value]; });
+    });
+}
+
+// log(1 + x) = sum_m c_m x^{[x] m}, c_m = (-1)^{m+1} / m, at that word
+template <typename T, int D, int K>
+__device__ __forceinline__ T log_of_word(const T *__restrict__ x, uint32_t idx, uint32_t d, const uint32_t (&off)[kDirectMaxDepth + 2])
+{
+    T power[K + 1];
+    powers_of_word<T, D, K>(x, idx, d, off, power);
+    T result = power[1];
+    static_for<2, K + 1>([&](auto mc) {
+        constexpr int m = decltype(mc)::value;
+        result += ((m & 1) ? T(1) : T(-1)) / T(m) * power[m];
+    });
+    return result;
+}
+
+}  // namespace sig
+
+#endif  // SIG_POWER_WORDS_H_

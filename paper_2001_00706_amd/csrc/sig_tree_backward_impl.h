@@ -27,7 +27,7 @@
 // P-1 letters.  There the last letter is known from the row and the others are the group's, so they are sorted into
 // channels once per group and batch, not once per word and increment.  What bounds the kernel is the issue of vector
 // instructions: per wavefront and increment 430 of them at d = N = 7 with the sums formed by lane exchanges, 330 this way
-// (756 -> 545 us for 32 paths of 128 points; d = 5, N = 7: 157 -> 95; d = 6, N = 6: 163 -> 90; 128 paths of 64 points at
+// (732 -> 520 us with the closing sums for 32 paths of 128 points; d = 5, N = 7: 157 -> 95; d = 6, N = 6: 163 -> 90; 128 paths of 64 points at
 // d = 7, N = 5: 92 -> 46).
 #ifndef SIG_TREE_BACKWARD_IMPL_H_
 #define SIG_TREE_BACKWARD_IMPL_H_

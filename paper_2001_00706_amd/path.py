@@ -71,5 +71,5 @@ class Path:
         signature, then for mode "words" the coefficients of the Lyndon words ("expand" keeps every word)."""
         if mode not in ("words", "expand"):
             raise ValueError('mode must be "words" or "expand"')
-        full = binding.sig_log(self.signature(start, end), self.d, self.depth)
-        return full if mode == "expand" else binding.sig_lyndon_gather(full, self.d, self.depth)
+        sig = self.signature(start, end)
+        return binding.sig_log(sig, self.d, self.depth) if mode == "expand" else binding.sig_log_words(sig, self.d, self.depth)

@@ -299,6 +299,10 @@ def test_lyndon_table_is_built_on_the_host(lib):
     assert lib.sig_lyndon_gather(p, 2, 2, 2, p, 7, sig.SIG_F32, p, 0) == sig.SIG_ERR_INVALID_ARG   # more entries than S
     assert lib.sig_lyndon_gather(p, 2, 2, 2, 0, 3, sig.SIG_F32, p, 0) == sig.SIG_ERR_INVALID_ARG
     assert lib.sig_lyndon_gather(0, 0, 2, 2, 0, 3, sig.SIG_F32, 0, 0) == sig.SIG_OK
+    assert lib.sig_log_words(p, 2, 2, 2, p, 7, sig.SIG_F32, p, 0) == sig.SIG_ERR_INVALID_ARG
+    assert lib.sig_log_words(p, 2, 2, 2, 0, 3, sig.SIG_F32, p, 0) == sig.SIG_ERR_INVALID_ARG
+    assert lib.sig_log_words(p, 2, 2, 10, p, 3, sig.SIG_F32, p, 0) == sig.SIG_ERR_UNSUPPORTED       # beyond depth 9
+    assert lib.sig_log_words(0, 0, 2, 2, 0, 3, sig.SIG_F32, 0, 0) == sig.SIG_OK
     assert lib.sig_lyndon_scatter(p, 2, 2, 2, p, 7, sig.SIG_F32, p, 0) == sig.SIG_ERR_INVALID_ARG
     assert lib.sig_lyndon_scatter(0, 2, 2, 2, p, 3, sig.SIG_F32, p, 0) == sig.SIG_ERR_INVALID_ARG
     assert lib.sig_lyndon_scatter(0, 0, 2, 2, 0, 3, sig.SIG_F32, 0, 0) == sig.SIG_OK

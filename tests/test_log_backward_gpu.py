@@ -85,6 +85,18 @@ def test_scatter_is_the_transpose_of_gather():
     assert np.array_equal(got, want)
 
 
+# a workgroup per row up to 8192 scalars (d = 2, N = 12 has 8190 and d = 90, N = 2 has 8190), two launches beyond (8372)
+@pytest.mark.parametrize("rows,d,N", [(3, 2, 12), (2, 90, 2), (3, 91, 2), (1, 1, 3)])
+def test_scatter_on_both_sides_of_the_row_limit(rows, d, N):
+    import torch
+    idx = orc.lyndon_indices(d, N)
+    g = np.random.default_rng(5).standard_normal((rows, len(idx))).astype(np.float32)
+    out = torch.full((rows, orc.channels(d, N)), 7.0, device="cuda:0")
+    want = np.zeros(tuple(out.shape), dtype=np.float32)
+    want[..., idx] = g
+    assert np.array_equal(host(sig.sig_lyndon_scatter(dev(g), d, N, out=out)), want)
+
+
 def test_workspace_is_checked():
     import torch
     d, N = 4, 7     # 21 844 scalars per signature: the chain of launches, which needs a workspace

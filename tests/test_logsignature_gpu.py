@@ -132,3 +132,16 @@ def test_log_refuses_to_work_in_place_and_empty_batches_are_fine():
     e = torch.zeros((0, 6), device="cuda:0")
     assert sig.sig_log(e, 2, 2).shape == (0, 6)
     assert sig.sig_lyndon_gather(e, 2, 2).shape == (0, 3)
+
+
+# the kernels for a shape known at compile time, in LDS (d = 2, 3, 4, 8) and, too deep or too large for them, the one that
+# forms a word by itself, with and without a compiled-in channel count; beyond depth 9 all words and a gather; one row and
+# a number of words that is no multiple of a workgroup's
+@pytest.mark.parametrize("dtype", [np.float32, np.float64], ids=["float32", "float64"])
+@pytest.mark.parametrize("rows,d,N", [(1, 2, 2), (130, 3, 6), (3, 4, 6), (2, 8, 4), (2, 4, 7), (5, 5, 5), (1, 7, 4), (3, 9, 2),
+                                      (2, 12, 3), (3, 2, 9), (2, 2, 10), (4, 6, 1), (3, 1, 4)])
+def test_kept_words_are_those_of_the_whole_logarithm(rows, d, N, dtype):
+    s = dev(orc.signature(uniform_paths(rows, 6, d, seed=rows + d + N, lo=-0.5, hi=0.5), N).astype(dtype))
+    got = sig.sig_log_words(s, d, N)
+    np.testing.assert_array_equal(host(got), host(sig.sig_log(s, d, N))[..., orc.lyndon_indices(d, N)])
+    assert sig.sig_log_words(s[:0], d, N).shape == (0, got.shape[-1])
