@@ -8,6 +8,7 @@ call raises.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 import threading
 
@@ -94,9 +95,20 @@ def _on_device(device):
     import torch
 
     index = device.index
-    if index is None or index == torch.cuda.current_device():
+    if index is None or index == _current_device():
         return _NO_GUARD
     return torch.cuda.device(device)
+
+
+def _current_device() -> int:
+    """torch's current device.  `torch.cuda.current_device()` looks at the state of torch's lazy initialisation first, every
+    time; a tensor on the GPU, which every call here has been handed, has seen to that."""
+    import torch
+
+    try:
+        return torch._C._cuda_getDevice()
+    except AttributeError:   # a torch without the raw accessor
+        return torch.cuda.current_device()
 
 
 def current_stream_handle() -> int:
@@ -110,7 +122,7 @@ def _current_stream() -> int:
     import torch
 
     try:
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        return torch._C._cuda_getCurrentRawStream(_current_device())
     except AttributeError:   # a torch without the raw accessor
         return torch.cuda.current_stream().cuda_stream
 
@@ -210,14 +222,21 @@ def load_library() -> ctypes.CDLL:
         return lib
 
 
+# Sizes that follow from their arguments alone are kept: every operation asks for two or three of them, and through
+# ctypes a question costs a third of a microsecond.
+_sizes = functools.lru_cache(maxsize=4096, typed=True)
+
+
 def sig_status_string(status: int) -> str:
     return load_library().sig_status_string(int(status)).decode()
 
 
+@_sizes
 def sig_signature_channels(d: int, N: int) -> int:
     return int(load_library().sig_signature_channels(d, N))
 
 
+@_sizes
 def sig_output_elems(B: int, L: int, d: int, N: int, stream: bool, basepoint: bool) -> int:
     return int(load_library().sig_output_elems(B, L, d, N, int(stream), int(basepoint)))
 
@@ -583,7 +602,7 @@ _lyndon_tables = {}
 def _lyndon_table(d: int, N: int, device):
     """The Lyndon index table on `device`, built once per (d, N, device)."""
     import torch
-    key = (d, N, str(device))
+    key = (d, N, device)
     with _lock:
         t = _lyndon_tables.get(key)
     if t is None:

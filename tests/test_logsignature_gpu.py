@@ -145,3 +145,17 @@ def test_kept_words_are_those_of_the_whole_logarithm(rows, d, N, dtype):
     got = sig.sig_log_words(s, d, N)
     np.testing.assert_array_equal(host(got), host(sig.sig_log(s, d, N))[..., orc.lyndon_indices(d, N)])
     assert sig.sig_log_words(s[:0], d, N).shape == (0, got.shape[-1])
+
+
+def test_logsignature_gradient_in_one_node():
+    """The gradient of the operation as a whole equals that of its parts in sequence, with an inverse and a basepoint tensor."""
+    import torch
+    for d, N, stream, inverse, mode in [(3, 4, False, False, "words"), (5, 3, True, True, "words"), (2, 5, False, True, "expand")]:
+        x = dev(uniform_paths(3, 7, d, seed=d, lo=-0.5, hi=0.5)).requires_grad_(True)
+        b = dev(uniform_paths(3, 1, d, seed=d + 1, lo=-0.5, hi=0.5)[:, 0]).requires_grad_(True)
+        out = sig.logsignature(x, N, stream=stream, basepoint=b, inverse=inverse, mode=mode)
+        parts = sig.signature_to_logsignature(sig.signature(x, N, stream=stream, basepoint=b, inverse=inverse), d, N, mode=mode)
+        assert torch.equal(out, parts)
+        w = torch.randn_like(out)
+        for got, want in zip(torch.autograd.grad(out, (x, b), w), torch.autograd.grad(parts, (x, b), w)):
+            assert torch.equal(got, want)
