@@ -497,11 +497,13 @@ int sig_backward_chunks_fastest(int64_t B, int64_t L, int d, int N, int basepoin
     sig::Shape sh;
     if (make_shape(B, L, d, N, 0, basepoint, sh) != SIG_OK) return 0;
     if (N < 3 || B < 1) return 1;   // depth 2 has a closed form with no walk at all
-    // What a call takes in microseconds, fitted to sweeps over 1 .. 128 paths of 100 .. 65 536 increments at eleven (d, N), in
-    // 1 to 1024 stretches (predicted / measured: 1 x 65 537 points, d = 4, N = 6 in 512: 208 / 236; 8 x 401, d = 7, N = 5 in
-    // 16: 145 / 139; 32 x 513, d = 4, N = 6 in 8: 100 / 106; 128 x 401, d = 16, N = 4 in one piece: 460 / 498).
-    //   * The walk: one increment takes 0.3 to 0.55 while a path's threads fill one wavefront (and at d = 4), 0.8 to 1.25 beyond,
-    //     up to about 160 000 threads at a time; more threads share the time out.
+    // What a call takes in microseconds, fitted to sweeps over 1 .. 128 paths of 100 .. 65 536 increments at twelve (d, N), in
+    // 1 to 1024 stretches (in one piece / in the stretches chosen, measured: 8 x 401 points, d = 7, N = 5: 246 / 115 in 8;
+    // 32 x 801, d = 4, N = 6: 357 / 111 in 8; 128 x 801, d = 16, N = 4: 983 / 838 in 2; 128 x 801, d = 7, N = 5 stays in one
+    // piece: 498 / 487 at best).
+    //   * The walk back in one piece: an increment takes 0.28 to 0.5 while a path's threads fill one wavefront (and at d = 4),
+    //     0.6 beyond, 0.8 to 1.2 from 9 channels on, up to about 130 000 threads at a time; more threads share the time out.
+    //     Stretches are also walked forward, for their signatures: 0.1 to 0.2 more per increment.
     //   * The rounds of products double with every doubling of the stretches: 10 for two more launches, about 4.5 where
     //     most rounds share one.
     //   * Every stretch's signature is written and read some dozen times: 3.5 per 10^6 bytes where four words move as a
@@ -510,11 +512,13 @@ int sig_backward_chunks_fastest(int64_t B, int64_t L, int d, int N, int basepoin
     const int64_t elem = dtype == SIG_F32 ? int64_t(sizeof(float)) : int64_t(sizeof(double));
     double threads = double(sh.pw[d <= 8 ? (N > 2 ? N - 2 : 1) : N - 1]);
     if (dtype == SIG_F32 && d == 16 && N == 4) threads = 512;
-    const double step = threads <= 64 || d == 4 ? 0.4 : 1.15, round = sh.S <= 512 ? 4.5 : 10.5;
+    const bool light = threads <= 64 || d == 4;
+    const double step = light ? 0.35 : d <= 8 ? 0.6 : 1.2, forward = d <= 8 && !light ? 0.2 : 0.1;
+    const double round = sh.S <= 512 ? 4.5 : 10.5;
     const double per_row = (d % 4 == 0 ? 3.5e-6 : 5e-6) * double(sh.S * elem);
     const auto walk = [&](int64_t K) {
-        const double load = double(B) * double(K) * threads / 160e3;
-        return double(sh.n_inc) / double(K) * step * (load > 1 ? load : 1);
+        const double load = double(B) * double(K) * threads / 130e3;
+        return double(sh.n_inc) / double(K) * (K > 1 ? step + forward : step) * (load > 1 ? load : 1);
     };
     // a call in stretches is a dozen launches and more instead of two: it has to gain that much on the host as well
     double best = walk(1) - 40, joined = 24;

@@ -337,19 +337,15 @@ hipError_t launch_backward_f32(const Shape &sh, const float *path, const float *
     if (backward_n2_supported(sh, SIG_F32)) return launch_backward_n2_f32(sh, path, gout, gpath, gbase, st);
     const bool aligned = (reinterpret_cast<uintptr_t>(path) | reinterpret_cast<uintptr_t>(sig) |
                           reinterpret_cast<uintptr_t>(gout) | reinterpret_cast<uintptr_t>(sh.basepoint_value)) % 16 == 0;
-    // Measured at L = 128 over B = 1..2048: with one gradient per path (final mode) the prefix-tree kernels beat the
-    // two register-resident families (by up to 3.6 times at d = 8) except at d = 4, N >= 5 below 512 paths; with a
-    // gradient per prefix (stream mode) the register-resident families stay ahead.
-    // d = 4, N = 6 in final mode: the top level's cotangent in registers, two wavefronts per path (105 us against 172
-    // on the prefix-tree kernels at 1024 paths of 128 points, 77 against 95 on the register-resident family at 32)
+    // d = 4, N = 6 in final mode from four paths per compute unit on: the top level's cotangent in registers, two wavefronts
+    // per path; with fewer paths the prefix-tree kernels' one wavefront of four words a lane is ahead (300 points: 187 us against
+    // 155 at 512 paths, 230 against 208 at 768, 228 against 257 at 896, 233 against 265 at 1024)
     const bool ws_aligned = workspace != nullptr && reinterpret_cast<uintptr_t>(workspace) % 16 == 0;
-    if (aligned && ws_aligned && backward_d4n6_supported(sh) && workspace_bytes >= backward_d4n6_workspace_bytes(sh))
+    if (aligned && ws_aligned && sh.B > 768 && backward_d4n6_supported(sh) && workspace_bytes >= backward_d4n6_workspace_bytes(sh))
         return launch_backward_d4n6_f32(sh, path, sig, gout, gpath, gbase, workspace, workspace_bytes, st);
-    const bool tree_first = !sh.stream && tree_backward_supported(sh) && !(sh.d == 4 && sh.N >= 5 && sh.B < 512);
-    if (aligned && !tree_first && backward_d4_supported(sh))
-        return launch_backward_d4_f32(sh, path, sig, gout, gpath, gbase, st);
-    if (aligned && !tree_first && backward_pow2_supported(sh))
-        return launch_backward_pow2_f32(sh, path, sig, gout, gpath, gbase, st);
+    // a gradient per prefix: the two register-resident families, where they beat the prefix-tree kernels (their rules say where)
+    if (aligned && backward_d4_supported(sh)) return launch_backward_d4_f32(sh, path, sig, gout, gpath, gbase, st);
+    if (aligned && backward_pow2_supported(sh)) return launch_backward_pow2_f32(sh, path, sig, gout, gpath, gbase, st);
     // d = 16, N = 4 (10 ms on the prefix-tree kernels at 256 paths of 1024 points); its workspace is a sixteenth of
     // theirs, which is what sig_backward_workspace_bytes reports for the shape
     if (aligned && backward_d16_supported(sh) && workspace != nullptr && workspace_bytes >= backward_d16_workspace_bytes(sh) &&

@@ -1,4 +1,4 @@
-// Gradient of the signature with respect to the path for d = 4, N = 4..6, fp32 (paper section 5.3,
+// Gradient of the stream of signatures with respect to the path for d = 4, N = 4..6, fp32 (paper section 5.3,
 // appendix C): the recurrences of sig_backward.hip with the whole working set in registers.
 //
 // One workgroup of 256 threads per path.  Thread t stands for the four-letter word u = w1 w2 w3 w4 whose
@@ -7,7 +7,7 @@
 //     u c c' (level 6, cotangent only: the top level of A is never needed), and
 //   * at its ancestors w1, w1 w2, w1 w2 w3 (levels 1..3), redundantly: the 4, 16 or 64 threads below an
 //     ancestor all hold and update the same value with the same arithmetic.
-// "Up" (undo the increment, form the Horner terms T^(k)_i) is then a scalar chain along the thread's own
+// "Up" (the Horner terms T^(k)_i) is then a scalar chain along the thread's own
 // word with no communication at all.  "Down", the chains D^(k)_i contracted with the increment, needs
 // sums over the 4 threads of a quad (level 4 -> 3), the 4 quads of a 16-lane row (3 -> 2) and the 4 rows
 // of a wavefront (2 -> 1): lane permutes inside a wavefront, no LDS, no barrier; wavefronts (first
@@ -15,8 +15,8 @@
 // over the four wavefronts, done once per tile of 64 increments from partial sums left in LDS.  Redundant
 // holders weigh their contribution to that sum by 1/4, 1/16, 1/64 (exact in binary).
 //
-// Stream mode reads the earlier signature from the forward output instead of undoing the increment, and
-// adds the output gradient of every entry on the way; both are fetched one increment ahead.
+// Stream mode only: the earlier signature comes from the forward output, so no increment is undone, and the output
+// gradient of every entry is added on the way; both are fetched one increment ahead.
 #include "sig_internal.h"
 #include "sig_mfma_common.h"
 
@@ -52,7 +52,7 @@ __device__ __forceinline__ float wave_sum_of_rows(float v)
     return v;
 }
 
-template <int N, bool STREAM>
+template <int N>
 __global__ void __launch_bounds__(256)
 sig_backward_d4_kernel(const float *__restrict__ path, const float *__restrict__ sig, const float *__restrict__ gout,
                        float *__restrict__ gpath, float *__restrict__ gbase, int64_t L, int64_t n_inc, int basepoint,
@@ -76,7 +76,7 @@ sig_backward_d4_kernel(const float *__restrict__ path, const float *__restrict__
     const f4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
     const f4 *x4 = reinterpret_cast<const f4 *>(path) + b * L;
     const f4 x_base = bpv != nullptr ? reinterpret_cast<const f4 *>(bpv)[b] : zero4;
-    const int64_t per_path = STREAM ? n_inc * int64_t(kS) : int64_t(kS);
+    const int64_t per_path = n_inc * int64_t(kS);
     const float *sg = sig + b * per_path;
     const float *go = gout + b * per_path;
     float *gp = gpath + b * L * 4;
@@ -106,11 +106,10 @@ sig_backward_d4_kernel(const float *__restrict__ path, const float *__restrict__
         return s;
     };
 
-    // G: cotangent of the signature after the increment being processed.  A: that signature (final mode).
-    Share G = load_share(STREAM ? go + (n_inc - 1) * int64_t(kS) : go, true);
+    // G: cotangent of the signature after the increment being processed.
+    Share G = load_share(go + (n_inc - 1) * int64_t(kS), true);
     Share A = {};
-    Share nextA = {}, nextG = {};   // stream mode: signature before, and output gradient of, the step to come
-    if constexpr (!STREAM) A = load_share(sg, false);
+    Share nextA = {}, nextG = {};   // signature before, and output gradient of, the step to come
 
     if (t < 4) dz_after[t] = 0.0f;   // no increment follows the last one
 
@@ -123,15 +122,13 @@ sig_backward_d4_kernel(const float *__restrict__ path, const float *__restrict__
             const f4 lo = i_hi > 0 ? x4[i_hi - 1] : x_base;
             *reinterpret_cast<f4 *>(zt + 4 * t) = x4[i_hi] - lo;
         }
-        if constexpr (STREAM) {
-            // entries for the first step of this tile (later ones are fetched one step ahead, below)
-            const int64_t s = t0 + nt - 1;
-            if (s > 0) {
-                nextA = load_share(sg + (s - 1) * int64_t(kS), false);
-                nextG = load_share(go + (s - 1) * int64_t(kS), true);
-            } else {
-                nextA = Share{};
-            }
+        // entries for the first step of this tile (later ones are fetched one step ahead, below)
+        const int64_t last = t0 + nt - 1;
+        if (last > 0) {
+            nextA = load_share(sg + (last - 1) * int64_t(kS), false);
+            nextG = load_share(go + (last - 1) * int64_t(kS), true);
+        } else {
+            nextA = Share{};
         }
         __syncthreads();
 
@@ -141,51 +138,42 @@ sig_backward_d4_kernel(const float *__restrict__ path, const float *__restrict__
             const float z1 = zt[4 * i + c1], z2 = zt[4 * i + c2], z3 = zt[4 * i + c3], z4 = zt[4 * i + c4];
 
             Share addG = {};
-            if constexpr (STREAM) {
-                A = nextA;      // signature after s increments = entry s-1 (zero for s = 0)
-                addG = nextG;   // output gradient of entry s-1, added to G once this step is done
-                if (i > 0) {    // fetch for step s-1 (i-1 >= 0 in this tile); across tiles the code above does it
-                    if (s - 1 > 0) {
-                        nextA = load_share(sg + (s - 2) * int64_t(kS), false);
-                        nextG = load_share(go + (s - 2) * int64_t(kS), true);
-                    } else {
-                        nextA = Share{};
-                    }
+            A = nextA;      // signature after s increments = entry s-1 (zero for s = 0)
+            addG = nextG;   // output gradient of entry s-1, added to G once this step is done
+            if (i > 0) {    // fetch for step s-1 (i-1 >= 0 in this tile); across tiles the code above does it
+                if (s - 1 > 0) {
+                    nextA = load_share(sg + (s - 2) * int64_t(kS), false);
+                    nextG = load_share(go + (s - 2) * int64_t(kS), true);
+                } else {
+                    nextA = Share{};
                 }
             }
 
             // ---- up: T[i][k] = T^(k)_i at this thread's word; a_i = the signature before the increment
             float T1[7], T2[7], T3[7], T4[7];
             f4 T5 = zero4;   // T^(6)_5[u c]
-            const float a1 = STREAM ? A.l1 : A.l1 - z1;
+            const float a1 = A.l1;
 #pragma unroll
             for (int k = 2; k <= N; ++k) T1[k] = __builtin_fmaf(z1, rk[k], a1);
-            const float a2 = STREAM ? A.l2 : __builtin_fmaf(-T1[2], z2, A.l2);
+            const float a2 = A.l2;
 #pragma unroll
             for (int k = 3; k <= N; ++k) T2[k] = __builtin_fmaf(T1[k], z2 * rk[k - 1], a2);
-            const float a3 = STREAM ? A.l3 : __builtin_fmaf(-T2[3], z3, A.l3);
+            const float a3 = A.l3;
 #pragma unroll
             for (int k = 4; k <= N; ++k) T3[k] = __builtin_fmaf(T2[k], z3 * rk[k - 2], a3);
             float a4 = 0.0f;
             f4 a5 = zero4;
             if constexpr (N >= 5) {
-                a4 = STREAM ? A.l4 : __builtin_fmaf(-T3[4], z4, A.l4);
+                a4 = A.l4;
 #pragma unroll
                 for (int k = 5; k <= N; ++k) T4[k] = __builtin_fmaf(T3[k], z4 * rk[k - 3], a4);
             }
             if constexpr (N >= 6) {
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    a5[c] = STREAM ? A.l5[c] : __builtin_fmaf(-T4[5], z[c], A.l5[c]);
+                    a5[c] = A.l5[c];
                     T5[c] = __builtin_fmaf(T4[6], z[c] * r2, a5[c]);
                 }
-            }
-            if constexpr (!STREAM) {
-                A.l1 = a1;
-                A.l2 = a2;
-                A.l3 = a3;
-                A.l4 = a4;
-                A.l5 = a5;
             }
 
             // ---- down
@@ -292,16 +280,14 @@ sig_backward_d4_kernel(const float *__restrict__ path, const float *__restrict__
             // the four wavefronts never wait for one another inside a tile: each leaves its partial sums in LDS
             if ((t & 63) < 4) part[i][wave][t & 3] = mine;
 
-            if constexpr (STREAM) {
-                if (s > 0) {
-                    G.l1 += addG.l1;
-                    G.l2 += addG.l2;
-                    G.l3 += addG.l3;
-                    G.l4 += addG.l4;
-                    G.l5 += addG.l5;
+            if (s > 0) {
+                G.l1 += addG.l1;
+                G.l2 += addG.l2;
+                G.l3 += addG.l3;
+                G.l4 += addG.l4;
+                G.l5 += addG.l5;
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) G.l6[c] += addG.l6[c];
-                }
+                for (int c = 0; c < 4; ++c) G.l6[c] += addG.l6[c];
             }
         }
 
@@ -337,18 +323,21 @@ hipError_t launch_d4(const Shape &sh, const float *path, const float *sig, const
 {
     const dim3 grid(static_cast<unsigned>(sh.B)), block(256);
     const float *bpv = static_cast<const float *>(sh.basepoint_value);
-    if (sh.stream)
-        hipLaunchKernelGGL((sig_backward_d4_kernel<N, true>), grid, block, 0, st, path, sig, gout, gpath, gbase, sh.L,
-                           sh.n_inc, sh.basepoint, bpv);
-    else
-        hipLaunchKernelGGL((sig_backward_d4_kernel<N, false>), grid, block, 0, st, path, sig, gout, gpath, gbase, sh.L,
-                           sh.n_inc, sh.basepoint, bpv);
+    hipLaunchKernelGGL((sig_backward_d4_kernel<N>), grid, block, 0, st, path, sig, gout, gpath, gbase, sh.L, sh.n_inc,
+                       sh.basepoint, bpv);
     return hipGetLastError();
 }
 
 }  // namespace
 
-bool backward_d4_supported(const Shape &sh) { return sh.d == 4 && sh.N >= 4 && sh.N <= 6 && sh.B <= 0x7fffffff; }
+// With one gradient per path the prefix-tree kernels are ahead everywhere (8 to 512 paths of 100 points, N = 5: 39 to 53 us,
+// 53 to 54 with this scheme).  Stream mode: N = 4 below 1024 paths (100 points: 58 us against 62 at 16 paths, 67 against 74 at
+// 512, 102 against 84 at 1024, 342 against 187 at 4096; 300 points: 191 against 291 at 512, 305 against 310 at 1024), N = 5 and
+// 6 everywhere (100 points, N = 5: 71 against 66 at 16 paths, 91 against 121 at 512, 302 against 349 at 2048).
+bool backward_d4_supported(const Shape &sh)
+{
+    return sh.stream && sh.d == 4 && sh.N >= 4 && sh.N <= 6 && (sh.N >= 5 ? sh.B <= 0x7fffffff : sh.B < 1024);
+}
 
 hipError_t launch_backward_d4_f32(const Shape &sh, const float *path, const float *sig, const float *gout, float *gpath,
                                   float *gbase, hipStream_t st)

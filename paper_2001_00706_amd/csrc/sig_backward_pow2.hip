@@ -1,4 +1,4 @@
-// Gradient of the signature with respect to the path for d = 2 (N = 2..9) and d = 8 (N = 2..5), fp32
+// Gradient of the stream of signatures with respect to the path for d = 2 (N = 2..7) and d = 8 (N = 3, 4), fp32
 // (paper section 5.3, appendix C): the register-resident scheme of sig_backward_d4.hip written once for any
 // power-of-two channel count.
 //
@@ -6,7 +6,7 @@
 // the threads below one first letter fill exactly one wavefront (or the whole path fits one).  A thread
 // holds the signature A and its cotangent G at its own word and at that word's ancestors (redundantly: all
 // threads below an ancestor carry the same value), and the up to two levels below its word as small arrays.
-// "Up" (undo the increment, Horner terms T^(k)_i) is a scalar chain along the thread's word.  "Down" sums
+// "Up" (Horner terms T^(k)_i) is a scalar chain along the thread's word.  "Down" sums
 // the chains D^(k)_i over the d siblings of each level with lane exchanges inside the wavefront; the only
 // workgroup-wide step is the sum of the increments' gradients over the wavefronts, once per tile of 64
 // increments.  See sig_backward.hip for the recurrences.
@@ -96,7 +96,7 @@ struct Pow2Shape {
     static_assert(U >= 0 && U <= 2, "at most two levels below the thread's word");
 };
 
-template <int D, int N, bool STREAM>
+template <int D, int N>
 __global__ void __launch_bounds__((Pow2Shape<D, N>::NTL))
 sig_backward_pow2_kernel(const float *__restrict__ path, const float *__restrict__ sig, const float *__restrict__ gout,
                          float *__restrict__ gpath, float *__restrict__ gbase, int64_t L, int64_t n_inc, int basepoint,
@@ -131,7 +131,7 @@ sig_backward_pow2_kernel(const float *__restrict__ path, const float *__restrict
 
     const int64_t b = blockIdx.x;
     const float *x = path + b * L * D;
-    const int64_t per_path = STREAM ? n_inc * int64_t(kS) : int64_t(kS);
+    const int64_t per_path = n_inc * int64_t(kS);
     const float *sg = sig + b * per_path;
     const float *go = gout + b * per_path;
     float *gp = gpath + b * L * D;
@@ -164,9 +164,8 @@ sig_backward_pow2_kernel(const float *__restrict__ path, const float *__restrict
     };
 
     // G: cotangent of the signature after the increment being processed.  A: that signature below its top level.
-    Share G = load_share(STREAM ? go + (n_inc - 1) * int64_t(kS) : go, true, true);
+    Share G = load_share(go + (n_inc - 1) * int64_t(kS), true, true);
     Share A = {}, nextA = {}, nextG = {};
-    if constexpr (!STREAM) A = load_share(sg, U >= 2, false);
 
     if (tl < D) dz_after[tl] = 0.0f;   // no increment follows the last one
 
@@ -180,7 +179,7 @@ sig_backward_pow2_kernel(const float *__restrict__ path, const float *__restrict
             const float lo = i_hi > 0 ? x[(i_hi - 1) * D + c] : bpv != nullptr ? bpv[b * D + c] : 0.0f;
             zt[i] = x[i_hi * D + c] - lo;
         }
-        if constexpr (STREAM && kPrefetch) {
+        if constexpr (kPrefetch) {
             const int64_t s = t0 + nt - 1;
             if (s > 0) {
                 nextA = load_share(sg + (s - 1) * int64_t(kS), U >= 2, false);
@@ -200,10 +199,10 @@ sig_backward_pow2_kernel(const float *__restrict__ path, const float *__restrict
             if constexpr (U >= 1) load_letters<D>(zt + i * D, zu);
 
             Share addG = {};
-            if constexpr (STREAM && !kPrefetch) {
+            if constexpr (!kPrefetch) {
                 A = s > 0 ? load_share(sg + (s - 1) * int64_t(kS), U >= 2, false) : Share{};
             }
-            if constexpr (STREAM && kPrefetch) {
+            if constexpr (kPrefetch) {
                 A = nextA;      // signature after s increments = output entry s-1 (zero for s = 0)
                 addG = nextG;   // output gradient of entry s-1, added once this step is done
                 if (i > 0) {
@@ -219,13 +218,13 @@ sig_backward_pow2_kernel(const float *__restrict__ path, const float *__restrict
             // ---- up: T[j][k] = T^(k)_j at this thread's word; the signature before the increment
             float T[P + 1][N + 2];
             float a_lo[P + 1];
-            a_lo[1] = STREAM ? A.lo[1] : A.lo[1] - zc[1];
+            a_lo[1] = A.lo[1];
 #pragma unroll
             for (int k = 2; k <= N; ++k) T[1][k] = __builtin_fmaf(zc[1], rk[k], a_lo[1]);
 #pragma unroll
             for (int j = 2; j <= P; ++j) {
                 if (j < N) {
-                    a_lo[j] = STREAM ? A.lo[j] : __builtin_fmaf(-T[j - 1][j], zc[j], A.lo[j]);
+                    a_lo[j] = A.lo[j];
 #pragma unroll
                     for (int k = j + 1; k <= N; ++k) T[j][k] = __builtin_fmaf(T[j - 1][k], zc[j] * rk[k - j + 1], a_lo[j]);
                 } else {
@@ -236,16 +235,8 @@ sig_backward_pow2_kernel(const float *__restrict__ path, const float *__restrict
             if constexpr (U >= 2) {
 #pragma unroll
                 for (int c = 0; c < D; ++c) {
-                    a_h1[c] = STREAM ? A.h1[c] : __builtin_fmaf(-T[P][P + 1], zu[c], A.h1[c]);
+                    a_h1[c] = A.h1[c];
                     Th1[c] = __builtin_fmaf(T[P][N], zu[c] * rk[2], a_h1[c]);
-                }
-            }
-            if constexpr (!STREAM) {
-#pragma unroll
-                for (int j = 1; j <= P; ++j) A.lo[j] = a_lo[j];
-                if constexpr (U >= 2) {
-#pragma unroll
-                    for (int c = 0; c < D; ++c) A.h1[c] = a_h1[c];
                 }
             }
 
@@ -296,19 +287,17 @@ sig_backward_pow2_kernel(const float *__restrict__ path, const float *__restrict
                 if ((tl & 63) == 0) part[i][wave][c] = total;
             }
 
-            if constexpr (STREAM) {
-                if (s > 0) {
-                    if constexpr (!kPrefetch) addG = load_share(go + (s - 1) * int64_t(kS), true, true);
+            if (s > 0) {
+                if constexpr (!kPrefetch) addG = load_share(go + (s - 1) * int64_t(kS), true, true);
 #pragma unroll
-                    for (int j = 1; j <= P; ++j) G.lo[j] += addG.lo[j];
-                    if constexpr (U >= 1) {
+                for (int j = 1; j <= P; ++j) G.lo[j] += addG.lo[j];
+                if constexpr (U >= 1) {
 #pragma unroll
-                        for (int c = 0; c < D; ++c) G.h1[c] += addG.h1[c];
-                    }
-                    if constexpr (U >= 2) {
+                    for (int c = 0; c < D; ++c) G.h1[c] += addG.h1[c];
+                }
+                if constexpr (U >= 2) {
 #pragma unroll
-                        for (int c = 0; c < D * D; ++c) G.h2[c] += addG.h2[c];
-                    }
+                    for (int c = 0; c < D * D; ++c) G.h2[c] += addG.h2[c];
                 }
             }
         }
@@ -346,21 +335,24 @@ hipError_t launch_pow2(const Shape &sh, const float *path, const float *sig, con
 {
     const dim3 grid(static_cast<unsigned>(sh.B)), block(Pow2Shape<D, N>::NTL);
     const float *bpv = static_cast<const float *>(sh.basepoint_value);
-    if (sh.stream)
-        hipLaunchKernelGGL((sig_backward_pow2_kernel<D, N, true>), grid, block, 0, st, path, sig, gout, gpath, gbase, sh.L,
-                           sh.n_inc, sh.basepoint, bpv);
-    else
-        hipLaunchKernelGGL((sig_backward_pow2_kernel<D, N, false>), grid, block, 0, st, path, sig, gout, gpath, gbase, sh.L,
-                           sh.n_inc, sh.basepoint, bpv);
+    hipLaunchKernelGGL((sig_backward_pow2_kernel<D, N>), grid, block, 0, st, path, sig, gout, gpath, gbase, sh.L, sh.n_inc,
+                       sh.basepoint, bpv);
     return hipGetLastError();
 }
 
 }  // namespace
 
+// Stream mode only; with one gradient per path the prefix-tree kernels serve these shapes.
+// d = 2: short paths and few of them, where the prefix-tree kernels' second launch shows (12 points, N = 5: 10 us against 13;
+// 20 points, N = 6: 17.4 against 18.8 at 64 paths; 50 points: 39.3 against 38.3; 100 points, N = 7, 2048 paths: 227 against 126).
+// d = 8, N = 3 below 640 paths (100 points: 122 us against 171 at 16, 146 against 153 at 512, 201 against 169 at 768, 931
+// against 286 at 4096), N = 4 everywhere (146 against 240 at 16 paths of 100 points, 167 against 187 at 2048 of 20).  N = 2 and
+// N = 5 are the prefix-tree kernels' (N = 2: 105 against 53 at 16 paths; N = 5: 551 against 287).
 bool backward_pow2_supported(const Shape &sh)
 {
-    if (sh.B > 0x7fffffff) return false;
-    return (sh.d == 2 && sh.N >= 2 && sh.N <= 9) || (sh.d == 8 && sh.N >= 2 && sh.N <= 5);
+    if (!sh.stream) return false;
+    if (sh.d == 2) return sh.N >= 2 && sh.N <= 7 && sh.B < 1024 && sh.n_inc * sh.N < 120;
+    return sh.d == 8 && ((sh.N == 3 && sh.B < 640) || (sh.N == 4 && sh.B <= 0x7fffffff));
 }
 
 hipError_t launch_backward_pow2_f32(const Shape &sh, const float *path, const float *sig, const float *gout, float *gpath,
@@ -374,17 +366,11 @@ hipError_t launch_backward_pow2_f32(const Shape &sh, const float *path, const fl
             case 4: return launch_pow2<2, 4>(sh, path, sig, gout, gpath, gbase, st);
             case 5: return launch_pow2<2, 5>(sh, path, sig, gout, gpath, gbase, st);
             case 6: return launch_pow2<2, 6>(sh, path, sig, gout, gpath, gbase, st);
-            case 7: return launch_pow2<2, 7>(sh, path, sig, gout, gpath, gbase, st);
-            case 8: return launch_pow2<2, 8>(sh, path, sig, gout, gpath, gbase, st);
-            default: return launch_pow2<2, 9>(sh, path, sig, gout, gpath, gbase, st);
+            default: return launch_pow2<2, 7>(sh, path, sig, gout, gpath, gbase, st);
         }
     }
-    switch (sh.N) {
-        case 2: return launch_pow2<8, 2>(sh, path, sig, gout, gpath, gbase, st);
-        case 3: return launch_pow2<8, 3>(sh, path, sig, gout, gpath, gbase, st);
-        case 4: return launch_pow2<8, 4>(sh, path, sig, gout, gpath, gbase, st);
-        default: return launch_pow2<8, 5>(sh, path, sig, gout, gpath, gbase, st);
-    }
+    return sh.N == 3 ? launch_pow2<8, 3>(sh, path, sig, gout, gpath, gbase, st)
+                     : launch_pow2<8, 4>(sh, path, sig, gout, gpath, gbase, st);
 }
 
 }  // namespace sig

@@ -88,7 +88,7 @@ def test_register_resident_kernels_every_depth(d, N):
 
 
 def test_final_mode_families_on_both_sides_of_their_batch_thresholds():
-    # with one gradient per path the prefix-tree kernels serve every shape but d = 4 at N >= 5 below 512 paths
+    # with one gradient per path the prefix-tree kernels serve every shape here
     check(brownian_paths(520, 6, 2, seed=3), 9, sample=[0, 1, 255, 519])
     check(brownian_paths(8, 6, 2, seed=4), 9)
     check(brownian_paths(515, 7, 4, seed=5), 5, sample=[0, 300, 514])
@@ -441,3 +441,16 @@ def test_tree_gradient_many_short_paths(d, N, L, dtype):
 def test_tree_gradient_split_groups(d, N):
     for dtype, L in ((np.float32, 36), (np.float64, 6)):
         check(brownian_paths(3, L, d, seed=d + N).astype(dtype), N, False)
+
+
+# Both sides of the lines between the prefix-tree kernels and those with a path's whole working set in registers: one gradient
+# per path at d = 4, N = 6 by the number of paths; a gradient per prefix by depth, number of paths and (d = 2) length
+@pytest.mark.parametrize("stream,d,N,B,L", [
+    (False, 4, 6, 768, 5), (False, 4, 6, 769, 5), (True, 4, 4, 1023, 4), (True, 4, 4, 1024, 4), (True, 8, 3, 639, 3),
+    (True, 8, 3, 640, 3), (True, 2, 2, 3, 60), (True, 2, 2, 3, 61), (True, 2, 3, 3, 40), (True, 2, 4, 3, 30), (True, 2, 5, 3, 24),
+    (True, 2, 5, 3, 25), (True, 2, 6, 3, 20), (True, 2, 7, 3, 18), (True, 2, 7, 3, 19), (True, 2, 7, 1023, 3), (True, 2, 7, 1024, 3)])
+def test_gradient_on_both_sides_of_the_register_resident_kernels_lines(stream, d, N, B, L):
+    x = brownian_paths(B, L, d, seed=B + N)
+    sample = None if B < 10 else [0, 1, B // 2, B - 1]
+    check(x, N, stream=stream, sample=sample)
+    check(x, N, stream=stream, sample=sample, misalign=True)
