@@ -3,7 +3,7 @@
 //
 // The scheme of sig_backward_d16.hip at the benchmark shape of the forward pass: the cotangent of the top level never
 // changes in final mode, so it stays in registers for the whole scan, and a thread owns a subtree deep enough that
-// most of its work is the two products with that cotangent.  One workgroup of two wavefronts per path; lane
+// most of its work is the two products with that cotangent.  Two wavefronts per path; lane
 // u = w_1 w_2 w_3 of wavefront h owns the words u c_4 with c_4 = 2h, 2h+1, the 8 words u c_4 c_5 and the 32 words
 // u c_4 c_5 c_6 below them: G_6 (32 registers), G_5, G_4, A_5, A_4.  Above its words a thread carries its own copy of the
 // signature at the prefixes w_1, w_1 w_2, u and, of the cotangents there, only the part that arrived through its own

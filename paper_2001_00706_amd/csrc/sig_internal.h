@@ -141,7 +141,7 @@ hipError_t launch_combine_grouped_backward_f64(const Shape &sh, int64_t group, c
 hipError_t launch_scatter_f32(const Shape &sh, const float *in, const int64_t *index, int64_t n, float *out, hipStream_t st);
 hipError_t launch_scatter_f64(const Shape &sh, const double *in, const int64_t *index, int64_t n, double *out, hipStream_t st);
 
-// Register-resident gradient kernel: fp32, d = 4, N = 4..6, 16-byte aligned buffers; needs no workspace.
+// Register-resident gradient kernel: stream mode, fp32, d = 4, N = 4..6, 16-byte aligned buffers; needs no workspace.
 bool backward_d4_supported(const Shape &sh);
 hipError_t launch_backward_d4_f32(const Shape &sh, const float *path, const float *sig, const float *gout, float *gpath,
                                   float *gbase, hipStream_t st);
@@ -153,7 +153,7 @@ int64_t backward_d16_workspace_bytes(const Shape &sh);
 hipError_t launch_backward_d16_f32(const Shape &sh, const float *path, const float *sig, const float *gout, float *gpath,
                                    float *gbase, void *workspace, int64_t workspace_bytes, hipStream_t st);
 
-// Gradient kernel for d = 4, N = 6, final mode, fp32, 16-byte aligned buffers: one workgroup of 128 threads per path,
+// Gradient kernel for d = 4, N = 6, final mode, fp32, 16-byte aligned buffers: two paths per workgroup of 256 threads,
 // a thread per word of three letters and half of the letters below it, the top level's cotangent in registers;
 // workspace: one gradient per increment, [B][n_inc][4] floats.
 bool backward_d4n6_supported(const Shape &sh);
@@ -161,7 +161,7 @@ int64_t backward_d4n6_workspace_bytes(const Shape &sh);
 hipError_t launch_backward_d4n6_f32(const Shape &sh, const float *path, const float *sig, const float *gout, float *gpath,
                                     float *gbase, void *workspace, int64_t workspace_bytes, hipStream_t st);
 
-// The same scheme for d = 2 (N = 2..9) and d = 8 (N = 2..5); buffers aligned to min(d, 4) floats.
+// The scheme of the d = 4 stream kernel for d = 2 (N = 2..7) and d = 8 (N = 3, 4), stream mode; buffers aligned to min(d, 4) floats.
 bool backward_pow2_supported(const Shape &sh);
 hipError_t launch_backward_pow2_f32(const Shape &sh, const float *path, const float *sig, const float *gout, float *gpath,
                                     float *gbase, hipStream_t st);
