@@ -385,7 +385,8 @@ int64_t sig_backward_workspace_bytes(int64_t B, int64_t L, int d, int N, int str
  *   chunks     2 .. 65536 (any number; more stretches than increments are not made).
  *   workspace  DEVICE pointer, 16-byte aligned, at least sig_backward_chunked_workspace_bytes(...) bytes, contents
  *              irrelevant on entry and undefined on return; overlapping calls must not share one.
- * Enqueued on `hip_stream` (2 log2(chunks) + 7 launches or so; 2 chunks + 5 with many paths of large signatures), no wait.
+ * Enqueued on `hip_stream` (3 to 7 launches for d = 2 .. 8 at N = 3 .. 9, where every stretch forms the products it needs by itself;
+ * otherwise 2 log2(chunks) + 7 or so, 2 chunks + 5 with many paths of large signatures), no wait.
  * Needs B <= 65535, the stretches' shape served by sig_forward and sig_backward, S < 2^31: otherwise SIG_ERR_UNSUPPORTED; other errors as for sig_backward.
  * Deterministic. */
 sig_status sig_backward_chunked(const void *path, const void *grad_out, int64_t B, int64_t L, int d, int N, int basepoint,

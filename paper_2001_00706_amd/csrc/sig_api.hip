@@ -3,6 +3,7 @@
 #include "sig_internal.h"
 
 #include <atomic>
+#include <cmath>
 
 // Scratch memory of sig_forward_chunked_static, the one entry point for callers that cannot allocate: every GPU the
 // library runs on holds its own copy of this array, at its own address, until the process ends.  In host code the
@@ -451,6 +452,31 @@ sig_status sig_backward_chunked(const void *path, const void *grad_out, int64_t 
     if (workspace == nullptr || workspace_bytes < pl.total || reinterpret_cast<uintptr_t>(workspace) % 16 != 0) return SIG_ERR_INVALID_ARG;
     sh.basepoint_value = basepoint_value;
     char *ws = static_cast<char *>(workspace);
+    if (sig::tree_stretches_supported(sh)) {
+        // The stretches' signatures below the top level, straight from the paths, then the walk, whose rows form the products they
+        // need by themselves: 3 launches up to 16 stretches (8 from memory), one more per factor of 8.
+        sig::Shape below;
+        if (make_shape(B, L, d, N - 1, 0, basepoint, below) != SIG_OK) return SIG_ERR_UNSUPPORTED;
+        below.basepoint_value = basepoint_value;
+        below.B = B * pl.K;
+        below.chunks = int(pl.K);
+        below.chunk_len = pl.m;
+        void *C = ws + pl.at_sigs, *group = ws + pl.at_prefix;
+        const Family scan = resolve(below, dtype, SIG_VARIANT_AUTO, path, C);
+        if (scan == Family::None) return SIG_ERR_UNSUPPORTED;
+        if (launch_scan(scan, below, dtype, path, C, hip_stream) != hipSuccess) return SIG_ERR_HIP;
+        const hipError_t err =
+            dtype == SIG_F32
+                ? sig::launch_tree_stretches_f32(sh, pl.K, pl.m, static_cast<const float *>(path), static_cast<const float *>(C),
+                                                 static_cast<float *>(group), static_cast<const float *>(grad_out),
+                                                 static_cast<float *>(grad_path), static_cast<float *>(grad_basepoint),
+                                                 ws + pl.at_inner, hip_stream)
+                : sig::launch_tree_stretches_f64(sh, pl.K, pl.m, static_cast<const double *>(path), static_cast<const double *>(C),
+                                                 static_cast<double *>(group), static_cast<const double *>(grad_out),
+                                                 static_cast<double *>(grad_path), static_cast<double *>(grad_basepoint),
+                                                 ws + pl.at_inner, hip_stream);
+        return err == hipSuccess ? SIG_OK : SIG_ERR_HIP;
+    }
     void *points = ws + pl.at_points, *sigs = ws + pl.at_sigs, *prefix = ws + pl.at_prefix, *suffix = ws + pl.at_suffix,
          *point_grads = ws + pl.at_point_grads, *inner = ws + pl.at_inner;
     const Family family = resolve(pl.rows, dtype, SIG_VARIANT_AUTO, points, sigs);
@@ -509,23 +535,72 @@ int sig_backward_chunks_hint(int64_t B, int64_t L, int d, int N, int basepoint, 
     return chunks;
 }
 
+// How many stretches are fastest on the prefix-tree kernels (tree_stretches_supported), and what a call takes in microseconds,
+// fitted to a sweep of 817 shapes over 1 .. 3000 paths of 30 .. 60 000 increments, d = 2 .. 8, N = 3 .. 9, both types, each in one piece and
+// in 2 to 1024 stretches.  Over the sweep its choice is 2.6 % off the best count in the mean (one piece: 130 %), and at 4 shapes more
+// than 3 % behind one piece (at most 15 %, 7 x 48, d = 7, N = 6: 61 | 70 us).  In one piece | in the stretches chosen: 256 x 100 points,
+// d = 6, N = 4: 53 | 29 us in 4; 110 x 239, d = 7, N = 4: 129 | 42 in 8; 1 x 21 491, d = 7, N = 5: 12 700 | 160 in 256.
+//   * An increment walked back takes about 2.2 ns per vector instruction of a thread while a SIMD holds one wavefront, and
+//     1.0 ns per wavefront once it holds several.  Stretches are also walked forward, to a level less: a quarter of that.
+//   * Then a step of products per stretch before and after a row's own (at most 15, or 7 per level of nodes): as many reads
+//     and multiply-adds as the suffixes of a thread's words have scalars, more where these are not in LDS.
+//   * A launch for every level of nodes, and the stretches' signatures written and read.
+static int tree_stretches_fastest(int64_t B, const sig::Shape &sh, sig_dtype dtype)
+{
+    const double d = sh.d, letters = sh.N - 2, words = double(sh.pw[sh.N - 2]);
+    const bool wide = dtype == SIG_F64;
+    const double elem = wide ? 2.0 : 1.0, f64 = wide ? 2.04 : 1.0;
+    const double back = 3 * d * d + 10 * d + 32 * letters, ahead = d * d + 3 * d + 5 * sh.N;   // instructions of an increment
+    const double product = letters * (d * d + 2 * d) * (wide ? 1.72 : 1.0) * (sh.d == 8 && sh.N >= 4 ? 2.28 : 1.0);
+    const int64_t single = double(sh.off[sh.N]) * 16 * 4 * elem <= 48000 ? 16 : 8;   // nodes without a level above them
+    const auto either = [](double a, double b) { return std::cbrt(a * a * a + b * b * b); };
+    const auto time = [&](int64_t K) {
+        const int64_t m = (sh.n_inc + K - 1) / K, rows = B * ((sh.n_inc + m - 1) / m);
+        const double per_group = words < 15 ? 16 : std::floor(240 / words);   // at most 64 words: rows that share four wavefronts
+        const double waves = (words > 64 ? double(rows) * std::ceil(words / 64) : 4 * std::ceil(double(rows) / per_group)) / 1024;
+        const double walk = either(2.16e-3 * back * (wide ? 1.26 : 1.0), 1.03e-3 * back * waves * f64);
+        if (K == 1) return 7 + double(sh.n_inc) * walk;
+        int64_t nodes = (sh.n_inc + m - 1) / m, steps = -1;
+        double t = 12.5 + 12.3e-6 * double(rows) * words * d * elem;
+        for (; nodes > single; nodes = (nodes + 7) / 8) {
+            steps += 7;
+            t += 8.3;
+        }
+        const double forward = either(0.107 + 0.513e-3 * ahead, 6.84e-3 * ahead * waves * f64 / d);
+        return t + double(m) * (walk + forward) + double(steps + nodes) * either(8.06e-3 * product, 3.49e-3 * product * waves * f64);
+    };
+    // 2048 paths of up to 16 words are four wavefronts a SIMD as they are (one piece | the best count: 2048 x 300 points, d = 2, N = 3
+    // 67 | 60 us, 4096 x 300 76 | 84, 9646 x 610, d = 3, N = 3 259 | 382, 4096 x 1100, d = 4, N = 4 474 | 388)
+    if (words <= 16 && B >= 2048) return 1;
+    // up to 40 us in one piece the host takes as long for the launches of either, and it has to gain something
+    double best = time(1);
+    if (best < 40) return 1;
+    best = 0.95 * best - 2;
+    int chunks = 1;
+    for (int64_t K = 2; K <= 65536 && sh.n_inc / K >= (K <= 16 ? 8 : 16); K *= 2) {
+        const double t = time(K);
+        if (t >= best) continue;
+        const int64_t bytes = sig_backward_chunked_workspace_bytes(B, sh.L, sh.d, sh.N, sh.basepoint, int(K), dtype);
+        if (bytes < 0 || bytes > (int64_t(2) << 30)) break;
+        best = t;
+        chunks = int(K);
+    }
+    return chunks;
+}
+
 int sig_backward_chunks_fastest(int64_t B, int64_t L, int d, int N, int basepoint, sig_dtype dtype)
 {
     if (dtype != SIG_F32 && dtype != SIG_F64) return 0;
     sig::Shape sh;
     if (make_shape(B, L, d, N, 0, basepoint, sh) != SIG_OK) return 0;
     if (N < 3 || B < 1) return 1;   // depth 2 has a closed form with no walk at all
-    // What a call takes in microseconds, fitted to a sweep of 2026 shapes drawn over 1 .. 20 000 paths of 40 .. 60 000 increments,
-    // d = 2 .. 16, N = 3 .. 9, both types, and 350 on a grid with d = 1, 20, 32, 64 and N = 10, 12 besides, each in one piece and in 2 to
-    // 1024 stretches.  Over the sweep its choice is 5.8 % off the best count in the mean (one piece: 182 %); at 6 shapes it is more than 3 %
-    // behind one piece, most at 197 x 2850, d = 7, N = 5, fp64 (4110 | 5188 in the 2 chosen).
-    // In one piece | in the stretches chosen: 8 x 401 points, d = 7, N = 5: 246 | 115 in 8; 32 x 801, d = 4, N = 6: 357 | 111 in 8; 512 x 1100,
-    // d = 4, N = 4: 388 | 154 in 8; 8 x 600, d = 32, N = 3: 376 | 184 in 8; 4096 x 300, d = 2, N = 3 stays in one piece (81 | 174 at best), 128 x 801,
-    // d = 7, N = 5 as well (498 | 487 at best).
-    //   * The walk back in one piece: an increment takes 0.28 to 0.5 while a path's threads fill one wavefront (and at d = 4),
-    //     0.6 beyond, 0.8 to 1.2 from 9 channels on, up to about 130 000 threads at a time (180 000 in fp64 from 9 channels on); more share the time out.  At most 16
-    //     paths share a workgroup, so a path of fewer words takes the room of 16 threads (with one channel of a workgroup).
-    //   * Stretches are also walked forward, for their signatures: 0.1 to 0.3 more per increment, at least a wavefront each.
+    if (sig::tree_stretches_supported(sh)) return tree_stretches_fastest(B, sh, dtype);
+    // What the other shapes take in microseconds, fitted to a sweep of shapes drawn over 1 .. 20 000 paths of 40 .. 60 000 increments,
+    // d = 9 .. 16, N = 3 .. 9, both types, and 350 on a grid with d = 1, 20, 32, 64 and N = 10, 12 besides, each in one piece and in 2 to
+    // 1024 stretches (in one piece | in the stretches chosen: 8 x 600 points, d = 32, N = 3: 376 | 184 in 8).
+    //   * The walk back in one piece: an increment takes 0.8 to 1.2 from 9 channels on, up to about 130 000 threads at a time
+    //     (180 000 in fp64 up to 16 channels); more share the time out.  One channel takes the room of a workgroup.
+    //   * Stretches are also walked forward, for their signatures: 0.15 to 0.3 more per increment.
     //   * Beyond depth 9 a workgroup per path works through every level: 24 an increment at 2046 scalars, 41 at 8190, 285 at 88 572.
     //   * The rounds of products double with every doubling of the stretches: 10 for two more launches, about 4.5 where
     //     most rounds share one.
@@ -533,12 +608,9 @@ int sig_backward_chunks_fastest(int64_t B, int64_t L, int d, int N, int basepoin
     //     vector, 5 to 6 else.
     //   * The launches around these: 24.
     const int64_t elem = dtype == SIG_F32 ? int64_t(sizeof(float)) : int64_t(sizeof(double));
-    double threads = double(sh.pw[d <= 8 ? N - 2 : N - 1]);
-    if (dtype == SIG_F32 && d == 16 && N == 4) threads = 512;
-    const bool light = threads <= 64 || d == 4;
-    double step = light ? 0.35 : d <= 8 ? 0.6 : 1.2, forward = d <= 8 && !light ? 0.2 : 0.15;
-    double forward_threads = threads > 64 ? threads : 64;
-    if (threads < 16) threads = 16;
+    double threads = dtype == SIG_F32 && d == 16 && N == 4 ? 512 : double(sh.pw[N - 1]);
+    double step = 1.2, forward = 0.15;
+    double forward_threads = threads;
     double per_row = (d % 4 == 0 ? 3.5e-6 : 5e-6) * double(sh.S * elem);
     if (N > 9) {
         step = 20 + 0.003 * double(sh.S);

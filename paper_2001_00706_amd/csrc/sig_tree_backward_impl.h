@@ -34,6 +34,7 @@
 
 #include "sig_internal.h"
 #include "sig_lane_ops.h"
+#include "sig_stretch_ops.h"
 
 #include <type_traits>
 
@@ -43,6 +44,8 @@ namespace {
 
 constexpr int kTbTile = 32;      // increments staged in LDS at a time
 constexpr int kTbMaxPaths = 16;  // paths that may share a workgroup
+constexpr int kStretchRadixLog2 = 3, kStretchLevels = 6;   // 8 stretches to a node, nodes of up to 8^5 stretches
+constexpr int kStretchStage = 32 * 1024;                   // bytes of them in LDS at a time, at least
 
 __host__ __device__ constexpr int64_t tb_off(int d, int k)   // offset of level k (1-based) in a flat element
 {
@@ -91,6 +94,11 @@ struct TbShape {
     static constexpr int kOther = int(sizeof(T)) * (kPathsPerGroup * kTbTile * kZRow + (kWide ? kTbTile * 4 * D : 1) + kRow);
     static constexpr int kRoom = (53 * 1024 - kOther) / (4 * kIncSize * int(sizeof(T)));
     static constexpr int kBatch = !kRows ? 1 : kRoom < 64 / kGroups ? (kRoom < 1 ? 1 : kRoom) : 64 / kGroups;
+    static constexpr int kRowsSize = kRows ? 4 * kBatch * kIncSize + kRow : 1;   // with a row of zeros
+    // Stretches: the same LDS holds their signatures before the walk, where there is room for enough of them.
+    static constexpr int kStage = kRowsSize > int(kStretchStage / sizeof(T)) ? kRowsSize : int(kStretchStage / sizeof(T));
+    static constexpr int kStagedNodes = int(kStage / tb_off(D, N));
+    static constexpr bool kNodesInLds = kStagedNodes >= 16;
 };
 
 // Orders a wavefront's own LDS writes before its reads of what other lanes wrote (LDS serves a wavefront in order; this keeps
@@ -112,11 +120,65 @@ __host__ __device__ constexpr double inv_factorial(int n)
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-template <typename T, int D, int N, bool STREAM, bool ROWS>
-__global__ void __launch_bounds__(256)
-sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restrict__ sig,
+// What a launch walks back over.
+enum TbMode {
+    kTbFinal,      // whole paths, from the gradient with respect to the signature
+    kTbStream,     // whole paths, the gradient arriving at every prefix
+    kTbStretches,  // final mode, every row one of the `chunks` stretches of its path (Shape::chunks): see StretchRows
+};
+
+// A walk over stretches (the gradient of paths that leave the chip idle, cut along their length; sig_backward_chunked.hip says why
+// and from what a stretch is walked).  Only the levels below the top take part in the products around it: a word of the top
+// level has no room for a suffix, and what it holds itself is not read.  A thread holds every prefix of its words, and the
+// cotangents of prefixes are split over the threads anyway, so each thread forms its share of the products by itself
+// (sig_stretch_ops.h): no launches for rounds of products, no copies of the points, and the increments' gradients land where one walk
+// over the whole path would leave them.  Before, with the products along a tree of launches | now: 256 paths of 100 points at d = 6,
+// N = 4 (one piece 53 us) 53 | 29 us; 110 x 239, d = 7, N = 4 129 | 42; 1 x 65 537, d = 4, N = 6 194 | 130; 1 x 832, d = 3, N = 7 80 | 52; 5 x 1775, d = 4,
+// N = 3 46 | 28; 817 shapes 0.64 of the time.  What bounds it: the walk's latency per increment, two trips to memory
+// ahead of it, 0.5 us a step of products from LDS, 1 to 2 from memory.
+//
+// The signatures of the stretches below the top level, [rows][levels below N], and of groups of them: a node of a level is the
+// product of kStretchRadix neighbours of the level below (fewer at the end of a path).  A row first forms the signature of its
+// path up to its end and the gradient with respect to it: it multiplies together what comes before, the largest nodes first, and
+// carries the gradient back through what comes after, the largest and last first.
+template <typename T>
+struct StretchRows {
+    int levels;                            // of which level 0 is the stretches themselves
+    int count[kStretchLevels];             // nodes of a level per path
+    const T *at[kStretchLevels];
+};
+
+// An address that is the same for all lanes of the wavefront, in scalar registers.
+template <typename T>
+__device__ __forceinline__ const T *wave_uniform(const T *p)
+{
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(a)), hi = __builtin_amdgcn_readfirstlane(uint32_t(a >> 32));
+    return reinterpret_cast<const T *>(uint64_t(hi) << 32 | lo);
+}
+
+// chunk_view with 32-bit divisions (a 64-bit one takes some 0.3 us of a lone wavefront's time); less than 2^31 rows.
+__device__ __forceinline__ ChunkView stretch_view(uint32_t row, const Shape &sh)
+{
+    const uint32_t path = row / uint32_t(sh.chunks);
+    const int64_t inc0 = int64_t(row - path * uint32_t(sh.chunks)) * sh.chunk_len, left = sh.n_inc - inc0;
+    return {int64_t(path), inc0, left < sh.chunk_len ? left : sh.chunk_len};
+}
+
+// Wavefronts per SIMD the walk over stretches must leave room for: what it has for whole paths.  The products ahead of it would
+// otherwise take registers (addresses of every suffix) that halve what is in flight through the whole walk.
+constexpr int tb_stretch_waves(int elem, int d, int N)
+{
+    if (elem == 8) return d <= 6 || (d == 7 && N >= 4 && N <= 6) ? 2 : 1;
+    return d <= 3 ? 4 : (d >= 6 && N == 3) || (d == 8 && N >= 8) ? 2 : 3;
+}
+
+template <typename T, int D, int N, int MODE, bool ROWS>
+__global__ void __launch_bounds__(256, (MODE == kTbStretches ? tb_stretch_waves(int(sizeof(T)), D, N) : 1))
+sig_tree_backward_kernel(Shape sh, StretchRows<T> nodes, const T *__restrict__ path, const T *__restrict__ sig,
                          const T *__restrict__ gout, T *__restrict__ partial)
 {
+    constexpr bool STREAM = MODE == kTbStream, STRETCHES = MODE == kTbStretches;
     using TS = TbShape<T, D, N, ROWS>;
     constexpr int U = TS::U, P = TS::P, PPG = TS::kPathsPerGroup;
     constexpr int H1 = U >= 1 ? D : 1, H2 = U >= 2 ? D * D : 1;
@@ -125,7 +187,7 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
     __shared__ __align__(16) T zt[PPG * kTbTile * ZR];
     __shared__ T part[TS::kWide ? kTbTile * 4 * D : 1];   // [increment of the tile][wavefront][channel]
     // [wavefront][increment of the batch][lane][number], and a row of zeros
-    __shared__ __align__(16) T rows[TS::kRows ? 4 * BATCH * INC + ROW : 1];
+    __shared__ __align__(16) T rows[STRETCHES && TS::kNodesInLds ? TS::kStage : TS::kRowsSize];
 
     constexpr int WPP = TS::kWavesPerPath;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -138,7 +200,7 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
     const int64_t row = TS::kMulti ? int64_t(blockIdx.x / TS::kGroupsPerPath) : int64_t(blockIdx.x) * PPG + slot;
     const bool live = lane < LANES && u_raw < TS::kWords && slot_raw < PPG && row < sh.B;
     const int64_t u = live ? u_raw : 0;   // idle threads shadow word 0 of a valid row and contribute nothing
-    const int64_t my_row = live ? row : (row < sh.B ? row : 0);
+    const int64_t my_row = STRETCHES ? (row < sh.B ? row : 0) : live ? row : (row < sh.B ? row : 0);   // the same either way
 
     int cl[P + 1];        // letters of the word
     int64_t pre[P + 1];   // index of its prefix of i letters inside level i
@@ -158,9 +220,14 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
 #pragma unroll
     for (int m = 0; m <= N + 1; ++m) rf[m] = T(inv_factorial(m));
 
+    // a row that is a stretch: its path, where it begins in it and its increments (the walk takes chunk_len for every row: the ones
+    // past the end of a shorter row are zero, change nothing and leave no partial sums)
+    ChunkView mine = {my_row, 0, sh.n_inc};
+    if constexpr (STRETCHES) mine = stretch_view(uint32_t(my_row), sh);
+    const int64_t n_walk = STRETCHES ? sh.chunk_len : sh.n_inc;
     const int64_t per_row = STREAM ? sh.n_inc * kS : kS;
     const T *sg = sig + my_row * per_row;
-    const T *go = gout + my_row * per_row;
+    const T *go = gout + mine.path * per_row;
 
     struct Share {
         T lo[P + 1];
@@ -189,9 +256,13 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
     };
 
     Share G = load_share(STREAM ? go + (sh.n_inc - 1) * kS : go, true, true, true);
-    if (!live) G = Share{};
+    if constexpr (!STRETCHES) {
+        if (!live) G = Share{};
+    }
     Share A = {};
-    if constexpr (!STREAM) A = load_share(sg, false, U >= 2, false);
+    if constexpr (!STREAM && !STRETCHES) {
+        A = load_share(sg, false, U >= 2, false);
+    }
     // Stream mode reads a row of the forward output and a row of its cotangent at every increment.  In fp32 both are
     // fetched an increment ahead of their use, so that a trip to memory is not part of every step of the chain.  In
     // fp64 they are fetched where they are used: two more shares of a flat element (up to 94 registers each at d = 6)
@@ -224,14 +295,16 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
 #pragma unroll
     for (int j = 1; j < P; ++j) gl[j] = TS::kRows ? __shfl(cl[j], some_lane) : 0;
     int64_t sum_at = 0;   // scalar offset of its partial sums, negative: none
+    int64_t sum_n = sh.n_inc;   // how many increments it has
     if constexpr (!TS::kWide) {
-        const int64_t mine = live ? (my_row * TS::kPartials + (TS::kRows ? u / D : u)) * sh.n_inc * D : -1;
-        sum_at = TS::kRows ? __shfl(mine, some_lane) : mine;
+        const int64_t at = live ? ((mine.path * TS::kPartials + (TS::kRows ? u / D : u)) * sh.n_inc + mine.inc0) * D : -1;
+        sum_at = TS::kRows ? __shfl(at, some_lane) : at;
+        if constexpr (STRETCHES) sum_n = TS::kRows ? __shfl(mine.n, some_lane) : mine.n;
     }
     T *my_rows = rows + wave * (BATCH * INC);
     const int my_row_at = lane * ROW + (lane + skip) / D * TS::kGroupPad;
     const T *zeros = rows + 4 * BATCH * INC;
-    if constexpr (TS::kRows) {
+    if constexpr (TS::kRows && !STRETCHES) {
         if (tid < ROW) rows[4 * BATCH * INC + tid] = T(0);   // the first tile's barriers come before its first use
     }
 
@@ -244,11 +317,30 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
     constexpr bool kFetchAhead = sizeof(T) == 4 || N == 2;
     constexpr bool kSkip = PPG > 4 || !kFetchAhead;   // a branch per scalar, worth it where many may be off
     T hi[kPerThread], lo[kPerThread];
+    __shared__ ChunkView served[STRETCHES ? PPG : 1];   // the rows of the workgroup, where they are stretches
+    if constexpr (STRETCHES) {
+        if (tid < PPG) {
+            const bool there = row0 + tid < sh.B;
+            served[tid] = stretch_view(uint32_t(there ? row0 + tid : row0), sh);
+            if (!there) served[tid].n = 0;
+        }
+        __syncthreads();
+    }
     auto fetch = [&](int64_t t0) {
 #pragma unroll
         for (int q = 0; q < kPerThread; ++q) {
             const int e = tid + 256 * q < kStaged ? tid + 256 * q : kStaged - 1;
             const int p = e / (kTbTile * D), i = (e / D) % kTbTile, c = e % D;
+            if constexpr (STRETCHES) {   // unconditional loads, on indices clamped into the path
+                const ChunkView r = served[p];
+                const bool on = t0 + i < r.n;
+                const T *x = path + r.path * sh.L * D;
+                const int64_t i_hi = (on ? r.inc0 + t0 + i : 0) + (sh.basepoint ? 0 : 1);
+                hi[q] = x[i_hi * D + c];
+                lo[q] = i_hi > 0 ? x[(i_hi - 1) * D + c] : bpv != nullptr ? bpv[r.path * D + c] : T(0);
+                if (!on) lo[q] = hi[q];
+                continue;
+            }
             const bool on = row0 + p < sh.B && t0 + i < sh.n_inc;
             const int64_t i_hi = (on ? t0 + i : 0) + (sh.basepoint ? 0 : 1);
             const T *x = path + (on ? row0 + p : row0) * sh.L * D, *b = bpv != nullptr ? bpv + (on ? row0 + p : row0) * D : nullptr;
@@ -260,10 +352,78 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
             if (!kSkip && !on) lo[q] = hi[q];
         }
     };
-    const int64_t last_tile = ((sh.n_inc - 1) / kTbTile) * kTbTile;
-    if constexpr (kFetchAhead) fetch(last_tile);
+    const int64_t last_tile = ((n_walk - 1) / kTbTile) * kTbTile;
+    if constexpr (kFetchAhead) fetch(last_tile);   // in one trip to memory with the gradient above
+    if constexpr (STRETCHES) {
+        constexpr int64_t kBelow = tb_off(D, N);            // scalars below the top level
+        constexpr int kStaged = TS::kStagedNodes;
+        constexpr int kInFlight = 16;
+        uint32_t at[P + 1] = {};
+#pragma unroll
+        for (int i = 1; i <= P; ++i) at[i] = uint32_t(pre[i]);
+        const int64_t row1 = row0 + PPG < sh.B ? row0 + PPG - 1 : sh.B - 1;   // the workgroup's last row
+        const uint32_t first_path = uint32_t(row0) / uint32_t(sh.chunks), last_path = uint32_t(row1) / uint32_t(sh.chunks);
+        for (int l = nodes.levels - 1; l >= 0; --l) {
+            const int shift = l * kStretchRadixLog2, count = nodes.count[l];
+            const bool top = l == nodes.levels - 1;
+            // a row's node is multiplied with its siblings: the nodes of the workgroup's rows and their siblings follow one another
+            const auto begin_of = [&](int c) { return top ? 0 : c >> (shift + kStretchRadixLog2) << kStretchRadixLog2; };
+            const auto end_of = [&](int c) {
+                const int end = begin_of(c) + (1 << kStretchRadixLog2);
+                return top || end > count ? count : end;
+            };
+            const int c = int(my_row - mine.path * sh.chunks);
+            const int64_t path0 = mine.path * count, node = path0 + (c >> shift);
+            const int64_t begin = path0 + begin_of(c), end = path0 + end_of(c), last = l == 0 ? node : node - 1;
+            if constexpr (TS::kNodesInLds) {
+                const int64_t from = first_path * count + begin_of(int(uint32_t(row0) - first_path * uint32_t(sh.chunks)));
+                const int64_t to = last_path * count + end_of(int(uint32_t(row1) - last_path * uint32_t(sh.chunks)));
+                const auto stage = [&](int64_t k0, int64_t k1) {
+                    __syncthreads();
+                    const T *src = nodes.at[l] + k0 * kBelow;
+                    const int n = int(k1 - k0) * int(kBelow);
+                    for (int e = tid; e < n; e += 256 * kInFlight) {   // so many reads on their way together
+                        T v[kInFlight];
+#pragma unroll
+                        for (int q = 0; q < kInFlight; ++q) v[q] = src[e + 256 * q < n ? e + 256 * q : n - 1];
+#pragma unroll
+                        for (int q = 0; q < kInFlight; ++q)
+                            if (e + 256 * q < n) rows[e + 256 * q] = v[q];
+                    }
+                    __syncthreads();
+                };
+                const int64_t pieces = (to - from + kStaged - 1) / kStaged;
+                for (int64_t p = 0; p < pieces; ++p) {
+                    const int64_t k0 = from + p * kStaged, k1 = k0 + kStaged < to ? k0 + kStaged : to;
+                    stage(k0, k1);
+                    for (int64_t k = begin > k0 ? begin : k0; k <= last && k < k1; ++k) {
+                        StretchFactor<T, D, P> f;
+                        f.read(at, rows + int(k - k0) * int(kBelow));
+                        f.multiply(A.lo, A.h1);
+                    }
+                }
+                for (int64_t p = pieces - 1; p >= 0; --p) {
+                    const int64_t k0 = from + p * kStaged, k1 = k0 + kStaged < to ? k0 + kStaged : to;
+                    if (p < pieces - 1) stage(k0, k1);
+                    for (int64_t k = (end < k1 ? end : k1) - 1; k > node && k >= k0; --k)
+                        stretch_carry_back<T, D, P>(G.lo, G.h1, G.h2, at, rows + int(k - k0) * int(kBelow));
+                }
+            } else {
+                const auto at_node = [&](int64_t k) { return TS::kWide ? wave_uniform(nodes.at[l] + k * kBelow) : nodes.at[l] + k * kBelow; };
+                for (int64_t k = begin; k <= last; ++k) {
+                    StretchFactor<T, D, P> f;
+                    f.read(at, at_node(k));
+                    f.multiply(A.lo, A.h1);
+                }
+                for (int64_t k = end - 1; k > node; --k) stretch_carry_back<T, D, P>(G.lo, G.h1, G.h2, at, at_node(k));
+            }
+        }
+        if (!live) G = Share{};
+        __syncthreads();   // the rows of the walk's numbers take the place of the nodes
+        if (TS::kRows && tid < ROW) rows[4 * BATCH * INC + tid] = T(0);
+    }
     for (int64_t t0 = last_tile; t0 >= 0; t0 -= kTbTile) {
-        const int nt = int(sh.n_inc - t0 < kTbTile ? sh.n_inc - t0 : kTbTile);
+        const int nt = int(n_walk - t0 < kTbTile ? n_walk - t0 : kTbTile);
         if constexpr (!kFetchAhead) fetch(t0);
         __syncthreads();
 #pragma unroll
@@ -438,7 +598,7 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
                         }
                         wave_lds_order();   // the next batch's rows overwrite these
                     } else {
-                        if (sum_inc <= ib && sum_at >= 0) {
+                        if (sum_inc <= ib && sum_at >= 0 && (!STRETCHES || t0 + i + ib - sum_inc < sum_n)) {
                             T *pp = partial + sum_at + (t0 + i + ib - sum_inc) * D;
 #pragma unroll
                             for (int c = 0; c < D; ++c) pp[c] = sum[c];
@@ -467,7 +627,7 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
                         if (lane == c) part[(i * 4 + wave) * D + c] = total;
                     }
                 } else {
-                    if (live) {
+                    if (live && (!STRETCHES || s < sum_n)) {
                         T *pp = partial + sum_at + s * D;
 #pragma unroll
                         for (int c = 0; c < D; ++c) pp[c] = dz[c];
@@ -501,7 +661,13 @@ sig_tree_backward_kernel(Shape sh, const T *__restrict__ path, const T *__restri
                 T total = q[0];
 #pragma unroll
                 for (int w = 1; w < WPP; ++w) total += q[w * D];
-                partial[(((row0 + p) * TS::kPartials + wg_group) * sh.n_inc + t0 + i) * D + c] = total;
+                if constexpr (STRETCHES) {
+                    const ChunkView r = served[p];
+                    if (t0 + i < r.n)
+                        partial[((r.path * TS::kPartials + wg_group) * sh.n_inc + r.inc0 + t0 + i) * D + c] = total;
+                } else {
+                    partial[(((row0 + p) * TS::kPartials + wg_group) * sh.n_inc + t0 + i) * D + c] = total;
+                }
             }
         }
     }
@@ -533,10 +699,12 @@ constexpr bool tb_wide_rows() { return sizeof(T) == 4 || (D < 8 && (D + N < 13 |
 template <typename T, int D, int N, bool STREAM, bool ROWS>
 hipError_t launch_tb_mode(const Shape &sh, const T *path, const T *sig, const T *gout, T *gpath, T *gbase, T *partial, hipStream_t st)
 {
+    constexpr int MODE = STREAM ? kTbStream : kTbFinal;
     using TS = TbShape<T, D, N, ROWS>;
     const int64_t groups = TS::kMulti ? sh.B * TS::kGroupsPerPath : (sh.B + TS::kPathsPerGroup - 1) / TS::kPathsPerGroup;
     if (groups > 0x7fffffff) return hipErrorNotSupported;
-    hipLaunchKernelGGL((sig_tree_backward_kernel<T, D, N, STREAM, ROWS>), dim3(unsigned(groups)), dim3(256), 0, st, sh, path, sig, gout, partial);
+    hipLaunchKernelGGL((sig_tree_backward_kernel<T, D, N, MODE, ROWS>), dim3(unsigned(groups)), dim3(256), 0, st, sh, StretchRows<T>{}, path, sig,
+                       gout, partial);
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     return launch_increment_sums<T>(sh, TS::kPartials, partial, gpath, gbase, st);
@@ -558,6 +726,136 @@ hipError_t launch_tb_dn(const Shape &sh, const T *path, const T *sig, const T *g
         const bool rows = tb_packed_rows(D, TbShape<T, D, N, false>::kWords, sh.B, sizeof(T), sh.stream != 0);
         return rows ? launch(std::true_type{}, std::true_type{}) : launch(std::false_type{}, std::false_type{});
     }
+}
+
+// Nodes of a level of the stretches' products from those of the level below, a thread per node and word of N - 2 letters.
+template <typename T, int D, int N>
+__global__ void __launch_bounds__(256)
+sig_stretch_group_kernel(int64_t nodes, int below, int above, const T *__restrict__ from, T *__restrict__ to)
+{
+    constexpr int P = N - 2;
+    constexpr int64_t kBelow = tb_off(D, N), kWords = tb_off(D, P + 1) - tb_off(D, P);
+    const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x, node = e / kWords;
+    if (node >= nodes) return;
+    const uint32_t u = uint32_t(e - node * kWords);
+    uint32_t at[P + 1] = {}, rest = u;
+#pragma unroll
+    for (int i = P; i >= 1; --i) {
+        at[i] = rest;
+        rest /= D;
+    }
+    T lo[P + 1] = {}, h1[D] = {};
+    const int64_t path = node / above;
+    const int i0 = int(node - path * above) << kStretchRadixLog2;
+    const int end = i0 + (1 << kStretchRadixLog2) < below ? i0 + (1 << kStretchRadixLog2) : below;
+    StretchFactor<T, D, P> next, f;
+    const T *C = from + path * below * kBelow;
+    next.read(at, C + i0 * kBelow);
+    for (int k = i0; k < end; ++k) {
+        f = next;
+        if (k + 1 < end) next.read(at, C + (k + 1) * kBelow);
+        __builtin_amdgcn_sched_barrier(0);   // the next factor is on its way while this one is multiplied on
+        f.multiply(lo, h1);
+    }
+    T *o = to + node * kBelow;
+    uint32_t width = 1;
+#pragma unroll
+    for (int i = P; i >= 1; --i) {   // a prefix is written by the first thread below it
+        if (u % width == 0) o[tb_off(D, i) + at[i]] = lo[i];
+        width *= D;
+    }
+#pragma unroll
+    for (int c = 0; c < D; ++c) o[tb_off(D, P + 1) + u * D + c] = h1[c];
+}
+
+template <typename T, int D, int N, bool ROWS>
+hipError_t launch_tb_stretches_mode(const Shape &sh, const Shape &rows, const StretchRows<T> &nodes, const T *path, const T *gout, T *gpath,
+                                    T *gbase, T *partial, hipStream_t st)
+{
+    using TS = TbShape<T, D, N, ROWS>;
+    const int64_t groups = TS::kMulti ? rows.B * TS::kGroupsPerPath : (rows.B + TS::kPathsPerGroup - 1) / TS::kPathsPerGroup;
+    if (groups > 0x7fffffff) return hipErrorNotSupported;
+    hipLaunchKernelGGL((sig_tree_backward_kernel<T, D, N, kTbStretches, ROWS>), dim3(unsigned(groups)), dim3(256), 0, st, rows, nodes, path,
+                       static_cast<const T *>(nullptr), gout, partial);
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+    return launch_increment_sums<T>(sh, TS::kPartials, partial, gpath, gbase, st);
+}
+
+template <typename T, int D, int N>
+hipError_t launch_tb_stretches_dn(const Shape &sh, const Shape &rows, StretchRows<T> nodes, T *group, const T *path, const T *gout, T *gpath,
+                                  T *gbase, T *partial, hipStream_t st)
+{
+    constexpr int64_t kBelow = tb_off(D, N), kGroupWords = tb_off(D, N - 1) - tb_off(D, N - 2);
+    // Up to so many nodes need no level above them: a step of the products takes 0.5 us from LDS, a launch 4 to 5 and from memory
+    // twice that and more (16 stretches, without | with a level above: 51 x 223 points, d = 2, N = 4 19.6 | 23.9 us; 9 x 1620 in 128 at
+    // d = 2, N = 4 26.9 | 30.9; from memory 12 x 723, d = 8, N = 5 191 | 152).
+    constexpr int kSingle = TbShape<T, D, N, false>::kNodesInLds ? 16 : 8;
+    while (nodes.count[nodes.levels - 1] > kSingle) {
+        if (nodes.levels == kStretchLevels) return hipErrorNotSupported;
+        const int n = nodes.count[nodes.levels - 1];
+        nodes.count[nodes.levels++] = (n + (1 << kStretchRadixLog2) - 1) >> kStretchRadixLog2;
+    }
+    for (int l = 1; l < nodes.levels; ++l) {
+        const int64_t count = sh.B * nodes.count[l], blocks = (count * kGroupWords + 255) / 256;
+        if (blocks > 0x7fffff) return hipErrorNotSupported;
+        hipLaunchKernelGGL((sig_stretch_group_kernel<T, D, N>), dim3(unsigned(blocks)), dim3(256), 0, st, count, nodes.count[l - 1],
+                           nodes.count[l], nodes.at[l - 1], group);
+        const hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return err;
+        nodes.at[l] = group;
+        group += count * kBelow;
+    }
+    // the lanes' numbers through LDS or not as for whole paths
+    if constexpr (TbShape<T, D, N, false>::kWide) {
+        return launch_tb_stretches_mode<T, D, N, tb_wide_rows<T, D, N, false>()>(sh, rows, nodes, path, gout, gpath, gbase, partial, st);
+    } else {
+        return tb_packed_rows(D, TbShape<T, D, N, false>::kWords, rows.B, sizeof(T), false)
+                   ? launch_tb_stretches_mode<T, D, N, true>(sh, rows, nodes, path, gout, gpath, gbase, partial, st)
+                   : launch_tb_stretches_mode<T, D, N, false>(sh, rows, nodes, path, gout, gpath, gbase, partial, st);
+    }
+}
+
+template <typename T, int D>
+hipError_t launch_tb_stretches_d(const Shape &sh, const Shape &rows, const StretchRows<T> &nodes, T *group, const T *path, const T *gout,
+                                 T *gpath, T *gbase, T *partial, hipStream_t st)
+{
+    switch (sh.N) {
+        case 3: return launch_tb_stretches_dn<T, D, 3>(sh, rows, nodes, group, path, gout, gpath, gbase, partial, st);
+        case 4: return launch_tb_stretches_dn<T, D, 4>(sh, rows, nodes, group, path, gout, gpath, gbase, partial, st);
+        case 5: return launch_tb_stretches_dn<T, D, 5>(sh, rows, nodes, group, path, gout, gpath, gbase, partial, st);
+        case 6: return launch_tb_stretches_dn<T, D, 6>(sh, rows, nodes, group, path, gout, gpath, gbase, partial, st);
+        case 7: return launch_tb_stretches_dn<T, D, 7>(sh, rows, nodes, group, path, gout, gpath, gbase, partial, st);
+        case 8: return launch_tb_stretches_dn<T, D, 8>(sh, rows, nodes, group, path, gout, gpath, gbase, partial, st);
+        case 9: return launch_tb_stretches_dn<T, D, 9>(sh, rows, nodes, group, path, gout, gpath, gbase, partial, st);
+    }
+    return hipErrorNotSupported;
+}
+
+// The walk back over stretches from their signatures C below the top level (see launch_tree_stretches in sig_internal.h).
+template <typename T>
+hipError_t launch_tb_stretches(const Shape &sh, int64_t K, int64_t m, const T *path, const T *C, T *group, const T *gout, T *gpath, T *gbase,
+                               T *partial, hipStream_t st)
+{
+    Shape rows = sh;
+    rows.B = sh.B * K;
+    rows.chunks = int(K);
+    rows.chunk_len = m;
+    if (rows.B > 0x7fffffff) return hipErrorNotSupported;
+    StretchRows<T> nodes = {};
+    nodes.levels = 1;
+    nodes.count[0] = int(K);
+    nodes.at[0] = C;
+    switch (sh.d) {
+        case 2: return launch_tb_stretches_d<T, 2>(sh, rows, nodes, group, path, gout, gpath, gbase, partial, st);
+        case 3: return launch_tb_stretches_d<T, 3>(sh, rows, nodes, group, path, gout, gpath, gbase, partial, st);
+        case 4: return launch_tb_stretches_d<T, 4>(sh, rows, nodes, group, path, gout, gpath, gbase, partial, st);
+        case 5: return launch_tb_stretches_d<T, 5>(sh, rows, nodes, group, path, gout, gpath, gbase, partial, st);
+        case 6: return launch_tb_stretches_d<T, 6>(sh, rows, nodes, group, path, gout, gpath, gbase, partial, st);
+        case 7: return launch_tb_stretches_d<T, 7>(sh, rows, nodes, group, path, gout, gpath, gbase, partial, st);
+        case 8: return launch_tb_stretches_d<T, 8>(sh, rows, nodes, group, path, gout, gpath, gbase, partial, st);
+    }
+    return hipErrorNotSupported;
 }
 
 template <int D, int N>

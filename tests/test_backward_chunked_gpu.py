@@ -67,6 +67,44 @@ def test_tree_of_products(B, L, d, N, chunks, dtype):
     check(brownian_paths(B, L, d, seed=L + d).astype(dtype), N, chunks)
 
 
+# Every kernel of the walk over stretches (d = 2..8 at N = 3..9), with the products from LDS and from memory, whole and short last
+# stretches, against the walk in one piece (both within the same distance of the oracle); 2 paths of words that share a
+# workgroup, or span several.
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("d", [2, 3, 4, 5, 6, 7, 8])
+def test_stretches_of_every_shape(d, dtype):
+    for N in range(3, 10):
+        S = orc.channels(d, N)
+        if S > 1_100_000:
+            continue
+        x = brownian_paths(2, 12, d, seed=d + N).astype(dtype)
+        g = np.random.default_rng(N).standard_normal((2, S)).astype(dtype)
+        whole = sig.sig_backward(dev(x), sig.sig_signature(dev(x), N), dev(g), N).cpu().numpy().astype(np.float64)
+        for chunks in (2, 3, 11):
+            got = chunked(x, g, N, chunks)
+            assert np.linalg.norm(got - whole) <= 2 * TOL[dtype] * np.linalg.norm(whole), (N, chunks)
+
+
+# counts around the lines where stretches are joined to nodes of 8: 16 and 17 with the products from LDS (d = 3, N = 4), 8 and 9 from
+# memory (d = 5, N = 6), nodes of nodes (130 and 71), a last node of one stretch; many paths to a workgroup, with an origin in front
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("B,L,d,N,chunks,basepoint", [
+    (5, 17, 3, 4, 16, False), (5, 18, 3, 4, 17, False), (3, 131, 3, 4, 130, False), (2, 9, 5, 6, 8, False), (2, 10, 5, 6, 9, False),
+    (1, 72, 5, 6, 71, False), (37, 19, 2, 3, 5, True), (37, 18, 2, 3, 17, True), (3, 32, 8, 4, 9, True),
+])
+def test_nodes_of_stretches(B, L, d, N, chunks, basepoint, dtype):
+    check(brownian_paths(B, L, d, seed=L).astype(dtype) + dtype(0.2 * basepoint), N, chunks, basepoint=basepoint)
+
+
+def test_a_path_with_nan_spoils_no_other():
+    x = brownian_paths(40, 21, 3, seed=1).astype(np.float32)
+    g = np.random.default_rng(2).standard_normal((40, orc.channels(3, 4))).astype(np.float32)
+    want = chunked(x, g, 4, 4)
+    x[7, 9] = np.nan
+    got = chunked(x, g, 4, 4)
+    assert np.isnan(got[7]).any() and np.array_equal(np.delete(got, 7, 0), np.delete(want, 7, 0))
+
+
 def test_stretches_two_to_a_workgroup():
     # 111 paths in 7 stretches are 777 rows of d = 4, N = 6: the kernel of that shape beyond 768 rows, an odd number of them
     check(brownian_paths(111, 29, 4, seed=2).astype(np.float32), 6, 7)
