@@ -1,11 +1,20 @@
 """`signature` and `logsignature` as differentiable PyTorch operations (paper section 5.3): the forward passes
 are `sig_signature`, `sig_log` and `sig_lyndon_gather`, the backward passes `sig_lyndon_scatter`,
-`sig_log_backward` and `sig_backward` (`sig_backward_chunked` for few long paths); all run in the HIP library.  Glue only."""
+`sig_log_backward` and `sig_backward` (`sig_backward_chunked` for few long paths); all run in the HIP library.  Glue only.
+
+Plain calls go through the same glue in C++ (`torch_node/sig_torch.cpp`), where the host is not what a small call waits for (forward
+and gradient, queued: 128 x 128 points, d = 4, N = 5, fp64: 65 or 103 us a pass through the functions below, by where the autograd
+engine's thread runs); it hands back what it does not take, and what the library refuses, and the functions below serve that."""
 from __future__ import annotations
 
 import torch
 
 from . import binding
+
+try:
+    from ._sig_torch import transform as _transform
+except ImportError as e:
+    raise ImportError("_sig_torch.so is missing or does not load: build it with `python -c 'import __graft_entry__ as g; g.build()'`") from e
 
 
 def _plain_signature(path, basepoint_value, depth, stream, basepoint):
@@ -153,6 +162,10 @@ def signature(path, depth: int, stream: bool = False, basepoint=False, inverse: 
 
     The gradient of few long paths is computed in stretches and takes up to 2 GiB besides its result while it runs, less
     where that much cannot be had (`sig_backward_chunks_fastest`, then `sig_backward_chunks_hint`, then none)."""
+    if initial is None and not torch.compiler.is_compiling():
+        out = _transform(path, depth, stream, basepoint, inverse, 0, None)
+        if out is not NotImplemented:
+            return out
     value = basepoint if isinstance(basepoint, torch.Tensor) else None
     flag = value is not None or bool(basepoint)
     if initial is None:
@@ -212,5 +225,11 @@ def logsignature(path, depth: int, stream: bool = False, basepoint=False, invers
     tensor `basepoint`)."""
     if mode not in ("words", "expand"):
         raise ValueError('mode must be "words" or "expand"')
+    if isinstance(path, torch.Tensor) and path.dim() == 3 and not torch.compiler.is_compiling():
+        table = binding._lyndon_tables.get((path.shape[2], depth, path.device)) if mode == "words" else None   # kept since the first call
+        if mode == "expand" or table is not None:
+            out = _transform(path, depth, stream, basepoint, inverse, 1 if mode == "expand" else 2, table)
+            if out is not NotImplemented:
+                return out
     value = basepoint if isinstance(basepoint, torch.Tensor) else None
     return _Logsignature.apply(path, value, int(depth), bool(stream), value is not None or bool(basepoint), bool(inverse), mode)

@@ -13,6 +13,8 @@ ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB_PATH = os.path.join(PKG_DIR, "libsig.so")
+NODE_SRC = os.path.join(PKG_DIR, "torch_node", "sig_torch.cpp")
+NODE_PATH = os.path.join(PKG_DIR, "_sig_torch.so")
 PEAKS_SRC = os.path.join(PKG_DIR, "peaks", "peak_probe.hip")
 PEAKS_LIB_PATH = os.path.join(PKG_DIR, "libsig_peaks.so")
 
@@ -82,6 +84,32 @@ def build_peaks_lib(verbose: bool = False) -> str:
     return PEAKS_LIB_PATH
 
 
+def build_node(verbose: bool = False) -> str:
+    """Compiles the autograd nodes (`torch_node/sig_torch.cpp`, host code) against torch and `libsig.so`, which has to be built,
+    into `_sig_torch.so`; returns its path."""
+    import sysconfig
+
+    import torch
+
+    torch_dir = os.path.dirname(torch.__file__)
+    tmp = NODE_PATH + f".tmp{os.getpid()}"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", INCLUDE, "-isystem", os.path.join(torch_dir, "include"),
+           "-isystem", os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", "/opt/rocm/include", NODE_SRC, "-o", tmp,
+           "-L", os.path.join(torch_dir, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+           "-L", PKG_DIR, "-l:libsig.so", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed on {NODE_SRC}:\n{res.stdout}\n{res.stderr}")
+    os.replace(tmp, NODE_PATH)
+    return NODE_PATH
+
+
 if __name__ == "__main__":
     print(build_lib(verbose=True))
+    print(build_node(verbose=True))
     print(build_peaks_lib(verbose=True))
