@@ -266,6 +266,26 @@ hipError_t launch_family(Family family, const sig::Shape &sh, sig_dtype dtype, c
     return launch_scan(family, ch, dtype, path, out, hip_stream);
 }
 
+// Final mode on the vector kernels: where the paths leave the chip idle they are cut into stretches that share a workgroup
+// (sig_tree_split_impl.h).  The call still counts as the family that serves the paths in one piece.
+bool cut_inside(Family family, const sig::Shape &sh)
+{
+    return !sh.stream && (family == Family::Tree || family == Family::RowStream || family == Family::Small);
+}
+
+// A call that leaves the choice of the kernels to the library.
+hipError_t launch_auto(Family family, const sig::Shape &sh, sig_dtype dtype, const void *path, void *out, hipStream_t hip_stream)
+{
+    if (cut_inside(family, sh)) {
+        const hipError_t err =
+            dtype == SIG_F32
+                ? sig::launch_tree_split_f32(sh, static_cast<const float *>(path), static_cast<float *>(out), hip_stream)
+                : sig::launch_tree_split_f64(sh, static_cast<const double *>(path), static_cast<double *>(out), hip_stream);
+        if (err != hipErrorNotSupported) return err;
+    }
+    return launch_family(family, sh, dtype, path, out, hip_stream);
+}
+
 bool valid_enums(sig_dtype dtype, sig_variant variant)
 {
     return (dtype == SIG_F32 || dtype == SIG_F64) &&
@@ -312,7 +332,8 @@ sig_status sig_forward_variant(const void *path, int64_t B, int64_t L, int d, in
     if (path == nullptr || out == nullptr) return SIG_ERR_INVALID_ARG;
     const Family family = resolve(sh, dtype, variant, path, out);
     if (family == Family::None) return SIG_ERR_UNSUPPORTED;
-    const hipError_t err = launch_family(family, sh, dtype, path, out, hip_stream);
+    const hipError_t err = variant == SIG_VARIANT_AUTO ? launch_auto(family, sh, dtype, path, out, hip_stream)
+                                                       : launch_family(family, sh, dtype, path, out, hip_stream);
     return err == hipSuccess ? SIG_OK : SIG_ERR_HIP;
 }
 
@@ -730,6 +751,13 @@ int sig_forward_chunks_hint(int64_t B, int64_t L, int d, int N, int basepoint, s
     }
     const int64_t shortest = (d == 8 && N >= 4 && N <= 6 && dtype == SIG_F32) ? 4096 : 512;
     if (B < 1 || B > 64 || sh.n_inc < shortest) return 1;
+    // sig_forward cuts the path by itself, inside a workgroup: ahead up to 80 increments a stretch (9 x 849 points, d = 3, N = 5 14 us
+    // against 27 in chunks, 3 x 806, d = 2, N = 6, fp64 12 | 33, 69 increments a stretch; 8 x 995, d = 3, N = 6, 124: 33 | 33, 6 x 551, d = 5, N = 5, fp64, 138: 45 | 32)
+    const Family family = resolve(sh, dtype, SIG_VARIANT_AUTO, nullptr, nullptr);
+    if (cut_inside(family, sh)) {
+        const int K = sig::tree_split_stretches(sh, dtype);
+        if (K > 1 && sh.n_inc <= 80 * int64_t(K)) return 1;
+    }
     const int64_t elem = dtype == SIG_F32 ? int64_t(sizeof(float)) : int64_t(sizeof(double));
     int chunks = 1;
     for (;;) {
@@ -1089,7 +1117,7 @@ sig_status sig_signature(const void *path, int64_t B, int64_t L, int d, int N, i
     if ((initial != nullptr || inverse) && !sig::combine_supported(sh)) return SIG_ERR_UNSUPPORTED;
     const Family family = resolve(sh, dtype, SIG_VARIANT_AUTO, path, out);
     if (family == Family::None) return SIG_ERR_UNSUPPORTED;
-    hipError_t err = launch_family(family, sh, dtype, path, out, hip_stream);
+    hipError_t err = launch_auto(family, sh, dtype, path, out, hip_stream);
     if (err != hipSuccess) return SIG_ERR_HIP;
     // what follows works on the rows of `out`, in place, behind the scan on the same stream
     sig::Shape rows = sh;

@@ -181,6 +181,12 @@ hipError_t launch_tree_wide(const Shape &sh, const double *path, double *out, hi
 hipError_t launch_tree_f32(const Shape &sh, const float *path, float *out, hipStream_t st);
 hipError_t launch_tree_f64(const Shape &sh, const double *path, double *out, hipStream_t st);
 
+// The same scan in final mode with a path cut into stretches that share a workgroup (see sig_tree_split_impl.h); hipErrorNotSupported, with
+// nothing enqueued, where that does not pay.
+hipError_t launch_tree_split_f32(const Shape &sh, const float *path, float *out, hipStream_t st);
+hipError_t launch_tree_split_f64(const Shape &sh, const double *path, double *out, hipStream_t st);
+int tree_split_stretches(const Shape &sh, sig_dtype dtype);   // how many (1: that is the case)
+
 // Row-stream family (d = 2..16 with one or two levels below a word of at most 64 per row; see sig_row_stream.hip): stream
 // mode, both passes of a stream scan cut into chunks (Shape::rows_in_stream), and final mode.
 bool row_stream_supported(const Shape &sh, sig_dtype dtype);

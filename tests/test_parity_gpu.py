@@ -685,3 +685,36 @@ def test_prefix_tree_family(B, L, d, N, dtype):
     if d ** N * L * B < 3_000_000:   # every prefix signature written (kept small for the oracle's sake)
         assert check(x, N, stream=True, variant=sig.SIG_VARIANT_TREE) is not None
         assert check(x, N, stream=True, basepoint=True, variant=sig.SIG_VARIANT_TREE) is not None
+
+
+# Paths cut into stretches that share a workgroup: counts of stretches up to the most a workgroup holds, the shortest path that is cut (33
+# points), last stretches that are short or empty, several paths to a workgroup and a last workgroup that is not full
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("B,L,d,N,basepoint", [
+    (1, 33, 3, 4, False), (7, 34, 2, 3, True), (5, 66, 2, 4, False), (3, 50, 5, 5, False), (9, 70, 6, 4, True), (2, 65, 4, 6, False),
+    (2, 66, 7, 5, False), (2, 70, 8, 4, False), (2, 40, 3, 7, True), (3, 1100, 2, 3, False), (2, 130, 9, 3, False), (130, 41, 16, 3, False),
+    (33, 300, 3, 3, True), (2, 97, 2, 9, False),
+])
+def test_stretches_that_share_a_workgroup(B, L, d, N, basepoint, dtype):
+    check(brownian_paths(B, L, d, seed=L + N).astype(dtype), N, basepoint=basepoint)
+
+
+# every kernel of that scan against the same path in one piece: some 70 roundings either way, 1e-5 and 2e-14 of the whole at most
+@pytest.mark.parametrize("dtype,tol", [(np.float32, 1e-5), (np.float64, 2e-14)])
+@pytest.mark.parametrize("d", list(range(2, 17)))
+def test_stretches_against_one_piece(d, dtype, tol):
+    for N in range(3, 10 if d <= 8 else 4):
+        if orc.channels(d, N) > 40_000:
+            continue
+        x = brownian_paths(3, 71, d, seed=N).astype(dtype)
+        got, want = gpu_signature(x, N).astype(np.float64), gpu_signature(x, N, variant=sig.SIG_VARIANT_TREE).astype(np.float64)
+        assert np.linalg.norm(got - want) <= tol * np.linalg.norm(want), N
+
+
+def test_infinite_signatures_stay_what_they_are_in_one_piece():
+    x = np.zeros((2, 40, 2), dtype=np.float32)
+    x[0] = brownian_paths(1, 40, 2, seed=1)[0]
+    x[1, 5:] = 1e30
+    got, want = gpu_signature(x, 4), gpu_signature(x, 4, variant=sig.SIG_VARIANT_TREE)
+    np.testing.assert_allclose(got[0], want[0], rtol=1e-4, atol=1e-5)
+    np.testing.assert_array_equal(np.isinf(got[1]), np.isinf(want[1]))
