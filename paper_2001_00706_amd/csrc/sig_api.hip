@@ -751,13 +751,6 @@ int sig_forward_chunks_hint(int64_t B, int64_t L, int d, int N, int basepoint, s
     }
     const int64_t shortest = (d == 8 && N >= 4 && N <= 6 && dtype == SIG_F32) ? 4096 : 512;
     if (B < 1 || B > 64 || sh.n_inc < shortest) return 1;
-    // sig_forward cuts the path by itself, inside a workgroup: ahead up to 80 increments a stretch (9 x 849 points, d = 3, N = 5 14 us
-    // against 27 in chunks, 3 x 806, d = 2, N = 6, fp64 12 | 33, 69 increments a stretch; 8 x 995, d = 3, N = 6, 124: 33 | 33, 6 x 551, d = 5, N = 5, fp64, 138: 45 | 32)
-    const Family family = resolve(sh, dtype, SIG_VARIANT_AUTO, nullptr, nullptr);
-    if (cut_inside(family, sh)) {
-        const int K = sig::tree_split_stretches(sh, dtype);
-        if (K > 1 && sh.n_inc <= 80 * int64_t(K)) return 1;
-    }
     const int64_t elem = dtype == SIG_F32 ? int64_t(sizeof(float)) : int64_t(sizeof(double));
     int chunks = 1;
     for (;;) {
@@ -805,6 +798,16 @@ static sig_status forward_chunked(const void *path, int64_t B, int64_t L, int d,
     if (!sig::combine_supported(sh)) return SIG_ERR_UNSUPPORTED;
     const Family family = resolve(sh, dtype, SIG_VARIANT_AUTO, path, workspace);
     if (family == Family::None) return SIG_ERR_UNSUPPORTED;
+    // Where sig_forward cuts the path inside a workgroup by itself, into stretches of 80 increments at most, that is ahead of any count
+    // (9 x 849 points, d = 3, N = 5 14 us against 27 in the hinted chunks, 3 x 806, d = 2, N = 6, fp64 12 | 33; 8 x 995, d = 3, N = 6, 124 increments a
+    // stretch 33 | 33, 6 x 551, d = 5, N = 5, fp64, 138: 45 | 32).
+    sig::Shape whole;
+    if (make_shape(B, L, d, N, 0, basepoint, whole) == SIG_OK) {
+        whole.basepoint_value = basepoint_value;
+        const Family one = resolve(whole, dtype, SIG_VARIANT_AUTO, path, out);
+        const int K = cut_inside(one, whole) ? sig::tree_split_stretches(whole, dtype) : 1;
+        if (K > 1 && whole.n_inc <= 80 * int64_t(K)) return launch_auto(one, whole, dtype, path, out, hip_stream) == hipSuccess ? SIG_OK : SIG_ERR_HIP;
+    }
     // every chunk scanned on its own ...
     char *ws0 = static_cast<char *>(workspace);
     char *ws1 = ws0 + sh.B * sh.S * elem;

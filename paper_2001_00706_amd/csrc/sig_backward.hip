@@ -313,8 +313,78 @@ bool wide_backward_preferred(const Shape &sh, sig_dtype dtype)
            !(sh.d == 16 && sh.N == 4) && wide_backward_supported(sh, dtype);
 }
 
+// Stream mode in K stretches of m increments (1: in one piece), and where its scratch memory lies.
+// The walk over the prefixes is a chain of 0.5 to 1.2 us an increment that a few paths wait for; cut, it is a launch for what every
+// stretch leaves at its front (sig_stream_carry_kernel), one for the stretches' signatures, and a walk over a K-th of the length
+// behind K steps of products.  As many stretches as are at least 8 increments long (16 for more than 16) while their threads are 170 000 at most
+// and 1400 for an increment of the path; a thread counts for more where a path does not fit a wavefront, since its steps of products
+// take longer, and from seven channels on.  Over 500 shapes of 1 to 2000 paths of 16 to 1100 points it takes 0.48 of the time in one piece, 1.3 % off the
+// best count in the mean (one piece | cut: 64 x 101, d = 5, N = 4 79 | 44 us in 8; 5 x 723, d = 5, N = 4 567 | 92 in 16; 369 x 64, d = 6, N = 4, fp64 stays near
+// 165 to 211; worst 383 x 66, d = 6, N = 4 64 | 73).
+struct StreamStretches {
+    int64_t K, m, at_C, at_carried, bytes;
+};
+
+static StreamStretches stream_stretches(const Shape &sh, sig_dtype dtype)
+{
+    StreamStretches pl = {1, sh.n_inc, 0, 0, 0};
+    if (!sh.stream || sh.d < 2 || sh.d > 8 || sh.N < 3 || sh.N > 6 || sh.n_inc < 40 || !tree_backward_supported(sh)) return pl;
+    const int64_t words = sh.pw[sh.N - 2], most = sh.n_inc < 121 ? 1400 * sh.n_inc : 170000;
+    const double threads = double(sh.B) * double(words < 16 ? 16 : words) * (words > 64 ? 1 + 0.01 * (sh.N - 2) * sh.d * sh.d : 1.0) *
+                           (sh.d >= 7 ? 2.0 : 1.0);
+    while (pl.K < 32 && sh.n_inc / (2 * pl.K) >= (pl.K < 16 ? 8 : 16) && double(2 * pl.K) * threads <= double(most)) pl.K *= 2;
+    // Two stretches have two launches more to make up for; at d = 8, N = 4 the kernel for one piece (sig_backward_pow2.hip) takes 1.5 us an
+    // increment where the walk reads its rows in 2.4 (146 x 76 points 116 | 159 in 8, 30 x 252 373 | 304 in 4, 131 in 16).
+    if (pl.K < (sh.d == 8 && sh.N == 4 ? 8 : 4)) {
+        pl.K = 1;
+        return pl;
+    }
+    pl.m = (sh.n_inc + pl.K - 1) / pl.K;
+    pl.K = (sh.n_inc + pl.m - 1) / pl.m;
+    const int64_t elem = dtype == SIG_F32 ? int64_t(sizeof(float)) : int64_t(sizeof(double));
+    const auto round_up = [](int64_t bytes) { return (bytes + 255) / 256 * 256; };
+    pl.at_C = round_up(tree_backward_workspace_bytes(sh, dtype));
+    pl.at_carried = pl.at_C + round_up(sh.B * (pl.K - 2) * sh.off[sh.N] * elem);
+    pl.bytes = pl.at_carried + sh.B * pl.K * tree_stream_carried(sh) * elem;
+    return pl;
+}
+
+template <typename T>
+static hipError_t launch_stream_stretches(const Shape &sh, const StreamStretches &pl, const T *path, const T *sig, const T *gout, T *gpath,
+                                          T *gbase, void *workspace, hipStream_t st)
+{
+    char *ws = static_cast<char *>(workspace);
+    T *C = reinterpret_cast<T *>(ws + pl.at_C), *carried = reinterpret_cast<T *>(ws + pl.at_carried);
+    if (pl.K > 2) {   // the signatures of the stretches between the first and the last, below the top level
+        Shape mid = sh;
+        mid.stream = 0;
+        mid.N = sh.N - 1;
+        mid.S = sh.off[sh.N];
+        mid.chunks = int(pl.K - 2);
+        mid.chunk_len = pl.m;
+        mid.n_inc = (pl.K - 2) * pl.m;
+        mid.B = sh.B * (pl.K - 2);
+        mid.basepoint = 0;
+        mid.basepoint_value = nullptr;
+        const int64_t start = sh.n_inc - (pl.K - 1) * pl.m;   // the increment the second stretch begins with
+        const T *from = path + (start - (sh.basepoint ? 1 : 0)) * sh.d;
+        hipError_t err;
+        if constexpr (sizeof(T) == 4)
+            err = launch_tree_f32(mid, from, C, st);
+        else
+            err = launch_tree_f64(mid, from, C, st);
+        if (err != hipSuccess) return err;
+    }
+    if constexpr (sizeof(T) == 4)
+        return launch_tree_stream_stretches_f32(sh, pl.K, pl.m, path, sig, gout, C, carried, gpath, gbase, workspace, st);
+    else
+        return launch_tree_stream_stretches_f64(sh, pl.K, pl.m, path, sig, gout, C, carried, gpath, gbase, workspace, st);
+}
+
 int64_t backward_workspace_bytes(const Shape &sh, sig_dtype dtype)
 {
+    const StreamStretches cut = stream_stretches(sh, dtype);
+    if (cut.K > 1) return cut.bytes;
     // signatures of up to 8 channels and depth 9 never reach the generic kernel
     if (backward_n2_supported(sh, dtype)) return 0;   // depth 2 in final mode: a closed form, nothing to keep
     if (wide_backward_preferred(sh, dtype)) return wide_backward_workspace_bytes(sh, dtype);
@@ -344,6 +414,9 @@ hipError_t launch_backward_f32(const Shape &sh, const float *path, const float *
     if (aligned && ws_aligned && sh.B > 768 && backward_d4n6_supported(sh) && workspace_bytes >= backward_d4n6_workspace_bytes(sh))
         return launch_backward_d4n6_f32(sh, path, sig, gout, gpath, gbase, workspace, workspace_bytes, st);
     // a gradient per prefix: the two register-resident families, where they beat the prefix-tree kernels (their rules say where)
+    const StreamStretches cut = stream_stretches(sh, SIG_F32);
+    if (cut.K > 1 && workspace != nullptr && workspace_bytes >= cut.bytes)
+        return launch_stream_stretches<float>(sh, cut, path, sig, gout, gpath, gbase, workspace, st);
     if (aligned && backward_d4_supported(sh)) return launch_backward_d4_f32(sh, path, sig, gout, gpath, gbase, st);
     if (aligned && backward_pow2_supported(sh)) return launch_backward_pow2_f32(sh, path, sig, gout, gpath, gbase, st);
     // d = 16, N = 4 (10 ms on the prefix-tree kernels at 256 paths of 1024 points); its workspace is a sixteenth of
@@ -364,6 +437,9 @@ hipError_t launch_backward_f64(const Shape &sh, const double *path, const double
                                double *gbase, void *workspace, int64_t workspace_bytes, hipStream_t st)
 {
     if (backward_n2_supported(sh, SIG_F64)) return launch_backward_n2_f64(sh, path, gout, gpath, gbase, st);
+    const StreamStretches cut = stream_stretches(sh, SIG_F64);
+    if (cut.K > 1 && workspace != nullptr && workspace_bytes >= cut.bytes)
+        return launch_stream_stretches<double>(sh, cut, path, sig, gout, gpath, gbase, workspace, st);
     if (wide_backward_preferred(sh, SIG_F64))
         return launch_wide_backward_f64(sh, path, sig, gout, gpath, gbase, workspace, workspace_bytes, st);
     if (tree_backward_supported(sh))

@@ -263,6 +263,14 @@ hipError_t launch_tree_stretches_f32(const Shape &sh, int64_t K, int64_t m, cons
 hipError_t launch_tree_stretches_f64(const Shape &sh, int64_t K, int64_t m, const double *path, const double *C, double *group, const double *gout,
                                      double *gpath, double *gbase, void *partial, hipStream_t st);
 
+// ... and in stream mode, d = 2..8 at N = 3..6: K >= 2 stretches of m increments counted from the end of the path.  C [B][K - 2]: the
+// signatures up to depth N - 1 of all but the first and the last; carried: [B][K][tree_stream_carried] scalars of scratch memory.
+int64_t tree_stream_carried(const Shape &sh);
+hipError_t launch_tree_stream_stretches_f32(const Shape &sh, int64_t K, int64_t m, const float *path, const float *sig, const float *gout,
+                                            const float *C, float *carried, float *gpath, float *gbase, void *partial, hipStream_t st);
+hipError_t launch_tree_stream_stretches_f64(const Shape &sh, int64_t K, int64_t m, const double *path, const double *sig, const double *gout,
+                                            const double *C, double *carried, double *gpath, double *gbase, void *partial, hipStream_t st);
+
 // Small-state family: S <= 512 scalars, one wavefront per path, state in LDS, words decoded once.
 bool small_supported(const Shape &sh);
 hipError_t launch_small_f32(const Shape &sh, const float *path, float *out, hipStream_t st);
