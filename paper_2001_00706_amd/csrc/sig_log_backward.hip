@@ -362,7 +362,7 @@ log_bwd_finish_kernel(Step stp, int64_t rows, T c_m, T c_last, int first, int la
 // passes are formed between two barriers.
 //   LDS layout (scalars): x[S] | R_N .. R_2 [r_stride] | G[2][S(N-1)] (G_2, G_3, ..) | gx[S] |
 //                         prod[2][kFusedRows][NT] | wsum[NT / 64]
-// NT = 256 threads for the smallest signatures (several workgroups per compute unit), 1024 beyond 2048 scalars,
+// NT = 256 threads for the smallest signatures (several workgroups per compute unit) or 512 (launch_log_backward says when), 1024 beyond 2048 scalars,
 // where one signature fills the LDS of a compute unit anyway and four wavefronts per SIMD issue faster than one.
 template <typename T, int NT>
 __global__ void __launch_bounds__(NT)
@@ -926,9 +926,8 @@ constexpr size_t kLbFusedMaxLds = 128 * 1024;
 constexpr int64_t kLbFusedSmall = 2048;   // scalars up to which the kernel is used at any batch size
 int fused_threads(const Shape &sh) { return sh.S <= kLbFusedSmall ? 256 : 1024; }
 int gather_threads(const Shape &sh) { return sh.S <= kLbFusedSmall ? 256 : 512; }   // as instantiated in launch_gather
-size_t fused_lds_bytes(const Shape &sh, const LbWorkspace &ws, size_t elem)
+size_t fused_lds_bytes(const Shape &sh, const LbWorkspace &ws, size_t elem, int nt)
 {
-    const int nt = fused_threads(sh);
     return size_t(2 * sh.S + ws.r_stride + 2 * ws.g_stride + 2 * kFusedRows * nt + nt / 64) * elem;
 }
 // The gather form of the single-launch kernel: d = 2 to depth 10, d = 4 to depth 6, d = 8 to depth 4 (the depths
@@ -953,7 +952,7 @@ bool use_gather(const Shape &sh, const LbWorkspace &ws, size_t elem)
 bool use_fused(const Shape &sh, const LbWorkspace &ws, size_t elem)
 {
     if (use_gather(sh, ws, elem)) return true;
-    return fused_lds_bytes(sh, ws, elem) <= kLbFusedMaxLds && (sh.S <= kLbFusedSmall || sh.B <= 256);
+    return fused_lds_bytes(sh, ws, elem, fused_threads(sh)) <= kLbFusedMaxLds && (sh.S <= kLbFusedSmall || sh.B <= 256);
 }
 
 // offset, inside a batch row's share of the R buffer, of R_m (m = 2..N): R_N first
@@ -1044,16 +1043,19 @@ hipError_t launch_log_backward(const Shape &sh, const T *x, const T *g, T *gx, v
     const LbWorkspace ws = plan_workspace(sh, int64_t(sizeof(T)));
     if (use_gather(sh, ws, sizeof(T))) return launch_gather<T>(sh, gather_lds_bytes(sh, ws, sizeof(T)), x, g, gx, st);
     if (use_fused(sh, ws, sizeof(T))) {
-        const size_t fused_lds = fused_lds_bytes(sh, ws, sizeof(T));
-        const bool small = fused_threads(sh) == 256;
-        auto kernel = small ? log_bwd_fused_kernel<T, 256> : log_bwd_fused_kernel<T, 1024>;
+        // With two signatures a compute unit or fewer, 512 threads for more than 768 scalars: what the kernel waits for is the chain of
+        // passes between its barriers, of which there are half as many (256 | 512 | 1024 threads, 256 signatures: d = 6, N = 4 25.6 | 21.1 | 21.1 us,
+        // d = 12, N = 3 19.6 | 13.6 | 12.8, d = 3, N = 6 45 | 41 | 45, d = 5, N = 3 10.1 | 10.2 | 11.4; 1024 signatures 29.9 | 29.0 | 49.5 at d = 6, N = 4).
+        const int nt = fused_threads(sh) == 1024 ? 1024 : sh.S > 768 && sh.B <= 512 ? 512 : 256;
+        const size_t fused_lds = fused_lds_bytes(sh, ws, sizeof(T), nt);
+        auto kernel = nt == 256 ? log_bwd_fused_kernel<T, 256> : nt == 512 ? log_bwd_fused_kernel<T, 512> : log_bwd_fused_kernel<T, 1024>;
         if (fused_lds > 64 * 1024) {
             const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(fused_lds));
             if (e != hipSuccess) return e;
         }
         const unsigned grid = unsigned(sh.B < (int64_t(1) << 20) ? sh.B : (int64_t(1) << 20));
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(small ? 256 : 1024), fused_lds, st, sh, ws.r_stride, x, g, gx);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(nt), fused_lds, st, sh, ws.r_stride, x, g, gx);
         return hipGetLastError();
     }
     char *base = static_cast<char *>(workspace);
