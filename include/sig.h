@@ -210,6 +210,12 @@ sig_status sig_combine(const void *a, const void *b, int64_t B, int d, int N, si
 sig_status sig_combine_strided(const void *a, int64_t a_stride, const void *b, int64_t b_stride, int64_t B, int d, int N,
                                sig_dtype dtype, void *out, int64_t out_stride, hipStream_t hip_stream);
 
+/* As sig_combine_strided with a^{-1} in the place of a: the inverse's scalars are those of `a` at the reversed words, negated for odd
+ * lengths (section 5.4), and read there.  With a and b the signatures of the prefixes x_1..x_i and x_1..x_j of a path this is
+ * Sig(x_i..x_j) without the inverses of the prefixes ever being formed. */
+sig_status sig_interval(const void *a, int64_t a_stride, const void *b, int64_t b_stride, int64_t B, int d, int N, sig_dtype dtype, void *out,
+                        int64_t out_stride, hipStream_t hip_stream);
+
 /* Group product of n signatures per batch row, in order: out[b] = sigs[b][0] [x] sigs[b][1] [x] ... [x] sigs[b][n-1]
  * (section 5.5, "combining adjacent intervals": the signatures of n consecutive intervals, each starting at the
  * point where the one before ends, joined without going back to the data).  Neighbours are multiplied pairwise in

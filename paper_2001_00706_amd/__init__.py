@@ -39,6 +39,7 @@ from .binding import (  # noqa: F401
     sig_combine_grouped_backward_workspace_bytes,
     sig_combine_many,
     sig_combine_strided,
+    sig_interval,
     sig_invert,
     sig_log,
     sig_log_backward,

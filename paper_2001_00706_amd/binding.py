@@ -44,6 +44,7 @@ EXPORTED_SYMBOLS = (
     "sig_backward_chunks_hint",
     "sig_backward_chunks_fastest",
     "sig_combine_strided",
+    "sig_interval",
     "sig_combine_backward",
     "sig_combine_backward_workspace_bytes",
     "sig_combine_grouped",
@@ -192,6 +193,8 @@ def load_library() -> ctypes.CDLL:
         lib.sig_combine_many_workspace_bytes.argtypes = [i64, i64, i32, i32, i32]
         lib.sig_combine_strided.restype = i32
         lib.sig_combine_strided.argtypes = [vp, i64, vp, i64, i64, i32, i32, i32, vp, i64, vp]
+        lib.sig_interval.restype = i32
+        lib.sig_interval.argtypes = [vp, i64, vp, i64, i64, i32, i32, i32, vp, i64, vp]
         lib.sig_log.restype = i32
         lib.sig_log.argtypes = [vp, i64, i32, i32, i32, vp, vp]
         lib.sig_log_words.restype = i32
@@ -544,6 +547,35 @@ def sig_invert(sig, d: int, N: int, out=None):
     with _on_device(sig.device):
         status = int(load_library().sig_invert(sig.data_ptr(), rows, d, N, dtype, out.data_ptr(),
                                                _current_stream()))
+    if status != SIG_OK:
+        raise SigError(status, sig_status_string(status))
+    return out
+
+
+def sig_interval(prefixes, start: int, end: int, d: int, N: int, out=None):
+    """The signatures of the points `start..end` (0 < start < end, 0-based) from those of the prefixes `[B, n, S]` (row t - 1: the points
+    0..t): the inverse of row start - 1 times row end - 1, in one product."""
+    import torch
+
+    _check_gpu("sig_interval", prefixes)
+    dtype = _dtype_of(prefixes)
+    S = sig_signature_channels(d, N)
+    if prefixes.dim() != 3 or prefixes.shape[2] != S or not prefixes.is_contiguous():
+        raise ValueError(f"prefixes must be contiguous with shape [B, n, {S}]")
+    B, n, _ = prefixes.shape
+    if not 0 < start < end <= n:
+        raise ValueError(f"need 0 < start < end <= {n}")
+    if out is None:
+        out = torch.empty((B, S), dtype=prefixes.dtype, device=prefixes.device)
+    elif out.dtype != prefixes.dtype or out.device != prefixes.device or not out.is_contiguous():
+        raise ValueError("out must be a contiguous tensor like prefixes")
+    elif B > 0 and B * S > out.numel():
+        raise ValueError("out is too small")
+    row = S * prefixes.element_size()
+    at = prefixes.data_ptr()
+    with _on_device(prefixes.device):
+        status = int(load_library().sig_interval(at + (start - 1) * row, n * S, at + (end - 1) * row, n * S, B, d, N, dtype,
+                                                 out.data_ptr(), S, _current_stream()))
     if status != SIG_OK:
         raise SigError(status, sig_status_string(status))
     return out

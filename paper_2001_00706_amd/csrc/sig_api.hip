@@ -683,6 +683,25 @@ sig_status sig_invert(const void *sig, int64_t rows, int d, int N, sig_dtype dty
     return err == hipSuccess ? SIG_OK : SIG_ERR_HIP;
 }
 
+sig_status sig_interval(const void *a, int64_t a_stride, const void *b, int64_t b_stride, int64_t B, int d, int N, sig_dtype dtype, void *out,
+                        int64_t out_stride, hipStream_t hip_stream)
+{
+    if (dtype != SIG_F32 && dtype != SIG_F64) return SIG_ERR_INVALID_ARG;
+    sig::Shape sh;
+    const sig_status st = make_rows_shape(B, d, N, sh);
+    if (st != SIG_OK) return st;
+    if (a_stride < 0 || b_stride < 0 || out_stride < sh.S) return SIG_ERR_INVALID_ARG;
+    if (B > 0 && (a_stride > kMaxElems / B || b_stride > kMaxElems / B || out_stride > kMaxElems / B)) return SIG_ERR_OVERFLOW;
+    if (B == 0) return SIG_OK;
+    if (a == nullptr || b == nullptr || out == nullptr) return SIG_ERR_INVALID_ARG;
+    if (!sig::combine_supported(sh)) return SIG_ERR_UNSUPPORTED;
+    const hipError_t err = dtype == SIG_F32 ? sig::launch_interval_f32(sh, static_cast<const float *>(a), a_stride, static_cast<const float *>(b),
+                                                                       b_stride, static_cast<float *>(out), out_stride, hip_stream)
+                                            : sig::launch_interval_f64(sh, static_cast<const double *>(a), a_stride, static_cast<const double *>(b),
+                                                                       b_stride, static_cast<double *>(out), out_stride, hip_stream);
+    return err == hipSuccess ? SIG_OK : SIG_ERR_HIP;
+}
+
 sig_status sig_combine_strided(const void *a, int64_t a_stride, const void *b, int64_t b_stride, int64_t B, int d, int N,
                                sig_dtype dtype, void *out, int64_t out_stride, hipStream_t hip_stream)
 {

@@ -90,7 +90,107 @@ hipError_t launch_combine(const Shape &sh, const T *a, const T *b, T *out, hipSt
     return hipGetLastError();
 }
 
+// The word at index i of level k = K (or k_runtime beyond the depths unrolled) of a^{-1} [x] b, for a signature a: the inverse's scalar at a
+// word is that of the reversed word of a, negated for odd lengths (section 5.4), so no inverse is formed.  rev is the reversal of the
+// prefix of j letters: taking its leading letter off leaves that of j - 1.  Terms and their order are those of product_word.
+template <typename T, int K>
+__device__ __forceinline__ T interval_word(const T *a, const T *b, uint32_t i, int k_runtime, uint32_t d)
+{
+    const int k = K > 0 ? K : k_runtime;
+    constexpr int kRoom = K > 0 ? K : SIG_MAX_DEPTH;
+    uint32_t rev = 0, rest = i, off[kRoom + 1], pw[kRoom + 1];
+    pw[0] = 1;
+    off[0] = 0;
+#pragma unroll
+    for (int j = 1; j <= k; ++j) {
+        pw[j] = pw[j - 1] * d;
+        off[j] = j == 1 ? 0 : off[j - 1] + pw[j - 1];
+        rev = rev * d + rest % d;
+        rest /= d;
+    }
+    T x[kRoom], y[kRoom];
+    const T whole = a[off[k] + rev], own = b[off[k] + i];
+    uint32_t suffix = 0;
+#pragma unroll
+    for (int j = k - 1; j >= 1; --j) {
+        const uint32_t letter = rev / pw[j];   // letter j + 1
+        rev -= letter * pw[j];
+        suffix += letter * pw[k - 1 - j];
+        x[j] = a[off[j] + rev];
+        y[j] = b[off[k - j] + suffix];
+    }
+    T acc = (k & 1 ? -whole : whole) + own;
+#pragma unroll
+    for (int j = k - 1; j >= 1; --j) acc += (j & 1 ? -x[j] : x[j]) * y[j];
+    return acc;
+}
+
+// out[p] = a[p]^{-1} [x] b[p], a thread per word; D: the channel count as a constant, or 0.
+template <typename T, int D>
+__global__ void __launch_bounds__(256)
+sig_interval_kernel(Shape sh, int64_t a_stride, int64_t b_stride, int64_t out_stride, const T *__restrict__ a, const T *__restrict__ b,
+                    T *__restrict__ out)
+{
+    const uint32_t d = D > 0 ? uint32_t(D) : uint32_t(sh.d), S = uint32_t(sh.S);
+    for (int64_t p = blockIdx.y; p < sh.B; p += gridDim.y) {
+        const T *ap = a + p * a_stride, *bp = b + p * b_stride;
+        for (uint32_t e = blockIdx.x * 256 + threadIdx.x; e < S; e += gridDim.x * 256) {
+            int k = 1;
+            uint32_t first = 0;
+            for (uint32_t size = d; e - first >= size; size *= d, ++k) first += size;
+            const uint32_t i = e - first;
+            T v;
+            switch (k) {
+                case 1: v = interval_word<T, 1>(ap, bp, i, 1, d); break;
+                case 2: v = interval_word<T, 2>(ap, bp, i, 2, d); break;
+                case 3: v = interval_word<T, 3>(ap, bp, i, 3, d); break;
+                case 4: v = interval_word<T, 4>(ap, bp, i, 4, d); break;
+                case 5: v = interval_word<T, 5>(ap, bp, i, 5, d); break;
+                case 6: v = interval_word<T, 6>(ap, bp, i, 6, d); break;
+                case 7: v = interval_word<T, 7>(ap, bp, i, 7, d); break;
+                case 8: v = interval_word<T, 8>(ap, bp, i, 8, d); break;
+                case 9: v = interval_word<T, 9>(ap, bp, i, 9, d); break;
+                default: v = interval_word<T, 0>(ap, bp, i, k, d); break;
+            }
+            out[p * out_stride + e] = v;
+        }
+    }
+}
+
+template <typename T>
+hipError_t launch_interval(const Shape &sh, const T *a, int64_t a_stride, const T *b, int64_t b_stride, T *out, int64_t out_stride,
+                           hipStream_t st)
+{
+    const dim3 grid(unsigned((sh.S + 255) / 256 < 4096 ? (sh.S + 255) / 256 : 4096), unsigned(sh.B < 65535 ? sh.B : 65535));
+    const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, sh, a_stride, b_stride, out_stride, a, b, out);
+        return hipGetLastError();
+    };
+    switch (sh.d) {
+        case 2: return go(sig_interval_kernel<T, 2>);
+        case 3: return go(sig_interval_kernel<T, 3>);
+        case 4: return go(sig_interval_kernel<T, 4>);
+        case 5: return go(sig_interval_kernel<T, 5>);
+        case 6: return go(sig_interval_kernel<T, 6>);
+        case 7: return go(sig_interval_kernel<T, 7>);
+        case 8: return go(sig_interval_kernel<T, 8>);
+    }
+    return go(sig_interval_kernel<T, 0>);
+}
+
 }  // namespace
+
+hipError_t launch_interval_f32(const Shape &sh, const float *a, int64_t a_stride, const float *b, int64_t b_stride, float *out,
+                               int64_t out_stride, hipStream_t st)
+{
+    return launch_interval<float>(sh, a, a_stride, b, b_stride, out, out_stride, st);
+}
+
+hipError_t launch_interval_f64(const Shape &sh, const double *a, int64_t a_stride, const double *b, int64_t b_stride, double *out,
+                               int64_t out_stride, hipStream_t st)
+{
+    return launch_interval<double>(sh, a, a_stride, b, b_stride, out, out_stride, st);
+}
 
 bool combine_supported(const Shape &sh) { return sh.S < (int64_t(1) << 31); }
 

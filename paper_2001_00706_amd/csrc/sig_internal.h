@@ -66,6 +66,12 @@ hipError_t launch_combine_f32(const Shape &sh, const float *a, const float *b, f
 hipError_t launch_combine_f64(const Shape &sh, const double *a, const double *b, double *out, hipStream_t st,
                               const int64_t *strides = nullptr);
 
+// out = a^{-1} [x] b of sh.B pairs of signatures, row p of each at p times its stride (S < 2^31; out overlaps neither).
+hipError_t launch_interval_f32(const Shape &sh, const float *a, int64_t a_stride, const float *b, int64_t b_stride, float *out,
+                               int64_t out_stride, hipStream_t st);
+hipError_t launch_interval_f64(const Shape &sh, const double *a, int64_t a_stride, const double *b, int64_t b_stride, double *out,
+                               int64_t out_stride, hipStream_t st);
+
 // Inverse of each of sh.B signatures (a signed permutation; `out` may be `in`), and multiplication on the
 // left in place: out[r] <- a[r / group] [x] out[r] for sh.B rows.  Both need S < 2^31.
 hipError_t launch_invert_f32(const Shape &sh, const float *in, float *out, hipStream_t st);

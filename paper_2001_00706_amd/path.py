@@ -1,9 +1,9 @@
 """`Path`: signatures of arbitrary intervals of a batch of paths in one group product each
 (paper section 4.2, section 5.5 "arbitrary intervals" and "keeping the signature up-to-date").
 
-Precomputed once: the signature of every prefix x_0..x_t (one stream-mode scan) and its inverse
-(a signed permutation).  A query Sig(x_i..x_j) = Sig(x_0..x_i)^{-1} [x] Sig(x_0..x_j) is then one
-strided `sig_combine` on rows of those two tensors, whatever the length of the path.  All
+Precomputed once: the signature of every prefix x_0..x_t (one stream-mode scan).  A query
+Sig(x_i..x_j) = Sig(x_0..x_i)^{-1} [x] Sig(x_0..x_j) is then one `sig_interval` on rows of that tensor, whatever the length of
+the path; the inverse, a signed permutation, is read out of the row it belongs to.  All
 arithmetic runs in the HIP library; this class only keeps the tensors and computes row offsets.
 """
 from __future__ import annotations
@@ -23,13 +23,11 @@ class Path:
         self._last_point = path[:, -1].contiguous()
         # row t-1 = Sig(x_0..x_t), t = 1..L-1
         self._sig = [binding.sig_signature(path.contiguous(), self.depth, stream=True)]
-        self._inv = [binding.sig_invert(self._sig[0], self.d, self.depth)]
         self._merge()
 
     def _merge(self):
         if len(self._sig) > 1:
             self._sig = [torch.cat(self._sig, dim=1)]
-            self._inv = [torch.cat(self._inv, dim=1)]
         self.n = self._sig[0].shape[1]   # number of increments seen so far
 
     @property
@@ -46,7 +44,6 @@ class Path:
         last_sig = self._sig[0][:, -1].contiguous()
         more = binding.sig_signature(new_points, self.depth, stream=True, basepoint=self._last_point, initial=last_sig)
         self._sig.append(more)
-        self._inv.append(binding.sig_invert(more, self.d, self.depth))
         self._last_point = new_points[:, -1].contiguous()
         self._merge()
 
@@ -56,15 +53,12 @@ class Path:
         if not (0 <= start < end <= self.n):
             raise ValueError(f"need 0 <= start < end <= {self.n}")
         sig = self._sig[0]
-        if out is None:
-            out = torch.empty((self.B, self.S), dtype=sig.dtype, device=sig.device)
-        row = self.n * self.S   # scalars between the same row of consecutive paths
-        b_rows = sig.reshape(-1)[(end - 1) * self.S:]
         if start == 0:
+            if out is None:
+                out = torch.empty((self.B, self.S), dtype=sig.dtype, device=sig.device)
             out.copy_(sig[:, end - 1])
             return out
-        a_rows = self._inv[0].reshape(-1)[(start - 1) * self.S:]
-        return binding.sig_combine_strided(a_rows, row, b_rows, row, self.B, self.d, self.depth, out, self.S)
+        return binding.sig_interval(sig, start, end, self.d, self.depth, out)
 
     def logsignature(self, start: int = 0, end: int | None = None, mode: str = "words"):
         """Logsignature of the points `start..end` inclusive (sections 2.3, 4.3): `sig_log` of that interval's

@@ -404,3 +404,20 @@ def test_path_logsignature_queries():
         got = host(p.logsignature(i, j))
         np.testing.assert_allclose(got, orc.logsignature(x[:, i:j + 1], N), rtol=0, atol=1e-10)
     assert host(p.logsignature(1, 4, mode="expand")).shape == (3, orc.channels(3, N))
+
+
+# an interval's signature straight from the prefixes: the scalars that the inverse and the product give, at every unrolled depth and beyond
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("B,n,d,N", [(3, 7, 2, 1), (2, 9, 2, 11), (3, 9, 3, 7), (1, 6, 2, 9), (5, 8, 4, 4), (2, 5, 5, 3), (2, 5, 6, 2), (1, 5, 7, 3), (2, 4, 8, 3), (2, 4, 11, 2), (70, 4, 3, 3)])
+def test_interval_without_the_inverse(B, n, d, N, dtype):
+    import torch
+    p = sig.sig_signature(dev(brownian_paths(B, n + 1, d, seed=n).astype(dtype)), N, stream=True)
+    inv = sig.sig_invert(p, d, N)
+    for start, end in ((1, 2), (1, n), (n - 1, n), (n // 2, n)):
+        got = sig.sig_interval(p, start, end, d, N)
+        want = sig.sig_combine(inv[:, start - 1].contiguous(), p[:, end - 1].contiguous(), d, N)
+        # the same N terms at most, each a product of two scalars of the prefixes: a rounding or two of them apart
+        assert (got - want).abs().max() <= 4 * N * np.finfo(dtype).eps * max(1.0, float(p.abs().max()) ** 2)
+    for start, end in ((0, 1), (2, 2), (1, n + 1)):
+        with pytest.raises(ValueError):
+            sig.sig_interval(p, start, end, d, N)
