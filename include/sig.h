@@ -116,8 +116,9 @@ int64_t sig_fused_fmas(int d, int N);
  * N > SIG_MAX_DEPTH, L < 2 (L < 1 with basepoint), an unknown dtype; SIG_ERR_OVERFLOW if a
  * size overflows; SIG_ERR_HIP if the launch failed.  B == 0 is SIG_OK and enqueues nothing.
  * Results are deterministic: the same inputs give bit-identical outputs on every call.
- * In final mode sig_forward scans every path (or every word-prefix shard of it) from end to end and never splits a
- * path over its length, since it has no workspace for partial results: a few very long paths (B * shards far below
+ * In final mode sig_forward has no workspace for partial results: the vector kernels cut the paths of a small batch into stretches
+ * that share a workgroup (up to 64 of 16 increments and more; the values then differ from an end-to-end scan by rounding only),
+ * everything else scans a path (or a word-prefix shard of it) from end to end.  A few very long paths (B * shards far below
  * the number of compute units, L in the tens of thousands) are served many times faster by sig_forward_chunked
  * (sig_forward_chunks_hint says when, and into how many chunks).  In stream mode the output itself has room for
  * partial results, and up to 512 paths of at least 128 increments are cut into chunks internally where the kernel
@@ -377,6 +378,7 @@ sig_status sig_backward(const void *path, const void *sig, const void *grad_out,
 
 /* Bytes of device workspace sig_backward needs for these arguments on the current device: 0 when the per-path
  * working set (the signature, its cotangent and the Horner terms, about 2.7 S scalars) fits on chip.
+ * In stream mode it covers the stretches that few paths are cut into (what they carry to their front, their signatures).
  * -1 on invalid or unsupported arguments. */
 int64_t sig_backward_workspace_bytes(int64_t B, int64_t L, int d, int N, int stream, int basepoint, sig_dtype dtype);
 
