@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import operator
 import os
 import threading
 
@@ -563,6 +564,7 @@ def sig_interval(prefixes, start: int, end: int, d: int, N: int, out=None):
     if prefixes.dim() != 3 or prefixes.shape[2] != S or not prefixes.is_contiguous():
         raise ValueError(f"prefixes must be contiguous with shape [B, n, {S}]")
     B, n, _ = prefixes.shape
+    start, end = operator.index(start), operator.index(end)   # integers of numpy's types and tensors of one integer as well
     if not 0 < start < end <= n:
         raise ValueError(f"need 0 < start < end <= {n}")
     if out is None:

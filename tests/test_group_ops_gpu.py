@@ -421,3 +421,15 @@ def test_interval_without_the_inverse(B, n, d, N, dtype):
     for start, end in ((0, 1), (2, 2), (1, n + 1)):
         with pytest.raises(ValueError):
             sig.sig_interval(p, start, end, d, N)
+
+
+def test_interval_bounds_of_every_integer_type():
+    # what np.searchsorted and torch.argmax hand back; a fraction stays refused
+    import torch
+    p = sig.Path(dev(brownian_paths(3, 12, 3, seed=22).astype(np.float32)), 4)
+    want, want_log = p.signature(2, 9), p.logsignature(2, 9)
+    for kind in (np.int64, np.int32, np.uint8, np.array, torch.tensor, lambda v: torch.tensor(v, device="cuda:0")):
+        assert torch.equal(p.signature(kind(2), kind(9)), want)
+        assert torch.equal(p.logsignature(kind(2), kind(9)), want_log)
+    with pytest.raises(TypeError):
+        p.signature(2.0, 9)
