@@ -225,7 +225,7 @@ def logsignature(path, depth: int, stream: bool = False, basepoint=False, invers
     tensor `basepoint`)."""
     if mode not in ("words", "expand"):
         raise ValueError('mode must be "words" or "expand"')
-    if isinstance(path, torch.Tensor) and path.dim() == 3 and not torch.compiler.is_compiling():
+    if type(depth) is int and isinstance(path, torch.Tensor) and path.dim() == 3 and not torch.compiler.is_compiling():
         table = binding._lyndon_tables.get((path.shape[2], depth, path.device)) if mode == "words" else None   # kept since the first call
         if mode == "expand" or table is not None:
             out = _transform(path, depth, stream, basepoint, inverse, 1 if mode == "expand" else 2, table)

@@ -106,6 +106,18 @@ def test_what_is_handed_back(monkeypatch):
         same(got, want)
 
 
+def test_depths_that_are_no_python_int(monkeypatch):
+    # the table of the kept words is looked up by depth, and an array has no hash
+    import torch
+    x = torch.from_numpy(brownian_paths(2, 9, 3, seed=5)).to("cuda:0")
+    want = sig.logsignature(x, 4)
+    for depth in (np.array(4), np.int64(4), torch.tensor(4), 4.0):
+        got, again, taken = both(monkeypatch, lambda: [sig.logsignature(x, depth)])
+        assert not any(taken)
+        same(got, again)
+        same(got, [want])
+
+
 def test_engine_semantics():
     import torch
     x = torch.from_numpy(brownian_paths(2, 9, 3, seed=5)).to("cuda:0").requires_grad_(True)
