@@ -226,7 +226,9 @@ def logsignature(path, depth: int, stream: bool = False, basepoint=False, invers
     if mode not in ("words", "expand"):
         raise ValueError('mode must be "words" or "expand"')
     if type(depth) is int and isinstance(path, torch.Tensor) and path.dim() == 3 and not torch.compiler.is_compiling():
-        table = binding._lyndon_tables.get((path.shape[2], depth, path.device)) if mode == "words" else None   # kept since the first call
+        # kept since the first call; beyond the depths of sig_log_words, which the node would find out behind the scan, not asked for
+        words = mode == "words" and depth <= binding._LOG_WORDS_MAX_DEPTH
+        table = binding._lyndon_tables.get((path.shape[2], depth, path.device)) if words else None
         if mode == "expand" or table is not None:
             out = _transform(path, depth, stream, basepoint, inverse, 1 if mode == "expand" else 2, table)
             if out is not NotImplemented:

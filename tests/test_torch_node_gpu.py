@@ -118,6 +118,17 @@ def test_depths_that_are_no_python_int(monkeypatch):
         same(got, [want])
 
 
+def test_depths_beyond_the_kept_words_alone_are_scanned_once(monkeypatch):
+    # sig_log_words ends at depth 9: the node is not asked for what it would hand back with the signature already formed
+    import torch
+    x = torch.from_numpy(brownian_paths(2, 9, 2, seed=5)).to("cuda:0")
+    for depth, asked in ((9, [True]), (10, []), (11, [])):
+        sig.logsignature(x, depth)   # the table of the kept words
+        got, want, taken = both(monkeypatch, lambda: [sig.logsignature(x, depth)])
+        assert taken == asked
+        same(got, want)
+
+
 def test_engine_semantics():
     import torch
     x = torch.from_numpy(brownian_paths(2, 9, 3, seed=5)).to("cuda:0").requires_grad_(True)
