@@ -7,14 +7,22 @@ and gradient, queued: 128 x 128 points, d = 4, N = 5, fp64: 65 or 103 us a pass 
 engine's thread runs); it hands back what it does not take, and what the library refuses, and the functions below serve that."""
 from __future__ import annotations
 
+import warnings
+
 import torch
 
 from . import binding
 
 try:
-    from ._sig_torch import transform as _transform
+    from ._sig_torch import built_with, transform as _transform
+    if built_with != torch.__version__:   # the node reaches into torch's own structures
+        raise ImportError(f"built against torch {built_with}, this is {torch.__version__}")
 except ImportError as e:
-    raise ImportError("_sig_torch.so is missing or does not load: build it with `python -c 'import __graft_entry__ as g; g.build()'`") from e
+    warnings.warn(f"_sig_torch.so does not load ({e}); calls go through slower Python functions.  Build it with "
+                  "`python -c 'import __graft_entry__ as g; g.build()'`", RuntimeWarning)
+
+    def _transform(*args):
+        return NotImplemented
 
 
 def _plain_signature(path, basepoint_value, depth, stream, basepoint):

@@ -95,6 +95,7 @@ def build_node(verbose: bool = False) -> str:
     tmp = NODE_PATH + f".tmp{os.getpid()}"
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DSIG_TORCH_VERSION="{torch.__version__}"',
            "-I", INCLUDE, "-isystem", os.path.join(torch_dir, "include"),
            "-isystem", os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
            "-isystem", sysconfig.get_paths()["include"], "-isystem", "/opt/rocm/include", NODE_SRC, "-o", tmp,

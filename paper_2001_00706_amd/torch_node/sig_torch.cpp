@@ -298,4 +298,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_sig_torch", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__sig_torch() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__sig_torch()
+{
+    PyObject *m = PyModule_Create(&module);
+    if (m != nullptr && PyModule_AddStringConstant(m, "built_with", SIG_TORCH_VERSION) < 0) Py_CLEAR(m);
+    return m;
+}

@@ -5,6 +5,8 @@ None of these launches a kernel, so they run without a GPU.
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -394,3 +396,25 @@ def test_product_package_does_not_touch_the_oracle():
         if f.endswith((".py", ".c", ".h")):
             text = open(os.path.join(ROOT, "oracle", f)).read()
             assert "paper_2001_00706_amd" not in text and "libsig.so" not in text, f
+
+
+def test_signature_without_the_compiled_nodes():
+    # a tree where only libsig.so was built, or another torch: a warning, and the Python functions serve every call
+    code = """
+import sys, warnings
+sys.modules["paper_2001_00706_amd._sig_torch"] = None
+import torch
+import paper_2001_00706_amd as sig
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    for call in (sig.signature, sig.logsignature):
+        try:
+            call(torch.zeros(1, 3, 2), 2)
+        except TypeError as e:
+            assert "on the GPU" in str(e), e
+        else:
+            assert False
+assert [w.category for w in seen] == [RuntimeWarning] and "_sig_torch.so" in str(seen[0].message)
+"""
+    res = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
