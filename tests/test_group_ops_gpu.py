@@ -433,3 +433,18 @@ def test_interval_bounds_of_every_integer_type():
         assert torch.equal(p.logsignature(kind(2), kind(9)), want_log)
     with pytest.raises(TypeError):
         p.signature(2.0, 9)
+
+
+# ... against the signature of the points themselves: fewer letters than are counted first (N = 1, 2), all of them first or last, a part of
+# the last words of a prefix missing (9 and 17 channels), several paths to a workgroup, depths beyond the unrolled ones
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("B,n,d,N", [(5, 6, 1, 5), (3, 7, 2, 4), (1, 9, 2, 12), (2, 6, 3, 6), (40, 5, 4, 5), (2, 6, 5, 6), (3, 5, 6, 4), (2, 5, 7, 4), (2, 5, 8, 4),
+                                     (2, 5, 9, 4), (3, 5, 12, 3), (1, 4, 16, 3), (2, 4, 17, 3), (300, 3, 20, 1), (1, 4, 64, 2), (1, 4, 3, 10)])
+def test_interval_against_the_oracle(B, n, d, N, dtype):
+    x = brownian_paths(B, n + 1, d, seed=n + d).astype(dtype)
+    p = sig.sig_signature(dev(x), N, stream=True)
+    largest = max(1.0, float(p.abs().max()))
+    for start, end in ((1, 2), (1, n), (n - 1, n)):
+        want = orc.signature(x[:, start:end + 1], N)
+        # n N roundings in a prefix's scalar, N products of two such scalars in a result
+        assert np.abs(host(sig.sig_interval(p, start, end, d, N)) - want).max() <= 2 * N * (n * N + 2) * np.finfo(dtype).eps * largest ** 2
