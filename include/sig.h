@@ -401,8 +401,9 @@ sig_status sig_backward_chunked(const void *path, const void *grad_out, int64_t 
                                 const void *basepoint_value, int chunks, sig_dtype dtype, void *grad_path, void *grad_basepoint,
                                 void *workspace, int64_t workspace_bytes, hipStream_t hip_stream);
 
-/* Bytes of workspace sig_backward_chunked needs (the stretches' points and point gradients, three signatures per
- * stretch, and what sig_backward needs for the stretches); -1 on invalid or unsupported arguments. */
+/* Bytes of workspace sig_backward_chunked needs; -1 on invalid or unsupported arguments.  For d = 2 .. 8 at N = 3 .. 9: the stretches'
+ * signatures up to depth N - 1, a seventh of them again for their products, and what sig_backward needs for the paths; otherwise the
+ * stretches' points and point gradients, three signatures per stretch, and what sig_backward needs for the stretches. */
 int64_t sig_backward_chunked_workspace_bytes(int64_t B, int64_t L, int d, int N, int basepoint, int chunks, sig_dtype dtype);
 
 /* A number of stretches to give sig_backward_chunked for this shape, a power of two that keeps the workspace small; 1 for

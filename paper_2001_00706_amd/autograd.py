@@ -51,7 +51,7 @@ def _signature_gradients(path, plain, basepoint_value, grad_out, args):
     while chunks > 1 and grad_path is None:   # few long paths: the walk back along the path cut into stretches
         try:
             grad_path = binding.sig_backward_chunked(path, grad_out, depth, chunks, basepoint=bp, grad_basepoint=grad_bp)
-        except torch.OutOfMemoryError:   # every stretch takes memory for three signatures: with fewer it may do
+        except torch.OutOfMemoryError:   # every stretch takes memory: with fewer it may do
             fewer = binding.sig_backward_chunks_hint(B, L, d, depth, bool(basepoint), binding._dtype_of(path))
             chunks = fewer if fewer < chunks else 1
     if grad_path is None:

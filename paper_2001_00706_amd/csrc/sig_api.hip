@@ -391,14 +391,15 @@ sig_status sig_backward(const void *path, const void *sig, const void *grad_out,
     return err == hipSuccess ? SIG_OK : SIG_ERR_HIP;
 }
 
-// Layout of a gradient computed stretch by stretch: K stretches of m increments per path, served as the B K short paths
-// of `rows`; the workspace holds, each 256-byte aligned, the stretches' points, their signatures (later the gradients),
-// the signatures up to the end of each and of what comes after it, the stretches' point gradients and the workspace of
-// the gradient kernels.
+// Layout of a gradient computed stretch by stretch: K stretches of m increments per path.  The workspace holds, each 256-byte
+// aligned: where the walk forms the products it needs by itself (tree_stretches_supported), the stretches' signatures below the top
+// level (at_sigs), the nodes of their products (at_nodes) and the walk's partial sums (at_inner); otherwise, the stretches served as
+// the B K short paths of `rows`, their points, their signatures (later the gradients), the signatures up to the end of each and of
+// what comes after it, the stretches' point gradients and the workspace of the gradient kernels.
 struct StretchPlan {
     int64_t K, m;
     sig::Shape rows;
-    int64_t at_points, at_sigs, at_prefix, at_suffix, at_point_grads, at_inner, inner_bytes, total;
+    int64_t at_points, at_sigs, at_nodes, at_prefix, at_suffix, at_point_grads, at_inner, inner_bytes, total;
 };
 
 static sig_status plan_backward_chunked(int64_t B, int64_t L, int d, int N, int basepoint, int chunks, sig_dtype dtype, sig::Shape &sh,
@@ -426,6 +427,15 @@ static sig_status plan_backward_chunked(int64_t B, int64_t L, int d, int N, int 
     const auto round_up = [](int64_t bytes) { return (bytes + 255) / 256 * 256; };
     const int64_t points = round_up(pl.rows.B * (pl.m + 1) * d * elem), sigs = round_up(pl.rows.B * sh.S * elem);
     if (sigs > kMaxElems || points > kMaxElems) return SIG_ERR_OVERFLOW;
+    if (sig::tree_stretches_supported(sh)) {
+        const int64_t below = sh.off[N] * elem;
+        pl.inner_bytes = sig::tree_backward_workspace_bytes(sh, dtype);
+        pl.at_sigs = 0;
+        pl.at_nodes = round_up(pl.rows.B * below);
+        pl.at_inner = pl.at_nodes + round_up(B * sig::tree_stretch_nodes(pl.K) * below);
+        pl.total = pl.at_inner + round_up(pl.inner_bytes);
+        return SIG_OK;
+    }
     pl.at_points = 0;
     pl.at_sigs = pl.at_points + points;
     pl.at_prefix = pl.at_sigs + sigs;
@@ -482,18 +492,18 @@ sig_status sig_backward_chunked(const void *path, const void *grad_out, int64_t 
         below.B = B * pl.K;
         below.chunks = int(pl.K);
         below.chunk_len = pl.m;
-        void *C = ws + pl.at_sigs, *group = ws + pl.at_prefix;
+        void *C = ws + pl.at_sigs, *nodes = ws + pl.at_nodes;
         const Family scan = resolve(below, dtype, SIG_VARIANT_AUTO, path, C);
         if (scan == Family::None) return SIG_ERR_UNSUPPORTED;
         if (launch_scan(scan, below, dtype, path, C, hip_stream) != hipSuccess) return SIG_ERR_HIP;
         const hipError_t err =
             dtype == SIG_F32
                 ? sig::launch_tree_stretches_f32(sh, pl.K, pl.m, static_cast<const float *>(path), static_cast<const float *>(C),
-                                                 static_cast<float *>(group), static_cast<const float *>(grad_out),
+                                                 static_cast<float *>(nodes), static_cast<const float *>(grad_out),
                                                  static_cast<float *>(grad_path), static_cast<float *>(grad_basepoint),
                                                  ws + pl.at_inner, hip_stream)
                 : sig::launch_tree_stretches_f64(sh, pl.K, pl.m, static_cast<const double *>(path), static_cast<const double *>(C),
-                                                 static_cast<double *>(group), static_cast<const double *>(grad_out),
+                                                 static_cast<double *>(nodes), static_cast<const double *>(grad_out),
                                                  static_cast<double *>(grad_path), static_cast<double *>(grad_basepoint),
                                                  ws + pl.at_inner, hip_stream);
         return err == hipSuccess ? SIG_OK : SIG_ERR_HIP;
@@ -550,7 +560,9 @@ int sig_backward_chunks_hint(int64_t B, int64_t L, int d, int N, int basepoint, 
         const int64_t next = int64_t(chunks) * 2;
         if (next * B > 1024 || sh.n_inc / next < 32 || next * next * per_stretch > sh.n_inc) break;
         const int64_t bytes = sig_backward_chunked_workspace_bytes(B, L, d, N, basepoint, int(next), dtype);
-        if (bytes < 0 || bytes > (int64_t(2) << 30)) break;
+        // 2 GiB, counting three signatures per stretch also where less is kept: large signatures fill the chip by themselves
+        const int64_t sigs = sig::tree_stretches_supported(sh) ? 3 * next * B * sh.S * elem : 0;
+        if (bytes < 0 || bytes + sigs > (int64_t(2) << 30)) break;
         chunks = int(next);
     }
     return chunks;

@@ -261,9 +261,10 @@ hipError_t launch_tree_backward_f64(const Shape &sh, const double *path, const d
                                     double *gpath, double *gbase, void *workspace, int64_t workspace_bytes, hipStream_t st);
 
 // The same family's walk back over K stretches of m increments per path, d = 2..8 at N = 3..9 (final mode).  C [B][K]: the stretches'
-// signatures up to depth N - 1; `group`: room for K / 7 + 6 more such rows per path; `partial`: tree_backward_workspace_bytes(sh).
-// Needs no signature of the paths.
+// signatures up to depth N - 1; `group`: room for tree_stretch_nodes(K) more such rows per path; `partial`:
+// tree_backward_workspace_bytes(sh).  Needs no signature of the paths.
 bool tree_stretches_supported(const Shape &sh);
+int64_t tree_stretch_nodes(int64_t K);
 hipError_t launch_tree_stretches_f32(const Shape &sh, int64_t K, int64_t m, const float *path, const float *C, float *group, const float *gout,
                                      float *gpath, float *gbase, void *partial, hipStream_t st);
 hipError_t launch_tree_stretches_f64(const Shape &sh, int64_t K, int64_t m, const double *path, const double *C, double *group, const double *gout,

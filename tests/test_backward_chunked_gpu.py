@@ -96,6 +96,23 @@ def test_nodes_of_stretches(B, L, d, N, chunks, basepoint, dtype):
     check(brownian_paths(B, L, d, seed=L).astype(dtype) + dtype(0.2 * basepoint), N, chunks, basepoint=basepoint)
 
 
+# the workspace's layout: exactly the bytes asked for, what lies behind them stays as it was
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("B,L,d,N,chunks", [(2, 11, 3, 3, 4), (3, 131, 2, 4, 65), (2, 601, 4, 5, 600), (1, 72, 5, 6, 71), (3, 40, 8, 4, 9), (1, 30, 7, 5, 8),
+                                            (2, 30, 9, 3, 4)])
+def test_the_workspace_asked_for_is_all_that_is_used(B, L, d, N, chunks, dtype):
+    import torch
+    code = sig.SIG_F32 if dtype == np.float32 else sig.SIG_F64
+    x = brownian_paths(B, L, d, seed=L).astype(dtype)
+    g = np.random.default_rng(L).standard_normal((B, orc.channels(d, N))).astype(dtype)
+    need = sig.sig_backward_chunked_workspace_bytes(B, L, d, N, False, chunks, code)
+    room = torch.full((need + (1 << 20),), 91, dtype=torch.uint8, device="cuda:0")
+    got = sig.sig_backward_chunked(dev(x), dev(g), N, chunks, workspace=room[:need])
+    want = orc.signature_backward(x, g, N, False, False)
+    assert np.linalg.norm(got.cpu().numpy() - want) <= TOL[dtype] * np.linalg.norm(want)
+    assert bool((room[need:] == 91).all())
+
+
 def test_a_path_with_nan_spoils_no_other():
     x = brownian_paths(40, 21, 3, seed=1).astype(np.float32)
     g = np.random.default_rng(2).standard_normal((40, orc.channels(3, 4))).astype(np.float32)

@@ -291,10 +291,18 @@ def test_backward_chunk_hint_and_workspace(lib):
     assert h(1, 1, 4, 6, 0, sig.SIG_F32) == 0 and h(1, 4096, 4, 6, 0, 9) == 0 and h(1, 4096, 0, 6, 0, sig.SIG_F32) == 0
     w = lib.sig_backward_chunked_workspace_bytes
     # 10 increments in 4 stretches of 3: 8 rows of 4 points (256-byte pieces: points, 3 x signatures, point gradients)
-    S = 3 + 9 + 27
+    S = 9 + 81 + 729
     piece = lambda n: (n + 255) // 256 * 256
-    inner = lib.sig_backward_workspace_bytes(8, 4, 3, 3, 0, 0, sig.SIG_F32)
-    assert w(2, 11, 3, 3, 0, 4, sig.SIG_F32) == 2 * piece(8 * 4 * 3 * 4) + 3 * piece(8 * S * 4) + piece(inner)
+    inner = lib.sig_backward_workspace_bytes(8, 4, 9, 3, 0, 0, sig.SIG_F32)
+    assert w(2, 11, 9, 3, 0, 4, sig.SIG_F32) == 2 * piece(8 * 4 * 9 * 4) + 3 * piece(8 * S * 4) + piece(inner)
+    # two to eight channels: the stretches' signatures to depth N - 1, nodes of 8 from the ninth stretch on, the whole paths' workspace
+    whole = lib.sig_backward_workspace_bytes(2, 11, 3, 3, 0, 0, sig.SIG_F32)
+    assert w(2, 11, 3, 3, 0, 4, sig.SIG_F32) == piece(8 * (3 + 9) * 4) + piece(whole)
+    whole = lib.sig_backward_workspace_bytes(3, 131, 2, 4, 0, 0, sig.SIG_F64)
+    assert w(3, 131, 2, 4, 0, 65, sig.SIG_F64) == piece(3 * 65 * 14 * 8) + piece(3 * (9 + 2) * 14 * 8) + piece(whole)
+    # 256 paths of 1000 points, d = 8, N = 5, in 16: less than a sixteenth of three signatures per stretch
+    rows = 256 * 16
+    assert w(256, 1000, 8, 5, 0, 16, sig.SIG_F32) * 16 < 3 * rows * lib.sig_signature_channels(8, 5) * 4
     assert w(2, 11, 3, 3, 0, 1, sig.SIG_F32) == -1 and w(2, 11, 3, 3, 0, 65537, sig.SIG_F32) == -1
     assert w(70000, 11, 3, 3, 0, 4, sig.SIG_F32) == -1 and w(0, 11, 3, 3, 0, 4, sig.SIG_F32) == 0
 
