@@ -264,9 +264,9 @@ hipError_t launch_backward_nt(const Shape &sh, const BackwardPlan &pl, const T *
     if (fits_lds<T>(pl)) {
         const size_t lds = (size_t(pl.small_elems) + size_t(pl.big_elems)) * sizeof(T);
         auto kernel = sig_backward_kernel<T, NT, true>;
-        if (lds > kLdsDefaultLimit) {
+        if (lds > kLdsDefaultLimit) {   // the most of any shape: the attribute is the process's, another thread may set it in between
             const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, int(lds_limit()));
             if (e != hipSuccess) return e;
         }
         const unsigned grid = unsigned(sh.B < (int64_t(1) << 20) ? sh.B : (int64_t(1) << 20));

@@ -1049,9 +1049,9 @@ hipError_t launch_log_backward(const Shape &sh, const T *x, const T *g, T *gx, v
         const int nt = fused_threads(sh) == 1024 ? 1024 : sh.S > 768 && sh.B <= 512 ? 512 : 256;
         const size_t fused_lds = fused_lds_bytes(sh, ws, sizeof(T), nt);
         auto kernel = nt == 256 ? log_bwd_fused_kernel<T, 256> : nt == 512 ? log_bwd_fused_kernel<T, 512> : log_bwd_fused_kernel<T, 1024>;
-        if (fused_lds > 64 * 1024) {
+        if (fused_lds > 64 * 1024) {   // the most of any shape: the attribute is the process's, another thread may set it in between
             const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, int(fused_lds));
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, int(kLbFusedMaxLds));
             if (e != hipSuccess) return e;
         }
         const unsigned grid = unsigned(sh.B < (int64_t(1) << 20) ? sh.B : (int64_t(1) << 20));

@@ -233,9 +233,9 @@ hipError_t launch_split_dn(const Shape &sh, const T *path, T *out, hipStream_t s
     const int64_t staged = paths * K * SS::kRow, joined = paths * (K / 2) * kS, groups = (sh.B + paths - 1) / paths;
     const size_t lds = size_t(staged > joined ? staged : joined) * sizeof(T);
     if (groups > 0x3fffff || lds > size_t(kSplitLds)) return hipErrorNotSupported;
-    if (lds > 64 * 1024) {
+    if (lds > 64 * 1024) {   // the most of any call: the attribute is the process's, another thread may set it in between
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(sig_tree_split_kernel<T, D, N>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kSplitLds);
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((sig_tree_split_kernel<T, D, N>), dim3(unsigned(groups)), dim3(unsigned(threads)), lds, st, sh, log2K, m, int(paths),

@@ -250,3 +250,31 @@ def test_gradcheck_through_the_logsignature_in_both_modes():
     s = dev(orc.signature(brownian_paths(2, 5, 2, seed=9), 3)).requires_grad_(True)
     assert torch.autograd.gradcheck(lambda t: sig.signature_to_logsignature(t, 2, 3), (s,), eps=1e-6, atol=1e-7,
                                     rtol=1e-6)
+
+
+def test_threads_that_launch_one_kernel_with_different_lds():
+    # the single-launch kernel takes 72 KB of LDS at d = N = 5 and 124 at d = 6, N = 5, where the runtime wants to be told beforehand
+    import threading
+    import torch
+    calls = []
+    for d in (5, 6):
+        s, g = (torch.randn((3, orc.channels(d, 5)), generator=torch.Generator().manual_seed(d + i)).to("cuda:0") for i in (0, 1))
+        calls.append((s, g, d, sig.sig_log_backward(s, g, d, 5)))
+    torch.cuda.synchronize()
+    failed = []
+
+    def work(s, g, d, want):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                outs = [sig.sig_log_backward(s, g, d, 5) for _ in range(100)]
+                torch.cuda.current_stream().synchronize()
+                assert all(torch.equal(out, want) for out in outs)
+        except Exception as e:
+            failed.append(e)
+
+    threads = [threading.Thread(target=work, args=c) for c in calls for _ in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed, failed
