@@ -590,7 +590,9 @@ static int tree_stretches_fastest(int64_t B, const sig::Shape &sh, sig_dtype dty
     const auto time = [&](int64_t K) {
         const int64_t m = (sh.n_inc + K - 1) / K, rows = B * ((sh.n_inc + m - 1) / m);
         const double per_group = words < 15 ? 16 : std::floor(240 / words);   // at most 64 words: rows that share four wavefronts
-        const double waves = (words > 64 ? double(rows) * std::ceil(words / 64) : 4 * std::ceil(double(rows) / per_group)) / 1024;
+        // 343 words (d = 7, N = 5) take two workgroups, a third of which is idle
+        const double row_waves = words > 256 && words < 512 ? 8 : std::ceil(words / 64);
+        const double waves = (words > 64 ? double(rows) * row_waves : 4 * std::ceil(double(rows) / per_group)) / 1024;
         const double walk = either(2.16e-3 * back * (wide ? 1.26 : 1.0), 1.03e-3 * back * waves * f64);
         if (K == 1) return 7 + double(sh.n_inc) * walk;
         int64_t nodes = (sh.n_inc + m - 1) / m, steps = -1;
@@ -603,8 +605,9 @@ static int tree_stretches_fastest(int64_t B, const sig::Shape &sh, sig_dtype dty
         return t + double(m) * (walk + forward) + double(steps + nodes) * either(8.06e-3 * product, 3.49e-3 * product * waves * f64);
     };
     // 2048 paths of up to 16 words are four wavefronts a SIMD as they are (one piece | the best count: 2048 x 300 points, d = 2, N = 3
-    // 67 | 60 us, 4096 x 300 76 | 84, 9646 x 610, d = 3, N = 3 259 | 382, 4096 x 1100, d = 4, N = 4 474 | 388)
-    if (words <= 16 && B >= 2048) return 1;
+    // 67 | 60 us, 4096 x 300 76 | 84, 9646 x 610, d = 3, N = 3 259 | 382, 4096 x 1100, d = 4, N = 4 474 | 388); up to 2600 long paths the cut is
+    // ahead from three channels on (in one piece 1.2 to 1.4 times the time of 4 stretches: 2050 x 1300, d = 4, N = 3, 2500 x 2000, d = 5, N = 3)
+    if (words <= 16 && B >= 2048 && (sh.d == 2 || sh.n_inc < 800 || B >= 2600)) return 1;
     // up to 40 us in one piece the host takes as long for the launches of either, and it has to gain something
     double best = time(1);
     if (best < 40) return 1;
@@ -618,6 +621,10 @@ static int tree_stretches_fastest(int64_t B, const sig::Shape &sh, sig_dtype dty
         best = t;
         chunks = int(K);
     }
+    // Two stretches at d = 7, whose words leave workgroups partly idle, were behind one piece (137 x 115 points, N = 5 86 | 109 us, 27 x 135, N = 6
+    // 112 | 139; elsewhere 0.8 to 1.08 of the time), and so were four of many short paths in fp64 (1349 x 61, d = 7, N = 3 46 | 57, 2018 x 135 96 | 110).
+    if (chunks == 2 && !wide && sh.d == 7) return 1;
+    if (chunks < 8 && wide && words <= 8 && sh.d >= 7 && B >= 1024) return 1;
     return chunks;
 }
 
@@ -831,13 +838,15 @@ static sig_status forward_chunked(const void *path, int64_t B, int64_t L, int d,
     if (family == Family::None) return SIG_ERR_UNSUPPORTED;
     // Where sig_forward cuts the path inside a workgroup by itself, into stretches of 80 increments at most, that is ahead of any count
     // (9 x 849 points, d = 3, N = 5 14 us against 27 in the hinted chunks, 3 x 806, d = 2, N = 6, fp64 12 | 33; 8 x 995, d = 3, N = 6, 124 increments a
-    // stretch 33 | 33, 6 x 551, d = 5, N = 5, fp64, 138: 45 | 32).
+    // stretch 33 | 33, 6 x 551, d = 5, N = 5, fp64, 138: 45 | 32).  Of 64 where no more than eight stretches of more than 15 KB fit (2 x 621, d = 5, N = 5,
+    // 78 increments: 32 | 27; 8 x 619, d = 7, N = 4, fp64 41 | 38; 36 x 532, d = 8, N = 4, fp64 59 | 45).
     sig::Shape whole;
     if (make_shape(B, L, d, N, 0, basepoint, whole) == SIG_OK) {
         whole.basepoint_value = basepoint_value;
         const Family one = resolve(whole, dtype, SIG_VARIANT_AUTO, path, out);
         const int K = cut_inside(one, whole) ? sig::tree_split_stretches(whole, dtype) : 1;
-        if (K > 1 && whole.n_inc <= 80 * int64_t(K)) return launch_auto(one, whole, dtype, path, out, hip_stream) == hipSuccess ? SIG_OK : SIG_ERR_HIP;
+        const int64_t longest = K <= 8 && sh.S * elem > 15000 ? 64 : 80;
+        if (K > 1 && whole.n_inc <= longest * K) return launch_auto(one, whole, dtype, path, out, hip_stream) == hipSuccess ? SIG_OK : SIG_ERR_HIP;
     }
     // every chunk scanned on its own ...
     char *ws0 = static_cast<char *>(workspace);

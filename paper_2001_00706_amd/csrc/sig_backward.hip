@@ -318,9 +318,17 @@ bool wide_backward_preferred(const Shape &sh, sig_dtype dtype)
 // stretch leaves at its front (sig_stream_carry_kernel), one for the stretches' signatures, and a walk over a K-th of the length
 // behind K steps of products.  As many stretches as are at least 8 increments long (16 for more than 16) while their threads are 170 000 at most
 // and 1400 for an increment of the path; a thread counts for more where a path does not fit a wavefront, since its steps of products
-// take longer, and from seven channels on.  Over 500 shapes of 1 to 2000 paths of 16 to 1100 points it takes 0.48 of the time in one piece, 1.3 % off the
-// best count in the mean (one piece | cut: 64 x 101, d = 5, N = 4 79 | 44 us in 8; 5 x 723, d = 5, N = 4 567 | 92 in 16; 369 x 64, d = 6, N = 4, fp64 stays near
-// 165 to 211; worst 383 x 66, d = 6, N = 4 64 | 73).
+// take longer, and from seven channels on.  Over 8500 shapes of 1 to 6000 paths of 39 to 400 increments, each timed in 1 to 32 stretches, it takes
+// 0.56 of the time in one piece, 3.5 % off the best count in the mean; 30 shapes are more than 4 % behind one piece, at most 21 % (one
+// piece | cut: 64 x 101, d = 5, N = 4 79 | 44 us in 8; 5 x 723, d = 5, N = 4 567 | 92 in 16; worst 1338 x 189, d = 3, N = 5 202 | 243).  Not cut are
+//   * paths whose rows of an increment take more than 2 MB (3 from seven channels on; in fp64 4.5 and 9): their walk already reads 4 to 8 TB/s,
+//     and the cut reads the cotangents twice (584 x 112, d = 4, N = 5 1.8 times the time of one piece, 2626 x 234, d = 4, N = 4 310 | 487);
+//   * nor, for longer rows, packed paths into more workgroups, of up to 53 KB of LDS, than there are compute units (712 x 52, d = 5, N = 4,
+//     317 of them 45 | 66; 417 x 55, d = 6, N = 4 54 | 76; 1235 x 62, d = 6, N = 3 55 | 73; with fewer letters the line would cost: d = 4, N = 3
+//     0.7 of the time beyond it);
+//   * nor into four so few increments that a step of products costs what the walk saves: at d = 4, N = 4 in fp32 against
+//     sig_backward_d4.hip fewer than 48, or 64 of 240 to 520 paths (491 x 41 27 | 33, 503 x 52 1.15 times one piece, 529 x 52 0.96, 125 x 64 39 | 33),
+//     in fp64 fewer than 64 of up to 7 paths from four channels on at N = 3 and 4 (5 x 50, d = 8, N = 3 75 | 95).
 struct StreamStretches {
     int64_t K, m, at_C, at_carried, bytes;
 };
@@ -330,12 +338,22 @@ static StreamStretches stream_stretches(const Shape &sh, sig_dtype dtype)
     StreamStretches pl = {1, sh.n_inc, 0, 0, 0};
     if (!sh.stream || sh.d < 2 || sh.d > 8 || sh.N < 3 || sh.N > 6 || sh.n_inc < 40 || !tree_backward_supported(sh)) return pl;
     const int64_t words = sh.pw[sh.N - 2], most = sh.n_inc < 121 ? 1400 * sh.n_inc : 170000;
+    const bool f32 = dtype == SIG_F32;
+    const double row_bytes = double(sh.B) * double(sh.S) * (f32 ? 4 : 8);
+    if (row_bytes > (f32 ? 2e6 : 4.5e6) * (sh.d < 7 ? 1 : f32 ? 1.5 : 2)) return pl;
     const double threads = double(sh.B) * double(words < 16 ? 16 : words) * (words > 64 ? 1 + 0.01 * (sh.N - 2) * sh.d * sh.d : 1.0) *
                            (sh.d >= 7 ? 2.0 : 1.0);
-    while (pl.K < 32 && sh.n_inc / (2 * pl.K) >= (pl.K < 16 ? 8 : 16) && double(2 * pl.K) * threads <= double(most)) pl.K *= 2;
-    // Two stretches have two launches more to make up for; at d = 8, N = 4 the kernel for one piece (sig_backward_pow2.hip) takes 1.5 us an
-    // increment where the walk reads its rows in 2.4 (146 x 76 points 116 | 159 in 8, 30 x 252 373 | 304 in 4, 131 in 16).
-    if (pl.K < (sh.d == 8 && sh.N == 4 ? 8 : 4)) {
+    // rows that share a workgroup (TbShape in sig_tree_backward_impl.h, with the lanes' numbers in LDS)
+    const int64_t fit = 4 * (64 / sh.d * sh.d) / words, rows = fit < 16 ? fit : 16;
+    const bool packed = words <= 64 && (sh.d >= 6 || (sh.d >= 4 && sh.N >= 4) || (!f32 && sh.d >= 5));
+    while (pl.K < 32 && sh.n_inc / (2 * pl.K) >= (pl.K < 16 ? 8 : 16) && double(2 * pl.K) * threads <= double(most) &&
+           !(packed && 2 * pl.K * sh.B > 256 * rows))
+        pl.K *= 2;
+    // Two stretches have two launches more to make up for; at d = 8, N = 4 in fp32 the kernel for one piece (sig_backward_pow2.hip) takes
+    // 1.5 us an increment where the walk reads its rows in 2.4 (146 x 76 points 116 | 159 in 8, 30 x 252 373 | 304 in 4, 131 in 16).
+    const bool few = f32 ? sh.d == 4 && sh.N == 4 && sh.n_inc < (sh.B >= 240 && sh.B < 520 ? 64 : 48)
+                         : sh.n_inc < 64 && sh.B < 8 && sh.d >= 4 && sh.N <= 4;
+    if (pl.K < ((f32 && sh.d == 8 && sh.N == 4) || few ? 8 : 4)) {
         pl.K = 1;
         return pl;
     }

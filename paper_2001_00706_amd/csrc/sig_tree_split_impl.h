@@ -198,17 +198,21 @@ sig_tree_split_kernel(Shape sh, int log2K, int m, int paths, const T *__restrict
     if (live && c == 0) store(out + row * kS);
 }
 
-// Stretches (a power of two; 1: none) for a batch: as many as a workgroup holds, of 16 increments and more, while the threads before
-// the last doubling are one wavefront per SIMD or less (100 points, in one piece | cut: 500 x d = 5, N = 5, 62 500 threads 23.8 | 15.2 us;
-// 1040 x d = 3, N = 5 18.4 | 9.6; 2306 x 667, d = 2, N = 6, fp64 197 | 81; in fp64 from six channels on, where a workgroup has a compute unit
-// to itself, up to 24 000: 286 x 162, d = 6, N = 5, 62 000 threads 65 | 73).  Below 32 increments there is nothing to gain (9 us either way), nor below
-// 64 from two stretches (1 x 51, d = 4, N = 6, fp64 12.2 | 13.0).
+// Stretches (a power of two, up to 256 in fp32 and 128 in fp64 at d = 2; 1: none) for a batch: as many as a workgroup holds, of 8 increments
+// and more, while the threads before the last doubling are one wavefront per SIMD or less (100 points, in one piece | cut: 500 x d = 5, N = 5,
+// 62 500 threads 23.8 | 15.2 us; 1040 x d = 3, N = 5 18.4 | 9.6; 2306 x 667, d = 2, N = 6, fp64 197 | 81; in fp64 from six channels on, where a
+// workgroup has a compute unit to itself, up to 24 000: 286 x 162, d = 6, N = 5, 62 000 threads 65 | 73).  Below 32 increments there is nothing to
+// gain (9 us either way), nor below 64 from two stretches (1 x 51, d = 4, N = 6, fp64 12.2 | 13.0), below 40 at d = 6, N = 5, where 37 KB a
+// signature are to be joined (102 x 33 10.7 | 12.3; 7 x 45 even), or below 128 at d = 8, N = 4 in fp64, where a thread's share spills (16 x 97
+// 1.14 times one piece, 130 0.94, 260 0.61).
 template <typename T, int D, int N>
 int split_count(const Shape &sh)
 {
     using SS = SplitShape<T, D, N>;
     constexpr int64_t kS = tree_off(D, N + 1), kFull = sizeof(T) == 8 && D >= 6 ? 24000 : 64 * 1024;
-    if (sh.n_inc < (4 * SS::kAllWords <= SS::kThreads ? 32 : 64) || sh.n_inc > (int64_t(1) << 30)) return 1;
+    constexpr bool kSpills = sizeof(T) == 8 && D == 8 && SS::U == 2;
+    constexpr int64_t kShortest = kSpills ? 128 : 4 * SS::kAllWords > SS::kThreads ? 64 : kS * int64_t(sizeof(T)) > 32 * 1024 ? 40 : 32;
+    if (sh.n_inc < kShortest || sh.n_inc > (int64_t(1) << 30)) return 1;
     int K = 1;
     while (2 * K * SS::kAllWords <= SS::kThreads && sh.n_inc >= 16 * K && int64_t(K) * kS * int64_t(sizeof(T)) <= kSplitLds &&
            sh.B <= kFull / (K * SS::kWords))

@@ -314,11 +314,22 @@ def test_count_of_stretches_against_measured_times(lib):
     for B, L, d, N, dtype in ((16384, 1100, 2, 3, sig.SIG_F32), (4096, 300, 2, 3, sig.SIG_F32), (4096, 1100, 2, 3, sig.SIG_F32),
                               (2048, 300, 2, 3, sig.SIG_F32), (16384, 1100, 4, 3, sig.SIG_F32), (4096, 1100, 4, 4, sig.SIG_F32),
                               (9646, 610, 3, 3, sig.SIG_F32), (9601, 431, 2, 3, sig.SIG_F64), (512, 2000, 1, 9, sig.SIG_F32),
-                              (512, 600, 1, 9, sig.SIG_F64), (32, 200, 32, 3, sig.SIG_F32)):
+                              (512, 600, 1, 9, sig.SIG_F64), (32, 200, 32, 3, sig.SIG_F32),
+                              (1349, 61, 7, 3, sig.SIG_F64), (1534, 66, 7, 3, sig.SIG_F64)):
         assert h(B, L, d, N, False, dtype) == 1, (B, L, d, N)
     for B, L, d, N, dtype in ((32, 600, 3, 10, sig.SIG_F32), (8, 600, 3, 10, sig.SIG_F64), (8, 2000, 3, 10, sig.SIG_F64),
                               (1, 65537, 4, 6, sig.SIG_F32), (512, 1100, 4, 4, sig.SIG_F32), (8, 2000, 2, 12, sig.SIG_F32)):
         assert h(B, L, d, N, False, dtype) >= 4, (B, L, d, N)
+    # two stretches: not at seven channels in fp32; stream mode, by the workspace, which is that of final mode where the paths stay in one piece
+    for B, L, d, N, dtype in ((137, 115, 7, 5, sig.SIG_F32), (27, 135, 7, 6, sig.SIG_F32), (177, 203, 7, 5, sig.SIG_F32)):
+        assert h(B, L, d, N, False, dtype) != 2, (B, L, d, N)
+    w = lib.sig_backward_workspace_bytes
+    for B, L, d, N, dtype, whole in ((491, 41, 4, 4, sig.SIG_F32, True), (491, 65, 4, 4, sig.SIG_F32, False), (491, 41, 4, 4, sig.SIG_F64, False),
+                                     (5, 50, 8, 3, sig.SIG_F64, True), (5, 65, 8, 3, sig.SIG_F64, False), (2, 54, 5, 4, sig.SIG_F64, True),
+                                     (712, 52, 5, 4, sig.SIG_F32, True), (500, 62, 5, 4, sig.SIG_F32, False), (417, 55, 6, 4, sig.SIG_F32, True),
+                                     (1235, 62, 6, 3, sig.SIG_F32, True), (298, 865, 4, 3, sig.SIG_F32, False), (162, 328, 8, 4, sig.SIG_F64, False), (584, 112, 4, 5, sig.SIG_F32, True),
+                                     (882, 335, 6, 4, sig.SIG_F32, True), (2626, 234, 4, 4, sig.SIG_F32, True), (50, 163, 4, 6, sig.SIG_F32, False)):
+        assert (w(B, L, d, N, 1, 0, dtype) == w(B, L, d, N, 0, 0, dtype)) == whole, (B, L, d, N, dtype)
 
 
 def test_lyndon_table_is_built_on_the_host(lib):
