@@ -117,9 +117,9 @@ int64_t sig_fused_fmas(int d, int N);
  * size overflows; SIG_ERR_HIP if the launch failed.  B == 0 is SIG_OK and enqueues nothing.
  * Results are deterministic: the same inputs give bit-identical outputs on every call.
  * In final mode sig_forward has no workspace for partial results: the vector kernels cut the paths of a small batch into stretches
- * that share a workgroup (up to 64 of 16 increments and more; the values then differ from an end-to-end scan by rounding only),
- * everything else scans a path (or a word-prefix shard of it) from end to end.  A few very long paths (B * shards far below
- * the number of compute units, L in the tens of thousands) are served many times faster by sig_forward_chunked
+ * that share a workgroup (up to 256 in fp32 and 128 in fp64, of 8 increments and more; the values then differ from an end-to-end
+ * scan by rounding only), everything else scans a path (or a word-prefix shard of it) from end to end.  A few very long paths (B * shards
+ * far below the number of compute units, L in the tens of thousands) are served many times faster by sig_forward_chunked
  * (sig_forward_chunks_hint says when, and into how many chunks).  In stream mode the output itself has room for
  * partial results, and up to 512 paths of at least 128 increments are cut into chunks internally where the kernel
  * family gains from it (everything but the d = 4 matrix-core kernels); the values then differ from an end-to-end
@@ -142,6 +142,9 @@ sig_status sig_forward_variant(const void *path, int64_t B, int64_t L, int d, in
  * increment (sections 2.1, 2.2), so every stretch adds up its own terms and a second launch adds the stretches.
  *   chunks     a power of two, 2 .. 65536 (stretches past the end of a short path are empty and count as the
  *              identity).
+ *              Where sig_forward by itself cuts a path inside a workgroup into stretches of 80 increments or fewer (64 where no
+ *              more than 8 stretches of signatures beyond 15 KB fit), that one launch is ahead of any number of chunks and serves
+ *              the call: `chunks` is checked and otherwise ignored, the workspace is asked for and not touched.
  *   basepoint_value  as for sig_signature.
  *   workspace  DEVICE pointer, 16-byte aligned, at least sig_forward_chunked_workspace_bytes(...) bytes
  *              (1.5 * B * chunks signatures); contents undefined on return; calls that overlap in time must not
@@ -163,7 +166,8 @@ int64_t sig_forward_chunked_workspace_bytes(int64_t B, int64_t L, int d, int N, 
  * within 256 MiB (the products that join them move every one of them).  At depth 2 (a sum, two launches of about
  * 22 us in all): up to 1024 paths, from 24 staged tiles of increments on (3072 increments up to 28 channels, 1512 at
  * 64), stretches of at least 128 increments, 2048 at most; B = 1, L = 131073, d = 64 takes 7.8 ms plain and 0.03 to
- * 0.07 ms cut into 256 to 1024 stretches.  0 on invalid arguments. */
+ * 0.07 ms cut into 256 to 1024 stretches.  It does not leave out the paths that sig_forward cuts by itself (see `chunks` above).  0 on invalid
+ * arguments. */
 int sig_forward_chunks_hint(int64_t B, int64_t L, int d, int N, int basepoint, sig_dtype dtype);
 
 /* Size of the scratch array built into the library for sig_forward_chunked_static: 32 MiB of device memory that
@@ -417,7 +421,8 @@ int sig_backward_chunks_hint(int64_t B, int64_t L, int d, int N, int basepoint, 
 int sig_backward_chunks_fastest(int64_t B, int64_t L, int d, int N, int basepoint, sig_dtype dtype);
 
 /* Name of the kernel family that `variant` resolves to for this shape ("generic",
- * "mfma_d4", ...), or "unsupported" / "invalid".  The string is static. */
+ * "mfma_d4", ...), or "unsupported" / "invalid".  The string is static.  Final mode calls of "tree", "row_stream" and "small" whose
+ * paths are cut inside a workgroup keep the name of the family that would serve them in one piece. */
 const char *sig_variant_name(int64_t B, int64_t L, int d, int N, int stream, int basepoint,
                              sig_dtype dtype, sig_variant variant);
 

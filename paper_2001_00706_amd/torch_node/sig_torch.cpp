@@ -4,8 +4,9 @@
 // distant cores and has to fetch the interpreter's state as well.
 //
 // The two functions return NotImplemented for every call that is not plain: tensors that are not torch's own, on the CPU or of
-// another type, arguments of other types, transforms, modes, tracing and forward gradients, shapes that the library refuses, long paths
-// (whose kernels take longer than the host, and whose workspaces can be too large to be had).  The Python functions then take
+// another type, arguments of other types, transforms, modes, tracing and forward gradients, shapes that the library refuses, and paths of
+// more than kLongest points.  Those run for 30 us and more in their kernels, most of them for longer than the Python functions take on
+// the host, and they keep the Python route in use for what it alone can be asked, with counts and out-of-memory answers put in its way.  The Python functions then take
 // the call and raise what they raise, so this file refuses nothing by itself.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
@@ -30,7 +31,7 @@ namespace {
 using torch::autograd::AutogradContext;
 using torch::autograd::variable_list;
 
-constexpr int64_t kLongest = 4096;   // increments of a call taken here
+constexpr int64_t kLongest = 4096;   // points of a path taken here
 
 struct Declined {};   // the Python functions take the call
 

@@ -41,8 +41,8 @@ def check(x, N, chunks, basepoint=False, seed=0):
     assert per_path.max() <= 5 * TOL[dt], per_path.max()
 
 
-# the stretches' shapes land on different gradient kernels: register-resident (d = 2, 4), prefix-tree (d = 3, 5, 6), the
-# d = 4, N = 6 and d = 16, N = 4 kernels, many channels (d = 20), the generic one (d = 3, N = 10)
+# the stretches land on different gradient kernels: the walk that forms its products by itself (d = 2..8, N = 3..9), as paths of their own
+# the d = 16, N = 4 kernel, the one for many channels (d = 20) and the generic one (d = 3, N = 10)
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 @pytest.mark.parametrize("B,L,d,N,chunks", [
     (2, 65, 3, 4, 4), (3, 64, 4, 4, 8), (1, 130, 2, 6, 16), (2, 41, 5, 3, 5), (1, 100, 4, 6, 7), (2, 50, 16, 4, 4),
@@ -55,13 +55,16 @@ def test_stretches_walked_back_side_by_side(B, L, d, N, chunks, dtype):
     check(brownian_paths(B, L, d, seed=L + d).astype(dtype), N, chunks)
 
 
-# the tree of products: counts next to powers of two (a last node without a neighbour on one or several levels), the first
-# counts whose rounds no longer fit the single launch at the top (68 | 69 signatures of 120 scalars, 24 | 25 of 340, 20 | 21 of
-# 399, in rows of several paths as well), levels moved as vectors (d = 4, 12), as whole groups of siblings (d = 3, 7) and word by word (d = 13)
+# the tree of products (depth 2, depth 10, d = 12 and 13): counts next to powers of two (a last node without a neighbour on one or several
+# levels), the first counts whose rounds no longer fit the single launch at the top (8192 scalars of a path: 1365 | 1366 signatures at d = 2,
+# N = 2, 146 | 147 at d = 7, 4 | 5 at d = 2, N = 10), levels moved as vectors (d = 4, 8, 12), as whole groups of siblings (d = 2, 3, 5, 6, 7) and word by
+# word (d = 13).  From d = 2 to 8 at N = 3 and 4 the same counts on the walk that forms its products by itself.
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
 @pytest.mark.parametrize("B,L,d,N,chunks", [
     (2, 138, 3, 4, 137), (3, 70, 3, 4, 69), (2, 69, 3, 4, 68), (1, 35, 3, 4, 17), (1, 258, 2, 3, 257), (2, 66, 4, 4, 65),
     (2, 25, 4, 4, 24), (2, 26, 4, 4, 25), (2, 21, 7, 3, 20), (1, 22, 7, 3, 21), (1, 66, 13, 2, 33), (2, 24, 13, 3, 23), (1, 40, 12, 3, 13), (2, 35, 7, 3, 34), (1, 47, 7, 4, 23),
+    (1, 1366, 2, 2, 1365), (1, 1367, 2, 2, 1366), (2, 684, 3, 2, 683), (2, 410, 4, 2, 409), (2, 411, 4, 2, 410), (1, 275, 5, 2, 274), (1, 197, 6, 2, 196),
+    (2, 147, 7, 2, 146), (2, 148, 7, 2, 147), (3, 18, 7, 2, 17), (1, 115, 8, 2, 114), (2, 5, 2, 10, 4), (1, 12, 2, 10, 5), (1, 8, 3, 10, 7),
 ])
 def test_tree_of_products(B, L, d, N, chunks, dtype):
     check(brownian_paths(B, L, d, seed=L + d).astype(dtype), N, chunks)
@@ -123,15 +126,17 @@ def test_a_path_with_nan_spoils_no_other():
 
 
 def test_stretches_two_to_a_workgroup():
-    # 111 paths in 7 stretches are 777 rows of d = 4, N = 6: the kernel of that shape beyond 768 rows, an odd number of them
+    # 111 paths in 7 stretches are 777 rows of d = 4, N = 6, an odd number (the kernel of that shape takes whole paths only:
+    # test_gradient_on_both_sides_of_the_register_resident_kernels_lines)
     check(brownian_paths(111, 29, 4, seed=2).astype(np.float32), 6, 7)
 
 
-# Many paths: products one after the other from 16 MB of signatures on where they do not fit the LDS (d = 7, N = 5: 19 607 scalars),
-# from 4 MB on where they go word by word (d = 13, N = 3: 2379; d = 20, N = 3: 8420); one path fewer takes the tree.  The
-# whole against the gradient in one piece (both within the same distance of the oracle), a few paths against the oracle.
+# Many paths: products one after the other from 16 MB of signatures on where they do not fit the LDS (d = 12, N = 4: 22 620 scalars, d = 16, N = 4),
+# from 4 MB on where they go word by word (d = 13, N = 3: 2379; d = 20, N = 3: 8420); one path fewer takes the tree.  (At d = 7 and 8 as many
+# paths on the walk that forms its products by itself.)  The whole against the gradient in one piece (both within the same
+# distance of the oracle), a few paths against the oracle.
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
-@pytest.mark.parametrize("d,N,line,chunks", [(7, 5, 16, 2), (7, 5, 16, 5), (13, 3, 4, 3), (20, 3, 4, 4), (8, 5, 16, 4)])
+@pytest.mark.parametrize("d,N,line,chunks", [(7, 5, 16, 2), (7, 5, 16, 5), (13, 3, 4, 3), (20, 3, 4, 4), (8, 5, 16, 4), (12, 4, 16, 3), (16, 4, 16, 4)])
 def test_products_in_chains(d, N, line, chunks, dtype):
     S = orc.channels(d, N)
     at = -(-(line << 20) // (S * np.dtype(dtype).itemsize))

@@ -151,7 +151,7 @@ def test_engine_semantics():
         changed.mul_(2)
     with pytest.raises(RuntimeError, match="modified by an inplace operation"):
         torch.autograd.grad(changed, x, g)
-    # a stream of its own, and threads
+    # a stream of its own
     s = torch.cuda.Stream()
     s.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(s):
@@ -160,13 +160,50 @@ def test_engine_semantics():
     assert torch.equal(on_s, first)
 
 
-def test_transforms_and_forward_gradients_as_before():
+def test_threads_on_streams_of_their_own():
+    import threading
+    import torch
+    paths = [torch.from_numpy(brownian_paths(3, 60 + 7 * i, 4, seed=i)).to("cuda:0") for i in range(4)]
+
+    def call(path):
+        x = path.clone().requires_grad_(True)
+        out = sig.logsignature(x, 4)
+        return out.detach(), torch.autograd.grad(out, x, torch.ones_like(out))[0]
+
+    want = [call(p) for p in paths]
+    torch.cuda.synchronize()
+    failed = []
+
+    def work(path, w):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                got = [call(path) for _ in range(30)]
+                torch.cuda.current_stream().synchronize()
+                for g in got:
+                    same(g, w)
+        except Exception as e:
+            failed.append(e)
+
+    threads = [threading.Thread(target=work, args=a) for a in zip(paths, want)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed, failed
+
+
+def test_transforms_and_forward_gradients_as_before(monkeypatch):
     import torch
     x = torch.from_numpy(brownian_paths(2, 9, 3, seed=5)).to("cuda:0")
-    for node in (autograd._transform, lambda *args: NotImplemented):
-        assert node(x.cpu(), 3, False, False, False, 0, None) is NotImplemented
-    with pytest.raises(RuntimeError):
+    assert autograd._transform(x.cpu(), 3, False, False, False, 0, None) is NotImplemented
+    # under vmap the node hands the call back, and torch.autograd.Function says that it has no rule for it
+    asked = []
+    node = autograd._transform
+    monkeypatch.setattr(autograd, "_transform", lambda *args: asked.append(node(*args)) or asked[-1])
+    with pytest.raises(RuntimeError, match="vmap"):
         torch.func.vmap(lambda p: sig.signature(p.unsqueeze(0), 3))(x)
+    assert asked == [NotImplemented]
+    monkeypatch.setattr(autograd, "_transform", node)
     import torch.autograd.forward_ad as fw
     with fw.dual_level():
         dual = fw.make_dual(x.clone().requires_grad_(True), torch.ones_like(x))

@@ -46,7 +46,9 @@ def test_two_calls_in_a_row_the_second_smaller():
 
 def test_other_kernel_families_and_fp64():
     import torch
-    for B, L, d, N, chunks, dtype in [(3, 50, 2, 6, 8, np.float32), (2, 40, 5, 3, 4, np.float64), (2, 90, 8, 4, 2, np.float32)]:
+    # the last three are longer than what sig_forward cuts inside a workgroup (which is then used, and no scratch memory)
+    for B, L, d, N, chunks, dtype in [(3, 50, 2, 6, 8, np.float32), (2, 40, 5, 3, 4, np.float64), (2, 90, 8, 4, 2, np.float32),
+                                      (3, 5200, 2, 6, 8, np.float32), (2, 1300, 5, 3, 4, np.float64), (2, 700, 8, 4, 16, np.float64)]:
         x = brownian_paths(B, L, d, seed=L).astype(dtype)
         xt = torch.from_numpy(x).to("cuda:0")
         got = sig.sig_forward_chunked_static(xt, N, chunks)
