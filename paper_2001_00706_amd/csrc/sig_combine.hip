@@ -107,11 +107,12 @@ struct IntervalGrid {
 constexpr int interval_first(int d) { return d == 2 ? 4 : d == 3 ? 3 : d <= 8 ? 2 : 1; }
 constexpr int interval_last(int d) { return d == 2 ? 3 : d == 3 ? 2 : d <= 8 ? 1 : 0; }
 
-// The `digits` digits of v in reverse.
+// The `digits` digits of v in reverse; UNROLL: at most so many of them, or 1 where they are a run-time value.
+template <int UNROLL>
 __device__ __forceinline__ uint32_t reversed_word(uint32_t v, int digits, uint32_t d)
 {
     uint32_t r = 0;
-#pragma unroll
+#pragma unroll(UNROLL)
     for (int i = 0; i < digits; ++i) {
         const uint32_t q = v / d;
         r = r * d + (v - q * d);
@@ -125,6 +126,7 @@ template <typename T, int D, int W, int K>
 __device__ __forceinline__ void interval_words(const Shape &sh, const IntervalGrid &grid, int k_runtime, uint32_t t, const T *a, const T *b, T *out)
 {
     const uint32_t d = D > 0 ? uint32_t(D) : uint32_t(sh.d);
+    constexpr int kUnroll = K > 0 ? K : 1;
     const int k = K > 0 ? K : k_runtime, letters = k - 1;
     const auto pw = [&](int j) {
         if constexpr (D > 0 && K > 0) {
@@ -146,8 +148,8 @@ __device__ __forceinline__ void interval_words(const Shape &sh, const IntervalGr
     const uint32_t v = t % pw(E);
     t /= pw(E);
     const uint32_t u_rev = t % pw(F), m = t / pw(F);
-    const uint32_t prefix = reversed_word(u_rev, F, d) * pw(letters - F) + m * pw(E) + v;
-    const uint32_t rev = reversed_word(v, E, d) * pw(letters - E) + reversed_word(m, letters - F - E, d) * pw(F) + u_rev;
+    const uint32_t prefix = reversed_word<kUnroll>(u_rev, F, d) * pw(letters - F) + m * pw(E) + v;
+    const uint32_t rev = reversed_word<kUnroll>(v, E, d) * pw(letters - E) + reversed_word<kUnroll>(m, letters - F - E, d) * pw(F) + u_rev;
     // the words of the prefix, moved as a vector unless some are missing
     typedef Siblings<T, W> V;
     const bool whole_v = W == D || c0 + W <= d;
@@ -169,7 +171,7 @@ __device__ __forceinline__ void interval_words(const Shape &sh, const IntervalGr
         }
         acc = own + acc;
     }
-#pragma unroll
+#pragma unroll(kUnroll)
     for (int j = letters; j >= 1; --j) {
         const T x = a[off(j) + rev % pw(j)];
         acc += (j & 1 ? -x : x) * words(b + off(k - j) + prefix % pw(letters - j) * d);

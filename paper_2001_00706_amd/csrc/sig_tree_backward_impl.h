@@ -168,7 +168,9 @@ __device__ __forceinline__ ChunkView stretch_view(uint32_t row, const Shape &sh)
 }
 
 // Wavefronts per SIMD the walk over stretches must leave room for: what it has for whole paths.  The products ahead of it would
-// otherwise take registers (addresses of every suffix) that halve what is in flight through the whole walk.
+// otherwise take registers (addresses of every suffix) that halve what is in flight through the whole walk.  Without | with: 64 x 400
+// points, d = 3, N = 8 175 | 140 us, 1 x 4000, d = 7, N = 6, fp64 535 | 415, 400 x 200, d = 7, N = 4, fp64 132 | 108, 1 x 4000, d = 4, N = 8, fp64 357 | 319,
+// 400 x 200, d = 2, N = 9 105 | 92; 160 other shapes within 3 %, but for d = 8, N = 4, which waits for spills (400 x 200 70 | 78).
 constexpr int tb_stretch_waves(int elem, int d, int N)
 {
     if (elem == 8) return d <= 6 || (d == 7 && N >= 4 && N <= 6) ? 2 : 1;

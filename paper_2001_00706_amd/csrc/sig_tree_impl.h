@@ -186,7 +186,7 @@ sig_tree_kernel(Shape sh, const T *__restrict__ path, T *__restrict__ out)
             // itself the compiler moves each next to its use where that saves registers, a wait per letter: 64 paths of 100
             // points at d = 2, N = 8 37.8 -> 24 us, d = 3, N = 8 40 -> 26.5, d = 5, N = 6 36 -> 26).  With seven channels
             // arithmetic may still move up between the reads, whose registers are the ones that run out first there (without that,
-            // N = 5: 1.06 to 1.08 times the time from 384 paths on; other depths and batches within 2 %).
+            // N = 5: 1.06 to 1.08 times the time from 384 paths on, 4 x 400 points at N = 7 1.05; other depths and batches within 3 %).
             T zl[P + 1], zu[D];
 #pragma unroll
             for (int i = 1; i <= P; ++i) zl[i] = zrow[cl[i]];

@@ -36,7 +36,8 @@ template <typename T, int D, int N, int U>
 __device__ __forceinline__ void split_increment(const T *zrow, const int *cl, const T *rk, T *A, T *B1, T *B2)
 {
     constexpr int P = N - U;
-    // every read is issued before the first is used, as there
+    // every read is issued before the first is used, as there (and with the same exception; in this kernel d = 7 is 0 to 5 % behind with it,
+    // 4 x 400 points, N = 4 20.0 us against 19.0)
     T zl[P + 1], zu[D];
 #pragma unroll
     for (int i = 1; i <= P; ++i) zl[i] = zrow[cl[i]];
