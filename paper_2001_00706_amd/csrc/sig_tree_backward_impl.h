@@ -841,7 +841,8 @@ sig_stream_carry_kernel(Shape sh, const T *__restrict__ path, const T *__restric
 #pragma unroll
         for (int c = 0; c < D * D; ++c) G.h2[c] += o.h2[c];
     };
-    const int m = int(sh.chunk_len), from = mine.inc0 < 0 ? int(-mine.inc0) : 0;   // increments from .. m - 1 are the path's
+    // the steps are those of increments from .. m - 1: none for the first stretch of a path, whose share no other begins from
+    const int m = int(sh.chunk_len), from = mine.inc0 <= 0 ? int(sh.chunk_len) : 0;
     const T *bpv = static_cast<const T *>(sh.basepoint_value);
     Share G = load(go + int64_t(m - 1) * kS);
     const int last_tile = (m - 1) / kTbTile * kTbTile;
@@ -897,7 +898,7 @@ sig_stream_carry_kernel(Shape sh, const T *__restrict__ path, const T *__restric
             if (more) add(G, ahead);
         }
     }
-    if (live) {
+    if (live && mine.inc0 > 0) {
         T *o = carried + row * kParts * kWords + u;
 #pragma unroll
         for (int i = 1; i <= P; ++i) o[(i - 1) * kWords] = G.lo[i];
