@@ -586,6 +586,7 @@ static int tree_stretches_fastest(int64_t B, const sig::Shape &sh, sig_dtype dty
     const double back = 3 * d * d + 10 * d + 32 * letters, ahead = d * d + 3 * d + 5 * sh.N;   // instructions of an increment
     const double product = letters * (d * d + 2 * d) * (wide ? 1.72 : 1.0) * (sh.d == 8 && sh.N >= 4 ? 2.28 : 1.0);
     const int64_t single = double(sh.off[sh.N]) * 16 * 4 * elem <= 48000 ? 16 : 8;   // nodes without a level above them
+    const bool whole_in_tiles = !wide && sig::tile_backward_preferred(sh);
     const auto either = [](double a, double b) { return std::cbrt(a * a * a + b * b * b); };
     const auto time = [&](int64_t K) {
         const int64_t m = (sh.n_inc + K - 1) / K, rows = B * ((sh.n_inc + m - 1) / m);
@@ -594,7 +595,7 @@ static int tree_stretches_fastest(int64_t B, const sig::Shape &sh, sig_dtype dty
         const double row_waves = words > 256 && words < 512 ? 8 : std::ceil(words / 64);
         const double waves = (words > 64 ? double(rows) * row_waves : 4 * std::ceil(double(rows) / per_group)) / 1024;
         const double walk = either(2.16e-3 * back * (wide ? 1.26 : 1.0), 1.03e-3 * back * waves * f64);
-        if (K == 1) return 7 + double(sh.n_inc) * walk;
+        if (K == 1) return whole_in_tiles ? sig::tile_backward_us(sh) : 7 + double(sh.n_inc) * walk;
         int64_t nodes = (sh.n_inc + m - 1) / m, steps = -1;
         double t = 12.5 + 12.3e-6 * double(rows) * words * d * elem;
         for (; nodes > single; nodes = (nodes + 7) / 8) {
@@ -611,7 +612,7 @@ static int tree_stretches_fastest(int64_t B, const sig::Shape &sh, sig_dtype dty
     // up to 40 us in one piece the host takes as long for the launches of either, and it has to gain something
     double best = time(1);
     if (best < 40) return 1;
-    best = 0.95 * best - 2;
+    if (!whole_in_tiles) best = 0.95 * best - 2;
     int chunks = 1;
     for (int64_t K = 2; K <= 65536 && sh.n_inc / K >= (K <= 16 ? 8 : 16); K *= 2) {
         const double t = time(K);
@@ -670,7 +671,14 @@ int sig_backward_chunks_fastest(int64_t B, int64_t L, int d, int N, int basepoin
     const double round = sh.S <= 512 ? 4.5 : 10.5;
     const auto walk = [&](int64_t K) {
         const auto shared = [&](double t) { return double(B) * double(K) * t > room ? double(B) * double(K) * t / room : 1.0; };
-        return double(sh.n_inc) / double(K) * (step * shared(threads) + (K > 1 ? forward * shared(forward_threads) : 0));
+        double back = double(sh.n_inc) / double(K) * step * shared(threads);
+        if (dtype == SIG_F32) {   // paths or stretches that are walked sixteen increments at a time
+            sig::Shape rows = sh;
+            rows.B = B * K;
+            rows.n_inc = (sh.n_inc + K - 1) / K;
+            if (sig::tile_backward_preferred(rows)) back = sig::tile_backward_us(rows);
+        }
+        return back + (K > 1 ? double(sh.n_inc) / double(K) * forward * shared(forward_threads) : 0);
     };
     // a call in stretches is a dozen launches and more instead of two: it has to gain that much on the host as well
     double best = walk(1) - 40, joined = 24;

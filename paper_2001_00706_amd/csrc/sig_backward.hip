@@ -404,6 +404,10 @@ int64_t backward_workspace_bytes(const Shape &sh, sig_dtype dtype)
     const StreamStretches cut = stream_stretches(sh, dtype);
     if (cut.K > 1) return cut.bytes;
     // signatures of up to 8 channels and depth 9 never reach the generic kernel
+    if (dtype == SIG_F32 && tile_backward_preferred(sh)) {   // at least what the prefix-tree kernels would take: streams kept whole report the same
+        const int64_t tree = sh.d <= 8 ? tree_backward_workspace_bytes(sh, dtype) : 0, tile = tile_backward_workspace_bytes(sh);
+        return tree > tile ? tree : tile;
+    }
     if (backward_n2_supported(sh, dtype)) return 0;   // depth 2 in final mode: a closed form, nothing to keep
     if (wide_backward_preferred(sh, dtype)) return wide_backward_workspace_bytes(sh, dtype);
     if (tree_backward_supported(sh)) return tree_backward_workspace_bytes(sh, dtype);
@@ -423,6 +427,9 @@ hipError_t launch_backward_f32(const Shape &sh, const float *path, const float *
     // points: d = 16: 14.5 us against 24, d = 64: 50 against 192, d = 100: 136 against 665)
     if (backward_n2_mfma_supported(sh)) return launch_backward_n2_mfma_f32(sh, path, gout, gpath, gbase, st);
     if (backward_n2_supported(sh, SIG_F32)) return launch_backward_n2_f32(sh, path, gout, gpath, gbase, st);
+    // sixteen increments at a time from depth 4 on, with the two deepest levels on the matrix cores
+    if (tile_backward_preferred(sh))
+        return launch_tile_backward_f32(sh, path, sig, gout, gpath, gbase, workspace, workspace_bytes, st);
     const bool aligned = (reinterpret_cast<uintptr_t>(path) | reinterpret_cast<uintptr_t>(sig) |
                           reinterpret_cast<uintptr_t>(gout) | reinterpret_cast<uintptr_t>(sh.basepoint_value)) % 16 == 0;
     // d = 4, N = 6 in final mode from four paths per compute unit on: the top level's cotangent in registers, two wavefronts

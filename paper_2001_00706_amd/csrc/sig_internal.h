@@ -246,6 +246,14 @@ hipError_t launch_backward_n2_f64(const Shape &sh, const double *path, const dou
 template <typename T>
 hipError_t launch_increment_sums(const Shape &sh, int64_t n_partials, const T *partial, T *gpath, T *gbase, hipStream_t st);
 
+// Gradient kernels that take sixteen increments at a time, the two deepest levels on the matrix cores (fp32, final mode, d = 3..8 at
+// N = 4..8, d = 9..16 at N = 4..6, any alignment; see sig_tile_backward_impl.h).  The workspace holds partial gradients per increment.
+bool tile_backward_preferred(const Shape &sh);
+double tile_backward_us(const Shape &sh);   // about how long a call takes
+int64_t tile_backward_workspace_bytes(const Shape &sh);
+hipError_t launch_tile_backward_f32(const Shape &sh, const float *path, const float *sig, const float *gout, float *gpath, float *gbase,
+                                    void *workspace, int64_t workspace_bytes, hipStream_t st);
+
 // Prefix-tree gradient kernels (d = 2..8 at N = 2..9, d = 9..16 at N = 2..6, any alignment): no communication between threads; the
 // per-increment partial gradients go to a workspace of `tree_backward_workspace_bytes` and are summed by a second
 // kernel.

@@ -1,0 +1,98 @@
+// Which calls the tile gradient kernels serve (see sig_tile_backward_impl.h; instantiated per channel count in the files beside this one).
+#include "sig_internal.h"
+
+#include <cmath>
+#include <type_traits>
+
+namespace sig {
+
+template <int D>
+hipError_t launch_tile_backward_d(const Shape &sh, const float *path, const float *sig, const float *gout, float *gpath, float *gbase,
+                                  float *partial, hipStream_t st);
+template <int D>
+int tile_groups_d(int64_t B, int N);
+
+namespace {
+
+// f of the channel count as a constant, 3 to 16
+template <typename F>
+auto with_channels(int d, F f)
+{
+    switch (d) {
+        case 3: return f(std::integral_constant<int, 3>{});
+        case 4: return f(std::integral_constant<int, 4>{});
+        case 5: return f(std::integral_constant<int, 5>{});
+        case 6: return f(std::integral_constant<int, 6>{});
+        case 7: return f(std::integral_constant<int, 7>{});
+        case 8: return f(std::integral_constant<int, 8>{});
+        case 9: return f(std::integral_constant<int, 9>{});
+        case 10: return f(std::integral_constant<int, 10>{});
+        case 11: return f(std::integral_constant<int, 11>{});
+        case 12: return f(std::integral_constant<int, 12>{});
+        case 13: return f(std::integral_constant<int, 13>{});
+        case 14: return f(std::integral_constant<int, 14>{});
+        case 15: return f(std::integral_constant<int, 15>{});
+        default: return f(std::integral_constant<int, 16>{});
+    }
+}
+
+int groups(const Shape &sh)
+{
+    if (sh.d < 3 || sh.d > 16) return 0;
+    return with_channels(sh.d, [&](auto d) { return tile_groups_d<decltype(d)::value>(sh.B, sh.N); });
+}
+
+}  // namespace
+
+// Microseconds of a call, fitted to 650 shapes of 1 to 4000 paths of 17 to 1100 points (off by 4 % in the mean where the chip is full): a
+// tile takes a lone wavefront 0.9 to 2.0, and a SIMD that holds two or three of them c; before the first one the matrices are cut into
+// pieces, s.  The products grow with the letters of a wavefront, the chains with the depth.
+double tile_backward_us(const Shape &sh)
+{
+    const double tiles = double((sh.n_inc + 15) / 16);
+    const double prefixes = double(sh.pw[sh.N - 3]), per_block = sh.d <= 4 ? 4 : sh.d <= 8 ? 2 : 0.5;   // of a wavefront
+    const double waves = double(sh.B) * std::ceil(prefixes / per_block) / 1024;
+    const double alone = sh.d <= 4 ? (sh.N >= 5 ? 1.15 : 1.0) : sh.d <= 8 ? (sh.N >= 5 ? 1.75 : 1.55) : (sh.N >= 5 ? 2.3 : 2.0);
+    const double s = sh.d <= 4 ? 0.8 : sh.d <= 8 ? 3.0 : 2.4;
+    const double c = sh.d <= 4   ? 0.75 + 0.07 * (sh.N - 6)
+                     : sh.d <= 8 ? 1.2 + 0.05 * (sh.d - 6.5) + 0.05 * (sh.N - 6)
+                                 : 0.48 + 0.153 * ((sh.d + 1) / 2) + 0.16 * (sh.N - 4);
+    return 9 + std::cbrt(std::pow(tiles * alone, 3.0) + std::pow(waves * (s + tiles * c), 3.0));
+}
+
+// Where they are used: from 24 increments on (fewer leave most of a tile, or of the time to set it up, unused), and where the prefix-tree
+// kernels take longer.  Those wait 0.4 us for an increment as long as the chip is not full; once it is, they take ct for an increment of 64
+// words.  At 9 channels and more that is longer from 32 increments on, up to a few channels only while few paths leave the chip idle: a block of sixteen
+// words has room for 10 at 5 channels, 12 at 6, and three wavefronts in four would multiply zeros (tile | before, us: 256 x 100 points, d = 6,
+// N = 4: 18 | 53; 64 x 200, d = 8, N = 5: 40 | 154; 256 x 1024, d = 16, N = 4: 770 | 1265; 1 x 1000, d = 13, N = 4: 128 | 985; 32 x 128,
+// d = N = 7: 485 | 505; against the rule 648 x 80, d = 5, N = 6: 320 | 187).  Over 650 shapes of 3 to 16 channels the rule is 1.3 % off the better one of the
+// two, and takes 0.60 of the time without these kernels.
+bool tile_backward_preferred(const Shape &sh)
+{
+    if (sh.stream || sh.n_inc < 24 || sh.S >= (int64_t(1) << 31) || groups(sh) == 0) return false;
+    // (d = 16, N = 4 has sig_backward_d16.hip for short paths: 256 x 31 points 60 | 52, 64 x 17 16 | 30)
+    if (sh.d == 16 && sh.N == 4) return sh.n_inc >= 48 || sh.B <= 64;
+    if (sh.d > 8) return sh.n_inc >= 32 || sh.B * sh.pw[sh.N - 3] <= 512;
+    // at d = 4, N = 6 many paths have a kernel of their own, sig_backward_d4n6.hip
+    const double ct = sh.d <= 4 ? (sh.N == 6 && sh.d == 4 && sh.B > 768 ? 0.19 : 0.27)
+                                : sh.d == 5 ? 0.33 : sh.d == 6 ? 0.37 : sh.d == 7 ? 0.47 : 0.44;
+    const double n = double(sh.n_inc), tree = std::fmax(0.4 * n, double(sh.B) * double(sh.pw[sh.N - 2]) / 65536 * n * ct);
+    return tile_backward_us(sh) - 9 <= tree;
+}
+
+int64_t tile_backward_workspace_bytes(const Shape &sh) 
+{
+    return sh.B * groups(sh) * sh.n_inc * sh.d * int64_t(sizeof(float));
+}
+
+hipError_t launch_tile_backward_f32(const Shape &sh, const float *path, const float *sig, const float *gout, float *gpath, float *gbase,
+                                    void *workspace, int64_t workspace_bytes, hipStream_t st)
+{
+    if (workspace == nullptr || workspace_bytes < tile_backward_workspace_bytes(sh)) return hipErrorInvalidValue;
+    float *partial = static_cast<float *>(workspace);
+    return with_channels(sh.d, [&](auto d) {
+        return launch_tile_backward_d<decltype(d)::value>(sh, path, sig, gout, gpath, gbase, partial, st);
+    });
+}
+
+}  // namespace sig
