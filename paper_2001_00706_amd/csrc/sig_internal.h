@@ -138,6 +138,14 @@ hipError_t launch_log_backward_f32(const Shape &sh, const float *sig, const floa
                                    hipStream_t st);
 hipError_t launch_log_backward_f64(const Shape &sh, const double *sig, const double *grad_log, double *grad_sig, void *workspace,
                                    hipStream_t st);
+// The same in one launch, a workgroup per signature, where an element fits the LDS (see sig_log_backward_local.hip): whole signatures
+// (hipErrorNotSupported, with nothing enqueued, where there is no kernel), and the steps from the one on whose cotangent g has
+// log_backward_local_levels(d) levels (0: none), r holding the R with 1, 2, .. levels.
+int log_backward_local_levels(int d);
+template <typename T>
+hipError_t launch_log_backward_whole(const Shape &sh, const T *x, const T *g, T *gx, hipStream_t st);
+template <typename T>
+hipError_t launch_log_backward_tail(const Shape &sh, const T *x, const T *r, int64_t r_stride, const T *g, int64_t g_stride, T *gx, hipStream_t st);
 // Gradient of the group product out = a [x] b; workspace: combine_backward_workspace_bytes.
 hipError_t launch_combine_backward_f32(const Shape &sh, const float *a, const float *b, const float *g, float *ga, float *gb,
                                        void *workspace, hipStream_t st);

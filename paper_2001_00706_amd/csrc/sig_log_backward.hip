@@ -1042,6 +1042,8 @@ hipError_t launch_log_backward(const Shape &sh, const T *x, const T *g, T *gx, v
     if (N == 1) return hipMemcpyAsync(gx, g, size_t(sh.B * sh.S) * sizeof(T), hipMemcpyDeviceToDevice, st);
     const LbWorkspace ws = plan_workspace(sh, int64_t(sizeof(T)));
     if (use_gather(sh, ws, sizeof(T))) return launch_gather<T>(sh, gather_lds_bytes(sh, ws, sizeof(T)), x, g, gx, st);
+    const hipError_t whole = launch_log_backward_whole<T>(sh, x, g, gx, st);
+    if (whole != hipErrorNotSupported) return whole;
     if (use_fused(sh, ws, sizeof(T))) {
         // With two signatures a compute unit or fewer, 512 threads for more than 768 scalars: what the kernel waits for is the chain of
         // passes between its barriers, of which there are half as many (256 | 512 | 1024 threads, 256 signatures: d = 6, N = 4 25.6 | 21.1 | 21.1 us,
@@ -1088,9 +1090,12 @@ hipError_t launch_log_backward(const Shape &sh, const T *x, const T *g, T *gx, v
             if (err != hipSuccess) return err;
         }
     }
+    const int local = N <= kDirectMaxDepth ? log_backward_local_levels(sh.d) : 0;
     for (int m = 1; m <= N - 1; ++m) {
-        const LbStep stp = plan_step(sh, N - m + 1);
         const T *G = m == 1 ? g : Gb[m & 1];
+        // from here on the elements fit the LDS: R_N, which has one level, comes first in the workspace
+        if (m > 1 && N - m + 1 == local) return launch_log_backward_tail<T>(sh, x, Rs, ws.r_stride, G, ws.g_stride, gx, st);
+        const LbStep stp = plan_step(sh, N - m + 1);
         const hipError_t err =
             launch_step_any<T>(stp, sh.B, x, int64_t(sh.S), int64_t(1), G, int64_t(m == 1 ? sh.S : ws.g_stride),
                                static_cast<const T *>(Rs + r_offset(sh, m + 1)), int64_t(ws.r_stride), apart, bpart, T(coef(m)), T(coef(N)),

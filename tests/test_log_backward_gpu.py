@@ -278,3 +278,20 @@ def test_threads_that_launch_one_kernel_with_different_lds():
     for t in threads:
         t.join()
     assert not failed, failed
+
+
+# a workgroup per signature with everything in LDS: every depth of the odd channel counts that have such a kernel, and the last steps of
+# signatures too large for it (their first steps go by the matrices); few and many rows
+@pytest.mark.parametrize("dtype", [np.float32, np.float64], ids=["float32", "float64"])
+@pytest.mark.parametrize("rows,d,N", [(3, 3, 3), (300, 3, 4), (2, 3, 5), (3, 3, 6), (300, 3, 7), (3, 3, 8), (2, 3, 9), (300, 5, 3), (3, 5, 4), (300, 5, 5),
+                                      (2, 5, 6), (2, 5, 7), (3, 6, 3), (300, 6, 4), (3, 6, 5), (2, 6, 6), (300, 7, 3), (3, 7, 4), (2, 7, 5),
+                                      (2, 4, 7), (2, 4, 8), (2, 8, 5), (2, 8, 6)] + [(3, d, 3) for d in range(9, 17)] +
+                         [(2, 9, 4), (300, 11, 4), (2, 16, 4), (2, 9, 5)])
+def test_elements_in_lds(rows, d, N, dtype):
+    x = orc.signature(1.3 * brownian_paths(rows, 7, d, seed=rows + d + N), N).astype(dtype)
+    g = np.random.default_rng(rows + N).standard_normal(x.shape).astype(dtype)
+    got = host(sig.sig_log_backward(dev(x), dev(g), d, N))
+    some = np.arange(0, rows, 37)
+    want = orc.tensor_log_backward(x[some], g[some], d, N)
+    scale = orc.tensor_log_backward(-np.abs(x[some].astype(np.float64)), np.abs(g[some].astype(np.float64)), d, N)
+    assert_grad_close(got[some], want, scale, d, N, dtype)
