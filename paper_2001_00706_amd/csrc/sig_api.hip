@@ -283,6 +283,9 @@ hipError_t launch_auto(Family family, const sig::Shape &sh, sig_dtype dtype, con
                 : sig::launch_tree_split_f64(sh, static_cast<const double *>(path), static_cast<double *>(out), hip_stream);
         if (err != hipErrorNotSupported) return err;
     }
+    // ... and where they do not, sixteen increments at a time go to the matrix cores (sig_tile_forward.hip says when that pays)
+    if (family == Family::Tree && dtype == SIG_F32 && sig::tile_forward_preferred(sh))
+        return sig::launch_tile_forward_f32(sh, static_cast<const float *>(path), static_cast<float *>(out), hip_stream);
     return launch_family(family, sh, dtype, path, out, hip_stream);
 }
 

@@ -1,0 +1,71 @@
+"""The signature kernels that take sixteen increments at a time (sig_tile_forward_impl.h), where they can go wrong: paths that end inside a
+tile or a span of tiles, channel counts that leave rows of a result without a word, a last workgroup with few wavefronts.
+
+Against the oracle, level by level.  Operands are cut into pieces exactly and products of less than 2^-24 of a term are left out; what adds up
+are the roundings of some n / 16 sums per entry, 2^-24 sqrt(n) of a level's largest terms.  5e-6 is ten times that for 300 increments, and is
+below what one lost increment of a path of 300 does to a level (1 / sqrt(300))."""
+import numpy as np
+import pytest
+
+import paper_2001_00706_amd as sig
+from oracle import sig_oracle as orc
+from paper_2001_00706_amd.inputs import brownian_paths
+
+pytestmark = pytest.mark.gpu
+
+TOL = 5e-6
+
+
+def check(B, L, d, N, basepoint="none", sample=None):
+    import torch
+    x = brownian_paths(B, L, d, seed=L + d) + np.float32(0.25)
+    some = np.arange(B) if sample is None else np.asarray(sample)
+    bp = {"none": None, "origin": True, "point": brownian_paths(B, 2, d, seed=7)[:, 1]}[basepoint]
+    xt = torch.from_numpy(x).to("cuda:0")
+    bt = torch.from_numpy(bp).to("cuda:0") if basepoint == "point" else bool(bp)
+    out = torch.full((B, orc.channels(d, N)), float("nan"), device="cuda:0")
+    sig.sig_signature(xt, N, basepoint=bt, out=out)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    assert np.all(np.isfinite(got)), "signature not fully written"
+    xs = x[some].astype(np.float64)
+    if basepoint == "point":
+        xs = np.concatenate([bp[some][:, None].astype(np.float64), xs], axis=1)
+    want = orc.signature(xs, N, False, basepoint == "origin")
+    at = 0
+    for k in range(1, N + 1):
+        a, b = got[some, at:at + d ** k], want[:, at:at + d ** k]
+        at += d ** k
+        assert np.linalg.norm(a - b) <= TOL * np.linalg.norm(b), k
+
+
+@pytest.mark.parametrize("L", [33, 34, 48, 49, 50, 64, 65, 66, 129, 300])
+@pytest.mark.parametrize("d,N", [(5, 6), (7, 5), (9, 5)])
+def test_lengths(L, d, N):
+    check(3, L, d, N)
+
+
+@pytest.mark.parametrize("basepoint", ["none", "origin", "point"])
+@pytest.mark.parametrize("d,N", [(5, 6), (5, 7), (6, 6), (7, 5), (7, 6), (8, 6), (9, 5), (10, 5), (11, 5), (9, 6)])
+def test_channels_and_depths(d, N, basepoint):
+    check(2, 43, d, N, basepoint)
+
+
+@pytest.mark.parametrize("B,L,d,N", [(40, 101, d, 4) for d in (9, 10, 11)] + [(90, 101, d, 4) for d in range(12, 17)]
+                         + [(8, 40, d, 5) for d in range(12, 17)])   # enough wavefronts for twelve channels and more
+def test_wide(B, L, d, N):
+    check(B, L, d, N, "origin", sample=[0, 1, B - 1])
+
+
+@pytest.mark.parametrize("d,N", [(5, 8), (6, 7), (7, 7), (8, 7), (6, 8), (12, 6)])
+def test_large_signatures(d, N):
+    check(1, 40, d, N, "point")
+
+
+def test_a_point_that_is_not_a_number_stays_in_its_words():
+    import torch
+    x = torch.from_numpy(brownian_paths(1, 60, 7, seed=3)).to("cuda:0")
+    x[0, 20, 6] = float("nan")
+    s = sig.sig_signature(x, 5)[0].cpu().numpy()
+    last = s[-7 ** 5:].reshape((7,) * 5)
+    assert np.all(np.isfinite(last[:6, :6, :6, :6, :6])) and np.isnan(last[6, 0, 0, 0, 0]) and np.isnan(last[0, 0, 0, 0, 6])
