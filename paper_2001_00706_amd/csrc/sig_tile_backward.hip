@@ -57,7 +57,9 @@ double tile_backward_us(const Shape &sh)
     const double c = sh.d <= 4   ? 0.75 + 0.07 * (sh.N - 6)
                      : sh.d <= 8 ? 1.2 + 0.05 * (sh.d - 6.5) + 0.05 * (sh.N - 6)
                                  : 0.48 + 0.153 * ((sh.d + 1) / 2) + 0.16 * (sh.N - 4);
-    return 9 + std::cbrt(std::pow(tiles * alone, 3.0) + std::pow(waves * (s + tiles * c), 3.0));
+    // from depth 5 on a path is gone through forward first, unless its signature was formed in the same tiles (0.87 to 0.89 of the time)
+    const double way = sh.N >= 5 && tile_forward_certain(sh) ? 0.9 : 1.0;
+    return 9 + std::cbrt(std::pow(tiles * alone * way, 3.0) + std::pow(waves * (s + tiles * c * way), 3.0));
 }
 
 // Where they are used: from 24 increments on (fewer leave most of a tile, or of the time to set it up, unused), and where the prefix-tree
@@ -65,7 +67,7 @@ double tile_backward_us(const Shape &sh)
 // words.  At 9 channels and more that is longer from 32 increments on, up to a few channels only while few paths leave the chip idle: a block of sixteen
 // words has room for 10 at 5 channels, 12 at 6, and three wavefronts in four would multiply zeros (tile | before, us: 256 x 100 points, d = 6,
 // N = 4: 18 | 53; 64 x 200, d = 8, N = 5: 40 | 154; 256 x 1024, d = 16, N = 4: 770 | 1265; 1 x 1000, d = 13, N = 4: 128 | 985; 32 x 128,
-// d = N = 7: 485 | 505; against the rule 648 x 80, d = 5, N = 6: 320 | 187).  Over 650 shapes of 3 to 16 channels the rule is 1.3 % off the better one of the
+// d = N = 7: 447 | 505; against the rule 648 x 80, d = 5, N = 6: 320 | 187).  Over 650 shapes of 3 to 16 channels the rule is 1.3 % off the better one of the
 // two, and takes 0.60 of the time without these kernels.
 bool tile_backward_preferred(const Shape &sh)
 {

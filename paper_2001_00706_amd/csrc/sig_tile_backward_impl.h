@@ -34,6 +34,8 @@
 // The signature handed in carries the rounding of the scan that made it; walked back by other sums it does not end at zero, and the
 // first points' gradients are off by what is left.  From depth 5 on the levels up to N - 2 are therefore formed anew ahead of the walk, by the
 // same sums (a tenth of the time; 8 paths of 128 points, d = 4, N = 8: off by 3.2e-6 without, 1.35e-6 with, 1.62e-6 on the prefix-tree kernels).
+// Where sig_tile_forward_impl.h makes the signature these are the sums it was made by, and nothing is gained by forming them again: the gradients are
+// the same bits (32 x 128 points, d = N = 7: 513 us with, 447 without; 100 x 900, d = 9, N = 5 1375 | 1195).
 #ifndef SIG_TILE_BACKWARD_IMPL_H_
 #define SIG_TILE_BACKWARD_IMPL_H_
 
@@ -74,7 +76,7 @@ struct TileShape {
 
 // One block per wavefront, over the whole path.
 template <int D, int N, bool IDENTITY>
-__device__ __forceinline__ void tl_walk(const Shape &sh, int groups, int rounds, int round, int tid, float *lds, const float *path,
+__device__ __forceinline__ void tl_walk(const Shape &sh, int groups, int rounds, bool anew, int round, int tid, float *lds, const float *path,
                                         const float *sig, const float *gout, float *partial)
 {
     using TS = TileShape<D, N>;
@@ -354,7 +356,7 @@ __device__ __forceinline__ void tl_walk(const Shape &sh, int groups, int rounds,
         }
     }
 
-    if constexpr (IDENTITY && N >= kTlForwardFrom) {
+    if (IDENTITY && N >= kTlForwardFrom && anew) {
         // The prefixes' and words' signatures once more from the start of the path: walked back they then end where they began, at zero.
 #pragma unroll
         for (int j = 2; j < M; ++j) ca[j] = 0.f;
@@ -579,7 +581,7 @@ __device__ __forceinline__ void tl_walk(const Shape &sh, int groups, int rounds,
 
 template <int D, int N, bool IDENTITY>
 __global__ void __launch_bounds__((64 * TileShape<D, N>::kWaves), (TileShape<D, N>::kOccupancy))
-sig_tile_backward_kernel(Shape sh, int groups, int rounds, const float *__restrict__ path, const float *__restrict__ sig,
+sig_tile_backward_kernel(Shape sh, int groups, int rounds, bool anew, const float *__restrict__ path, const float *__restrict__ sig,
                          const float *__restrict__ gout, float *__restrict__ partial)
 {
     __shared__ __align__(16) float lds[TileShape<D, N>::kLds];
@@ -588,7 +590,7 @@ sig_tile_backward_kernel(Shape sh, int groups, int rounds, const float *__restri
         // 117 moved to memory and back, 1.6 times the time).
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
-        tl_walk<D, N, IDENTITY>(sh, groups, rounds, round, tid, lds, path, sig, gout, partial);
+        tl_walk<D, N, IDENTITY>(sh, groups, rounds, anew, round, tid, lds, path, sig, gout, partial);
     }
 }
 
@@ -615,10 +617,11 @@ hipError_t launch_tile_backward_dn(const Shape &sh, const float *path, const flo
     const int groups = tile_groups_dn<D, N>(sh.B, rounds);
     if (sh.B > 0x7fffffff / groups) return hipErrorNotSupported;
     const dim3 grid(unsigned(sh.B * groups)), threads(64 * TS::kWaves);
+    const bool anew = !tile_forward_certain(sh);
     if (sh.from_identity)
-        hipLaunchKernelGGL((sig_tile_backward_kernel<D, N, true>), grid, threads, 0, st, sh, groups, rounds, path, sig, gout, partial);
+        hipLaunchKernelGGL((sig_tile_backward_kernel<D, N, true>), grid, threads, 0, st, sh, groups, rounds, anew, path, sig, gout, partial);
     else
-        hipLaunchKernelGGL((sig_tile_backward_kernel<D, N, false>), grid, threads, 0, st, sh, groups, rounds, path, sig, gout, partial);
+        hipLaunchKernelGGL((sig_tile_backward_kernel<D, N, false>), grid, threads, 0, st, sh, groups, rounds, anew, path, sig, gout, partial);
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     return launch_increment_sums<float>(sh, groups, partial, gpath, gbase, st);

@@ -17,7 +17,7 @@ hipError_t launch_tile_forward_d(const Shape &sh, const float *path, float *out,
 //    from 32768 wavefronts d = 5 N = 7 366 paths of 68 156 | 176.
 //  - from 12 channels on, paths with fewer than 1024 wavefronts altogether wait for each tile's operands: d = 15 N = 4, 3 of 1037 161 | 188,
 //    but 84 paths of 690 on 14 channels 207 | 132.
-bool tile_forward_preferred(const Shape &sh)
+static bool tile_forward_sizes(const Shape &sh)
 {
     if (sh.stream || sh.chunks != 1 || sh.d < 5 || sh.d > 16 || sh.N > (sh.d <= 8 ? 8 : 6) || sh.S >= (int64_t(1) << 31)) return false;
     if (sh.N < (sh.d <= 6 ? 6 : sh.d == 7 ? 5 : 4) || sh.n_inc < (sh.N == 4 ? 96 : 32)) return false;
@@ -27,6 +27,23 @@ bool tile_forward_preferred(const Shape &sh)
     if (sh.d <= 6 && waves > 8192 && sh.n_inc < 64) return false;
     if (sh.d == 5 && sh.N == 7 && waves > 32768) return false;
     return sh.d < 12 || waves >= 1024;
+}
+
+// Paths that the prefix-tree kernels would cut inside a workgroup stay there: that is faster and up to four times as exact.  And the gradient
+// has to be taken in tiles as well.  It walks the signature back to the start of the path, and is as exact as its roundings are those of the way there:
+// the prefix tree's gradient from the tiles' signature had 1.2 to 1.5 times the error (d = N = 7, 32 paths of 128 points 2.1e-6 | 1.4e-6), in tiles
+// it has 0.6 to 1 of it (1.2e-6).
+bool tile_forward_preferred(const Shape &sh)
+{
+    return tile_forward_sizes(sh) && tree_split_stretches(sh, SIG_F32) == 1 && tile_backward_preferred(sh);
+}
+
+// Whether sig_forward forms this call's signature in tiles, for certain: 8 and 16 channels have matrix kernels of their own for some calls, and
+// up to 64 paths of 512 increments may be scanned in chunks.
+bool tile_forward_certain(const Shape &sh)
+{
+    return sh.from_identity && tile_forward_sizes(sh) && sh.d != 8 && sh.d != 16 && (sh.B > 64 || sh.n_inc < 512) &&
+           tree_split_stretches(sh, SIG_F32) == 1;
 }
 
 hipError_t launch_tile_forward_f32(const Shape &sh, const float *path, float *out, hipStream_t st)
