@@ -276,6 +276,9 @@ bool cut_inside(Family family, const sig::Shape &sh)
 // A call that leaves the choice of the kernels to the library.
 hipError_t launch_auto(Family family, const sig::Shape &sh, sig_dtype dtype, const void *path, void *out, hipStream_t hip_stream)
 {
+    // Every prefix of not too many paths: a lane per increment, one launch (sig_tile_stream.hip says when that pays)
+    if (dtype == SIG_F32 && sig::tile_stream_preferred(sh))
+        return sig::launch_tile_stream_f32(sh, static_cast<const float *>(path), static_cast<float *>(out), hip_stream);
     if (cut_inside(family, sh)) {
         const hipError_t err =
             dtype == SIG_F32

@@ -1,0 +1,58 @@
+"""Stream mode with a lane per increment (sig_tile_stream.hip), where it can go wrong: paths that end inside or at the edge of sixty-four
+increments, channel counts and depths with and without letters above a workgroup's words.
+
+Against the oracle, level by level over all rows.  A scalar is a sum of n increments' terms by a tree over 64 lanes and a chain of n / 64, so it is
+as exact as the one increment at a time of the other kernels: 2^-24 sqrt(n) of a level's terms per level, 5e-6 is ten times that at 300."""
+import numpy as np
+import pytest
+
+import paper_2001_00706_amd as sig
+from oracle import sig_oracle as orc
+from paper_2001_00706_amd.inputs import brownian_paths
+
+pytestmark = pytest.mark.gpu
+
+TOL = 5e-6
+
+
+def check(B, L, d, N, basepoint="none"):
+    import torch
+    x = brownian_paths(B, L, d, seed=L + d) + np.float32(0.25)
+    bp = {"none": None, "origin": True, "point": brownian_paths(B, 2, d, seed=7)[:, 1]}[basepoint]
+    xt = torch.from_numpy(x).to("cuda:0")
+    bt = torch.from_numpy(bp).to("cuda:0") if basepoint == "point" else bool(bp)
+    out = torch.full((B, L - (basepoint == "none"), orc.channels(d, N)), float("nan"), device="cuda:0")
+    sig.sig_signature(xt, N, stream=True, basepoint=bt, out=out)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    assert np.all(np.isfinite(got)), "rows not fully written"
+    xs = x.astype(np.float64)
+    if basepoint == "point":
+        xs = np.concatenate([bp[:, None].astype(np.float64), xs], axis=1)
+    want = orc.signature(xs, N, True, basepoint == "origin")
+    at = 0
+    for k in range(1, N + 1):
+        a, b = got[..., at:at + d ** k], want[..., at:at + d ** k]
+        at += d ** k
+        assert np.linalg.norm(a - b) <= TOL * np.linalg.norm(b), k
+
+
+@pytest.mark.parametrize("L", [2, 3, 16, 17, 18, 33, 34, 64, 65, 66, 128, 129, 130, 300])
+@pytest.mark.parametrize("d,N", [(4, 4), (5, 4), (3, 3)])
+def test_lengths(L, d, N):
+    check(2, L, d, N)
+
+
+@pytest.mark.parametrize("basepoint", ["none", "origin", "point"])
+@pytest.mark.parametrize("d,N", [(d, N) for d, most in ((2, 8), (3, 7), (4, 6), (5, 5), (6, 5), (7, 5)) for N in range(3, most + 1)])
+def test_channels_and_depths(d, N, basepoint):
+    check(2, 71, d, N, basepoint)
+
+
+def test_a_point_that_is_not_a_number_stays_in_later_rows():
+    import torch
+    x = torch.from_numpy(brownian_paths(1, 130, 5, seed=3)).to("cuda:0")
+    x[0, 70, 4] = float("nan")
+    s = sig.sig_signature(x, 4, stream=True)[0].cpu().numpy()
+    last = s[:, -5 ** 4:].reshape((-1,) + (5,) * 4)
+    assert np.all(np.isfinite(s[:69])) and np.all(np.isfinite(last[:, :4, :4, :4, :4])) and np.all(np.isnan(last[69:, 4, 0, 0, 0]))
