@@ -278,7 +278,7 @@ hipError_t launch_auto(Family family, const sig::Shape &sh, sig_dtype dtype, con
 {
     // Every prefix of not too many paths: a lane per increment, one launch (sig_tile_stream.hip says when that pays)
     if (dtype == SIG_F32 && sig::tile_stream_preferred(sh))
-        return sig::launch_tile_stream_f32(sh, static_cast<const float *>(path), static_cast<float *>(out), hip_stream);
+        return sig::launch_tile_stream_f32(sh, static_cast<const float *>(path), nullptr, static_cast<float *>(out), hip_stream);
     if (cut_inside(family, sh)) {
         const hipError_t err =
             dtype == SIG_F32
@@ -1174,12 +1174,16 @@ sig_status sig_signature(const void *path, int64_t B, int64_t L, int d, int N, i
     if ((initial != nullptr || inverse) && !sig::combine_supported(sh)) return SIG_ERR_UNSUPPORTED;
     const Family family = resolve(sh, dtype, SIG_VARIANT_AUTO, path, out);
     if (family == Family::None) return SIG_ERR_UNSUPPORTED;
-    hipError_t err = launch_auto(family, sh, dtype, path, out, hip_stream);
+    // (the stream kernel with a lane per increment begins with `initial`: no product per row)
+    const bool begun = initial != nullptr && dtype == SIG_F32 && sig::tile_stream_preferred(sh);
+    hipError_t err = begun ? sig::launch_tile_stream_f32(sh, static_cast<const float *>(path), static_cast<const float *>(initial),
+                                                         static_cast<float *>(out), hip_stream)
+                           : launch_auto(family, sh, dtype, path, out, hip_stream);
     if (err != hipSuccess) return SIG_ERR_HIP;
     // what follows works on the rows of `out`, in place, behind the scan on the same stream
     sig::Shape rows = sh;
     rows.B = sh.B * (sh.stream ? sh.n_inc : 1);
-    if (initial != nullptr) {
+    if (initial != nullptr && !begun) {
         const int64_t group = sh.stream ? sh.n_inc : 1;
         err = dtype == SIG_F32
                   ? sig::launch_left_mul_f32(rows, static_cast<const float *>(initial), group, static_cast<float *>(out), hip_stream)

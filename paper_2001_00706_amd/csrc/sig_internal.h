@@ -205,9 +205,9 @@ int tree_split_stretches(const Shape &sh, sig_dtype dtype);   // how many (1: th
 // N = 4..6, any alignment; see sig_tile_forward_impl.h).
 bool tile_forward_preferred(const Shape &sh);
 bool tile_forward_certain(const Shape &sh);   // (where tile_backward_preferred holds)
-// a lane per increment in stream mode (sig_tile_stream.hip)
+// a lane per increment in stream mode (sig_tile_stream.hip); `initial` [B][S]: the signature of what came before, or null
 bool tile_stream_preferred(const Shape &sh);
-hipError_t launch_tile_stream_f32(const Shape &sh, const float *path, float *out, hipStream_t st);
+hipError_t launch_tile_stream_f32(const Shape &sh, const float *path, const float *initial, float *out, hipStream_t st);
 hipError_t launch_tile_forward_f32(const Shape &sh, const float *path, float *out, hipStream_t st);
 
 // Row-stream family (d = 2..16 with one or two levels below a word of at most 64 per row; see sig_row_stream.hip): stream

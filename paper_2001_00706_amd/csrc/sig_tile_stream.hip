@@ -67,7 +67,7 @@ __device__ __forceinline__ float ts_last(float v) { return tl_float(__builtin_am
 
 template <int D, int N>
 __global__ void __launch_bounds__((TileStreamShape<D, N>::kThreads))
-sig_tile_stream_kernel(Shape sh, const float *__restrict__ path, float *__restrict__ result)
+sig_tile_stream_kernel(Shape sh, const float *__restrict__ path, const float *__restrict__ initial, float *__restrict__ result)
 {
     using TS = TileStreamShape<D, N>;
     constexpr int M = TS::M, Y = TS::Y;
@@ -103,7 +103,23 @@ sig_tile_stream_kernel(Shape sh, const float *__restrict__ path, float *__restri
 #pragma unroll
     for (int k = 0; k <= N; ++k) rf[k] = tl_inv_factorial(k);
     // the signature before the current sixty-four: the word's prefixes, the word, and below
-    float ca[M + 1] = {}, cb[D] = {}, cc[D][D] = {};
+    float ca[M + 1] = {}, cb[D] = {}, cc[D][D] = {}, first1[D] = {};
+    if (initial != nullptr) {   // what came before the path: the sums begin with it
+        const float *from = initial + row * kS;
+        int rest = u * TS::kWaves + wave;
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            first1[c] = from[c];
+            cb[c] = from[tl_off(D, N - 1) + rest * D + c];
+#pragma unroll
+            for (int k = 0; k < D; ++k) cc[c][k] = from[tl_off(D, N) + (int64_t(rest) * D + c) * D + k];
+        }
+#pragma unroll
+        for (int j = M; j >= 2; --j) {
+            ca[j] = from[tl_off(D, j) + rest];
+            rest /= D;
+        }
+    }
     float *my = rows + lane * TS::kPitch;
     // Where the lane's scalars of a row of the workgroup are, and where they go in a row of the result, in bytes.  Lanes without one, and those of a prefix of u that
     // belongs to an earlier workgroup, store the row's last scalar once more.
@@ -139,8 +155,8 @@ sig_tile_stream_kernel(Shape sh, const float *__restrict__ path, float *__restri
         for (int c = 0; c < D; ++c) {
             const float lo = ts_before(hi[c], last[c]);
             z[c] = hi[c] - lo;
-            level1[c] = hi[c] - start[c];
-            before1[c] = lo - start[c];
+            level1[c] = hi[c] - start[c] + first1[c];
+            before1[c] = lo - start[c] + first1[c];
             last[c] = ts_last(hi[c]);
         }
         if (t0 + kTsRows < sh.n_inc) {   // the next points are on their way meanwhile
@@ -214,7 +230,7 @@ sig_tile_stream_kernel(Shape sh, const float *__restrict__ path, float *__restri
 }
 
 template <int D, int N>
-hipError_t launch_tile_stream_dn(const Shape &sh, const float *path, float *out, hipStream_t st)
+hipError_t launch_tile_stream_dn(const Shape &sh, const float *path, const float *initial, float *out, hipStream_t st)
 {
     using TS = TileStreamShape<D, N>;
     if (sh.B > 0x7fffffff / TS::kGroups) return hipErrorNotSupported;
@@ -223,24 +239,25 @@ hipError_t launch_tile_stream_dn(const Shape &sh, const float *path, float *out,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, TS::kBytes);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((sig_tile_stream_kernel<D, N>), dim3(unsigned(sh.B * TS::kGroups)), dim3(TS::kThreads), TS::kBytes, st, sh, path, out);
+    hipLaunchKernelGGL((sig_tile_stream_kernel<D, N>), dim3(unsigned(sh.B * TS::kGroups)), dim3(TS::kThreads), TS::kBytes, st, sh, path, initial,
+                       out);
     return hipGetLastError();
 }
 
 template <int D>
-hipError_t launch_tile_stream_d(const Shape &sh, const float *path, float *out, hipStream_t st)
+hipError_t launch_tile_stream_d(const Shape &sh, const float *path, const float *initial, float *out, hipStream_t st)
 {
     switch (sh.N) {
-        case 3: return launch_tile_stream_dn<D, 3>(sh, path, out, st);
-        case 4: return launch_tile_stream_dn<D, 4>(sh, path, out, st);
-        case 5: return launch_tile_stream_dn<D, 5>(sh, path, out, st);
+        case 3: return launch_tile_stream_dn<D, 3>(sh, path, initial, out, st);
+        case 4: return launch_tile_stream_dn<D, 4>(sh, path, initial, out, st);
+        case 5: return launch_tile_stream_dn<D, 5>(sh, path, initial, out, st);
     }
     if constexpr (D <= 4)
-        if (sh.N == 6) return launch_tile_stream_dn<D, 6>(sh, path, out, st);
+        if (sh.N == 6) return launch_tile_stream_dn<D, 6>(sh, path, initial, out, st);
     if constexpr (D <= 3)
-        if (sh.N == 7) return launch_tile_stream_dn<D, 7>(sh, path, out, st);
+        if (sh.N == 7) return launch_tile_stream_dn<D, 7>(sh, path, initial, out, st);
     if constexpr (D == 2)
-        if (sh.N == 8) return launch_tile_stream_dn<D, 8>(sh, path, out, st);
+        if (sh.N == 8) return launch_tile_stream_dn<D, 8>(sh, path, initial, out, st);
     return hipErrorNotSupported;
 }
 
@@ -270,15 +287,15 @@ bool tile_stream_preferred(const Shape &sh)
     return sh.B * sh.S <= most;
 }
 
-hipError_t launch_tile_stream_f32(const Shape &sh, const float *path, float *out, hipStream_t st)
+hipError_t launch_tile_stream_f32(const Shape &sh, const float *path, const float *initial, float *out, hipStream_t st)
 {
     switch (sh.d) {
-        case 2: return launch_tile_stream_d<2>(sh, path, out, st);
-        case 3: return launch_tile_stream_d<3>(sh, path, out, st);
-        case 4: return launch_tile_stream_d<4>(sh, path, out, st);
-        case 5: return launch_tile_stream_d<5>(sh, path, out, st);
-        case 6: return launch_tile_stream_d<6>(sh, path, out, st);
-        case 7: return launch_tile_stream_d<7>(sh, path, out, st);
+        case 2: return launch_tile_stream_d<2>(sh, path, initial, out, st);
+        case 3: return launch_tile_stream_d<3>(sh, path, initial, out, st);
+        case 4: return launch_tile_stream_d<4>(sh, path, initial, out, st);
+        case 5: return launch_tile_stream_d<5>(sh, path, initial, out, st);
+        case 6: return launch_tile_stream_d<6>(sh, path, initial, out, st);
+        case 7: return launch_tile_stream_d<7>(sh, path, initial, out, st);
     }
     return hipErrorNotSupported;
 }

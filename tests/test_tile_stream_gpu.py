@@ -56,3 +56,19 @@ def test_a_point_that_is_not_a_number_stays_in_later_rows():
     s = sig.sig_signature(x, 4, stream=True)[0].cpu().numpy()
     last = s[:, -5 ** 4:].reshape((-1,) + (5,) * 4)
     assert np.all(np.isfinite(s[:69])) and np.all(np.isfinite(last[:, :4, :4, :4, :4])) and np.all(np.isnan(last[69:, 4, 0, 0, 0]))
+
+
+@pytest.mark.parametrize("d,N", [(2, 3), (2, 7), (3, 5), (4, 4), (5, 3), (5, 5), (7, 4)])
+def test_begun_with_what_came_before(d, N):
+    """The second half of a path on top of the first half's signature: the rows of the whole path."""
+    import torch
+    x = brownian_paths(3, 140, d, seed=d)
+    xt = torch.from_numpy(x).to("cuda:0")
+    first = sig.sig_signature(xt[:, :60].contiguous(), N)
+    rows = sig.sig_signature(xt[:, 60:].contiguous(), N, stream=True, basepoint=xt[:, 59].contiguous(), initial=first)
+    want = orc.signature(x.astype(np.float64), N, True)[:, 59:]
+    at = 0
+    for k in range(1, N + 1):
+        a, b = rows[..., at:at + d ** k].cpu().numpy(), want[..., at:at + d ** k]
+        at += d ** k
+        assert np.linalg.norm(a - b) <= TOL * np.linalg.norm(b), k
