@@ -14,7 +14,7 @@ import torch
 from . import binding
 
 try:
-    from ._sig_torch import built_with, transform as _transform
+    from ._sig_torch import built_with, interval as _interval, transform as _transform
     if built_with != torch.__version__:   # the node reaches into torch's own structures
         raise ImportError(f"built against torch {built_with}, this is {torch.__version__}")
 except ImportError as e:
@@ -23,6 +23,8 @@ except ImportError as e:
 
     def _transform(*args):
         return NotImplemented
+
+    _interval = _transform
 
 
 def _plain_signature(path, basepoint_value, depth, stream, basepoint):

@@ -11,6 +11,7 @@ from __future__ import annotations
 import torch
 
 from . import binding
+from .autograd import _interval
 
 
 class Path:
@@ -58,6 +59,10 @@ class Path:
                 out = torch.empty((self.B, self.S), dtype=sig.dtype, device=sig.device)
             out.copy_(sig[:, end - 1])
             return out
+        if out is None:
+            found = _interval(sig, start, end, self.d, self.depth)
+            if found is not NotImplemented:
+                return found
         return binding.sig_interval(sig, start, end, self.d, self.depth, out)
 
     def logsignature(self, start: int = 0, end: int | None = None, mode: str = "words"):

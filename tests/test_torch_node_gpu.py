@@ -208,3 +208,22 @@ def test_transforms_and_forward_gradients_as_before(monkeypatch):
     with fw.dual_level():
         dual = fw.make_dual(x.clone().requires_grad_(True), torch.ones_like(x))
         assert autograd._transform(dual, 3, False, False, False, 0, None) is NotImplemented
+
+
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+@pytest.mark.parametrize("B,L,d,N", [(1, 4, 2, 3), (5, 9, 3, 4), (3, 6, 12, 2)])
+def test_path_query_in_the_node(B, L, d, N, dtype):
+    """The node's interval gives the bits of the Python function's, and leaves to it what is not plain."""
+    import torch
+    from paper_2001_00706_amd import binding
+    from paper_2001_00706_amd.autograd import _interval
+    x = torch.from_numpy(brownian_paths(B, L, d, seed=L)).to("cuda:0", getattr(torch, dtype))
+    p = sig.Path(x, N)
+    rows = p._sig[0]
+    for start, end in ((1, 2), (1, L - 1), (L - 2, L - 1)):
+        got = _interval(rows, start, end, d, N)
+        assert got is not NotImplemented and torch.equal(got, binding.sig_interval(rows, start, end, d, N))
+        assert torch.equal(p.signature(start, end), got)
+    for args in ((rows, 0, 2, d, N), (rows, 2, 2, d, N), (rows, 1, L, d, N), (rows, 1, 2, d + 1, N), (rows, 1, 2, d, 0), (rows, 1, 2, d, 10 ** 30),
+                 (rows.cpu(), 1, 2, d, N), (rows.transpose(0, 1), 1, 2, d, N), (rows.half(), 1, 2, d, N), (rows, True, 2, d, N), (rows, 1, 2, d)):
+        assert _interval(*args) is NotImplemented
