@@ -118,6 +118,11 @@ hipError_t launch_product_chain(const Shape &sh, sig_dtype dtype, int64_t paths,
 hipError_t launch_product_reduce(const Shape &sh, sig_dtype dtype, int64_t paths, int64_t K, void *C, void *spare, void *out,
                                  hipStream_t st);
 
+// Products of R >= 2 consecutive signatures each, [products][R][S] to [products][S] (sig_reduce_group.hip; hipErrorNotSupported where it has no kernel, and
+// hipSuccess without a launch for `to` == null where it has).
+hipError_t launch_reduce_group_f32(const Shape &sh, int64_t products, int R, const float *from, float *to, hipStream_t st);
+hipError_t launch_reduce_group_f64(const Shape &sh, int64_t products, int R, const double *from, double *to, hipStream_t st);
+
 // Plumbing of the gradient computed stretch by stretch (sig_backward_chunked.hip); `sh` is the whole call's shape
 // except for the adjoint, which takes the shape of the B K stretches.  K stretches of m increments per path.
 hipError_t launch_stretch_gather(const Shape &sh, sig_dtype dtype, int64_t K, int64_t m, const void *path, void *rows, hipStream_t st);
