@@ -5,6 +5,8 @@
 // of the one before), of whose nine products the six to eight largest are summed in fp32, the small ones first; what is left
 // out is 2^-24 of a term and less.  A sum of 16 such terms is off by 7.7e-8 of its norm where a chain of fp32 multiply-adds is off by 7.4e-8.
 // The matrix cores take them at 16 times the fp32 rate, so six products are 2.7 times as fast as one fp32 instruction.
+// An infinity has no such pieces (its rest is not a number, nor is infinity times a zero piece): where a result would be infinite, by overflow or because a
+// point or a cotangent is, these kernels give NaN.  Which results are finite is the same as on the other kernels.
 #ifndef SIG_TILE_COMMON_H_
 #define SIG_TILE_COMMON_H_
 

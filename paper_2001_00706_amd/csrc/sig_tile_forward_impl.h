@@ -76,6 +76,7 @@ sig_tile_forward_kernel(Shape sh, const float *__restrict__ path, float *__restr
             rest /= D;
         }
     }
+    float broken = 0.f;   // NaN if an increment of the first letter but the path's last is not finite
     float ca[M] = {}, cam[LL] = {};   // the signature at its prefixes of 2 .. letters and at the words, before the current tile
     f4 acc[RB][CT];
 #pragma unroll
@@ -136,6 +137,7 @@ sig_tile_forward_kernel(Shape sh, const float *__restrict__ path, float *__restr
 #pragma unroll
             for (int i = 0; i < LL; ++i) zc[i] = zrow[letter0 + i];
             const float z1 = zrow[cl[1]], a1 = pf[(tile * 16 + s) * ZR + cl[1]];
+            broken = __builtin_fmaf(0.f, tile * 16 + s < nt - 1 || t0 + kSpan < sh.n_inc ? z1 : 0.f, broken);
             float Hh[N + 1];   // T^(k)_j / (k-j)! of the prefix of j letters
 #pragma unroll
             for (int k = 2; k <= N; ++k) Hh[k] = __builtin_fmaf(z1, rf[k], a1 * rf[k - 1]);
@@ -219,6 +221,7 @@ sig_tile_forward_kernel(Shape sh, const float *__restrict__ path, float *__restr
                 }
             }
         }
+    broken = tl_last(tl_prefix(broken));
     if (there && s == 0) {
 #pragma unroll
         for (int i = 0; i < LL; ++i)
@@ -233,7 +236,7 @@ sig_tile_forward_kernel(Shape sh, const float *__restrict__ path, float *__restr
                         out[tl_off(D, j) + rest] = ca[j];
                     } else {
                         const float base = !sh.basepoint ? x[rest] : bpv != nullptr ? bpv[row * D + rest] : 0.f;
-                        out[rest] = x[(sh.L - 1) * D + rest] - base;
+                        out[rest] = x[(sh.L - 1) * D + rest] - base + broken;   // the sum of the increments, where one is not a number
                     }
                 }
                 first = first && cl[j] == 0;

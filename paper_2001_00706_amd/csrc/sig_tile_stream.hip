@@ -148,6 +148,8 @@ sig_tile_stream_kernel(Shape sh, const float *__restrict__ path, const float *__
         slot[r] = (my_row * unsigned(kS) + slot[r]) * 4;
     }
 
+    bool broken = false;             // an increment before the current sixty-four was not finite
+    float broken1[D] = {}, last1[D] = {};   // ... NaN in its channels, and level 1 before them
     for (int64_t t0 = 0; t0 < sh.n_inc; t0 += kTsRows) {
         const int nt = int(sh.n_inc - t0 < kTsRows ? sh.n_inc - t0 : kTsRows);
         float z[D], level1[D], before1[D];
@@ -159,6 +161,23 @@ sig_tile_stream_kernel(Shape sh, const float *__restrict__ path, const float *__
             before1[c] = lo - start[c] + first1[c];
             last[c] = ts_last(hi[c]);
         }
+        // Level 1 is a difference of points: what a sum of the increments would have kept of one that is not finite is put back.
+        float zeros = 0.f;
+#pragma unroll
+        for (int c = 0; c < D; ++c) zeros = __builtin_fmaf(0.f, z[c], zeros);
+        broken = broken || __builtin_amdgcn_ballot_w64(!(zeros == 0.f)) != 0;
+        if (broken) {
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+                const float sum = broken1[c] + ts_sum(0.f * z[c]);
+                const float first = t0 == 0 ? first1[c] : last1[c];
+                level1[c] += ts_before(sum, broken1[c]);
+                broken1[c] = ts_last(sum);
+                before1[c] = ts_before(level1[c], first);
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < D; ++c) last1[c] = ts_last(level1[c]);
         if (t0 + kTsRows < sh.n_inc) {   // the next points are on their way meanwhile
             const int64_t i = t0 + kTsRows + lane < sh.n_inc ? t0 + kTsRows + lane : sh.n_inc - 1;
 #pragma unroll

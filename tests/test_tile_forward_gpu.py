@@ -69,3 +69,17 @@ def test_a_point_that_is_not_a_number_stays_in_its_words():
     s = sig.sig_signature(x, 5)[0].cpu().numpy()
     last = s[-7 ** 5:].reshape((7,) * 5)
     assert np.all(np.isfinite(last[:6, :6, :6, :6, :6])) and np.isnan(last[6, 0, 0, 0, 0]) and np.isnan(last[0, 0, 0, 0, 6])
+
+
+@pytest.mark.parametrize("what", ["nan", "inf"])
+@pytest.mark.parametrize("at", [0, 1, 30, 31, 32, 58, 59])
+@pytest.mark.parametrize("d,N", [(7, 5), (5, 6), (9, 5)])
+def test_what_is_finite(d, N, at, what):
+    """The same scalars of signature and gradient are finite as in 64 bits (an infinity may come out as NaN)."""
+    import torch
+    x = torch.from_numpy(brownian_paths(2, 60, d, seed=3)).to("cuda:0")
+    x[0, at, 1] = float(what)
+    s, want = sig.sig_signature(x, N), sig.sig_signature(x.double(), N)
+    assert torch.equal(torch.isfinite(s), torch.isfinite(want))
+    g = sig.sig_backward(x, s, torch.ones_like(s), N)
+    assert torch.equal(torch.isfinite(g), torch.isfinite(sig.sig_backward(x.double(), want, torch.ones_like(want), N)))

@@ -72,3 +72,14 @@ def test_begun_with_what_came_before(d, N):
         a, b = rows[..., at:at + d ** k].cpu().numpy(), want[..., at:at + d ** k]
         at += d ** k
         assert np.linalg.norm(a - b) <= TOL * np.linalg.norm(b), k
+
+
+@pytest.mark.parametrize("what", ["nan", "inf"])
+@pytest.mark.parametrize("at", [0, 20, 63, 64, 65, 100, 129])
+@pytest.mark.parametrize("d,N", [(4, 4), (5, 3), (2, 6)])
+def test_what_is_finite(d, N, at, what):
+    import torch
+    x = torch.from_numpy(brownian_paths(2, 130, d, seed=3)).to("cuda:0")
+    x[0, at, 1] = float(what)
+    rows = sig.sig_signature(x, N, stream=True)
+    assert torch.equal(torch.isfinite(rows), torch.isfinite(sig.sig_signature(x.double(), N, stream=True)))
