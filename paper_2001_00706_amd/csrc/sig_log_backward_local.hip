@@ -199,9 +199,17 @@ hipError_t launch_local(const Shape &sh, const T *x, const T *r, int64_t r_strid
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
         if (e != hipSuccess) return e;
     }
-    if (sh.B > 0x7fffffff) return hipErrorNotSupported;
-    hipLaunchKernelGGL(kernel, dim3(unsigned(sh.B)), dim3(LS::NT), kBytes, st, sh.N, sh.S, x, r, r_stride, g, g_stride, gx);
-    return hipGetLastError();
+    // A grid has less than 2^32 threads.  (Workgroups that go on to further signatures would keep the places worked out for all of them in
+    // registers: 1024 of d = 3, N = 6 took 34 us instead of 14.)
+    constexpr int64_t kMost = int64_t(1) << 22;
+    for (int64_t first = 0; first < sh.B; first += kMost) {
+        const int64_t count = sh.B - first < kMost ? sh.B - first : kMost;
+        hipLaunchKernelGGL(kernel, dim3(unsigned(count)), dim3(LS::NT), kBytes, st, sh.N, sh.S, x + first * sh.S, WHOLE ? r : r + first * r_stride,
+                           r_stride, g + first * g_stride, g_stride, gx + first * sh.S);
+        const hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return err;
+    }
+    return hipSuccess;
 }
 
 }  // namespace

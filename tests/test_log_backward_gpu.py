@@ -295,3 +295,18 @@ def test_elements_in_lds(rows, d, N, dtype):
     want = orc.tensor_log_backward(x[some], g[some], d, N)
     scale = orc.tensor_log_backward(-np.abs(x[some].astype(np.float64)), np.abs(g[some].astype(np.float64)), d, N)
     assert_grad_close(got[some], want, scale, d, N, dtype)
+
+
+# more signatures than workgroups of 256 and of 512 threads make up a grid (less than 2^32 threads): all alike but for their first scalar
+@pytest.mark.parametrize("rows,d,N", [((1 << 24) + 3, 3, 3), ((1 << 23) + 3, 9, 3)])
+def test_more_signatures_than_a_grid_holds(rows, d, N):
+    import torch
+    S, some = orc.channels(d, N), torch.tensor([0, 1, 1 << 20, rows // 2, rows - 1])
+    s1, g1 = (torch.randn(S, generator=torch.Generator().manual_seed(i)).to("cuda:0") * 0.3 for i in (0, 1))
+    s, g, out = (torch.empty((rows, S), device="cuda:0") for _ in range(3))
+    s[:], g[:] = s1, g1
+    s[:, 0] = (torch.arange(rows, device="cuda:0") % 1021) / 1021
+    sig.sig_log_backward(s, g, d, N, out=out)
+    want = sig.sig_log_backward(s[some].contiguous(), g[some].contiguous(), d, N)
+    assert torch.equal(out[some], want)
+    assert torch.equal(out[rows - 1021:], out[rows - 2042:rows - 1021])   # the rows that leave the same rest
