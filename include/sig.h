@@ -426,6 +426,11 @@ int sig_backward_chunks_fastest(int64_t B, int64_t L, int d, int N, int basepoin
 const char *sig_variant_name(int64_t B, int64_t L, int d, int N, int stream, int basepoint,
                              sig_dtype dtype, sig_variant variant);
 
+/* Whether sig_forward (gradient == 0) or sig_backward (gradient != 0) takes this call in fp32 with the kernels that work on sixteen or
+ * sixty-four increments at a time: 0 if not, otherwise how many blocks of words a wavefront of theirs takes one after the other (1 but for
+ * gradients of many words).  Host arithmetic only; -1 on invalid arguments. */
+int sig_tile_rounds(int64_t B, int64_t L, int d, int N, int stream, int basepoint, int gradient);
+
 /* Static English text for a status code. */
 const char *sig_status_string(sig_status status);
 

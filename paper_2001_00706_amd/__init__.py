@@ -63,6 +63,7 @@ from .binding import (  # noqa: F401
     sig_output_elems,
     sig_signature_channels,
     sig_status_string,
+    sig_tile_rounds,
     sig_variant_name,
 )
 

@@ -65,6 +65,7 @@ EXPORTED_SYMBOLS = (
     "sig_signature",
     "sig_backward_workspace_bytes",
     "sig_variant_name",
+    "sig_tile_rounds",
     "sig_status_string",
 )
 
@@ -220,6 +221,8 @@ def load_library() -> ctypes.CDLL:
         lib.sig_backward_workspace_bytes.argtypes = [i64, i64, i32, i32, i32, i32, i32]
         lib.sig_variant_name.restype = ctypes.c_char_p
         lib.sig_variant_name.argtypes = [i64, i64, i32, i32, i32, i32, i32, i32]
+        lib.sig_tile_rounds.restype = i32
+        lib.sig_tile_rounds.argtypes = [i64, i64, i32, i32, i32, i32, i32]
         lib.sig_status_string.restype = ctypes.c_char_p
         lib.sig_status_string.argtypes = [i32]
         _lib = lib
@@ -267,6 +270,12 @@ def sig_fused_fmas(d: int, N: int) -> int:
 def sig_variant_name(B: int, L: int, d: int, N: int, stream: bool, basepoint: bool,
                      dtype: int = SIG_F32, variant: int = SIG_VARIANT_AUTO) -> str:
     return load_library().sig_variant_name(B, L, d, N, int(stream), int(basepoint), dtype, variant).decode()
+
+
+def sig_tile_rounds(B: int, L: int, d: int, N: int, stream: bool = False, basepoint: bool = False, gradient: bool = False) -> int:
+    """How many blocks of words a wavefront takes one after the other where the kernels that work on sixteen or sixty-four increments
+    at a time serve the fp32 call (its gradient if `gradient`); 0 where they do not."""
+    return int(load_library().sig_tile_rounds(B, L, d, N, int(stream), int(basepoint), int(gradient)))
 
 
 def sig_forward_raw(path_ptr: int, B: int, L: int, d: int, N: int, stream: int, basepoint: int,

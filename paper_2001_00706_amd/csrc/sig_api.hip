@@ -273,12 +273,20 @@ bool cut_inside(Family family, const sig::Shape &sh)
     return !sh.stream && (family == Family::Tree || family == Family::RowStream || family == Family::Small);
 }
 
-// A call that leaves the choice of the kernels to the library.
+// A call that leaves the choice of the kernels to the library: in stream mode not too many paths with a lane per increment, in one launch
+// (sig_tile_stream.hip says when that pays), in final mode sixteen increments at a time on the matrix cores where the paths are not cut inside a
+// workgroup (sig_tile_forward.hip).
+bool in_tiles(Family family, const sig::Shape &sh, sig_dtype dtype)
+{
+    if (dtype != SIG_F32) return false;
+    return sh.stream ? sig::tile_stream_preferred(sh) : family == Family::Tree && sig::tile_forward_preferred(sh);
+}
+
 hipError_t launch_auto(Family family, const sig::Shape &sh, sig_dtype dtype, const void *path, void *out, hipStream_t hip_stream)
 {
-    // Every prefix of not too many paths: a lane per increment, one launch (sig_tile_stream.hip says when that pays)
-    if (dtype == SIG_F32 && sig::tile_stream_preferred(sh))
-        return sig::launch_tile_stream_f32(sh, static_cast<const float *>(path), nullptr, static_cast<float *>(out), hip_stream);
+    if (in_tiles(family, sh, dtype))
+        return sh.stream ? sig::launch_tile_stream_f32(sh, static_cast<const float *>(path), nullptr, static_cast<float *>(out), hip_stream)
+                         : sig::launch_tile_forward_f32(sh, static_cast<const float *>(path), static_cast<float *>(out), hip_stream);
     if (cut_inside(family, sh)) {
         const hipError_t err =
             dtype == SIG_F32
@@ -286,9 +294,6 @@ hipError_t launch_auto(Family family, const sig::Shape &sh, sig_dtype dtype, con
                 : sig::launch_tree_split_f64(sh, static_cast<const double *>(path), static_cast<double *>(out), hip_stream);
         if (err != hipErrorNotSupported) return err;
     }
-    // ... and where they do not, sixteen increments at a time go to the matrix cores (sig_tile_forward.hip says when that pays)
-    if (family == Family::Tree && dtype == SIG_F32 && sig::tile_forward_preferred(sh))
-        return sig::launch_tile_forward_f32(sh, static_cast<const float *>(path), static_cast<float *>(out), hip_stream);
     return launch_family(family, sh, dtype, path, out, hip_stream);
 }
 
@@ -1175,7 +1180,7 @@ sig_status sig_signature(const void *path, int64_t B, int64_t L, int d, int N, i
     const Family family = resolve(sh, dtype, SIG_VARIANT_AUTO, path, out);
     if (family == Family::None) return SIG_ERR_UNSUPPORTED;
     // (the stream kernel with a lane per increment begins with `initial`: no product per row)
-    const bool begun = initial != nullptr && dtype == SIG_F32 && sig::tile_stream_preferred(sh);
+    const bool begun = initial != nullptr && sh.stream && in_tiles(family, sh, dtype);
     hipError_t err = begun ? sig::launch_tile_stream_f32(sh, static_cast<const float *>(path), static_cast<const float *>(initial),
                                                          static_cast<float *>(out), hip_stream)
                            : launch_auto(family, sh, dtype, path, out, hip_stream);
@@ -1227,6 +1232,15 @@ const char *sig_variant_name(int64_t B, int64_t L, int d, int N, int stream, int
         case Family::None: break;
     }
     return "unsupported";
+}
+
+int sig_tile_rounds(int64_t B, int64_t L, int d, int N, int stream, int basepoint, int gradient)
+{
+    sig::Shape sh;
+    if (make_shape(B, L, d, N, stream, basepoint, sh) != SIG_OK) return -1;
+    if (B == 0) return 0;
+    if (gradient) return sig::tile_backward_preferred(sh) ? sig::tile_backward_rounds(sh) : 0;
+    return in_tiles(resolve(sh, SIG_F32, SIG_VARIANT_AUTO, nullptr, nullptr), sh, SIG_F32) ? 1 : 0;
 }
 
 const char *sig_status_string(sig_status status)

@@ -35,6 +35,9 @@ struct Shape {
     int64_t off[SIG_MAX_DEPTH + 2];  // off[k] = offset of level k (1-based) in a signature; off[N+1] = S
 };
 
+// A grid has less than 2^32 threads: one of more is launched modulo 2^32, without an error.
+constexpr bool grid_holds(int64_t groups, int64_t threads) { return groups <= 0xffffffffll / threads; }
+
 // Which stretch of which path the scan of output row `row` folds in.
 struct ChunkView {
     int64_t path;   // index of the path (for the path pointer and the basepoint value)
@@ -118,8 +121,8 @@ hipError_t launch_product_chain(const Shape &sh, sig_dtype dtype, int64_t paths,
 hipError_t launch_product_reduce(const Shape &sh, sig_dtype dtype, int64_t paths, int64_t K, void *C, void *spare, void *out,
                                  hipStream_t st);
 
-// Products of R >= 2 consecutive signatures each, [products][R][S] to [products][S] (sig_reduce_group.hip; hipErrorNotSupported where it has no kernel, and
-// hipSuccess without a launch for `to` == null where it has).
+// Products of R >= 2 consecutive signatures each, [products][R][S] to [products][S] (sig_reduce_group.hip; hipErrorNotSupported where it has no
+// kernel, or a grid does not hold the call).
 hipError_t launch_reduce_group_f32(const Shape &sh, int64_t products, int R, const float *from, float *to, hipStream_t st);
 hipError_t launch_reduce_group_f64(const Shape &sh, int64_t products, int R, const double *from, double *to, hipStream_t st);
 
@@ -272,6 +275,7 @@ hipError_t launch_increment_sums(const Shape &sh, int64_t n_partials, const T *p
 // N = 4..8, d = 9..16 at N = 4..6, any alignment; see sig_tile_backward_impl.h).  The workspace holds partial gradients per increment.
 bool tile_backward_preferred(const Shape &sh);
 double tile_backward_us(const Shape &sh);   // about how long a call takes
+int tile_backward_rounds(const Shape &sh);  // how many blocks of words a wavefront takes one after the other
 int64_t tile_backward_workspace_bytes(const Shape &sh);
 hipError_t launch_tile_backward_f32(const Shape &sh, const float *path, const float *sig, const float *gout, float *gpath, float *gbase,
                                     void *workspace, int64_t workspace_bytes, hipStream_t st);

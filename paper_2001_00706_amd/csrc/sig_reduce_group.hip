@@ -121,8 +121,7 @@ hipError_t launch_dn(int64_t products, int R, const T *from, T *to, hipStream_t 
 {
     using GS = GroupShape<T, D, N>;
     if constexpr (GS::kServed) {
-        if (products > 0x7fffffff / GS::kGroups) return hipErrorNotSupported;
-        if (to == nullptr) return hipSuccess;
+        if (!grid_holds(products * GS::kGroups, GS::kThreads)) return hipErrorNotSupported;
         hipLaunchKernelGGL((sig_reduce_group_kernel<T, D, N>), dim3(unsigned(products * GS::kGroups)), dim3(GS::kThreads), 0, st, R, from, to);
         return hipGetLastError();
     }

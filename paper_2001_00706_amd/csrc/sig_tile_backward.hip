@@ -10,7 +10,7 @@ template <int D>
 hipError_t launch_tile_backward_d(const Shape &sh, const float *path, const float *sig, const float *gout, float *gpath, float *gbase,
                                   float *partial, hipStream_t st);
 template <int D>
-int tile_groups_d(int64_t B, int N);
+int tile_groups_d(int64_t B, int N, int &rounds);
 
 namespace {
 
@@ -36,10 +36,15 @@ auto with_channels(int d, F f)
     }
 }
 
-int groups(const Shape &sh)
+int groups(const Shape &sh, int &rounds)
 {
     if (sh.d < 3 || sh.d > 16) return 0;
-    return with_channels(sh.d, [&](auto d) { return tile_groups_d<decltype(d)::value>(sh.B, sh.N); });
+    return with_channels(sh.d, [&](auto d) { return tile_groups_d<decltype(d)::value>(sh.B, sh.N, rounds); });
+}
+int groups(const Shape &sh)
+{
+    int rounds;
+    return groups(sh, rounds);
 }
 
 }  // namespace
@@ -71,7 +76,9 @@ double tile_backward_us(const Shape &sh)
 // two, and takes 0.60 of the time without these kernels.
 bool tile_backward_preferred(const Shape &sh)
 {
-    if (sh.stream || sh.n_inc < 24 || sh.S >= (int64_t(1) << 31) || groups(sh) == 0) return false;
+    if (sh.stream || sh.n_inc < 24 || sh.S >= (int64_t(1) << 31)) return false;
+    const int workgroups = groups(sh);   // of up to four wavefronts
+    if (workgroups == 0 || !grid_holds(sh.B * workgroups, 256)) return false;
     // (d = 16, N = 4 has sig_backward_d16.hip for short paths: 256 x 31 points 60 | 52, 64 x 17 16 | 30)
     if (sh.d == 16 && sh.N == 4) return sh.n_inc >= 48 || sh.B <= 64;
     if (sh.d > 8) return sh.n_inc >= 32 || sh.B * sh.pw[sh.N - 3] <= 512;
@@ -82,7 +89,14 @@ bool tile_backward_preferred(const Shape &sh)
     return tile_backward_us(sh) - 9 <= tree;
 }
 
-int64_t tile_backward_workspace_bytes(const Shape &sh) 
+int tile_backward_rounds(const Shape &sh)
+{
+    int rounds = 0;
+    groups(sh, rounds);
+    return rounds;
+}
+
+int64_t tile_backward_workspace_bytes(const Shape &sh)
 {
     return sh.B * groups(sh) * sh.n_inc * sh.d * int64_t(sizeof(float));
 }

@@ -6,7 +6,7 @@ namespace sig {
 #define SIG_TILE(D)                                                                                                          \
     template hipError_t launch_tile_backward_d<D>(const Shape &, const float *, const float *, const float *, float *, float *, \
                                                   float *, hipStream_t);                                                     \
-    template int tile_groups_d<D>(int64_t, int);
+    template int tile_groups_d<D>(int64_t, int, int &);
 SIG_TILE(3)
 SIG_TILE(4)
 #undef SIG_TILE

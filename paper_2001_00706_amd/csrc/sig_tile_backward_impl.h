@@ -615,7 +615,7 @@ hipError_t launch_tile_backward_dn(const Shape &sh, const float *path, const flo
     using TS = TileShape<D, N>;
     int rounds;
     const int groups = tile_groups_dn<D, N>(sh.B, rounds);
-    if (sh.B > 0x7fffffff / groups) return hipErrorNotSupported;
+    if (!grid_holds(sh.B * groups, 64 * TS::kWaves)) return hipErrorNotSupported;
     const dim3 grid(unsigned(sh.B * groups)), threads(64 * TS::kWaves);
     const bool anew = !tile_forward_certain(sh);
     if (sh.from_identity)
@@ -649,9 +649,8 @@ hipError_t launch_tile_backward_d(const Shape &sh, const float *path, const floa
 }
 
 template <int D>
-int tile_groups_d(int64_t B, int N)   // workgroups of a path, 0 where there is no kernel
+int tile_groups_d(int64_t B, int N, int &rounds)   // workgroups of a path, 0 where there is no kernel
 {
-    int rounds;
     switch (N) {
         case 4: return tile_groups_dn<D, 4>(B, rounds);
         case 5: return tile_groups_dn<D, 5>(B, rounds);

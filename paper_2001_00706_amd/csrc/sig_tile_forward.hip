@@ -24,6 +24,7 @@ static bool tile_forward_sizes(const Shape &sh)
     double waves = double(sh.B);   // four prefixes of N - 3 letters to a wavefront, or one
     for (int k = 0; k < sh.N - 3; ++k) waves *= sh.d;
     if (sh.d <= 8) waves /= 4;
+    if (waves >= (1 << 25)) return false;   // at most twice as many with those that round up: a grid has less than 2^32 threads
     if (sh.d <= 6 && waves > 8192 && sh.n_inc < 64) return false;
     if (sh.d == 5 && sh.N == 7 && waves > 32768) return false;
     return sh.d < 12 || waves >= 1024;

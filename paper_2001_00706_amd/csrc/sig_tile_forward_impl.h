@@ -251,7 +251,7 @@ hipError_t launch_tile_forward_dn(const Shape &sh, const float *path, float *out
 {
     using TS = TileForwardShape<D, N>;
     constexpr int kBytes = TS::kLds * int(sizeof(float));
-    if (sh.B > 0x7fffffff / TS::kGroups) return hipErrorNotSupported;
+    if (!grid_holds(sh.B * TS::kGroups, 64 * TS::kWaves)) return hipErrorNotSupported;
     if (kBytes > 64 * 1024) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(sig_tile_forward_kernel<D, N>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);

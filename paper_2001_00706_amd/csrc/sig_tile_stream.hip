@@ -252,7 +252,7 @@ template <int D, int N>
 hipError_t launch_tile_stream_dn(const Shape &sh, const float *path, const float *initial, float *out, hipStream_t st)
 {
     using TS = TileStreamShape<D, N>;
-    if (sh.B > 0x7fffffff / TS::kGroups) return hipErrorNotSupported;
+    if (!grid_holds(sh.B * TS::kGroups, TS::kThreads)) return hipErrorNotSupported;
     if (TS::kBytes > 64 * 1024) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(sig_tile_stream_kernel<D, N>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, TS::kBytes);

@@ -437,3 +437,16 @@ assert [w.category for w in seen] == [RuntimeWarning] and "_sig_torch.so" in str
 """
     res = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
     assert res.returncode == 0, res.stderr
+
+
+def test_tiles_are_left_to_others_where_a_grid_does_not_hold_them(lib):
+    """A grid has less than 2^32 threads: 2^24 workgroups of 256 at most (gradient), 2^25 wavefronts before rounding up (forward)."""
+    h = sig.sig_tile_rounds
+    assert h((1 << 24) - 1, 41, 4, 4, gradient=True) == 1 and h(1 << 24, 41, 4, 4, gradient=True) == 0
+    assert h((1 << 24) - 1, 101, 4, 5, gradient=True) == 1 and h(1 << 24, 101, 4, 5, gradient=True) == 0
+    assert h((1 << 25) // 9, 101, 9, 4) == 1 and h((1 << 25) // 9 + 1, 101, 9, 4) == 0
+    # which calls go in tiles at all; invalid arguments
+    assert h(32, 128, 7, 7) == 1 and h(32, 128, 7, 7, gradient=True) == 5 and h(32, 16, 2, 4) == 0 and h(0, 128, 7, 7) == 0
+    assert h(64, 101, 5, 4, stream=True, basepoint=True) == 1 and h(64, 15, 5, 4, stream=True) == 0
+    assert h(64, 101, 5, 4, stream=True, gradient=True) == 0
+    assert h(2, 1, 3, 4) == -1 and h(2, 9, 0, 4) == -1
