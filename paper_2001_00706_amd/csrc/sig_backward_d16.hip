@@ -209,7 +209,7 @@ sig_backward_d16_n4_kernel(const float *__restrict__ path, const float *__restri
 
 bool backward_d16_supported(const Shape &sh)
 {
-    return sh.d == 16 && sh.N == 4 && !sh.stream && sh.chunks <= 1 && sh.B <= 0x7fffffff;
+    return sh.d == 16 && sh.N == 4 && !sh.stream && sh.chunks <= 1 && grid_holds(sh.B, kBwThreads);
 }
 
 int64_t backward_d16_workspace_bytes(const Shape &sh) { return sh.B * sh.n_inc * kD16 * int64_t(sizeof(float)); }

@@ -338,7 +338,7 @@ hipError_t launch_d4(const Shape &sh, const float *path, const float *sig, const
 // the two was not looked for).
 bool backward_d4_supported(const Shape &sh)
 {
-    return sh.stream && sh.d == 4 && sh.N >= 4 && sh.N <= 6 && (sh.N >= 5 ? sh.B <= 0x7fffffff : sh.B < 1024 || sh.B * sh.n_inc < 12500);
+    return sh.stream && sh.d == 4 && sh.N >= 4 && sh.N <= 6 && (sh.N >= 5 ? grid_holds(sh.B, 256) : sh.B < 1024 || sh.B * sh.n_inc < 12500);
 }
 
 hipError_t launch_backward_d4_f32(const Shape &sh, const float *path, const float *sig, const float *gout, float *gpath,

@@ -213,7 +213,7 @@ sig_backward_d4_n6_kernel(const float *__restrict__ path, const float *__restric
 
 bool backward_d4n6_supported(const Shape &sh)
 {
-    return sh.d == 4 && sh.N == 6 && !sh.stream && sh.chunks <= 1 && sh.B <= 0x7fffffff;
+    return sh.d == 4 && sh.N == 6 && !sh.stream && sh.chunks <= 1 && grid_holds((sh.B + kG4Paths - 1) / kG4Paths, kG4Threads);
 }
 
 int64_t backward_d4n6_workspace_bytes(const Shape &sh) { return sh.B * sh.n_inc * 4 * int64_t(sizeof(float)); }

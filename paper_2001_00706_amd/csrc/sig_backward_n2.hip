@@ -131,7 +131,7 @@ hipError_t launch_backward_n2_t(const Shape &sh, const T *path, const T *gout, T
     const size_t lds = n2_lds_bytes<T>(sh.d, ppg);
     const int passes = n2_passes(sh);
     const int64_t groups = sh.B * ((sh.L + int64_t(ppg) * passes - 1) / (int64_t(ppg) * passes));
-    if (lds > 64 * 1024 || groups > 0x7fffffff) return hipErrorNotSupported;
+    if (lds > 64 * 1024 || !grid_holds(groups, 256)) return hipErrorNotSupported;
     hipLaunchKernelGGL((sig_backward_n2_kernel<T>), dim3(unsigned(groups)), dim3(256), lds, st, sh, ppg, passes, path, gout, gpath,
                        gbase);
     return hipGetLastError();
@@ -145,7 +145,7 @@ bool backward_n2_supported(const Shape &sh, sig_dtype dtype)
     if (sh.N != 2 || sh.stream || sh.chunks > 1 || !sh.from_identity || sh.d < 1 || sh.d > 255) return false;
     const int ppg = n2_points_per_group(sh.d);
     const size_t lds = dtype == SIG_F32 ? n2_lds_bytes<float>(sh.d, ppg) : n2_lds_bytes<double>(sh.d, ppg);
-    return lds <= 64 * 1024 && sh.B * ((sh.L + ppg - 1) / ppg) <= 0x7fffffff;
+    return lds <= 64 * 1024 && grid_holds(sh.B * ((sh.L + ppg - 1) / ppg), 256);
 }
 
 hipError_t launch_backward_n2_f32(const Shape &sh, const float *path, const float *gout, float *gpath, float *gbase, hipStream_t st)

@@ -200,7 +200,7 @@ bool b2m_plan(const Shape &sh, bool vector_loads, B2mPlan &pl)
     const auto groups = [&]() { return interior <= 0 ? int64_t(1) : (interior + int64_t(pl.round_points) * pl.rounds - 1) / (int64_t(pl.round_points) * pl.rounds); };
     while (pl.rounds > 1 && sh.B * groups() < 1024) pl.rounds /= 2;
     pl.groups_per_path = groups();
-    return sh.B * pl.groups_per_path <= 0x7fffffff;
+    return grid_holds(sh.B * pl.groups_per_path, 256);
 }
 
 }  // namespace

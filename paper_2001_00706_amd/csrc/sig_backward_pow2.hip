@@ -299,7 +299,7 @@ bool backward_pow2_supported(const Shape &sh)
     if (!sh.stream) return false;
     if (sh.d == 2)
         return sh.N >= 2 && sh.N <= 7 && sh.n_inc * sh.N < 120 && sh.B * sh.n_inc < (sh.N <= 5 ? 35000 : sh.N == 6 ? 14000 : 7000);
-    return sh.d == 8 && ((sh.N == 3 && sh.B < 640) || (sh.N == 4 && sh.B <= 0x7fffffff));
+    return sh.d == 8 && ((sh.N == 3 && sh.B < 640) || (sh.N == 4 && grid_holds(sh.B, Pow2Shape<8, 4>::NTL)));
 }
 
 hipError_t launch_backward_pow2_f32(const Shape &sh, const float *path, const float *sig, const float *gout, float *gpath,

@@ -273,7 +273,7 @@ bool n2_plan(const Shape &sh, size_t elem, const void *path, N2Plan &pl, bool st
     if (2 * loads_per_point > 256 * kBatch) return false;
     if ((pl.tile + 1) * loads_per_point > 256 * kBatch) pl.tile = int(256 * kBatch / loads_per_point) - 1;
     const int64_t groups = blocks >= 256 ? sh.B * pl.groups_per_path : (sh.B + pl.paths_per_group - 1) / pl.paths_per_group;
-    return groups <= 0x7fffffff && n2_lds(pl, elem) <= 64 * 1024;
+    return grid_holds(groups, 256) && n2_lds(pl, elem) <= 64 * 1024;
 }
 
 template <typename T>
@@ -307,7 +307,7 @@ hipError_t launch_forward_n2_chunked_t(const Shape &sh, const T *path, T *partia
     const hipError_t err = launch_forward_n2_t<T>(sh, path, partial, st, true);
     if (err != hipSuccess) return err;
     const int64_t groups = sh.B / sh.chunks * ((sh.S + 15) / 16);
-    if (groups > 0x7fffffff) return hipErrorNotSupported;
+    if (!grid_holds(groups, 256)) return hipErrorNotSupported;
     hipLaunchKernelGGL((sig_forward_n2_sum_kernel<T>), dim3(unsigned(groups)), dim3(256), 0, st, sh, path, partial, out);
     return hipGetLastError();
 }

@@ -221,7 +221,7 @@ bool n2m_plan(const Shape &sh, const void *path, N2mPlan &pl)
     pl.tile = int(tile / 4 * 4);
     if (pl.tile < 4) return false;
     const int64_t groups = pl.groups_per_path > 1 ? sh.B * pl.groups_per_path : (sh.B + pl.paths_per_group - 1) / pl.paths_per_group;
-    return groups <= 0x7fffffff && n2m_lds(pl) <= 64 * 1024;
+    return grid_holds(groups, 256) && n2m_lds(pl) <= 64 * 1024;
 }
 
 template <int V>

@@ -964,11 +964,13 @@ int64_t r_offset(const Shape &sh, int m)
 }
 
 template <typename T, int D>
-void launch_r(const Shape &sh, const T *x, T *r_out, int64_t r_stride, hipStream_t st)
+hipError_t launch_r(const Shape &sh, const T *x, T *r_out, int64_t r_stride, hipStream_t st)
 {
     const int64_t threads = sh.B * sh.off[sh.N];
+    if (!grid_holds(threads + kLbThreads, 1)) return hipErrorNotSupported;
     hipLaunchKernelGGL((log_bwd_r_kernel<T, D>), dim3(unsigned((threads + kLbThreads - 1) / kLbThreads)), dim3(kLbThreads), 0, st, sh, x,
                        r_out, r_stride);
+    return hipGetLastError();
 }
 
 // One step of the chain of launches; see the two kernels.
@@ -978,12 +980,12 @@ hipError_t launch_step(const Step &stp, int64_t rows, const T *x, int64_t x_stri
                        T *gx, int64_t gx_stride, hipStream_t st)
 {
     const int64_t wgs = rows * int64_t(stp.wgs);
-    if (wgs > 0x7fffffff) return hipErrorNotSupported;
+    const int64_t threads = rows * (int64_t(stp.S_next) + stp.S_cur + (plus_g ? stp.S_cur - stp.S_next : 0));
+    if (!grid_holds(wgs, kLbThreads) || !grid_holds(threads + kLbThreads, 1)) return hipErrorNotSupported;
     hipLaunchKernelGGL((log_bwd_main_kernel<T, Step>), dim3(unsigned(wgs)), dim3(kLbThreads), 0, st, stp, x, x_stride, x_group, G, g_stride,
                        R, r_stride, apart, bpart);
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    const int64_t threads = rows * (int64_t(stp.S_next) + stp.S_cur + (plus_g ? stp.S_cur - stp.S_next : 0));
     hipLaunchKernelGGL((log_bwd_finish_kernel<T, Step>), dim3(unsigned((threads + kLbThreads - 1) / kLbThreads)), dim3(kLbThreads), 0, st,
                        stp, rows, c_m, c_last, first, last, plus_g, G, g_stride, apart, bpart, G_next, gn_stride, gx, gx_stride);
     return hipGetLastError();
@@ -1060,6 +1062,17 @@ hipError_t launch_log_backward(const Shape &sh, const T *x, const T *g, T *gx, v
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(nt), fused_lds, st, sh, ws.r_stride, x, g, gx);
         return hipGetLastError();
     }
+    // a grid has less than 2^32 threads: more signatures than the first step's launches hold are taken in parts, one after the other
+    const int64_t most = 0xffff0000ll / (int64_t(plan_step(sh, N).wgs) * kLbThreads + 2 * sh.S);
+    if (sh.B > most && most > 0) {
+        for (int64_t first = 0; first < sh.B; first += most) {
+            Shape part = sh;
+            part.B = sh.B - first < most ? sh.B - first : most;
+            const hipError_t err = launch_log_backward<T>(part, x + first * sh.S, g + first * sh.S, gx + first * sh.S, workspace, st);
+            if (err != hipSuccess) return err;
+        }
+        return hipSuccess;
+    }
     char *base = static_cast<char *>(workspace);
     T *Rs = reinterpret_cast<T *>(base + ws.r_off);
     T *Gb[2] = {reinterpret_cast<T *>(base + ws.g0_off), reinterpret_cast<T *>(base + ws.g1_off)};
@@ -1068,22 +1081,23 @@ hipError_t launch_log_backward(const Shape &sh, const T *x, const T *g, T *gx, v
     auto coef = [](int m) { return (m & 1 ? T(1) : T(-1)) / T(m); };
 
     if (N <= kDirectMaxDepth) {
+        hipError_t err;
         switch (sh.d) {
-            case 2: launch_r<T, 2>(sh, x, Rs, ws.r_stride, st); break;
-            case 3: launch_r<T, 3>(sh, x, Rs, ws.r_stride, st); break;
-            case 4: launch_r<T, 4>(sh, x, Rs, ws.r_stride, st); break;
-            case 5: launch_r<T, 5>(sh, x, Rs, ws.r_stride, st); break;
-            case 6: launch_r<T, 6>(sh, x, Rs, ws.r_stride, st); break;
-            case 7: launch_r<T, 7>(sh, x, Rs, ws.r_stride, st); break;
-            case 8: launch_r<T, 8>(sh, x, Rs, ws.r_stride, st); break;
-            default: launch_r<T, 0>(sh, x, Rs, ws.r_stride, st); break;
+            case 2: err = launch_r<T, 2>(sh, x, Rs, ws.r_stride, st); break;
+            case 3: err = launch_r<T, 3>(sh, x, Rs, ws.r_stride, st); break;
+            case 4: err = launch_r<T, 4>(sh, x, Rs, ws.r_stride, st); break;
+            case 5: err = launch_r<T, 5>(sh, x, Rs, ws.r_stride, st); break;
+            case 6: err = launch_r<T, 6>(sh, x, Rs, ws.r_stride, st); break;
+            case 7: err = launch_r<T, 7>(sh, x, Rs, ws.r_stride, st); break;
+            case 8: err = launch_r<T, 8>(sh, x, Rs, ws.r_stride, st); break;
+            default: err = launch_r<T, 0>(sh, x, Rs, ws.r_stride, st); break;
         }
-        const hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
     } else {
         for (int m = N; m >= 2; --m) {
             const int n = N - m + 1;
             const int64_t threads = sh.B * sh.off[n + 1];
+            if (!grid_holds(threads + kLbThreads, 1)) return hipErrorNotSupported;
             hipLaunchKernelGGL((log_bwd_horner_kernel<T>), dim3(unsigned((threads + kLbThreads - 1) / kLbThreads)), dim3(kLbThreads), 0, st, sh,
                                n, coef(m), x, m == N ? nullptr : Rs + r_offset(sh, m + 1), Rs + r_offset(sh, m), ws.r_stride);
             const hipError_t err = hipGetLastError();

@@ -247,7 +247,7 @@ sig_mfma_d4_kernel(const float *__restrict__ path, float *__restrict__ out, int6
 
 const char *mfma_kernel_name(const Shape &sh)
 {
-    if (sh.d != 4 || sh.stream || sh.B > 0x7fffffff) return nullptr;
+    if (sh.d != 4 || sh.stream || !grid_holds(sh.B, 64)) return nullptr;
     return (sh.N >= 4 && sh.N <= 6) ? "mfma_d4" : nullptr;
 }
 

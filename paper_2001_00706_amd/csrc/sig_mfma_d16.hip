@@ -203,7 +203,7 @@ sig_mfma_d16_n4_kernel(const float *__restrict__ path, float *__restrict__ out, 
 
 const char *mfma_d16_kernel_name(const Shape &sh)
 {
-    if (sh.d == 16 && sh.N == 4 && !sh.stream && sh.B <= 0x7fffffff) return "mfma_d16";
+    if (sh.d == 16 && sh.N == 4 && !sh.stream && grid_holds(sh.B, 512)) return "mfma_d16";
     return nullptr;
 }
 

@@ -443,13 +443,13 @@ hipError_t launch_shard(const Shape &sh, const float *path, float *out, hipStrea
 
 const char *mfma_shard_kernel_name(const Shape &sh)
 {
-    if (sh.d != 4 || sh.N < 4 || sh.N > 7 || sh.B > 0x1fffffff) return nullptr;
+    if (sh.d != 4 || sh.N < 4 || sh.N > 7 || !grid_holds(sh.B * 4, 64)) return nullptr;
     return "mfma_d4_shard";
 }
 
 const char *mfma_stream_kernel_name(const Shape &sh)
 {
-    if (sh.d != 4 || sh.N < 4 || sh.N > 6 || !sh.stream || sh.chunks > 1 || sh.B > 0x7fffffff) return nullptr;
+    if (sh.d != 4 || sh.N < 4 || sh.N > 6 || !sh.stream || sh.chunks > 1 || !grid_holds(sh.B, 256)) return nullptr;
     return "mfma_d4_stream";
 }
 

@@ -387,7 +387,7 @@ hipError_t launch8(const Shape &sh, const float *path, float *out, hipStream_t s
 
 const char *mfma_d8_kernel_name(const Shape &sh)
 {
-    if (sh.d != 8 || sh.N < 4 || sh.N > 6 || sh.stream || sh.B > 0x1ffffff) return nullptr;
+    if (sh.d != 8 || sh.N < 4 || sh.N > 6 || sh.stream || !grid_holds(sh.B * 64, 64)) return nullptr;
     return "mfma_d8_shard";
 }
 

@@ -336,7 +336,7 @@ hipError_t launch_row_stream_dn(const Shape &sh, const T *path, T *out, hipStrea
 {
     if constexpr (RowShape<T, D, N>::kServed) {
         const int64_t groups = (sh.B + RowShape<T, D, N>::R - 1) / RowShape<T, D, N>::R;
-        if (groups > 0x7fffffff) return hipErrorNotSupported;
+        if (!grid_holds(groups, 64)) return hipErrorNotSupported;
         hipLaunchKernelGGL((sig_row_stream_kernel<T, D, N>), dim3(unsigned(groups)), dim3(64), 0, st, sh, path, out);
         return hipGetLastError();
     } else {

@@ -756,7 +756,7 @@ hipError_t launch_tb_mode(const Shape &sh, const T *path, const T *sig, const T 
     constexpr int MODE = STREAM ? kTbStream : kTbFinal;
     using TS = TbShape<T, D, N, ROWS>;
     const int64_t groups = TS::kMulti ? sh.B * TS::kGroupsPerPath : (sh.B + TS::kPathsPerGroup - 1) / TS::kPathsPerGroup;
-    if (groups > 0x7fffffff) return hipErrorNotSupported;
+    if (!grid_holds(groups, 256)) return hipErrorNotSupported;
     hipLaunchKernelGGL((sig_tree_backward_kernel<T, D, N, MODE, ROWS>), dim3(unsigned(groups)), dim3(256), 0, st, sh, StretchRows<T>{}, path, sig,
                        gout, partial);
     const hipError_t err = hipGetLastError();
@@ -915,7 +915,7 @@ hipError_t launch_tb_stream_stretches_mode(const Shape &sh, const Shape &rows, c
 {
     using TS = TbShape<T, D, N, ROWS>;
     const int64_t groups = TS::kMulti ? rows.B * TS::kGroupsPerPath : (rows.B + TS::kPathsPerGroup - 1) / TS::kPathsPerGroup;
-    if (groups > 0x7fffffff) return hipErrorNotSupported;
+    if (!grid_holds(groups, 256)) return hipErrorNotSupported;
     hipLaunchKernelGGL((sig_tree_backward_kernel<T, D, N, kTbStreamStretches, ROWS>), dim3(unsigned(groups)), dim3(256), 0, st, rows, nodes, path,
                        sig, gout, partial);
     const hipError_t err = hipGetLastError();
@@ -1028,7 +1028,7 @@ hipError_t launch_tb_stretches_mode(const Shape &sh, const Shape &rows, const St
 {
     using TS = TbShape<T, D, N, ROWS>;
     const int64_t groups = TS::kMulti ? rows.B * TS::kGroupsPerPath : (rows.B + TS::kPathsPerGroup - 1) / TS::kPathsPerGroup;
-    if (groups > 0x7fffffff) return hipErrorNotSupported;
+    if (!grid_holds(groups, 256)) return hipErrorNotSupported;
     hipLaunchKernelGGL((sig_tree_backward_kernel<T, D, N, kTbStretches, ROWS>), dim3(unsigned(groups)), dim3(256), 0, st, rows, nodes, path,
                        static_cast<const T *>(nullptr), gout, partial);
     const hipError_t err = hipGetLastError();

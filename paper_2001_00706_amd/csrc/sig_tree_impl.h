@@ -246,7 +246,7 @@ hipError_t launch_tree_dn(const Shape &sh, const T *path, T *out, hipStream_t st
 {
     using TS = TreeShape<D, N>;
     const int64_t groups = TS::kWords >= 256 ? sh.B * TS::kGroupsPerPath : (sh.B + TS::kPathsPerGroup - 1) / TS::kPathsPerGroup;
-    if (groups > 0x7fffffff) return hipErrorNotSupported;
+    if (!grid_holds(groups, 256)) return hipErrorNotSupported;
     hipLaunchKernelGGL((sig_tree_kernel<T, D, N>), dim3(unsigned(groups)), dim3(256), 0, st, sh, path, out);
     return hipGetLastError();
 }

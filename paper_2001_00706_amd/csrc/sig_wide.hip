@@ -224,7 +224,7 @@ hipError_t launch_wide_t(const Shape &sh, const T *path, T *out, hipStream_t st)
     const size_t lds = size_t(pl.paths_per_group) * kWideTile * size_t(pl.dpad) * sizeof(T);
     if (lds > 64 * 1024) return hipErrorNotSupported;
     const int64_t groups = pl.threads >= 256 ? sh.B * pl.groups_per_path : (sh.B + pl.paths_per_group - 1) / pl.paths_per_group;
-    if (groups > 0x7fffffff) return hipErrorNotSupported;
+    if (!grid_holds(groups, 256)) return hipErrorNotSupported;
     const dim3 grid{unsigned(groups)}, block{256};
 #define SIG_WIDE_LAUNCH(NN)                                                                                   \
     if (pl.block == 64)                                                                                       \

@@ -349,7 +349,7 @@ bool wb_plan(const Shape &sh, size_t elem, WbPlan &pl)
     pl.jblocks = (sh.d + pl.block - 1) / pl.block;
     pl.dpad = pl.jblocks * pl.block;
     pl.groups_per_path = (pl.waves_per_block * pl.jblocks + 3) / 4;
-    if (sh.B * pl.groups_per_path > 0x7fffffff) return false;
+    if (!grid_holds(sh.B * pl.groups_per_path, 256)) return false;
     return elem * size_t(5 * kWbTile) * size_t(pl.dpad) <= 64 * 1024;
 }
 

@@ -297,11 +297,12 @@ def test_elements_in_lds(rows, d, N, dtype):
     assert_grad_close(got[some], want, scale, d, N, dtype)
 
 
-# more signatures than workgroups of 256 and of 512 threads make up a grid (less than 2^32 threads): all alike but for their first scalar
-@pytest.mark.parametrize("rows,d,N", [((1 << 24) + 3, 3, 3), ((1 << 23) + 3, 9, 3)])
+# more signatures than workgroups of 256 and of 512 threads, or two threads a scalar, make up a grid (less than 2^32 threads): all alike but for
+# their first scalar
+@pytest.mark.parametrize("rows,d,N", [((1 << 24) + 3, 3, 3), ((1 << 23) + 3, 9, 3), (160001, 4, 7)])
 def test_more_signatures_than_a_grid_holds(rows, d, N):
     import torch
-    S, some = orc.channels(d, N), torch.tensor([0, 1, 1 << 20, rows // 2, rows - 1])
+    S, some = orc.channels(d, N), torch.tensor([0, 1, 1 << 17, rows // 2, rows - 1])   # (all below the smallest count)
     s1, g1 = (torch.randn(S, generator=torch.Generator().manual_seed(i)).to("cuda:0") * 0.3 for i in (0, 1))
     s, g, out = (torch.empty((rows, S), device="cuda:0") for _ in range(3))
     s[:], g[:] = s1, g1
