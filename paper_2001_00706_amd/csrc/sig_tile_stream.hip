@@ -282,20 +282,53 @@ hipError_t launch_tile_stream_d(const Shape &sh, const float *path, const float 
 
 }  // namespace
 
-// Where that is faster than what served these calls, both timed over 700 shapes (rows of B S scalars side by side; us, before | now).  Sixty-four
-// increments take a workgroup 1.5 to 4 us, and a full chip stores 2.5 to 4 TB/s:
+// The longest path, in increments, up to which that is faster than what serves these calls otherwise, by the number of paths.
+//
+// Sixty-four increments take a workgroup 1 to 6 us however long the path is.  The kernels before cut a path into chunks, the more of them the longer it
+// is and the fewer paths there are (sig_api.hip, stream_chunks: 32 for up to 64 paths of 4096 increments, 16 up to 128, 8 up to 256, 4 up to 512):
+// their time grows with the square root.  One path, us, before | now: d = 3, N = 4 1000 increments 39 | 39, 4000 73 | 145, 60 000 507 | 2124; d = 2,
+// N = 4 4000 85 | 67, 8000 97 | 130; d = 5, N = 4 4000 194 | 189, 60 000 737 | 2780; d = 6, N = 4 1000 91 | 72, 60 000 639 | 4088.  Many paths of large
+// signatures are bound by the stores, which the kernels before do in whole rows: once the output is beyond the 256 MB of the last-level cache they are
+// ahead (400 paths, d = 2, N = 7, 700 increments 0.65 of their time, 1500 1.22).  Timed over 1600 shapes of up to 100 000 increments.
+struct LongestPath {
+    int d, N, paths_8, paths_32, paths_64, paths_128, paths_256, more;   // up to so many paths
+};
+constexpr int kAny = 0x7fffffff;
+constexpr LongestPath kLongest[] = {
+    {2, 3, 2000, 2000, 2000, kAny, kAny, kAny},  {2, 4, 4095, 4095, kAny, kAny, kAny, kAny},   {2, 5, 4095, 4095, kAny, kAny, kAny, kAny},
+    {2, 6, 4095, 4095, 20000, kAny, 8000, 4000}, {2, 7, 20000, 20000, 40000, 2000, 1000, 900}, {2, 8, 20000, 20000, 4000, 1000, 500, 500},
+    {3, 3, 3000, 3000, 3000, kAny, kAny, kAny},  {3, 4, 1000, 1000, 1000, 1300, kAny, kAny},   {3, 5, 1000, 1000, 1000, 1000, 450, 300},
+    {3, 6, 3500, 3500, 1500, 1000, 1000, 1000},  {3, 7, 8000, 1500, 1000, 1000, 1000, 1000},   {4, 3, 1000, 1000, 1000, 3000, kAny, kAny},
+    {5, 3, 400, 400, 400, 400, 400, 400},        {5, 4, 4000, 3500, 4000, 500, 300, 300},      {5, 5, 8000, 4000, 1500, 1500, 1500, 1500},
+    {6, 3, 300, 300, 300, 300, 300, 300},        {6, 4, 1500, 2000, 2000, 2000, 2000, 2000},   {7, 3, 160, 160, 160, 160, 160, 160},
+    {7, 4, 1200, 2000, 1500, 1500, 1500, 1500},   // the others' kernels are not cut, or slower at any length (d = 4, N = 4..6; d = 6, 7 at N = 5)
+};
+static bool short_enough(const Shape &sh)
+{
+    for (const LongestPath &l : kLongest)
+        if (l.d == sh.d && l.N == sh.N)
+            return sh.n_inc <= (sh.B <= 8     ? l.paths_8
+                                : sh.B <= 32  ? l.paths_32
+                                : sh.B <= 64  ? l.paths_64
+                                : sh.B <= 128 ? l.paths_128
+                                : sh.B <= 256 ? l.paths_256
+                                              : l.more);
+    return true;
+}
+
+// Where it pays otherwise, both timed over 700 shapes of up to 1100 points (rows of B S scalars side by side; us, before | now).  A full chip stores
+// 2.5 to 4 TB/s:
 //  - the kernels before wait 0.3 to 0.45 us for an increment or, in chunks, some 20 to 60 for three launches: 64 x 101 points, d = 5, N = 4 32 | 11;
 //    25 x 165, d = 7, N = 5 757 | 96; 8 x 227, d = 4, N = 5 24 | 11.5.  Under 20 increments most lanes have none.
 //  - with many paths they store up to 6 TB/s: 745 x 119, d = 4, N = 4 23 | 34, 1287 x 20, d = 5, N = 4 17 | 36; at d = 4, N = 5 from 30 paths on
 //    (55 x 84 11.6 | 12.8).
 //  - at depth 3 from 5 channels on a path is a single workgroup of d (d + 1) sums a wavefront, and from some length on the chunks are ahead:
 //    11 x 469, d = 5 26 | 24, 18 x 1047 37 | 50; 1 x 507, d = 6 26 | 32; 10 x 108, d = 7 17 | 12, 9 x 342 25 | 31.
-// Over 400 drawn shapes the rule takes 0.60 of the time and has 0.80 of the error of before.
+// Over 400 drawn shapes of that range the rule takes 0.60 of the time and has 0.80 of the error of before.
 bool tile_stream_preferred(const Shape &sh)
 {
     if (!sh.stream || sh.chunks != 1 || sh.rows_in_stream || !sh.from_identity || sh.d < 2 || sh.d > 7 || sh.N < 3 || sh.n_inc < 20) return false;
-    if (sh.N > (sh.d == 2 ? 8 : sh.d == 3 ? 7 : sh.d == 4 ? 6 : 5)) return false;
-    if (sh.N == 3 && sh.d >= 5 && sh.n_inc > (sh.d == 5 ? 400 : sh.d == 6 ? 300 : 160)) return false;
+    if (sh.N > (sh.d == 2 ? 8 : sh.d == 3 ? 7 : sh.d == 4 ? 6 : 5) || !short_enough(sh)) return false;
     const int64_t k = 1000;
     const int64_t most = sh.d <= 3    ? 120 * k
                          : sh.d == 4  ? (sh.N == 3 ? 120 * k : sh.N == 4 ? 54 * k : sh.N == 5 ? 24 * k : 80 * k)

@@ -83,3 +83,17 @@ def test_what_is_finite(d, N, at, what):
     x[0, at, 1] = float(what)
     rows = sig.sig_signature(x, N, stream=True)
     assert torch.equal(torch.isfinite(rows), torch.isfinite(sig.sig_signature(x.double(), N, stream=True)))
+
+
+# on both sides of the longest path that is taken, by the number of paths; longer ones go in chunks
+@pytest.mark.parametrize("B,d,N,longest", [(1, 3, 4, 1000), (16, 2, 3, 2000), (65, 4, 3, 3000), (40, 3, 6, 1500), (130, 3, 5, 450), (2, 6, 4, 1500)])
+def test_long_streams(B, d, N, longest):
+    import torch
+    for L in (longest + 1, longest + 2):
+        assert sig.sig_tile_rounds(B, L, d, N, stream=True) == (L == longest + 1)
+        x = brownian_paths(B, L, d, seed=d)
+        some = [0, 1, 63, 64, L // 2, L - 2]
+        got = sig.sig_signature(torch.from_numpy(x).to("cuda:0"), N, stream=True)[:2, some].cpu().numpy()
+        want = orc.signature(x[:2].astype(np.float64), N, True)[:, some]
+        for sl in orc.level_slices(d, N):
+            assert np.linalg.norm(got[..., sl] - want[..., sl]) <= TOL * (L / 300) ** 0.5 * np.linalg.norm(want[..., sl])
