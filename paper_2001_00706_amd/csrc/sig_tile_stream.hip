@@ -330,7 +330,7 @@ bool tile_stream_preferred(const Shape &sh)
     if (!sh.stream || sh.chunks != 1 || sh.rows_in_stream || !sh.from_identity || sh.d < 2 || sh.d > 7 || sh.N < 3 || sh.n_inc < 20) return false;
     if (sh.N > (sh.d == 2 ? 8 : sh.d == 3 ? 7 : sh.d == 4 ? 6 : 5) || !short_enough(sh)) return false;
     const int64_t k = 1000;
-    const int64_t most = sh.d <= 3    ? 120 * k
+    const int64_t most = sh.d <= 3    ? (sh.d == 3 && sh.N == 5 ? 100 * k : 120 * k)   // 300 x 21, d = 3, N = 5 10.3 | 12.5
                          : sh.d == 4  ? (sh.N == 3 ? 120 * k : sh.N == 4 ? 54 * k : sh.N == 5 ? 24 * k : 80 * k)
                          : sh.N == 3  ? (sh.d == 7 ? 40 * k : 120 * k)
                          : sh.N == 4  ? 150 * k
