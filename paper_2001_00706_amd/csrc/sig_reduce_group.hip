@@ -38,6 +38,14 @@ __device__ __forceinline__ void add_keeping(T &sum, T &lost, T v)
     sum = t;
 }
 
+// ... and in the end: a sum that is infinite has lost what is no number.
+template <typename T>
+__device__ __forceinline__ T with_lost(T sum, T lost)
+{
+    const T t = sum + lost;
+    return t == t ? t : sum;
+}
+
 // to[r] = the product of the signatures r R .. r R + R - 1 of `from`, R >= 2
 template <typename T, int D, int N>
 __global__ void __launch_bounds__((GroupShape<T, D, N>::kThreads))
@@ -110,10 +118,10 @@ sig_reduce_group_kernel(int R, const T *__restrict__ from, T *__restrict__ to)
     if (!there) return;
     T *out = to + product * kS;
 #pragma unroll
-    for (int j = 0; j < D; ++j) out[tl_off(D, N) + int64_t(w) * D + j] = leaf[j] + leaf_lost[j];
+    for (int j = 0; j < D; ++j) out[tl_off(D, N) + int64_t(w) * D + j] = with_lost(leaf[j], leaf_lost[j]);
 #pragma unroll
     for (int k = N - 1; k >= 1; --k)   // by the first word below
-        if (wk[N - 1] % int(tl_pow(D, N - 1 - k)) == 0) out[tl_off(D, k) + wk[k]] = p[k] + p_lost[k];
+        if (wk[N - 1] % int(tl_pow(D, N - 1 - k)) == 0) out[tl_off(D, k) + wk[k]] = with_lost(p[k], p_lost[k]);
 }
 
 template <typename T, int D, int N>

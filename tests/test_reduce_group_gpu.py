@@ -27,3 +27,17 @@ def test_chunked_scan(B, chunks, d, N, dtype):
         a, b = got[:, at:at + d ** k], want[:, at:at + d ** k]
         at += d ** k
         assert np.linalg.norm(a - b) <= (5e-6 if dtype == np.float32 else 1e-13) * np.linalg.norm(b), k
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("chunks,d,N", [(16, 4, 6), (128, 4, 6), (64, 7, 4)])
+def test_overflow_is_infinite_not_nan(chunks, d, N, dtype):
+    """A straight path whose deepest level, all of it positive, overflows in the last products: the running sums give infinities, and what they
+    have lost by then is no number."""
+    import torch
+    most = float(np.finfo(dtype).max)
+    end = 1e3 ** (1 / N) * most ** (1 / N) * float(np.prod(np.arange(1, N + 1, dtype=float) ** (1 / N)))
+    x = np.linspace(0, end, 2 * chunks + 1).astype(dtype)[None, :, None].repeat(d, 2)
+    got = sig.sig_forward_chunked(torch.from_numpy(np.ascontiguousarray(x)).to("cuda:0"), N, chunks).cpu().numpy()[0]
+    below = orc.channels(d, N - 1)
+    assert np.all(np.isfinite(got[:below])) and np.all(np.isposinf(got[below:]))
