@@ -5,8 +5,9 @@
 // of the one before), of whose nine products the six to eight largest are summed in fp32, the small ones first; what is left
 // out is 2^-24 of a term and less.  A sum of 16 such terms is off by 7.7e-8 of its norm where a chain of fp32 multiply-adds is off by 7.4e-8.
 // The matrix cores take them at 16 times the fp32 rate, so six products are 2.7 times as fast as one fp32 instruction.
-// An infinity has no such pieces (its rest is not a number, nor is infinity times a zero piece): where a result would be infinite, by overflow or because a
-// point or a cotangent is, these kernels give NaN.  Which results are finite is the same as on the other kernels.
+// An infinity has no such pieces (its rest is not a number, nor is infinity times a zero piece), and a product of two increments may overflow where the
+// scalar that it is a factor of would not.  A signature with a scalar that is not finite is therefore formed once more, one increment after the other
+// (tl_one_by_one).  A gradient that would be infinite, because a cotangent is or by overflow, comes out as NaN.
 #ifndef SIG_TILE_COMMON_H_
 #define SIG_TILE_COMMON_H_
 
@@ -15,6 +16,7 @@
 
 #include <type_traits>
 
+#include "sig_internal.h"
 #include "sig_lane_ops.h"
 
 namespace sig {
@@ -151,6 +153,68 @@ __device__ __forceinline__ void tl_wave_order()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
+// One increment after the other, for paths whose scalars overflow or are no numbers: the word u of N - 1 letters, its prefixes and its children,
+// formed as in sig_tree_impl.h.  visit(s, a, leaf) behind increment s: a[k] is the prefix of k letters, leaf the children.  The increments end at the
+// n_inc points from `at` on, the first starts from `base` (null: the origin); the signature from `initial` (null: the identity).
+template <int D, int N, typename Visit>
+__device__ __forceinline__ void tl_one_by_one(const float *at, int64_t n_inc, const float *base, const float *initial, int u, Visit visit)
+{
+    constexpr int P = N - 1;
+    int letter[P + 1];
+    float a[P + 1], leaf[D], lo[D];
+    int rest = u;
+#pragma unroll
+    for (int k = P; k >= 1; --k) {
+        letter[k] = rest % D;
+        a[k] = initial != nullptr ? initial[tl_off(D, k) + rest] : 0.f;
+        rest /= D;
+    }
+#pragma unroll
+    for (int c = 0; c < D; ++c) {
+        leaf[c] = initial != nullptr ? initial[tl_off(D, N) + int64_t(u) * D + c] : 0.f;
+        lo[c] = base != nullptr ? base[c] : 0.f;
+    }
+#pragma unroll 1
+    for (int64_t s = 0; s < n_inc; ++s, at += D) {
+        float z[D], h[N + 1];
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            const float hi = at[c];
+            z[c] = hi - lo[c];
+            lo[c] = hi;
+        }
+#pragma unroll
+        for (int i = 1; i <= P; ++i) {
+            float zi = z[0];
+#pragma unroll
+            for (int c = 1; c < D; ++c) zi = letter[i] == c ? z[c] : zi;
+            const float before = a[i];
+            a[i] = i == 1 ? before + zi : __builtin_fmaf(h[i], zi, before);
+#pragma unroll
+            for (int k = i + 1; k <= N; ++k) {
+                const float r = 1.f / float(k - i + 1);
+                h[k] = i == 1 ? __builtin_fmaf(zi, r, before) : __builtin_fmaf(h[k], zi * r, before);
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < D; ++c) leaf[c] = __builtin_fmaf(h[N], z[c], leaf[c]);
+        visit(s, a, leaf);
+    }
+}
+
+// That word, its children and the prefixes it is the first below into a signature.
+template <int D, int N>
+__device__ __forceinline__ void tl_store_word(float *out, int u, const float (&a)[N], const float (&leaf)[D])
+{
+#pragma unroll
+    for (int c = 0; c < D; ++c) out[tl_off(D, N) + int64_t(u) * D + c] = leaf[c];
+#pragma unroll
+    for (int k = N - 1; k >= 1; --k) {
+        const int below = int(tl_pow(D, N - 1 - k));
+        if (u % below == 0) out[tl_off(D, k) + u / below] = a[k];
+    }
 }
 
 }  // namespace

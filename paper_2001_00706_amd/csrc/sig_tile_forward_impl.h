@@ -43,10 +43,12 @@ struct TileForwardShape {
     static constexpr int kAtPos = kSpan * ZR, kAtZt = 2 * kSpan * ZR, kAtQt = kAtZt + (D + 1) * kSpan, kAtOps = kAtQt + (D + 1) * kSpan;
     static constexpr int kAtTrans = kAtOps + kTiles * CT * 3 * 256, kLds = kAtTrans + kWaves * kTrans;
     static_assert(kLds * 4 <= 80 * 1024 && kAtOps % 4 == 0 && kAtZt % 4 == 0);
+    // wavefronts per SIMD: eight wavefronts with more than 128 registers have a compute unit for themselves
+    static constexpr int kOccupancy = (D == 16 && N >= 5) || (D == 7 && N == 8) ? 2 : 4;
 };
 
 template <int D, int N>
-__global__ void __launch_bounds__((64 * TileForwardShape<D, N>::kWaves), 2)
+__global__ void __launch_bounds__((64 * TileForwardShape<D, N>::kWaves), (TileForwardShape<D, N>::kOccupancy))
 sig_tile_forward_kernel(Shape sh, const float *__restrict__ path, float *__restrict__ result)
 {
     using TS = TileForwardShape<D, N>;
@@ -76,7 +78,7 @@ sig_tile_forward_kernel(Shape sh, const float *__restrict__ path, float *__restr
             rest /= D;
         }
     }
-    float broken = 0.f;   // NaN if an increment of the first letter but the path's last is not finite
+    float wild = 0.f;   // NaN if an increment of the first letter is not finite, or a scalar
     float ca[M] = {}, cam[LL] = {};   // the signature at its prefixes of 2 .. letters and at the words, before the current tile
     f4 acc[RB][CT];
 #pragma unroll
@@ -137,7 +139,7 @@ sig_tile_forward_kernel(Shape sh, const float *__restrict__ path, float *__restr
 #pragma unroll
             for (int i = 0; i < LL; ++i) zc[i] = zrow[letter0 + i];
             const float z1 = zrow[cl[1]], a1 = pf[(tile * 16 + s) * ZR + cl[1]];
-            broken = __builtin_fmaf(0.f, tile * 16 + s < nt - 1 || t0 + kSpan < sh.n_inc ? z1 : 0.f, broken);
+            wild = __builtin_fmaf(0.f, z1, wild);
             float Hh[N + 1];   // T^(k)_j / (k-j)! of the prefix of j letters
 #pragma unroll
             for (int k = 2; k <= N; ++k) Hh[k] = __builtin_fmaf(z1, rf[k], a1 * rf[k - 1]);
@@ -207,6 +209,27 @@ sig_tile_forward_kernel(Shape sh, const float *__restrict__ path, float *__restr
 
     // ---- results: a lane holds column lane % 16 of four words
     float *out = result + row * kS;
+    float wilds[4] = {wild, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int t = 0; t < CT; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) wilds[i] = __builtin_fmaf(0.f, acc[b][t][i], wilds[i]);
+#pragma unroll
+    for (int j = 2; j < M; ++j) wilds[j & 3] = __builtin_fmaf(0.f, ca[j], wilds[j & 3]);
+#pragma unroll
+    for (int i = 0; i < LL; ++i) wilds[i & 3] = __builtin_fmaf(0.f, cam[i], wilds[i & 3]);
+    wild = wilds[0] + wilds[1] + wilds[2] + wilds[3];
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(wild == 0.f)) != 0, 0)) {   // see sig_tile_common.h
+        constexpr int kBelow = (LW == 8 ? 4 : 1) * D * D;     // words of N - 1 letters below the wavefront's prefixes
+        const float *base = !sh.basepoint ? x : bpv != nullptr ? bpv + row * D : nullptr;
+        for (int u = unit * kBelow + lane; u < (unit + 1) * kBelow && u < TS::kPrefixes * D * D; u += 64)
+            tl_one_by_one<D, N>(x + (sh.basepoint ? 0 : D), sh.n_inc, base, nullptr, u, [&](int64_t i, const float(&a)[N], const float(&leaf)[D]) {
+                if (i + 1 == sh.n_inc) tl_store_word<D, N>(out, u, a, leaf);
+            });
+        return;
+    }
 #pragma unroll
     for (int b = 0; b < RB; ++b)
 #pragma unroll
@@ -221,7 +244,6 @@ sig_tile_forward_kernel(Shape sh, const float *__restrict__ path, float *__restr
                 }
             }
         }
-    broken = tl_last(tl_prefix(broken));
     if (there && s == 0) {
 #pragma unroll
         for (int i = 0; i < LL; ++i)
@@ -236,7 +258,7 @@ sig_tile_forward_kernel(Shape sh, const float *__restrict__ path, float *__restr
                         out[tl_off(D, j) + rest] = ca[j];
                     } else {
                         const float base = !sh.basepoint ? x[rest] : bpv != nullptr ? bpv[row * D + rest] : 0.f;
-                        out[rest] = x[(sh.L - 1) * D + rest] - base + broken;   // the sum of the increments, where one is not a number
+                        out[rest] = x[(sh.L - 1) * D + rest] - base;
                     }
                 }
                 first = first && cl[j] == 0;

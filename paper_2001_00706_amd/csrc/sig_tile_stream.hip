@@ -38,6 +38,8 @@ struct TileStreamShape {
     static constexpr int kPitch = kScalars | 1;                               // lanes that write a column fall on different banks
     static constexpr int kBytes = kTsRows * kPitch * 4;
     static_assert(kBytes <= 110 * 1024);
+    // wavefronts per SIMD at least: what the code behind the last row needs must not take them (d = 6, N = 5, 35 x 23 points: 24.0 us with four, 20.8 with five)
+    static constexpr int kOccupancy = D == 4 ? 8 : D == 6 ? 5 : D == 7 ? 4 : 1;
 };
 
 // The sums over the lanes up to this one of several values, side by side: a step waits for the one before.
@@ -66,7 +68,7 @@ __device__ __forceinline__ float ts_before(float v, float first)
 __device__ __forceinline__ float ts_last(float v) { return tl_float(__builtin_amdgcn_readlane(tl_bits(v), 63)); }
 
 template <int D, int N>
-__global__ void __launch_bounds__((TileStreamShape<D, N>::kThreads))
+__global__ void __launch_bounds__((TileStreamShape<D, N>::kThreads), (TileStreamShape<D, N>::kOccupancy))
 sig_tile_stream_kernel(Shape sh, const float *__restrict__ path, const float *__restrict__ initial, float *__restrict__ result)
 {
     using TS = TileStreamShape<D, N>;
@@ -80,6 +82,23 @@ sig_tile_stream_kernel(Shape sh, const float *__restrict__ path, const float *__
     const int u = int(block < octets ? block / 8 % TS::kGroups : block % TS::kGroups);
     const float *x = path + row * sh.L * D;
     float *out = result + row * sh.n_inc * kS;
+    const float *points = x + (sh.basepoint ? 0 : D);   // where the increments end
+    const int n_inc = int(sh.n_inc);
+
+    // Whether the rows are formed once more (see sig_tile_common.h), and what that needs.  Kept in registers up to there it would take more than 80 scalar ones,
+    // with which a SIMD holds seven wavefronts (673 x 81 points, d = 3, N = 4: 13.9 us, 12.4 with 78).
+    struct Cold {
+        int anew, first_word;
+        const float *points, *base, *initial;
+        float *out;
+        int n_inc;
+    };
+    __shared__ Cold cold;
+    if (tid == 0) {
+        const float *bpv = static_cast<const float *>(sh.basepoint_value);
+        cold = {0, u * TS::kWaves * D, points, !sh.basepoint ? x : bpv != nullptr ? bpv + row * D : nullptr,
+                initial != nullptr ? initial + row * kS : nullptr, out, n_inc};
+    }
 
     int letter[M + 1];
     {
@@ -91,13 +110,11 @@ sig_tile_stream_kernel(Shape sh, const float *__restrict__ path, const float *__
         }
     }
     float start[D], last[D], hi[D];
-    const int64_t first_point = sh.basepoint ? 0 : 1;
 #pragma unroll
     for (int c = 0; c < D; ++c) {
         const float *bpv = static_cast<const float *>(sh.basepoint_value);
         start[c] = last[c] = !sh.basepoint ? x[c] : bpv != nullptr ? bpv[row * D + c] : 0.f;
-        const int64_t i = lane < sh.n_inc ? lane : sh.n_inc - 1;
-        hi[c] = x[(i + first_point) * D + c];
+        hi[c] = points[int64_t(lane < n_inc ? lane : n_inc - 1) * D + c];
     }
     float rf[N + 1];
 #pragma unroll
@@ -148,10 +165,11 @@ sig_tile_stream_kernel(Shape sh, const float *__restrict__ path, const float *__
         slot[r] = (my_row * unsigned(kS) + slot[r]) * 4;
     }
 
-    bool broken = false;             // an increment before the current sixty-four was not finite
+    int infinite = 0;                // an increment was
+    bool broken = false;             // an increment up to the current sixty-four was not finite
     float broken1[D] = {}, last1[D] = {};   // ... NaN in its channels, and level 1 before them
-    for (int64_t t0 = 0; t0 < sh.n_inc; t0 += kTsRows) {
-        const int nt = int(sh.n_inc - t0 < kTsRows ? sh.n_inc - t0 : kTsRows);
+    for (int t0 = 0; t0 < n_inc; t0 += kTsRows) {
+        const int nt = n_inc - t0 < kTsRows ? n_inc - t0 : kTsRows;
         float z[D], level1[D], before1[D];
 #pragma unroll
         for (int c = 0; c < D; ++c) {
@@ -169,6 +187,7 @@ sig_tile_stream_kernel(Shape sh, const float *__restrict__ path, const float *__
         if (broken) {
 #pragma unroll
             for (int c = 0; c < D; ++c) {
+                if (__builtin_amdgcn_ballot_w64(__builtin_isinf(z[c])) != 0) infinite = 1;
                 const float sum = broken1[c] + ts_sum(0.f * z[c]);
                 const float first = t0 == 0 ? first1[c] : last1[c];
                 level1[c] += ts_before(sum, broken1[c]);
@@ -178,10 +197,10 @@ sig_tile_stream_kernel(Shape sh, const float *__restrict__ path, const float *__
         }
 #pragma unroll
         for (int c = 0; c < D; ++c) last1[c] = ts_last(level1[c]);
-        if (t0 + kTsRows < sh.n_inc) {   // the next points are on their way meanwhile
-            const int64_t i = t0 + kTsRows + lane < sh.n_inc ? t0 + kTsRows + lane : sh.n_inc - 1;
+        if (t0 + kTsRows < n_inc) {   // the next points are on their way meanwhile
+            const int64_t i = t0 + kTsRows + lane < n_inc ? t0 + kTsRows + lane : n_inc - 1;
 #pragma unroll
-            for (int c = 0; c < D; ++c) hi[c] = x[(i + first_point) * D + c];
+            for (int c = 0; c < D; ++c) hi[c] = points[i * D + c];
         }
         const auto of = [&](const float (&v)[D], int c) {   // c the same in all lanes
             float r = v[0];
@@ -230,9 +249,29 @@ sig_tile_stream_kernel(Shape sh, const float *__restrict__ path, const float *__
                 mc[b * D + c] = v[c];
             }
         }
+        // A scalar that is not finite stays so to the end of the path.  Where a point is not a number that is as it should be; an infinity or an overflow
+        // is summed in another order here, and may be NaN only for that.  (Ahead of the last rows' stores: behind them this would wait for them.)
+        if (t0 + kTsRows >= n_inc) {
+            const auto each = [&](auto look_at) {
+#pragma unroll
+                for (int j = 2; j <= M; ++j) look_at(0, ca[j]);
+#pragma unroll
+                for (int b = 0; b < D; ++b) {
+                    look_at(b, cb[b]);
+#pragma unroll
+                    for (int c = 0; c < D; ++c) look_at(b + c, cc[b][c]);
+                }
+            };
+            float sums[4] = {};
+            each([&](int i, float v) { sums[i & 3] = __builtin_fmaf(0.f, v, sums[i & 3]); });
+            if (__builtin_expect(!(sums[0] + sums[1] + sums[2] + sums[3] == 0.f) || broken, 0)) {
+                each([&](int, float v) { infinite |= __builtin_isinf(v); });
+                if (lane == 0 && (infinite || !broken)) cold.anew = 1;
+            }
+        }
         lds_barrier();   // not __syncthreads(): the next points and the rows' stores stay in flight
         // ---- the rows, a wavefront at a time
-        char *to = reinterpret_cast<char *>(out + t0 * kS);
+        char *to = reinterpret_cast<char *>(out + int64_t(t0) * kS);
 #pragma unroll 4
         for (int t = wave * TS::kTogether; t < nt; t += TS::kWaves * TS::kTogether) {
             if (TS::kTogether > 1 && (my_row >= TS::kTogether || t + my_row >= nt)) continue;
@@ -245,6 +284,21 @@ sig_tile_stream_kernel(Shape sh, const float *__restrict__ path, const float *__
             for (int r = 0; r < TS::kSlots; ++r) *reinterpret_cast<float *>(row_to + slot[r]) = v[r];
         }
         lds_barrier();
+    }
+
+    if (__builtin_expect(cold.anew, 0)) {
+        __threadfence();   // the rows stored so far lie under those to come
+        __syncthreads();
+        const auto uniform = [](const float *p) {
+            const uint64_t v = reinterpret_cast<uint64_t>(p);
+            const unsigned high = __builtin_amdgcn_readfirstlane(unsigned(v >> 32)), low = __builtin_amdgcn_readfirstlane(unsigned(v));   // (int: would carry its sign)
+            return reinterpret_cast<float *>(uint64_t(high) << 32 | low);
+        };
+        float *to = uniform(cold.out);
+        const int n = __builtin_amdgcn_readfirstlane(cold.n_inc), thread = wave * 64 + lane, word = cold.first_word + thread;
+        if (thread < TS::kWaves * D)
+            tl_one_by_one<D, N>(uniform(cold.points), n, uniform(cold.base), uniform(cold.initial), word,
+                                [&](int64_t s, const float(&a)[N], const float(&leaf)[D]) { tl_store_word<D, N>(to + s * kS, word, a, leaf); });
     }
 }
 
@@ -282,37 +336,41 @@ hipError_t launch_tile_stream_d(const Shape &sh, const float *path, const float 
 
 }  // namespace
 
-// The longest path, in increments, up to which that is faster than what serves these calls otherwise, by the number of paths.
-//
-// Sixty-four increments take a workgroup 1 to 6 us however long the path is.  The kernels before cut a path into chunks, the more of them the longer it
-// is and the fewer paths there are (sig_api.hip, stream_chunks: 32 for up to 64 paths of 4096 increments, 16 up to 128, 8 up to 256, 4 up to 512):
-// their time grows with the square root.  One path, us, before | now: d = 3, N = 4 1000 increments 39 | 39, 4000 73 | 145, 60 000 507 | 2124; d = 2,
-// N = 4 4000 85 | 67, 8000 97 | 130; d = 5, N = 4 4000 194 | 189, 60 000 737 | 2780; d = 6, N = 4 1000 91 | 72, 60 000 639 | 4088.  Many paths of large
-// signatures are bound by the stores, which the kernels before do in whole rows: once the output is beyond the 256 MB of the last-level cache they are
-// ahead (400 paths, d = 2, N = 7, 700 increments 0.65 of their time, 1500 1.22).  Timed over 1600 shapes of up to 100 000 increments.
+// The longest path, in increments, up to which that is faster than what serves these calls otherwise, by the number of paths, and with more than 64
+// paths the largest output, in millions of scalars.
+//  - Sixty-four increments take a workgroup 1 to 6 us however long the path is.  The kernels before cut a path into chunks, the more of them the longer it
+//    is and the fewer paths there are (sig_api.hip, stream_chunks: 32 for up to 64 paths of 4096 increments, 16 up to 128, 8 up to 256, 4 up to 512):
+//    their time grows with the square root.  One path, us, before | now: d = 3, N = 4 1000 increments 39 | 39, 4000 73 | 145, 60 000 507 | 2124; d = 2,
+//    N = 4 4000 85 | 67, 8000 97 | 130; d = 5, N = 4 4000 194 | 189, 60 000 737 | 2780; d = 6, N = 4 1000 91 | 72, 60 000 639 | 4088.
+//  - Many paths of large signatures are bound by the stores, which the kernels before do in whole rows: with an output around the 256 MB of the
+//    last-level cache they are ahead (400 paths, d = 2, N = 7, 700 increments, 284 MB, 0.65 of their time, 1500 1.22; 128, d = 3, N = 5, 1000
+//    increments, 186 MB, 0.97, 1500 1.28).
+// Timed over 1600 shapes of up to 100 000 increments.
 struct LongestPath {
-    int d, N, paths_8, paths_32, paths_64, paths_128, paths_256, more;   // up to so many paths
+    int d, N, paths_8, paths_32, paths_64, paths_128, more;   // up to so many paths
+    int millions;
 };
 constexpr int kAny = 0x7fffffff;
 constexpr LongestPath kLongest[] = {
-    {2, 3, 2000, 2000, 2000, kAny, kAny, kAny},  {2, 4, 4095, 4095, kAny, kAny, kAny, kAny},   {2, 5, 4095, 4095, kAny, kAny, kAny, kAny},
-    {2, 6, 4095, 4095, 20000, kAny, 8000, 4000}, {2, 7, 20000, 20000, 40000, 2000, 1000, 900}, {2, 8, 20000, 20000, 4000, 1000, 500, 500},
-    {3, 3, 3000, 3000, 3000, kAny, kAny, kAny},  {3, 4, 1000, 1000, 1000, 1300, kAny, kAny},   {3, 5, 1000, 1000, 1000, 1000, 450, 300},
-    {3, 6, 3500, 3500, 1500, 1000, 1000, 1000},  {3, 7, 8000, 1500, 1000, 1000, 1000, 1000},   {4, 3, 1000, 1000, 1000, 3000, kAny, kAny},
-    {5, 3, 400, 400, 400, 400, 400, 400},        {5, 4, 4000, 3500, 4000, 500, 300, 300},      {5, 5, 8000, 4000, 1500, 1500, 1500, 1500},
-    {6, 3, 300, 300, 300, 300, 300, 300},        {6, 4, 1500, 2000, 2000, 2000, 2000, 2000},   {7, 3, 160, 160, 160, 160, 160, 160},
-    {7, 4, 1200, 2000, 1500, 1500, 1500, 1500},   // the others' kernels are not cut, or slower at any length (d = 4, N = 4..6; d = 6, 7 at N = 5)
+    {2, 3, 2000, 2000, 2000, kAny, kAny, kAny}, {2, 4, 4095, 4095, kAny, kAny, kAny, kAny}, {2, 5, 4095, 4095, kAny, kAny, kAny, kAny},
+    {2, 6, 4095, 4095, 20000, kAny, kAny, 300}, {2, 7, 20000, 20000, 40000, kAny, kAny, 75}, {2, 8, 20000, 20000, 4000, kAny, kAny, 55},
+    {3, 3, 3000, 3000, 3000, kAny, kAny, kAny}, {3, 4, 1000, 1000, 1000, 1300, kAny, kAny}, {3, 5, 1000, 1000, 1000, kAny, kAny, 46},
+    {3, 6, 3500, 3500, 1500, 1000, 1000, kAny}, {3, 7, 8000, 1500, 1000, 1000, 1000, kAny}, {4, 3, 1000, 1000, 1000, 3000, kAny, kAny},
+    {5, 3, 400, 400, 400, 400, 400, kAny},      {5, 4, 4000, 3500, 4000, kAny, kAny, 50},   {5, 5, 8000, 4000, 1500, 1500, 1500, kAny},
+    {6, 3, 300, 300, 300, 300, 300, kAny},      {6, 4, 1500, 2000, 2000, 2000, 2000, kAny}, {7, 3, 160, 160, 160, 160, 160, kAny},
+    {7, 4, 1200, 2000, 1500, 1500, 1500, kAny},   // the others' kernels are not cut, or slower at any length (d = 4, N = 4..6; d = 6, 7 at N = 5)
 };
 static bool short_enough(const Shape &sh)
 {
     for (const LongestPath &l : kLongest)
-        if (l.d == sh.d && l.N == sh.N)
+        if (l.d == sh.d && l.N == sh.N) {
+            if (sh.B > 64 && sh.B * sh.n_inc * sh.S > int64_t(l.millions) * 1000000) return false;
             return sh.n_inc <= (sh.B <= 8     ? l.paths_8
                                 : sh.B <= 32  ? l.paths_32
                                 : sh.B <= 64  ? l.paths_64
                                 : sh.B <= 128 ? l.paths_128
-                                : sh.B <= 256 ? l.paths_256
                                               : l.more);
+        }
     return true;
 }
 
@@ -327,7 +385,8 @@ static bool short_enough(const Shape &sh)
 // Over 400 drawn shapes of that range the rule takes 0.60 of the time and has 0.80 of the error of before.
 bool tile_stream_preferred(const Shape &sh)
 {
-    if (!sh.stream || sh.chunks != 1 || sh.rows_in_stream || !sh.from_identity || sh.d < 2 || sh.d > 7 || sh.N < 3 || sh.n_inc < 20) return false;
+    if (!sh.stream || sh.chunks != 1 || sh.rows_in_stream || !sh.from_identity || sh.d < 2 || sh.d > 7 || sh.N < 3 || sh.n_inc < 20 || sh.n_inc >= (1 << 30))
+        return false;
     if (sh.N > (sh.d == 2 ? 8 : sh.d == 3 ? 7 : sh.d == 4 ? 6 : 5) || !short_enough(sh)) return false;
     const int64_t k = 1000;
     const int64_t most = sh.d <= 3    ? (sh.d == 3 && sh.N == 5 ? 100 * k : 120 * k)   // 300 x 21, d = 3, N = 5 10.3 | 12.5

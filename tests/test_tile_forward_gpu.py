@@ -75,7 +75,7 @@ def test_a_point_that_is_not_a_number_stays_in_its_words():
 @pytest.mark.parametrize("at", [0, 1, 30, 31, 32, 58, 59])
 @pytest.mark.parametrize("d,N", [(7, 5), (5, 6), (9, 5)])
 def test_what_is_finite(d, N, at, what):
-    """The same scalars of signature and gradient are finite as in 64 bits (an infinity may come out as NaN)."""
+    """The same scalars of signature and gradient are finite as in 64 bits (an infinite gradient may come out as NaN)."""
     import torch
     x = torch.from_numpy(brownian_paths(2, 60, d, seed=3)).to("cuda:0")
     x[0, at, 1] = float(what)
@@ -83,3 +83,51 @@ def test_what_is_finite(d, N, at, what):
     assert torch.equal(torch.isfinite(s), torch.isfinite(want))
     g = sig.sig_backward(x, s, torch.ones_like(s), N)
     assert torch.equal(torch.isfinite(g), torch.isfinite(sig.sig_backward(x.double(), want, torch.ones_like(want), N)))
+
+
+# What overflows, is infinite or is no number: as one increment at a time.  The largest points make products of two increments overflow whose scalars
+# are finite, an increment overflows between two finite points, sums overflow and infinities of both signs meet.
+WILD = ["one channel", "far points", "largest", "inf", "last inf", "overflowing increment", "huge", "nan"]
+
+
+def wild_path(kind, B, L, d):
+    x = brownian_paths(B, L, d, seed=3)
+    if kind == "one channel":
+        x[1] = 1
+        x[1, :, 0] = 1e20 * brownian_paths(1, L, 1, seed=3)[0, :, 0]
+    elif kind == "far points":
+        x[1, :, 0] *= 1e20
+    elif kind == "largest":
+        x[1, L // 2:, 1] = np.finfo(np.float32).max
+    elif kind in ("inf", "nan"):
+        x[1, L // 2, 1] = float(kind)
+    elif kind == "last inf":
+        x[1, -1, 1] = np.inf
+    elif kind == "overflowing increment":
+        x[1, :L // 2, 1], x[1, L // 2:, 1] = -3e38, 3e38
+    elif kind == "huge":
+        x[1] *= 1e9
+    return x
+
+
+def assert_wild_as(got, want):
+    """Nothing that is finite, or infinite, one increment at a time is less than that (sums that come close to an overflow in another order may stay finite)."""
+    assert not np.any(np.isfinite(want) & ~np.isfinite(got)) and not np.any(np.isnan(got) & ~np.isnan(want))
+    infinite = np.isinf(got) & np.isinf(want)
+    assert np.array_equal(got[infinite], want[infinite])
+
+
+@pytest.mark.parametrize("kind", WILD)
+@pytest.mark.parametrize("d,N", [(7, 5), (5, 6), (9, 5), (13, 4)])
+def test_overflow_and_infinities_are_those_of_single_increments(d, N, kind):
+    import torch
+    B, L = 90 if d == 13 else 3, 100
+    assert sig.sig_tile_rounds(B, L, d, N) == 1
+    x = wild_path(kind, B, L, d)
+    xt = torch.from_numpy(x).to("cuda:0")
+    for basepoint in (False, True):
+        got = sig.sig_forward(xt, N, basepoint=basepoint).cpu().numpy()
+        want = sig.sig_forward(xt, N, basepoint=basepoint, variant=sig.SIG_VARIANT_TREE).cpu().numpy()
+        assert_wild_as(got, want)
+        for b in (0, B - 1):   # the other paths' results are not touched
+            assert np.all(np.isfinite(got[b])) and np.linalg.norm(got[b] - want[b]) <= TOL * np.linalg.norm(want[b])

@@ -9,6 +9,7 @@ import pytest
 import paper_2001_00706_amd as sig
 from oracle import sig_oracle as orc
 from paper_2001_00706_amd.inputs import brownian_paths
+from tests.test_tile_forward_gpu import WILD, assert_wild_as, wild_path
 
 pytestmark = pytest.mark.gpu
 
@@ -86,7 +87,7 @@ def test_what_is_finite(d, N, at, what):
 
 
 # on both sides of the longest path that is taken, by the number of paths; longer ones go in chunks
-@pytest.mark.parametrize("B,d,N,longest", [(1, 3, 4, 1000), (16, 2, 3, 2000), (65, 4, 3, 3000), (40, 3, 6, 1500), (130, 3, 5, 450), (2, 6, 4, 1500)])
+@pytest.mark.parametrize("B,d,N,longest", [(1, 3, 4, 1000), (16, 2, 3, 2000), (65, 4, 3, 3000), (40, 3, 6, 1500), (130, 3, 5, 974), (2, 6, 4, 1500)])
 def test_long_streams(B, d, N, longest):
     import torch
     for L in (longest + 1, longest + 2):
@@ -97,3 +98,39 @@ def test_long_streams(B, d, N, longest):
         want = orc.signature(x[:2].astype(np.float64), N, True)[:, some]
         for sl in orc.level_slices(d, N):
             assert np.linalg.norm(got[..., sl] - want[..., sl]) <= TOL * (L / 300) ** 0.5 * np.linalg.norm(want[..., sl])
+
+
+@pytest.mark.parametrize("kind", WILD)
+@pytest.mark.parametrize("d,N", [(2, 5), (3, 4), (4, 5), (5, 4), (7, 3)])
+def test_overflow_and_infinities_are_those_of_single_increments(d, N, kind):
+    import torch
+    B, L = 3, 120   # (streams of 128 increments and more are cut into chunks by the prefix-tree kernels)
+    x = wild_path(kind, B, L, d)
+    xt = torch.from_numpy(x).to("cuda:0")
+    for basepoint in (False, True):
+        assert sig.sig_tile_rounds(B, L, d, N, stream=True, basepoint=basepoint) == 1
+        got = sig.sig_forward(xt, N, stream=True, basepoint=basepoint).cpu().numpy()
+        want = sig.sig_forward(xt, N, stream=True, basepoint=basepoint, variant=sig.SIG_VARIANT_TREE).cpu().numpy()
+        assert_wild_as(got, want)
+        for b in (0, 2):
+            assert np.all(np.isfinite(got[b])) and np.linalg.norm(got[b] - want[b]) <= TOL * np.linalg.norm(want[b])
+
+
+@pytest.mark.parametrize("what", ["inf", "nan", "large"])
+def test_what_came_before_is_not_finite(what):
+    """`initial` with an infinity, a NaN or scalars that overflow in the products: as a product per row makes them."""
+    import torch
+    d, N, L = 4, 4, 100
+    x = torch.from_numpy(np.abs(brownian_paths(2, L, d, seed=3)).cumsum(1)).to("cuda:0")
+    before = sig.sig_forward(x, N)
+    if what == "large":
+        before[1] *= 3e38 / before[1].abs().max()
+    else:
+        before[1, 1] = float(what)
+    assert sig.sig_tile_rounds(2, L, d, N, stream=True) == 1
+    got = sig.sig_signature(x, N, stream=True, initial=before).cpu().numpy()
+    rows = sig.sig_forward(x, N, stream=True)
+    want = torch.stack([sig.sig_combine(before, rows[:, i].contiguous(), d, N) for i in range(L - 1)], 1).cpu().numpy()
+    assert np.linalg.norm(got[0] - want[0]) <= TOL * np.linalg.norm(want[0])
+    finite = np.isfinite(want[1])
+    assert np.array_equal(np.isfinite(got[1]), finite) and np.array_equal(np.isnan(got[1]), np.isnan(want[1]))
