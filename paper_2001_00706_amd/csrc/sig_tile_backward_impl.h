@@ -18,7 +18,7 @@
 // g_N below sixteen words in registers for the whole path and takes sixteen increments in about the time the prefix-tree kernels
 // take for two or three.
 //
-// The operands are cut into bfloat16 pieces (sig_tile_common.h).
+// The operands are cut into bfloat16 pieces, of which eight products are taken up to eight channels and six beyond (sig_tile_common.h).
 //
 // A block of sixteen words: a prefix of N - 3 letters and all 16 last letters (9 to 16 channels), two prefixes and 8, or four and 4.  From 9
 // channels on two wavefronts share a block, half of the letters w and j each: cotangents are linear, so each carries its share of e1 and
@@ -126,42 +126,26 @@ __device__ __forceinline__ void tl_walk(const Shape &sh, int groups, int rounds,
             for (int v = 0; v < 2; ++v) {
                 const float *src = v == 0 ? zf + i * ZR : qf + i * LW;
                 TlWords *o = ops + (tile * 2 + v) * TS::kB * 64 + ln;
-                unsigned h[8], m[8], l[8];
+                TlWords y, y2, y3;
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const TlPieces pc = tl_split(src[LW == 16 ? 8 * (c & 1) + k : k % LW]);
-                    h[k] = pc.h;
-                    m[k] = pc.m;
-                    l[k] = pc.l;
-                }
-                const auto pack = [](const unsigned(&y)[8]) {
-                    return TlWords{tl_pack(y[0], y[1]), tl_pack(y[2], y[3]), tl_pack(y[4], y[5]), tl_pack(y[6], y[7])};
-                };
-                if constexpr (LW == 4) {   // [h m] [l h] [m l] [h m]
-                    unsigned y[8];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        y[k] = c == 1 ? l[k] : c == 2 ? m[k] : h[k];
-                        y[4 + k] = c == 1 ? h[k] : c == 2 ? l[k] : m[k];
+                for (int k = 0; k < (LW == 4 ? 2 : 4); ++k) {   // two letters at a time
+                    const float *at = src + (LW == 16 ? 8 * (c & 1) : 0) + 2 * k;
+                    const TlPieces p = LW == 16 ? tl_split_pair_nearest(at[0], at[1]) : tl_split_pair(at[0], at[1]);
+                    if constexpr (LW == 4) {   // [h m] [l h] [m l] [h m]
+                        y[k] = c == 1 ? p.l : c == 2 ? p.m : p.h;
+                        y[2 + k] = c == 1 ? p.h : c == 2 ? p.l : p.m;
+                    } else if constexpr (LW == 8) {   // l h l m, h m h m
+                        y[k] = c == 1 ? p.h : c == 3 ? p.m : p.l;
+                        y2[k] = (c & 1) ? p.m : p.h;
+                    } else {   // h h l l, m m m m, h h h h
+                        y[k] = c < 2 ? p.h : p.l;
+                        y2[k] = p.m;
+                        y3[k] = p.h;
                     }
-                    o[0] = pack(y);
-                } else if constexpr (LW == 8) {   // l h l m, h m h m
-                    unsigned y[8], y2[8];
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        y[k] = c == 1 ? h[k] : c == 3 ? m[k] : l[k];
-                        y2[k] = (c & 1) ? m[k] : h[k];
-                    }
-                    o[0] = pack(y);
-                    o[64] = pack(y2);
-                } else {   // h h l l, m m m m, h h h h
-                    unsigned y[8];
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) y[k] = c < 2 ? h[k] : l[k];
-                    o[0] = pack(y);
-                    o[64] = pack(m);
-                    o[128] = pack(h);
                 }
+                o[0] = y;
+                if constexpr (LW >= 8) o[64] = y2;
+                if constexpr (LW == 16) o[128] = y3;
             }
         }
         __syncthreads();
@@ -247,40 +231,45 @@ __device__ __forceinline__ void tl_walk(const Shape &sh, int groups, int rounds,
             tl_wave_order();
             const float *g = mine + (ok ? ((lane & 15) / LW * D + letter) * kRow : 0);
             // pieces by quarter: 4 letters [h h] [h m] [m m] [l l]; 8 letters, small products first: h l m l, then h h m m
-            unsigned first[2][LW];
+            unsigned first[2][LW / 2];
 #pragma unroll
             for (int w = 0; w < LW; ++w) {
-                unsigned one[LW], two[LW];
+                unsigned one[LW / 2], two[LW / 2];   // letters j and j + 1 in a word
                 const float aw = a_v[w];
 #pragma unroll
-                for (int j = 0; j < LW; ++j) {
-                    const float v = ok && w < D && j < D ? g[w < D && j < D ? w * D + j : 0] : 0.f;
-                    if (j < D) at_end[j] = __builtin_fmaf(v, aw, at_end[j]);
-                    const TlPieces e = tl_split(v);
+                for (int j = 0; j < LW; j += 2) {
+                    float v[2];
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        v[k] = ok && w < D && j + k < D ? g[w < D && j + k < D ? w * D + j + k : 0] : 0.f;
+                        if (j + k < D) at_end[j + k] = __builtin_fmaf(v[k], aw, at_end[j + k]);
+                    }
+                    const TlPieces e = tl_split_pair(v[0], v[1]);
                     if constexpr (LW == 4) {
-                        one[j] = c < 2 ? e.h : c == 2 ? e.m : e.l;
-                        two[j] = c == 0 ? e.h : c < 3 ? e.m : e.l;
+                        one[j / 2] = c < 2 ? e.h : c == 2 ? e.m : e.l;
+                        two[j / 2] = c == 0 ? e.h : c < 3 ? e.m : e.l;
                     } else {
-                        one[j] = c == 0 ? e.h : c == 2 ? e.m : e.l;
-                        two[j] = c < 2 ? e.h : e.m;
+                        one[j / 2] = c == 0 ? e.h : c == 2 ? e.m : e.l;
+                        two[j / 2] = c < 2 ? e.h : e.m;
                     }
                 }
                 if constexpr (LW == 4) {
-                    if (w < D) AD[w < D ? w : 0][0] = TlWords{tl_pack(one[0], one[1]), tl_pack(one[2], one[3]), tl_pack(two[0], two[1]), tl_pack(two[2], two[3])};
+                    if (w < D) AD[w < D ? w : 0][0] = TlWords{one[0], one[1], two[0], two[1]};
                 } else if (w < D) {
-                    AD[w < D ? w : 0][0] = TlWords{tl_pack(one[0], one[1]), tl_pack(one[2], one[3]), tl_pack(one[4], one[5]), tl_pack(one[6], one[7])};
-                    AD[w < D ? w : 0][TS::kA - 1] = TlWords{tl_pack(two[0], two[1]), tl_pack(two[2], two[3]), tl_pack(two[4], two[5]), tl_pack(two[6], two[7])};
+                    AD[w < D ? w : 0][0] = TlWords{one[0], one[1], one[2], one[3]};
+                    AD[w < D ? w : 0][TS::kA - 1] = TlWords{two[0], two[1], two[2], two[3]};
                 }
                 if (w % 2 == 0) {
 #pragma unroll
-                    for (int j = 0; j < D; ++j) {
+                    for (int j = 0; j < LW / 2; ++j) {
                         first[0][j] = one[j];
                         first[1][j] = two[j];
                     }
                 } else {
 #pragma unroll
                     for (int j = 0; j < D; ++j) {
-                        const unsigned u = tl_pack(first[0][j], one[j]), v = tl_pack(first[1][j], two[j]);
+                        const unsigned u = j % 2 == 0 ? tl_pack_lower(first[0][j / 2], one[j / 2]) : tl_pack(first[0][j / 2], one[j / 2]);
+                        const unsigned v = j % 2 == 0 ? tl_pack_lower(first[1][j / 2], two[j / 2]) : tl_pack(first[1][j / 2], two[j / 2]);
                         if constexpr (LW == 4) {
                             AH[j][0][w / 2] = u;
                             AH[j][0][2 + w / 2] = v;
@@ -318,23 +307,24 @@ __device__ __forceinline__ void tl_walk(const Shape &sh, int groups, int rounds,
             for (int e = 0; e < 8; ++e) a8[e] = ok && !upper && k0 + e < D ? a[k0 + e < D ? k0 + e : 0] : 0.f;
 #pragma unroll
             for (int w = 0; w < HW; ++w) {
-                unsigned one[8], two[8], hone[8], htwo[8];
                 const bool wok = ok && w0 + w < D;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const bool on = wok && k0 + e < D;
-                    const float v = on ? g[on ? (w0 + w) * D + k0 + e : 0] : 0.f, h = on ? g[on ? (k0 + e) * D + w0 + w : 0] : 0.f;
-                    at_end[w] = __builtin_fmaf(h, a8[e], at_end[w]);
-                    const TlPieces pv = tl_split(v), ph = tl_split(h);
-                    one[e] = upper ? pv.h : pv.l;
-                    two[e] = upper ? pv.m : pv.h;
-                    hone[e] = upper ? ph.h : ph.l;
-                    htwo[e] = upper ? ph.m : ph.h;
+                for (int e = 0; e < 4; ++e) {   // two letters at a time
+                    float v[2], h[2];
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) {
+                        const int i = k0 + 2 * e + k;
+                        const bool on = wok && i < D;
+                        v[k] = on ? g[on ? (w0 + w) * D + i : 0] : 0.f;
+                        h[k] = on ? g[on ? i * D + w0 + w : 0] : 0.f;
+                        at_end[w] = __builtin_fmaf(h[k], a8[2 * e + k], at_end[w]);
+                    }
+                    const TlPieces pv = tl_split_pair(v[0], v[1]), ph = tl_split_pair(h[0], h[1]);
+                    AD[w][0][e] = upper ? pv.h : pv.l;
+                    AD[w][TS::kA - 1][e] = upper ? pv.m : pv.h;
+                    AH[w][0][e] = upper ? ph.h : ph.l;
+                    AH[w][TS::kA - 1][e] = upper ? ph.m : ph.h;
                 }
-                AD[w][0] = TlWords{tl_pack(one[0], one[1]), tl_pack(one[2], one[3]), tl_pack(one[4], one[5]), tl_pack(one[6], one[7])};
-                AD[w][TS::kA - 1] = TlWords{tl_pack(two[0], two[1]), tl_pack(two[2], two[3]), tl_pack(two[4], two[5]), tl_pack(two[6], two[7])};
-                AH[w][0] = TlWords{tl_pack(hone[0], hone[1]), tl_pack(hone[2], hone[3]), tl_pack(hone[4], hone[5]), tl_pack(hone[6], hone[7])};
-                AH[w][TS::kA - 1] = TlWords{tl_pack(htwo[0], htwo[1]), tl_pack(htwo[2], htwo[3]), tl_pack(htwo[4], htwo[5]), tl_pack(htwo[6], htwo[7])};
             }
         }
 #pragma unroll

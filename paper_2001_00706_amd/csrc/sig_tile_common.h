@@ -1,10 +1,14 @@
 // What the kernels that take sixteen increments at a time share: sums over the sixteen lanes of a row, and products of 32-bit numbers on
 // the matrix cores' bfloat16 instructions.
 //
-// Operands are 32-bit numbers cut into three bfloat16 pieces of 8 bits, high, middle and low (exact: each piece is the truncated rest
-// of the one before), of whose nine products the six to eight largest are summed in fp32, the small ones first; what is left
-// out is 2^-24 of a term and less.  A sum of 16 such terms is off by 7.7e-8 of its norm where a chain of fp32 multiply-adds is off by 7.4e-8.
-// The matrix cores take them at 16 times the fp32 rate, so six products are 2.7 times as fast as one fp32 instruction.
+// Operands are 32-bit numbers cut into three bfloat16 pieces of 8 bits, high, middle and low (exact: each piece is what is left of those before),
+// of whose nine products six or eight are summed in fp32, the small ones first.  The matrix cores take them at 16 times the fp32 rate, so six products
+// are 2.7 times as fast as one fp32 instruction.  Truncated, a middle piece is below 2^-7 of its number and a low one below 2^-15, of its sign.
+//  - Eight products (gradients up to eight channels) leave out the low pieces' one, 2^-30 of a term.
+//  - Six leave out up to 2^-21 of a term and 2^-23 in the mean, of the term's sign, where a multiply-add rounds off 2^-24.  The scan has a rounding per tile
+//    instead of one per increment, and is 0.77 to 0.9 as far off as the prefix tree all the same; rounded pieces, 3 to 5 % of its time, brought 0.73 to 0.84.
+//  - Gradients from nine channels on take six too, but the pieces of the increments are rounded to nearest, at most 2^-8 and 2^-17 and of either sign:
+//    1.5 2^-23 of a term is left out, and does not add up over terms.
 // An infinity has no such pieces (its rest is not a number, nor is infinity times a zero piece), and a product of two increments may overflow where the
 // scalar that it is a factor of would not.  A signature with a scalar that is not finite is therefore formed once more, one increment after the other
 // (tl_one_by_one).  A gradient that would be infinite, because a cotangent is or by overflow, comes out as NaN.
@@ -49,7 +53,7 @@ __host__ __device__ constexpr float tl_inv_factorial(int n)
 __device__ __forceinline__ unsigned tl_bits(float x) { return __builtin_bit_cast(unsigned, x); }
 __device__ __forceinline__ float tl_float(unsigned x) { return __builtin_bit_cast(float, x); }
 
-// The pieces of x, each in the upper half of a word.
+// The pieces of x, each in the upper half of a word: every piece what is left of those before, truncated.
 struct TlPieces {
     unsigned h, m, l;
 };
@@ -62,7 +66,30 @@ __device__ __forceinline__ TlPieces tl_split(float x)
     p.l = tl_bits(r - tl_float(p.m));
     return p;
 }
+// The upper or the lower halves of two words, the first's in the lower half.
 __device__ __forceinline__ unsigned tl_pack(unsigned first, unsigned second) { return __builtin_amdgcn_perm(second, first, 0x07060302u); }
+__device__ __forceinline__ unsigned tl_pack_lower(unsigned first, unsigned second) { return __builtin_amdgcn_perm(second, first, 0x05040100u); }
+// The pieces of two numbers, packed: truncated,
+__device__ __forceinline__ TlPieces tl_split_pair(float a, float b)
+{
+    const TlPieces p = tl_split(a), q = tl_split(b);
+    return {tl_pack(p.h, q.h), tl_pack(p.m, q.m), tl_pack(p.l, q.l)};
+}
+// or rounded to nearest.  (Above the largest bfloat16 the nearest is an infinity: the high piece of such a number is that largest.)
+__device__ __forceinline__ unsigned tl_nearest(float a, float b)
+{
+    typedef float F2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 B2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((F2{a, b}), B2));
+}
+__device__ __forceinline__ TlPieces tl_split_pair_nearest(float a, float b)
+{
+    constexpr float most = 3.38953139e38f;   // 2^128 - 2^120
+    const unsigned h = tl_nearest(__builtin_amdgcn_fmed3f(a, -most, most), __builtin_amdgcn_fmed3f(b, -most, most));
+    const float ra = a - tl_float(h << 16), rb = b - tl_float(h & 0xffff0000u);
+    const unsigned m = tl_nearest(ra, rb);
+    return {h, m, tl_nearest(ra - tl_float(m << 16), rb - tl_float(m & 0xffff0000u))};
+}
 
 __device__ __forceinline__ f4 tl_mfma(TlWords a, TlWords b, f4 c)
 {

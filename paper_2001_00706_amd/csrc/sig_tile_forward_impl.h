@@ -43,8 +43,9 @@ struct TileForwardShape {
     static constexpr int kAtPos = kSpan * ZR, kAtZt = 2 * kSpan * ZR, kAtQt = kAtZt + (D + 1) * kSpan, kAtOps = kAtQt + (D + 1) * kSpan;
     static constexpr int kAtTrans = kAtOps + kTiles * CT * 3 * 256, kLds = kAtTrans + kWaves * kTrans;
     static_assert(kLds * 4 <= 80 * 1024 && kAtOps % 4 == 0 && kAtZt % 4 == 0);
-    // wavefronts per SIMD: eight wavefronts with more than 128 registers have a compute unit for themselves
-    static constexpr int kOccupancy = (D == 16 && N >= 5) || (D == 7 && N == 8) ? 2 : 4;
+    // wavefronts per SIMD at least; four where a few registers more than 128 would leave a workgroup of eight wavefronts a compute unit for itself (d = 14,
+    // N = 5, 15 x 239 points: 71 us, 98 with 129)
+    static constexpr int kOccupancy = (D == 8 && N == 8) || (D == 14 && N == 5) || (D == 15 && N == 6) ? 4 : 2;
 };
 
 template <int D, int N>
