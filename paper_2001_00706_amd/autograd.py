@@ -57,8 +57,9 @@ def _signature_gradients(path, plain, basepoint_value, grad_out, args):
             fewer = binding.sig_backward_chunks_hint(B, L, d, depth, bool(basepoint), binding._dtype_of(path))
             chunks = fewer if fewer < chunks else 1
     if grad_path is None:
+        scanned = stream or binding.sig_forward_chunks_hint(B, L, d, depth, bool(basepoint), binding._dtype_of(path)) <= 1   # by _plain_signature
         grad_path = binding.sig_backward(path, plain, grad_out, depth, stream=stream, basepoint=bp,
-                                         grad_basepoint=grad_bp)
+                                         grad_basepoint=grad_bp, scanned=scanned)
     return grad_path, grad_bp
 
 

@@ -40,6 +40,7 @@ EXPORTED_SYMBOLS = (
     "sig_forward_chunked_static_max_bytes",
     "sig_combine",
     "sig_backward",
+    "sig_backward_scanned",
     "sig_backward_chunked",
     "sig_backward_chunked_workspace_bytes",
     "sig_backward_chunks_hint",
@@ -171,6 +172,8 @@ def load_library() -> ctypes.CDLL:
         lib.sig_combine.argtypes = [vp, vp, i64, i32, i32, i32, vp, vp]
         lib.sig_backward.restype = i32
         lib.sig_backward.argtypes = [vp, vp, vp, i64, i64, i32, i32, i32, i32, vp, i32, vp, vp, vp, i64, vp]
+        lib.sig_backward_scanned.restype = i32
+        lib.sig_backward_scanned.argtypes = lib.sig_backward.argtypes
         lib.sig_backward_chunked.restype = i32
         lib.sig_backward_chunked.argtypes = [vp, vp, i64, i64, i32, i32, i32, vp, i32, i32, vp, vp, vp, i64, vp]
         lib.sig_backward_chunked_workspace_bytes.restype = i64
@@ -401,7 +404,7 @@ def _basepoint_args(path, basepoint):
 
 
 def sig_backward(path, sig, grad_out, N: int, stream: bool = False, basepoint=False,
-                 grad_path=None, workspace=None, grad_basepoint=None):
+                 grad_path=None, workspace=None, grad_basepoint=None, scanned: bool = False):
     """Gradient with respect to `path` of a loss whose gradient with respect to
     `sig = sig_forward(path, N, stream, basepoint)` is `grad_out`; all GPU torch tensors.
 
@@ -409,6 +412,7 @@ def sig_backward(path, sig, grad_out, N: int, stream: bool = False, basepoint=Fa
     (then `sig` comes from `sig_signature`); `grad_basepoint`, if given, receives its gradient.
     `workspace` is a uint8 GPU tensor of at least `sig_backward_workspace_bytes(...)` bytes; one is
     allocated through torch when the call needs it and none is given.
+    `scanned`: `sig` is just what `sig_forward` or `sig_signature` returned for this batch, which may save time.
     """
     import torch
 
@@ -440,7 +444,8 @@ def sig_backward(path, sig, grad_out, N: int, stream: bool = False, basepoint=Fa
             workspace = torch.empty(need, dtype=torch.uint8, device=path.device)
         ws_ptr, ws_bytes = (workspace.data_ptr(), workspace.numel() * workspace.element_size()) \
             if workspace is not None else (0, 0)
-        status = int(load_library().sig_backward(
+        lib = load_library()
+        status = int((lib.sig_backward_scanned if scanned else lib.sig_backward)(
             path.data_ptr(), sig.data_ptr(), grad_out.data_ptr(), B, L, d, N, int(stream), bp_flag,
             bp_value.data_ptr() if bp_value is not None else 0, dtype, grad_path.data_ptr(),
             grad_basepoint.data_ptr() if grad_basepoint is not None else 0,

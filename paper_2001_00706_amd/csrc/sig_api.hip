@@ -67,6 +67,7 @@ sig_status make_shape(int64_t B, int64_t L, int d, int N, int stream, int basepo
     sh.chunks = 1;
     sh.rows_in_stream = 0;
     sh.from_identity = 1;
+    sh.scanned = 0;
     sh.chunk_len = 0;
     sh.n_inc = basepoint ? L : L - 1;
     // path elements B*L*d and output elements B*[n_inc*]S must stay below kMaxElems
@@ -96,6 +97,7 @@ sig_status make_rows_shape(int64_t rows, int d, int N, sig::Shape &sh)
     sh.chunks = 1;
     sh.rows_in_stream = 0;
     sh.from_identity = 1;
+    sh.scanned = 0;
     sh.chunk_len = 0;
     return SIG_OK;
 }
@@ -376,9 +378,9 @@ int64_t sig_backward_workspace_bytes(int64_t B, int64_t L, int d, int N, int str
     return sig::backward_workspace_bytes(sh, dtype);
 }
 
-sig_status sig_backward(const void *path, const void *sig, const void *grad_out, int64_t B, int64_t L, int d, int N,
-                        int stream, int basepoint, const void *basepoint_value, sig_dtype dtype, void *grad_path,
-                        void *grad_basepoint, void *workspace, int64_t workspace_bytes, hipStream_t hip_stream)
+static sig_status backward_call(const void *path, const void *sig, const void *grad_out, int64_t B, int64_t L, int d, int N, int stream,
+                                int basepoint, const void *basepoint_value, sig_dtype dtype, void *grad_path, void *grad_basepoint,
+                                void *workspace, int64_t workspace_bytes, hipStream_t hip_stream, int scanned)
 {
     if (dtype != SIG_F32 && dtype != SIG_F64) return SIG_ERR_INVALID_ARG;
     sig::Shape sh;
@@ -388,6 +390,7 @@ sig_status sig_backward(const void *path, const void *sig, const void *grad_out,
     if (path == nullptr || sig == nullptr || grad_out == nullptr || grad_path == nullptr) return SIG_ERR_INVALID_ARG;
     if (!sh.basepoint && (basepoint_value != nullptr || grad_basepoint != nullptr)) return SIG_ERR_INVALID_ARG;
     sh.basepoint_value = basepoint_value;
+    sh.scanned = scanned;
     const int64_t need = sig::backward_workspace_bytes(sh, dtype);
     if (need < 0) return SIG_ERR_UNSUPPORTED;
     if (need > 0 && (workspace == nullptr || workspace_bytes < need)) return SIG_ERR_INVALID_ARG;
@@ -400,6 +403,22 @@ sig_status sig_backward(const void *path, const void *sig, const void *grad_out,
                                        static_cast<const double *>(grad_out), static_cast<double *>(grad_path),
                                        static_cast<double *>(grad_basepoint), workspace, workspace_bytes, hip_stream);
     return err == hipSuccess ? SIG_OK : SIG_ERR_HIP;
+}
+
+sig_status sig_backward(const void *path, const void *sig, const void *grad_out, int64_t B, int64_t L, int d, int N,
+                        int stream, int basepoint, const void *basepoint_value, sig_dtype dtype, void *grad_path,
+                        void *grad_basepoint, void *workspace, int64_t workspace_bytes, hipStream_t hip_stream)
+{
+    return backward_call(path, sig, grad_out, B, L, d, N, stream, basepoint, basepoint_value, dtype, grad_path, grad_basepoint, workspace,
+                         workspace_bytes, hip_stream, 0);
+}
+
+sig_status sig_backward_scanned(const void *path, const void *sig, const void *grad_out, int64_t B, int64_t L, int d, int N,
+                                int stream, int basepoint, const void *basepoint_value, sig_dtype dtype, void *grad_path,
+                                void *grad_basepoint, void *workspace, int64_t workspace_bytes, hipStream_t hip_stream)
+{
+    return backward_call(path, sig, grad_out, B, L, d, N, stream, basepoint, basepoint_value, dtype, grad_path, grad_basepoint, workspace,
+                         workspace_bytes, hip_stream, 1);
 }
 
 // Layout of a gradient computed stretch by stretch: K stretches of m increments per path.  The workspace holds, each 256-byte

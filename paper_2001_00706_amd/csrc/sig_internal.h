@@ -31,6 +31,8 @@ struct Shape {
     // Gradient calls: 0 when the signature handed in belongs to a longer path of which the rows are stretches (the
     // walk back then starts from that signature and must not assume that a row's own increments make it up).
     int from_identity;
+    // Gradient calls: 1 when the signature handed in is what sig_forward wrote for this very call, so that its roundings are known.
+    int scanned;
     int64_t pw[SIG_MAX_DEPTH + 1];   // pw[k] = d^k, k = 0..N
     int64_t off[SIG_MAX_DEPTH + 2];  // off[k] = offset of level k (1-based) in a signature; off[N+1] = S
 };
@@ -212,7 +214,7 @@ int tree_split_stretches(const Shape &sh, sig_dtype dtype);   // how many (1: th
 // Final mode, sixteen increments at a time with the two deepest levels on the matrix cores (fp32, whole paths, d = 5..8 at N = 4..8, d = 9..16 at
 // N = 4..6, any alignment; see sig_tile_forward_impl.h).
 bool tile_forward_preferred(const Shape &sh);
-bool tile_forward_certain(const Shape &sh);   // (where tile_backward_preferred holds)
+bool tile_forward_certain(const Shape &sh);   // sig_forward does so for certain (where tile_backward_preferred holds)
 // a lane per increment in stream mode (sig_tile_stream.hip); `initial` [B][S]: the signature of what came before, or null
 bool tile_stream_preferred(const Shape &sh);
 hipError_t launch_tile_stream_f32(const Shape &sh, const float *path, const float *initial, float *out, hipStream_t st);

@@ -34,8 +34,8 @@
 // The signature handed in carries the rounding of the scan that made it; walked back by other sums it does not end at zero, and the
 // first points' gradients are off by what is left.  From depth 5 on the levels up to N - 2 are therefore formed anew ahead of the walk, by the
 // same sums (a tenth of the time; 8 paths of 128 points, d = 4, N = 8: off by 3.2e-6 without, 1.35e-6 with, 1.62e-6 on the prefix-tree kernels).
-// Where sig_tile_forward_impl.h makes the signature these are the sums it was made by, and nothing is gained by forming them again: the gradients are
-// the same bits (32 x 128 points, d = N = 7: 513 us with, 447 without; 100 x 900, d = 9, N = 5 1375 | 1195).
+// Where the caller says that sig_forward made the signature (Shape::scanned), and it did so in sig_tile_forward_impl.h, these are the sums it was made by, and
+// nothing is gained by forming them again: the gradients are the same bits (32 x 128 points, d = N = 7: 513 us with, 447 without; 100 x 900, d = 9, N = 5 1375 | 1195).
 #ifndef SIG_TILE_BACKWARD_IMPL_H_
 #define SIG_TILE_BACKWARD_IMPL_H_
 
@@ -607,7 +607,7 @@ hipError_t launch_tile_backward_dn(const Shape &sh, const float *path, const flo
     const int groups = tile_groups_dn<D, N>(sh.B, rounds);
     if (!grid_holds(sh.B * groups, 64 * TS::kWaves)) return hipErrorNotSupported;
     const dim3 grid(unsigned(sh.B * groups)), threads(64 * TS::kWaves);
-    const bool anew = !tile_forward_certain(sh);
+    const bool anew = !sh.scanned || !tile_forward_certain(sh);
     if (sh.from_identity)
         hipLaunchKernelGGL((sig_tile_backward_kernel<D, N, true>), grid, threads, 0, st, sh, groups, rounds, anew, path, sig, gout, partial);
     else

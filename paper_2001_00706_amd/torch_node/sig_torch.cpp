@@ -172,9 +172,12 @@ variable_list signature_gradients(const at::Tensor &path, const at::Tensor &plai
     }
     const int64_t need = sig_backward_workspace_bytes(B, L, int(d), N, int(c.stream), bp, type);
     const at::Tensor ws = need > 0 ? bytes_like(path, need) : at::Tensor();
-    const sig_status status = sig_backward(path.data_ptr(), plain.data_ptr(), grad.data_ptr(), B, L, int(d), N, int(c.stream), bp,
-                                           or_null(value), type, grad_path.data_ptr(), grad_value_at, need > 0 ? ws.data_ptr() : nullptr,
-                                           need, stream_of(path));
+    // `plain` is as the scan left it, unless plain_signature went by stretches
+    const bool scanned = c.stream || sig_forward_chunks_hint(B, L, int(d), N, bp, type) <= 1;
+    const sig_status status = (scanned ? sig_backward_scanned : sig_backward)(path.data_ptr(), plain.data_ptr(), grad.data_ptr(), B, L, int(d), N,
+                                                                              int(c.stream), bp, or_null(value), type, grad_path.data_ptr(),
+                                                                              grad_value_at, need > 0 ? ws.data_ptr() : nullptr, need,
+                                                                              stream_of(path));
     if (status != SIG_OK) raise_status(status);
     return {grad_path, grad_value};
 }
