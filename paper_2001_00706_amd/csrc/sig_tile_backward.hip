@@ -72,8 +72,8 @@ double tile_backward_us(const Shape &sh)
 // words.  At 9 channels and more that is longer from 32 increments on, up to a few channels only while few paths leave the chip idle: a block of sixteen
 // words has room for 10 at 5 channels, 12 at 6, and three wavefronts in four would multiply zeros (tile | before, us: 256 x 100 points, d = 6,
 // N = 4: 18 | 53; 64 x 200, d = 8, N = 5: 40 | 154; 256 x 1024, d = 16, N = 4: 770 | 1265; 1 x 1000, d = 13, N = 4: 128 | 985; 32 x 128,
-// d = N = 7: 447 | 505; against the rule 648 x 80, d = 5, N = 6: 320 | 187).  Over 650 shapes of 3 to 16 channels the rule is 1.3 % off the better one of the
-// two, and takes 0.60 of the time without these kernels.
+// d = N = 7: 430 | 505; against the rule 648 x 80, d = 5, N = 6: 320 | 187).  Over 650 shapes of 3 to 16 channels the rule is 1.3 % off the better one of the
+// two, and takes 0.60 of the time without these kernels; of 240 shapes at its line the worst is 1.03 (49 x 123, d = 7, N = 6: 109 | 106).
 bool tile_backward_preferred(const Shape &sh)
 {
     if (sh.stream || sh.n_inc < 24 || sh.S >= (int64_t(1) << 31)) return false;
@@ -82,6 +82,9 @@ bool tile_backward_preferred(const Shape &sh)
     // (d = 16, N = 4 has sig_backward_d16.hip for short paths: 256 x 31 points 60 | 52, 64 x 17 16 | 30)
     if (sh.d == 16 && sh.N == 4) return sh.n_inc >= 48 || sh.B <= 64;
     if (sh.d > 8) return sh.n_inc >= 32 || sh.B * sh.pw[sh.N - 3] <= 512;
+    // (from 641 paths of d = 4, N = 6 on a SIMD's fourth set of wavefronts is nearly empty, which the fit does not see: 640 x 80 points 53.8 | 57.1, 680 x 80
+    // 61.8 | 56.7, 680 x 400 248 | 266)
+    if (sh.d == 4 && sh.N == 6 && sh.B > 640 && sh.B <= 768 && sh.n_inc < 200) return false;
     // at d = 4, N = 6 many paths have a kernel of their own, sig_backward_d4n6.hip
     const double ct = sh.d <= 4 ? (sh.N == 6 && sh.d == 4 && sh.B > 768 ? 0.19 : 0.27)
                                 : sh.d == 5 ? 0.33 : sh.d == 6 ? 0.37 : sh.d == 7 ? 0.47 : 0.44;

@@ -450,3 +450,5 @@ def test_tiles_are_left_to_others_where_a_grid_does_not_hold_them(lib):
     assert h(64, 101, 5, 4, stream=True, basepoint=True) == 1 and h(64, 15, 5, 4, stream=True) == 0
     assert h(64, 101, 5, 4, stream=True, gradient=True) == 0
     assert h(2, 1, 3, 4) == -1 and h(2, 9, 0, 4) == -1
+    # d = 4, N = 6 between 641 and 768 paths: the prefix tree up to 199 increments
+    assert h(640, 81, 4, 6, gradient=True) > 0 and h(641, 200, 4, 6, gradient=True) == 0 and h(768, 201, 4, 6, gradient=True) > 0
