@@ -1047,9 +1047,9 @@ hipError_t launch_log_backward(const Shape &sh, const T *x, const T *g, T *gx, v
     const hipError_t whole = launch_log_backward_whole<T>(sh, x, g, gx, st);
     if (whole != hipErrorNotSupported) return whole;
     if (use_fused(sh, ws, sizeof(T))) {
-        // With two signatures a compute unit or fewer, 512 threads for more than 768 scalars: what the kernel waits for is the chain of
-        // passes between its barriers, of which there are half as many (256 | 512 | 1024 threads, 256 signatures: d = 6, N = 4 25.6 | 21.1 | 21.1 us,
-        // d = 12, N = 3 19.6 | 13.6 | 12.8, d = 3, N = 6 45 | 41 | 45, d = 5, N = 3 10.1 | 10.2 | 11.4; 1024 signatures 29.9 | 29.0 | 49.5 at d = 6, N = 4).
+        // Left to this kernel up to 2048 scalars are depth 2 and a single channel.  With two signatures a compute unit or fewer, 512 threads for more than 768
+        // scalars (28 channels): what it waits for is the chain of passes between its barriers, of which there are half as many (256 | 512 threads, us,
+        // 256 signatures: d = 44 10.2 | 7.6, fp64 11.0 | 8.4, d = 28 7.6 | 7.6; 1024: d = 44 12.6 | 10.4, d = 28 7.8 | 8.3, fp64 8.7 | 11.7).
         const int nt = fused_threads(sh) == 1024 ? 1024 : sh.S > 768 && sh.B <= 512 ? 512 : 256;
         const size_t fused_lds = fused_lds_bytes(sh, ws, sizeof(T), nt);
         auto kernel = nt == 256 ? log_bwd_fused_kernel<T, 256> : nt == 512 ? log_bwd_fused_kernel<T, 512> : log_bwd_fused_kernel<T, 1024>;

@@ -76,7 +76,7 @@ double tile_backward_us(const Shape &sh)
 // two, and takes 0.60 of the time without these kernels; of 240 shapes at its line the worst is 1.03 (49 x 123, d = 7, N = 6: 109 | 106).
 bool tile_backward_preferred(const Shape &sh)
 {
-    if (sh.stream || sh.n_inc < 24 || sh.S >= (int64_t(1) << 31)) return false;
+    if (sh.stream || sh.n_inc < 24 || sh.S >= (int64_t(1) << 31) || (!sh.from_identity && sh.d <= 8)) return false;
     const int workgroups = groups(sh);   // of up to four wavefronts
     if (workgroups == 0 || !grid_holds(sh.B * workgroups, 256)) return false;
     // (d = 16, N = 4 has sig_backward_d16.hip for short paths: 256 x 31 points 60 | 52, 64 x 17 16 | 30)

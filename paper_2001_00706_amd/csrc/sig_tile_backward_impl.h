@@ -608,10 +608,14 @@ hipError_t launch_tile_backward_dn(const Shape &sh, const float *path, const flo
     if (!grid_holds(sh.B * groups, 64 * TS::kWaves)) return hipErrorNotSupported;
     const dim3 grid(unsigned(sh.B * groups)), threads(64 * TS::kWaves);
     const bool anew = !sh.scanned || !tile_forward_certain(sh);
-    if (sh.from_identity)
+    if (sh.from_identity) {
         hipLaunchKernelGGL((sig_tile_backward_kernel<D, N, true>), grid, threads, 0, st, sh, groups, rounds, anew, path, sig, gout, partial);
-    else
-        hipLaunchKernelGGL((sig_tile_backward_kernel<D, N, false>), grid, threads, 0, st, sh, groups, rounds, anew, path, sig, gout, partial);
+    } else {   // stretches: up to eight channels they have kernels of their own (tree_stretches_supported)
+        if constexpr (D > 8)
+            hipLaunchKernelGGL((sig_tile_backward_kernel<D, N, false>), grid, threads, 0, st, sh, groups, rounds, anew, path, sig, gout, partial);
+        else
+            return hipErrorNotSupported;
+    }
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     return launch_increment_sums<float>(sh, groups, partial, gpath, gbase, st);
