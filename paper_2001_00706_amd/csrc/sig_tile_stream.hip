@@ -354,10 +354,10 @@ constexpr int kAny = 0x7fffffff;
 constexpr LongestPath kLongest[] = {
     {2, 3, 2000, 2000, 2000, kAny, kAny, kAny}, {2, 4, 4095, 4095, kAny, kAny, kAny, kAny}, {2, 5, 4095, 4095, kAny, kAny, kAny, kAny},
     {2, 6, 4095, 4095, 20000, kAny, kAny, 300}, {2, 7, 20000, 20000, 40000, kAny, kAny, 75}, {2, 8, 20000, 20000, 4000, kAny, kAny, 55},
-    {3, 3, 3000, 3000, 3000, kAny, kAny, kAny}, {3, 4, 1000, 1000, 1000, 1300, kAny, kAny}, {3, 5, 1000, 1000, 1000, kAny, kAny, 46},
+    {3, 3, 3000, 3000, 3000, kAny, kAny, kAny}, {3, 4, 1000, 1000, 1000, 1300, kAny, kAny}, {3, 5, 1000, 1000, 1000, kAny, kAny, 50},
     {3, 6, 3500, 3500, 1500, 1000, 1000, kAny}, {3, 7, 8000, 1500, 1000, 1000, 1000, kAny}, {4, 3, 1000, 1000, 1000, 3000, kAny, kAny},
     {5, 3, 400, 400, 400, 400, 400, kAny},      {5, 4, 4000, 3500, 4000, kAny, kAny, 50},   {5, 5, 8000, 4000, 1500, 1500, 1500, kAny},
-    {6, 3, 300, 300, 300, 300, 300, kAny},      {6, 4, 1500, 2000, 2000, 2000, 2000, kAny}, {7, 3, 160, 160, 160, 160, 160, kAny},
+    {6, 3, 300, 300, 300, 300, 300, kAny},      {6, 4, 1500, 2000, 2000, 2000, 2000, 120}, {7, 3, 160, 160, 160, 160, 160, kAny},
     {7, 4, 1200, 2000, 1500, 1500, 1500, kAny},   // the others' kernels are not cut, or slower at any length (d = 4, N = 4..6; d = 6, 7 at N = 5)
 };
 static bool short_enough(const Shape &sh)

@@ -89,7 +89,7 @@ def test_what_is_finite(d, N, at, what):
 
 
 # on both sides of the longest path that is taken, by the number of paths; longer ones go in chunks
-@pytest.mark.parametrize("B,d,N,longest", [(1, 3, 4, 1000), (16, 2, 3, 2000), (65, 4, 3, 3000), (40, 3, 6, 1500), (130, 3, 5, 974), (2, 6, 4, 1500)])
+@pytest.mark.parametrize("B,d,N,longest", [(1, 3, 4, 1000), (16, 2, 3, 2000), (65, 4, 3, 3000), (40, 3, 6, 1500), (130, 3, 5, 1059), (2, 6, 4, 1500)])
 def test_long_streams(B, d, N, longest):
     import torch
     for L in (longest + 1, longest + 2):
