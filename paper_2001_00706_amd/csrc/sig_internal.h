@@ -22,6 +22,8 @@ struct Shape {
     // and n_inc increments; chunk c folds in the increments c*chunk_len .. min((c+1)*chunk_len, n_inc) - 1 and
     // basepoint_value is indexed by path.  chunks == 1: B counts paths.
     int chunks;
+    // Gradient calls: 1 when the signature handed in is what sig_forward wrote for this very call, so that its roundings are known.
+    int scanned;
     int64_t chunk_len;
     // Chunked scans whose rows live inside a stream-mode output [paths][n_inc][S] (served by the small-state, prefix-tree,
     // row and many-channel families): with stream == 0 a chunk that has increments writes its signature to the row of its
@@ -31,8 +33,6 @@ struct Shape {
     // Gradient calls: 0 when the signature handed in belongs to a longer path of which the rows are stretches (the
     // walk back then starts from that signature and must not assume that a row's own increments make it up).
     int from_identity;
-    // Gradient calls: 1 when the signature handed in is what sig_forward wrote for this very call, so that its roundings are known.
-    int scanned;
     int64_t pw[SIG_MAX_DEPTH + 1];   // pw[k] = d^k, k = 0..N
     int64_t off[SIG_MAX_DEPTH + 2];  // off[k] = offset of level k (1-based) in a signature; off[N+1] = S
 };
