@@ -116,14 +116,17 @@ int64_t sig_fused_fmas(int d, int N);
  * N > SIG_MAX_DEPTH, L < 2 (L < 1 with basepoint), an unknown dtype; SIG_ERR_OVERFLOW if a
  * size overflows; SIG_ERR_HIP if the launch failed.  B == 0 is SIG_OK and enqueues nothing.
  * Results are deterministic: the same inputs give bit-identical outputs on every call.
+ * A point that is not finite makes the signature's scalars infinite or NaN as folding in one increment after the other does; so does overflow, but
+ * where a sum comes near the largest number the order of its terms, which differs between kernels, decides.
  * In final mode sig_forward has no workspace for partial results: the vector kernels cut the paths of a small batch into stretches
  * that share a workgroup (up to 256 in fp32 and 128 in fp64, of 8 increments and more; the values then differ from an end-to-end
  * scan by rounding only), everything else scans a path (or a word-prefix shard of it) from end to end.  A few very long paths (B * shards
  * far below the number of compute units, L in the tens of thousands) are served many times faster by sig_forward_chunked
- * (sig_forward_chunks_hint says when, and into how many chunks).  In stream mode the output itself has room for
- * partial results, and up to 512 paths of at least 128 increments are cut into chunks internally where the kernel
- * family gains from it (everything but the d = 4 matrix-core kernels); the values then differ from an end-to-end
- * scan by rounding only, and `out` is read as well as written while the call runs. */
+ * (sig_forward_chunks_hint says when, and into how many chunks).  In fp32 stream mode with 2 to 7 channels, paths of
+ * up to some hundred to some thousand increments (by shape) are scanned 64 increments at a time in one launch.  Otherwise the output itself
+ * has room for partial results, and up to 512 paths of at least 128 increments are cut into chunks internally where the kernel
+ * family gains from it (everything but the d = 4 matrix-core kernels); `out` is then read as well as written while the call runs.
+ * Either way the values differ from an end-to-end scan by rounding only. */
 sig_status sig_forward(const void *path, int64_t B, int64_t L, int d, int N,
                        int stream, int basepoint, sig_dtype dtype,
                        void *out, hipStream_t hip_stream);
@@ -136,8 +139,9 @@ sig_status sig_forward_variant(const void *path, int64_t B, int64_t L, int d, in
 /* sig_forward (final mode) as a parallel reduction over the length of the path (section 5.1: the scan is a
  * reduction with respect to an associative operation, so it may be split into chunks): every path is cut into
  * `chunks` stretches of ceil(n_inc / chunks) increments, all B * chunks stretches are scanned at once by the
- * kernels of sig_forward, and neighbouring results are joined pairwise by sig_combine's product (Chen's identity,
- * eq. "grouplike") in log2(chunks) rounds.  Worth it when B alone cannot fill the device and L is long.
+ * kernels of sig_forward, and the results are joined by sig_combine's product (Chen's identity, eq. "grouplike"): eight neighbours at
+ * a time for d = 2..8 where a path has many of them or large ones, pairs otherwise.  Where products overflow, which scalars become
+ * infinite and which NaN depends on the order.  Worth it when B alone cannot fill the device and L is long.
  * At depth 2 nothing is multiplied: level 2 is a plain sum over the increments of (midpoint - first point) (x)
  * increment (sections 2.1, 2.2), so every stretch adds up its own terms and a second launch adds the stretches.
  *   chunks     a power of two, 2 .. 65536 (stretches past the end of a short path are empty and count as the
@@ -289,7 +293,8 @@ sig_status sig_invert(const void *sig, int64_t rows, int d, int N, sig_dtype dty
  *   initial    DEVICE pointer [B][S] or NULL: the signature of the data that came before this path (whose last
  *              point is this path's first point, or its basepoint).  The result is initial [x] Sig(path), in stream
  *              mode for every prefix: the signature of everything so far (section 5.5, "keeping the signature
- *              up-to-date").  Applied by one product per output signature, in place, after the scan.
+ *              up-to-date").  Applied by one product per output signature, in place, after the scan, or where the stream
+ *              kernel for 64 increments at a time serves the call, as what that scan begins with.
  *   inverse    != 0: every signature written is replaced by its group inverse (section 5.4), after `initial` has
  *              been applied; `initial` itself is always a plain (not inverted) signature.
  * Everything else, and the errors, as for sig_forward; with `initial` or `inverse`, S must be below 2^31. */
@@ -335,7 +340,7 @@ sig_status sig_log_words(const void *sig, int64_t rows, int d, int N, const int6
  *   sig, grad_log  DEVICE pointers [rows][S], read only.   grad_sig  DEVICE pointer [rows][S], overwritten; must
  *              not overlap the other two.
  *   workspace  DEVICE pointer, 16-byte aligned, at least sig_log_backward_workspace_bytes(...) bytes (0 for N = 1
- *              and for signatures small enough for the single-launch kernel; then it may be NULL); contents
+ *              and for signatures small enough for one of the single-launch kernels; then it may be NULL); contents
  *              undefined on return.
  * Errors as for sig_combine; a missing, short or misaligned workspace is SIG_ERR_INVALID_ARG. */
 sig_status sig_log_backward(const void *sig, const void *grad_log, int64_t rows, int d, int N, sig_dtype dtype,
@@ -369,13 +374,15 @@ sig_status sig_lyndon_scatter(const void *grad_logsig, int64_t rows, int d, int 
  *   workspace  DEVICE pointer to at least sig_backward_workspace_bytes(...) bytes, 16-byte aligned, contents
  *              irrelevant on entry and undefined on return; may be NULL when that size is 0.  Calls that overlap
  *              in time must not share a workspace.
- * Enqueued on `hip_stream`, no wait.  Served: d <= 16 at the depths of the register-resident and prefix-tree
- * kernels; any d at N = 2..9 (up to 204 channels, 102 in fp64; depth 2 in final mode by a closed form up to d = 122,
+ * Enqueued on `hip_stream`, no wait.  Served: d <= 16 at the depths of the register-resident, tile (sixteen increments at a time:
+ * fp32, final mode, d = 3..16 from depth 4 on) and prefix-tree kernels; any d at N = 2..9 (up to 204 channels, 102 in fp64; depth 2 in final mode by a closed form up to d = 122,
  * 85 in fp64); everything else with d <= 64 and S < 2^30 on a generic kernel that is two to three orders of
  * magnitude slower per increment; otherwise SIG_ERR_UNSUPPORTED.  Other errors as for sig_forward; a missing or
  * short workspace is SIG_ERR_INVALID_ARG.  Deterministic: the same call gives the same bits.  The number of paths has a
  * part in which kernel serves a call and in how its sums are grouped, so a path's gradient may differ in the last bits
- * between batches of different sizes. */
+ * between batches of different sizes; and with `sig` made in a batch of another size or otherwise than by sig_forward, whose roundings
+ * the walk back does not meet again, the first points' gradients may be a fifth further off.  Where a cotangent is not finite or a
+ * gradient overflows, the tile kernels give NaN where others may give an infinity. */
 sig_status sig_backward(const void *path, const void *sig, const void *grad_out, int64_t B, int64_t L, int d, int N,
                         int stream, int basepoint, const void *basepoint_value, sig_dtype dtype, void *grad_path,
                         void *grad_basepoint, void *workspace, int64_t workspace_bytes, hipStream_t hip_stream);
@@ -430,8 +437,9 @@ int sig_backward_chunks_hint(int64_t B, int64_t L, int d, int N, int basepoint, 
 int sig_backward_chunks_fastest(int64_t B, int64_t L, int d, int N, int basepoint, sig_dtype dtype);
 
 /* Name of the kernel family that `variant` resolves to for this shape ("generic",
- * "mfma_d4", ...), or "unsupported" / "invalid".  The string is static.  Final mode calls of "tree", "row_stream" and "small" whose
- * paths are cut inside a workgroup keep the name of the family that would serve them in one piece. */
+ * "mfma_d4", ...), or "unsupported" / "invalid".  The string is static.  Calls whose paths are cut inside
+ * a workgroup or taken sixteen or sixty-four increments at a time (sig_tile_rounds) keep the name of the family that would serve them
+ * otherwise. */
 const char *sig_variant_name(int64_t B, int64_t L, int d, int N, int stream, int basepoint,
                              sig_dtype dtype, sig_variant variant);
 

@@ -403,13 +403,13 @@ int64_t backward_workspace_bytes(const Shape &sh, sig_dtype dtype)
 {
     const StreamStretches cut = stream_stretches(sh, dtype);
     if (cut.K > 1) return cut.bytes;
-    // signatures of up to 8 channels and depth 9 never reach the generic kernel
     if (dtype == SIG_F32 && tile_backward_preferred(sh)) {   // at least what the prefix-tree kernels would take: streams kept whole report the same
         const int64_t tree = sh.d <= 8 ? tree_backward_workspace_bytes(sh, dtype) : 0, tile = tile_backward_workspace_bytes(sh);
         return tree > tile ? tree : tile;
     }
     if (backward_n2_supported(sh, dtype)) return 0;   // depth 2 in final mode: a closed form, nothing to keep
     if (wide_backward_preferred(sh, dtype)) return wide_backward_workspace_bytes(sh, dtype);
+    // signatures of up to 8 channels and depth 9 never reach the generic kernel
     if (tree_backward_supported(sh)) return tree_backward_workspace_bytes(sh, dtype);
     if (wide_backward_supported(sh, dtype)) return wide_backward_workspace_bytes(sh, dtype);   // beyond 16 channels
     BackwardPlan pl;

@@ -276,7 +276,8 @@ struct Tree {
     {
         T *from = C, *other = spare;
         int64_t n = K;
-        // eight at a time: three rounds in the time of one and a half
+        // eight at a time: three rounds in the time of one and a half (400 shapes of up to 512 paths of 1024 chunks: 0.88 of a call's time, the worst
+        // 23 paths of 2817 points, d = 5, N = 6, in 64 chunks 167 | 173 us)
         while (n > 1 && !top_fits(sh, paths, n)) {
             const int R = n >= 8 ? 8 : int(n);
             T *to = n > R ? other : out;

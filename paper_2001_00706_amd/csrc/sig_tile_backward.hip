@@ -70,10 +70,11 @@ double tile_backward_us(const Shape &sh)
 // Where they are used: from 24 increments on (fewer leave most of a tile, or of the time to set it up, unused), and where the prefix-tree
 // kernels take longer.  Those wait 0.4 us for an increment as long as the chip is not full; once it is, they take ct for an increment of 64
 // words.  At 9 channels and more that is longer from 32 increments on, up to a few channels only while few paths leave the chip idle: a block of sixteen
-// words has room for 10 at 5 channels, 12 at 6, and three wavefronts in four would multiply zeros (tile | before, us: 256 x 100 points, d = 6,
-// N = 4: 18 | 53; 64 x 200, d = 8, N = 5: 40 | 154; 256 x 1024, d = 16, N = 4: 770 | 1265; 1 x 1000, d = 13, N = 4: 128 | 985; 32 x 128,
-// d = N = 7: 430 | 505; against the rule 648 x 80, d = 5, N = 6: 320 | 187).  Over 650 shapes of 3 to 16 channels the rule is 1.3 % off the better one of the
-// two, and takes 0.60 of the time without these kernels; of 240 shapes at its line the worst is 1.03 (49 x 123, d = 7, N = 6: 109 | 106).
+// words has room for 10 at 5 channels, 12 at 6, and three wavefronts in four would multiply zeros (tile | before, us: 256 x 101 points, d = 6,
+// N = 4: 17 | 53; 64 x 201, d = 8, N = 5: 46 | 156; 256 x 1024, d = 16, N = 4: 748 | 1268; 1 x 1001, d = 13, N = 4: 126 | 986; 32 x 128,
+// d = N = 7: 427 | 504; against the rule 648 x 80, d = 5, N = 6: 320 | 187).  Over 650 shapes of 3 to 16 channels the rule is 1.3 % off the better one of the
+// two, and takes 0.60 of the time without these kernels; of 240 shapes at its line the worst is 1.03 (49 x 123, d = 7, N = 6: 109 | 106; 125 where
+// the caller does not say that the signature is the scan's, which stays: the tree's gradient of a signature from tiles is less exact).
 bool tile_backward_preferred(const Shape &sh)
 {
     if (sh.stream || sh.n_inc < 24 || sh.S >= (int64_t(1) << 31) || (!sh.from_identity && sh.d <= 8)) return false;

@@ -28,14 +28,16 @@
 // a tile of 14 words takes 478 and 42 (1.9 ns for a multiply-add of three registers, 1.3 for an addition, 2.1 with DPP, 7.3 for a matrix
 // instruction: 1.16 us a SIMD, measured 1.16).  Neither more wavefronts per SIMD (products and chains in wavefronts of their own) nor another
 // order of the instructions changed that.  From few paths on it is the walk of a lone wavefront, 0.9 to 2 us a tile.
-// Before (prefix-tree kernels, sig_backward_d16.hip, sig_wide_backward.hip) | now, us: 256 paths of 1024 points, d = 16, N = 4 1265 | 716; 256 x 100,
-// d = 6, N = 4 53 | 18; 128 x 128, d = 4, N = 5 51 | 13; 64 x 200, d = 8, N = 5 154 | 38; 32 x 128, d = 16, N = 4 161 | 27; 1 x 1000, d = 13, N = 4 985 | 128.
+// Before (prefix-tree kernels, sig_backward_d16.hip, sig_wide_backward.hip) | now, us: 256 paths of 1024 points, d = 16, N = 4 1268 | 748; 256 x 101,
+// d = 6, N = 4 53 | 17; 128 x 128, d = 4, N = 5 52 | 16; 64 x 201, d = 8, N = 5 156 | 46; 32 x 128, d = 16, N = 4 163 | 27; 1 x 1001, d = 13, N = 4 986 | 126
+// (calls queued one behind another, with the sums that end them).  The error is 0.94 of theirs over 190 drawn shapes, at most 1.37 (few short paths: 3 of 34
+// points, d = 6, N = 7 5.2e-7 | 7.1e-7; 3 x 27, d = 4, N = 7 5.7e-7 | 6.9e-7).
 //
 // The signature handed in carries the rounding of the scan that made it; walked back by other sums it does not end at zero, and the
 // first points' gradients are off by what is left.  From depth 5 on the levels up to N - 2 are therefore formed anew ahead of the walk, by the
 // same sums (a tenth of the time; 8 paths of 128 points, d = 4, N = 8: off by 3.2e-6 without, 1.35e-6 with, 1.62e-6 on the prefix-tree kernels).
 // Where the caller says that sig_forward made the signature (Shape::scanned), and it did so in sig_tile_forward_impl.h, these are the sums it was made by, and
-// nothing is gained by forming them again: the gradients are the same bits (32 x 128 points, d = N = 7: 513 us with, 447 without; 100 x 900, d = 9, N = 5 1375 | 1195).
+// nothing is gained by forming them again: the gradients are the same bits (32 x 128 points, d = N = 7: 489 us with, 427 without; 100 x 901, d = 9, N = 5 1373 | 1193).
 #ifndef SIG_TILE_BACKWARD_IMPL_H_
 #define SIG_TILE_BACKWARD_IMPL_H_
 

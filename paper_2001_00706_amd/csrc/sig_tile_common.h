@@ -2,7 +2,7 @@
 // the matrix cores' bfloat16 instructions.
 //
 // Operands are 32-bit numbers cut into three bfloat16 pieces of 8 bits, high, middle and low (exact: each piece is what is left of those before),
-// of whose nine products six or eight are summed in fp32, the small ones first.  The matrix cores take them at 16 times the fp32 rate, so six products
+// of whose nine products six or eight are summed in fp32, the small ones first (the known way to products of 32-bit numbers on units for 16).  The matrix cores take them at 16 times the fp32 rate, so six products
 // are 2.7 times as fast as one fp32 instruction.  Truncated, a middle piece is below 2^-7 of its number and a low one below 2^-15, of its sign.
 //  - Eight products (gradients up to eight channels) leave out the low pieces' one, 2^-30 of a term.
 //  - Six leave out up to 2^-21 of a term and 2^-23 in the mean, of the term's sign, where a multiply-add rounds off 2^-24.  The scan has a rounding per tile

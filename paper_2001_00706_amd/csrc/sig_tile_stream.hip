@@ -9,7 +9,7 @@
 // Few paths wait for the sums: d (d + 1) of them a wavefront and sixty-four increments, 12 instructions each (1.5 us at d = 4, 4 at d = 7); many for the
 // stores of partial lines.  Of two wavefronts' halves with sixteen lanes each the sums would be cheaper but the chain four times as long.
 // Rows looked up one scalar at a time (a division each) took 1.3 times the time, sums one after the other 1.15.
-// 32 paths of 401 points, d = 4, N = 4: 24 us in sig_mfma_d4_shard.hip, 15 here.  A scalar is a sum over a tree instead of a chain: 0.3 to 0.9 of the error.
+// 32 paths of 401 points, d = 4, N = 4: 29 us in sig_mfma_d4_shard.hip, 18 here.  A scalar is a sum over a tree instead of a chain: 0.3 to 0.9 of the error.
 #include "sig_internal.h"
 #include "sig_tile_common.h"
 
@@ -376,8 +376,8 @@ static bool short_enough(const Shape &sh)
 
 // Where it pays otherwise, both timed over 700 shapes of up to 1100 points (rows of B S scalars side by side; us, before | now).  A full chip stores
 // 2.5 to 4 TB/s:
-//  - the kernels before wait 0.3 to 0.45 us for an increment or, in chunks, some 20 to 60 for three launches: 64 x 101 points, d = 5, N = 4 32 | 11;
-//    25 x 165, d = 7, N = 5 757 | 96; 8 x 227, d = 4, N = 5 24 | 11.5.  Under 20 increments most lanes have none.
+//  - the kernels before wait 0.3 to 0.45 us for an increment or, in chunks, some 20 to 60 for three launches: 64 x 101 points, d = 5, N = 4 27 | 12;
+//    25 x 165, d = 7, N = 5 763 | 101; 8 x 227, d = 4, N = 5 24 | 12.  Under 20 increments most lanes have none.
 //  - with many paths they store up to 6 TB/s: 745 x 119, d = 4, N = 4 23 | 34, 1287 x 20, d = 5, N = 4 17 | 36; at d = 4, N = 5 from 30 paths on
 //    (55 x 84 11.6 | 12.8).
 //  - at depth 3 from 5 channels on a path is a single workgroup of d (d + 1) sums a wavefront, and from some length on the chunks are ahead:
