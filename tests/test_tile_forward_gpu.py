@@ -16,10 +16,10 @@ pytestmark = pytest.mark.gpu
 TOL = 5e-6
 
 
-def check(B, L, d, N, basepoint="none", sample=None, misalign=False):
+def check(B, L, d, N, basepoint="none", sample=None, misalign=False, tiles=1):
     """`misalign`: by four bytes, which leaves calls of 8 and 16 channels to the vector kernels."""
     import torch
-    assert misalign or sig.sig_tile_rounds(B, L, d, N, basepoint=basepoint != "none") == 1
+    assert misalign or sig.sig_tile_rounds(B, L, d, N, basepoint=basepoint != "none") == tiles
     x = brownian_paths(B, L, d, seed=L + d) + np.float32(0.25)
     some = np.arange(B) if sample is None else np.asarray(sample)
     bp = {"none": None, "origin": True, "point": brownian_paths(B, 2, d, seed=7)[:, 1]}[basepoint]
@@ -69,6 +69,13 @@ def test_large_signatures(d, N):
 @pytest.mark.parametrize("B,L,d,N", [(2, 43, 8, 5), (2, 43, 8, 6), (3, 101, 8, 4), (90, 101, 16, 4)])
 def test_unaligned(B, L, d, N, basepoint):
     check(B, L, d, N, basepoint, sample=[0, 1, B - 1], misalign=True)
+
+
+# shapes beside those above that the matrix kernels of 8 and 16 channels and the prefix tree keep
+@pytest.mark.parametrize("B,L,d,N,basepoint", [(2, 43, 8, 6, "none"), (2, 43, 8, 6, "origin"), (2, 43, 8, 6, "point"), (90, 101, 16, 4, "origin"),
+                                               (1, 40, 6, 8, "point")])
+def test_left_to_the_others(B, L, d, N, basepoint):
+    check(B, L, d, N, basepoint, sample=[0, B - 1], tiles=0)
 
 
 def test_a_point_that_is_not_a_number_stays_in_its_words():

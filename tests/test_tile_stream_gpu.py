@@ -40,7 +40,7 @@ def check(B, L, d, N, basepoint="none"):
         assert np.linalg.norm(a - b) <= TOL * np.linalg.norm(b), k
 
 
-@pytest.mark.parametrize("L", [2, 16, 20, 21, 22, 33, 34, 64, 65, 66, 128, 129, 130, 300])
+@pytest.mark.parametrize("L", [2, 3, 16, 17, 18, 20, 21, 22, 33, 34, 64, 65, 66, 128, 129, 130, 300])
 @pytest.mark.parametrize("d,N", [(4, 4), (5, 4), (3, 3)])
 def test_lengths(L, d, N):
     check(2, L, d, N)
